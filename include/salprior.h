@@ -137,8 +137,8 @@ int64_t sp_tape_generation(const sp_ctx* ctx);
  *   rgb_prev [H][W][3] uint8, frame t-1, or NULL (first frame: the motion feature is 0).
  *   S_out    [Hc][Wc] float: S = sum_k w_k C_k.
  *   C_out    [8][Hc][Wc] float conspicuity maps, or NULL.
- * When the context records a tape, the checkpoint of this frame's pyramid level c_min
- * and S are stored for the adjoint. */
+ * When the context records a tape, this frame's across-scale sums (with their
+ * normalisation parameters) and S are stored for the adjoint. */
 int saliency_forward(sp_ctx* ctx, const uint8_t* rgb_t, const uint8_t* rgb_prev, float* S_out, float* C_out);
 
 /* Kalman prior update (Section 6) from a saliency map (Section 5).
@@ -233,7 +233,7 @@ int sp_step(sp_ctx* ctx, const uint8_t* rgb_t, const uint8_t* rgb_prev, const ui
  * prior updates since the reset).
  *   grad_prior [T][H][W] float: dL/d prior_t for every recorded step.
  *   grad_w [8], grad_q [1], grad_r [1] float (device): dL/dw, dL/dQ, dL/dR.
- * The conspicuity maps are recomputed from the checkpointed pyramid level c_min. */
+ * The conspicuity maps come from the recorded across-scale sums. */
 int saliency_backward(sp_ctx* ctx, const float* grad_prior, int32_t T, float* grad_w, float* grad_q,
                       float* grad_r);
 
@@ -336,8 +336,7 @@ int64_t sp_batch_tape_generation(const sp_batch* b);
  *   sp_batch_backward: gradients of every stream's loss L_i, given grad_prior (HOST array
  *     of n device pointers, [T][H][W] float each, dL_i/dprior_t), for exactly T = the
  *     steps recorded since the reset.  grad_w: device [n][8], grad_q, grad_r: device [n].
- *     The conspicuity maps are recomputed from every stream's checkpointed level c_min,
- *     a few frames of every stream per launch.
+ *     The conspicuity maps come from every stream's recorded across-scale sums.
  * The host arrays are read during the call; the device buffers must stay valid until
  * the stream reaches the call's launches.  The tables the calls upload are staged in
  * pinned host memory; refilling a stage waits for its previous upload. */

@@ -354,10 +354,8 @@ void fill_taps(StreamDesc& sd, const sp_params& p) {
 }
 
 // Fills the geometry/parameter part of a stream description and takes its scratch
-// from `bump`.  Levels below `first_level` get no base storage (level c_min of a
-// recompute stream reads its checkpoint instead).
-void layout_stream(StreamDesc& sd, const Geo& g, const sp_params& p, Bump& bump, int first_level, bool rgb_parts,
-                   int rgb_min_tiles = 192) {
+// from `bump`.
+void layout_stream(StreamDesc& sd, const Geo& g, const sp_params& p, Bump& bump, int rgb_min_tiles = 192) {
   std::memset(&sd, 0, sizeof sd);
   sd.H = g.H;
   sd.W = g.W;
@@ -393,17 +391,15 @@ void layout_stream(StreamDesc& sd, const Geo& g, const sp_params& p, Bump& bump,
   sd.dt_r = std::min(SP_DT_RMAX, (int)std::ceil(std::sqrt(176.0) * (double)p.dt_sigma));
   sd.dt_k = (float)(-1.0 / (2.0 * (double)p.dt_sigma * (double)p.dt_sigma * std::log(2.0)));
   fill_taps(sd, p);
-  for (int l = std::max(1, first_level); l <= g.top; ++l)
+  for (int l = 1; l <= g.top; ++l)
     sd.base[l] = bump.take<float>((size_t)4 * g.Hl[l] * g.Wl[l]);
   for (int l = 1; l <= g.top; ++l)
     if (g.used & (1u << l)) sd.gab[l] = bump.take<float>((size_t)4 * g.Hl[l] * g.Wl[l]);
-  if (rgb_parts) {
-    const RgbTiling t = rgb_tiling(g, rgb_min_tiles);
-    sd.n_rgb = t.count();
-    sd.rgb_tr = t.tr;
-    sd.rgb_max_part = bump.take<uint32_t>(sd.n_rgb);
-    sd.rgb_d2_part = bump.take<unsigned long long>(sd.n_rgb);
-  }
+  const RgbTiling t = rgb_tiling(g, rgb_min_tiles);
+  sd.n_rgb = t.count();
+  sd.rgb_tr = t.tr;
+  sd.rgb_max_part = bump.take<uint32_t>(sd.n_rgb);
+  sd.rgb_d2_part = bump.take<unsigned long long>(sd.n_rgb);
   sd.cs_part = bump.take<float>((size_t)3 * off);
   sd.fbar = bump.take<float>((size_t)SP_NCH * g.Hl[g.c_max] * g.Wl[g.c_max]);
   sd.fbar_part = bump.take<float>((size_t)3 * SP_NCH * sd.n_cmax_tiles);
@@ -472,9 +468,6 @@ int upload_jobs(JobStore& js, hipStream_t st) {
   HIPCHK(hipStreamSynchronize(st));
   return SP_OK;
 }
-
-// Per-stream phase program of the forward saliency map.
-enum ProgPart { PROG_ALL, PROG_RECOMPUTE };
 
 double now_gain(int64_t t, double Pprev, double Q, double R, double* P) {
   if (t == 0) {
@@ -555,6 +548,7 @@ struct sp_ctx {
   StreamDesc* d_sd = nullptr;
   JobStore jobs;
   std::vector<Phase> fwd, prior, mrf, bwd;
+  Phase dot;                      // recorded conspicuity dotted with the saliency adjoint
   // Kalman state
   int64_t t = 0;
   double P = 0.0;
@@ -565,7 +559,8 @@ struct sp_ctx {
   int64_t tape_valid_from = 0;   // tape covers steps since the last reset only
   bool tape_ok = true;
   int64_t tape_gen = 0;           // bumped whenever the recorded clip stops being the current one
-  float* ckpt = nullptr;          // [cap][4][Hcmin][Wcmin]
+  float* fbar_tape = nullptr;     // [cap][8][Hc][Wc] across-scale sums F-bar
+  float* np_tape = nullptr;       // [cap][8][4] their N(.) parameters
   float* S_tape = nullptr;        // [cap][Hc][Wc]
   float* f_tape = nullptr;        // [cap][H][W]
   float* ms_tape = nullptr;       // [cap][2]
@@ -582,10 +577,7 @@ struct sp_ctx {
   float* cx = nullptr;            // [cap][8]
   double* gK_scratch = nullptr;   // [cap] dL/dK_t, then [cap][8] the steps' shares of dL/dw
   int n_lvl0_tiles = 0;
-  int CH = 0;                     // frames per recompute chunk
-  StreamDesc* d_rsd = nullptr;    // [CH] recompute streams
-  StepIO* d_rio = nullptr;        // [cap] io of every tape frame (checkpoint and adjoint buffers)
-  std::vector<Phase> rec;         // recompute phases (stream-major, CH streams)
+  StepIO* d_rio = nullptr;        // [cap] io of every tape frame (F-bar and adjoint buffers)
   float* S_scratch = nullptr;     // [Hc][Wc] saliency map of the autotuner's steps
   // variants of the prior
   float* f_map = nullptr;         // [H][W] distance-transform prediction (f_mode 1)
@@ -657,28 +649,33 @@ int run_phase(sp_ctx* c, const Phase& ph, const StreamDesc* sds, const StepIO* i
   return SP_OK;
 }
 
+// Tape slots of the step about to run that the saliency kernels fill.
+void tape_forward(const sp_ctx* c, StepIO& io) {
+  const size_t t = (size_t)c->t, plane = (size_t)c->g.Hl[c->g.c_max] * c->g.Wl[c->g.c_max];
+  io.fbar = c->fbar_tape + t * SP_NCH * plane;
+  io.np_tape = c->np_tape + t * 4 * SP_NCH;
+  io.S_tape = c->S_tape + t * plane;
+}
+
 void build_forward_jobs(std::vector<std::vector<Job>>& parts, std::vector<int>& kinds, const StreamDesc& sd,
-                        const Geo& g, int s, ProgPart which, int nc) {
+                        const Geo& g, int s, int nc) {
   auto push = [&](int kind, std::vector<Job> v) {
     parts.push_back(std::move(v));
     kinds.push_back(kind);
   };
-  if (which == PROG_ALL) {
-    std::vector<Job> v;
-    rgb_jobs(v, s, sd, g);
-    push(JOB_RGB, v);
-    v.clear();
-    add_tiles(v, s, 1, g.Hl[1], g.Wl[1], JOB_FEAT);
-    push(JOB_FEAT, v);
-  }
-  const int from = (which == PROG_ALL) ? 1 : g.c_min;
+  std::vector<Job> v;
+  rgb_jobs(v, s, sd, g);
+  push(JOB_RGB, v);
+  v.clear();
+  add_tiles(v, s, 1, g.Hl[1], g.Wl[1], JOB_FEAT);
+  push(JOB_FEAT, v);
   std::vector<std::vector<Job>> mid;
   std::vector<Job> fin;
   bool big = false;
-  pyramid_stages(g, s, from, mid, fin, &big);
+  pyramid_stages(g, s, 1, mid, fin, &big);
   for (auto& m : mid) push(JOB_DOWN, m);
   if (!fin.empty()) push(big ? JOB_TAIL : JOB_DOWN, fin);
-  std::vector<Job> v;
+  v.clear();
   const bool gp = gpath_ok(g);
   if (gp) {
     for (int k = 0; k < SP_NCH; k += nc) add_tiles(v, s, k, g.Hl[g.c_max], g.Wl[g.c_max], JOB_CSG);
@@ -706,7 +703,7 @@ void build_forward_jobs(std::vector<std::vector<Job>>& parts, std::vector<int>& 
   }
   v.clear();
   add_tiles(v, s, 0, g.Hl[g.c_max], g.Wl[g.c_max]);
-  push(which == PROG_ALL ? JOB_CONSP : JOB_CONSP_DOT, v);
+  push(JOB_CONSP, v);
 }
 
 // 8x8 blocks of every map of the N(.) adjoint: the 8 across-scale sums and every pair's 8
@@ -939,7 +936,7 @@ int forward_phases(const Geo& g, const sp_params& p, const StreamDesc& sd, const
   const size_t ca_lds = nc * (gpath_ok(g) ? csg_lds_bytes(g) : csapply_lds_bytes(g));
   if (sp_csapply_reserve_lds(ca_lds) != hipSuccess)
     return fail(SP_EHIP, "cannot reserve %zu bytes of LDS for the across-scale sum", ca_lds);
-  build_forward_jobs(parts, kinds, sd, g, 0, PROG_ALL, nc);
+  build_forward_jobs(parts, kinds, sd, g, 0, nc);
   for (size_t i = 0; i < parts.size(); ++i) {
     const bool grp = kinds[i] == JOB_CSAPPLY || kinds[i] == JOB_CSG;
     const bool pyr = kinds[i] == JOB_DOWN || kinds[i] == JOB_TAIL;   // flag: Gabor radius
@@ -1023,12 +1020,11 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
   c->n_lvl0_tiles = ntiles(H, W);
   const int Hc = g.Hl[g.c_max], Wc = g.Wl[g.c_max];
   const size_t HW = (size_t)H * W;
-  c->CH = c->cap > 0 ? std::min(c->cap, 32) : 0;
   // two passes over the layout: size, then place
   for (int pass = 0; pass < 2; ++pass) {
     Bump b;
     b.base = c->arena;
-    layout_stream(c->h_sd, g, *p, b, 1, true);
+    layout_stream(c->h_sd, g, *p, b);
     c->d_sd = b.take<StreamDesc>(1);
     c->pi_state[0] = b.take<float>(HW);
     c->pi_state[1] = b.take<float>(HW);
@@ -1044,9 +1040,9 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
       c->ssm[0] = b.take<float>((size_t)Hc * Wc);
       c->ssm[1] = b.take<float>((size_t)Hc * Wc);
     }
-    std::vector<StreamDesc> rsd(c->CH);
     if (c->cap > 0) {
-      c->ckpt = b.take<float>((size_t)c->cap * 4 * g.Hl[g.c_min] * g.Wl[g.c_min]);
+      c->fbar_tape = b.take<float>((size_t)c->cap * SP_NCH * Hc * Wc);
+      c->np_tape = b.take<float>((size_t)c->cap * 4 * SP_NCH);
       c->S_tape = b.take<float>((size_t)c->cap * Hc * Wc);
       c->f_tape = b.take<float>((size_t)c->cap * HW);
       c->ms_tape = b.take<float>((size_t)c->cap * 2);
@@ -1060,9 +1056,7 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
       c->dot_part = b.take<float>((size_t)c->cap * c->h_sd.n_cmax_tiles * SP_NCH);
       c->cx = b.take<float>((size_t)c->cap * SP_NCH);
       c->gK_scratch = b.take<double>((size_t)c->cap * (1 + SP_NCH));
-      c->d_rsd = b.take<StreamDesc>(c->CH);
       c->d_rio = b.take<StepIO>(c->cap);
-      for (int i = 0; i < c->CH; ++i) layout_stream(rsd[i], g, *p, b, g.c_min + 1, false);
       pixadj_layout(c, b);
     }
     if (pass == 0) {
@@ -1076,20 +1070,18 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
       // upload static tables
       hipError_t e = hipMemcpyAsync(c->d_sd, &c->h_sd, sizeof(StreamDesc), hipMemcpyHostToDevice, c->stream);
       if (e == hipSuccess && c->cap > 0) {
-        e = hipMemcpyAsync(c->d_rsd, rsd.data(), sizeof(StreamDesc) * c->CH, hipMemcpyHostToDevice, c->stream);
         std::vector<StepIO> rio(c->cap);
-        const size_t cstride = (size_t)4 * g.Hl[g.c_min] * g.Wl[g.c_min];
         const size_t plane = (size_t)Hc * Wc;
         for (int t = 0; t < c->cap; ++t) {
           std::memset(&rio[t], 0, sizeof(StepIO));
-          rio[t].ckpt = c->ckpt + (size_t)t * cstride;
+          rio[t].fbar = c->fbar_tape + (size_t)t * SP_NCH * plane;
+          rio[t].np_tape = c->np_tape + (size_t)t * 4 * SP_NCH;
           rio[t].gs = c->gs_all + (size_t)t * plane;
           rio[t].ms_tape = c->ms_tape + 2 * (size_t)t;
           rio[t].dot = c->dot_part + (size_t)t * c->h_sd.n_cmax_tiles * SP_NCH;
           rio[t].cx = c->cx + (size_t)t * SP_NCH;
         }
-        if (e == hipSuccess)
-          e = hipMemcpyAsync(c->d_rio, rio.data(), sizeof(StepIO) * c->cap, hipMemcpyHostToDevice, c->stream);
+        e = hipMemcpyAsync(c->d_rio, rio.data(), sizeof(StepIO) * c->cap, hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         if (e == hipSuccess) e = pixadj_upload(c);
       }
@@ -1129,13 +1121,11 @@ int ctx_build_tables(sp_ctx* c) {
   c->prior.clear();
   c->mrf.clear();
   c->bwd.clear();
-  c->rec.clear();
   c->dt.clear();
   {
     int nc = 0;
     int rc = forward_phases(g, c->p, c->h_sd, c->tune, c->jobs, c->fwd, &nc);
     if (rc) return rc;
-    const size_t ca_lds = nc * (gpath_ok(g) ? csg_lds_bytes(g) : csapply_lds_bytes(g));
     auto order = [&](std::vector<Job> v) {
       if (c->tune.xcd) xcd_order(v);
       return v;
@@ -1161,27 +1151,7 @@ int ctx_build_tables(sp_ctx* c) {
     v.clear();
     add_tiles(v, 0, 0, Hc, Wc);
     c->bwd.push_back(c->jobs.add(JOB_BWD_GS, 0, v, 1));
-    if (c->CH > 0) {
-      std::vector<std::vector<Job>> all;
-      std::vector<int> kk;
-      for (int s = 0; s < c->CH; ++s) {
-        std::vector<std::vector<Job>> ps;
-        std::vector<int> ks;
-        build_forward_jobs(ps, ks, c->h_sd, g, s, PROG_RECOMPUTE, nc);
-        if (all.empty()) {
-          all.resize(ps.size());
-          kk = ks;
-        }
-        for (size_t i = 0; i < ps.size(); ++i) all[i].insert(all[i].end(), ps[i].begin(), ps[i].end());
-      }
-      for (size_t i = 0; i < all.size(); ++i) {
-        const bool grp = kk[i] == JOB_CSAPPLY || kk[i] == JOB_CSG;
-        const bool pyr = kk[i] == JOB_DOWN || kk[i] == JOB_TAIL;
-        const int gflag = nc | (kk[i] == JOB_CSG ? csg_set(g) << 8 : 0);
-        c->rec.push_back(c->jobs.add(kk[i], grp ? gflag : (pyr ? c->p.gabor_radius : 0), all[i], c->CH));
-        if (grp) c->rec.back().lds = ca_lds;
-      }
-    }
+    c->dot = c->jobs.add(JOB_CONSP_DOT, 0, v, 1);
   }
   return upload_jobs(c->jobs, c->stream);
 }
@@ -1337,9 +1307,7 @@ int saliency_forward(sp_ctx* c, const uint8_t* rgb_t, const uint8_t* rgb_prev, f
   if (c->cap > 0) {
     if (c->t >= c->cap) return fail(SP_ESTATE, "tape holds %d frames; call sp_reset before frame %lld", c->cap,
                                     (long long)c->t);
-    const Geo& g = c->g;
-    io.ckpt = c->ckpt + (size_t)c->t * 4 * g.Hl[g.c_min] * g.Wl[g.c_min];
-    io.S_tape = c->S_tape + (size_t)c->t * g.Hl[g.c_max] * g.Wl[g.c_max];
+    tape_forward(c, io);
   }
   for (const Phase& ph : c->fwd) {
     int rc = run_phase(c, ph, c->d_sd, nullptr, &io, ph.n);
@@ -1454,8 +1422,7 @@ int sp_step(sp_ctx* c, const uint8_t* rgb_t, const uint8_t* rgb_prev, const uint
   io.K = (float)K;
   io.t = (int32_t)std::min<int64_t>(c->t, 0x7fffffff);
   if (c->cap > 0) {
-    io.ckpt = c->ckpt + (size_t)c->t * 4 * g.Hl[g.c_min] * g.Wl[g.c_min];
-    io.S_tape = c->S_tape + (size_t)c->t * g.Hl[g.c_max] * g.Wl[g.c_max];
+    tape_forward(c, io);
     io.f_tape = c->f_tape + (size_t)c->t * g.H * g.W;
     io.ms_tape = c->ms_tape + (size_t)c->t * 2;
   }
@@ -1498,10 +1465,10 @@ int sp_saliency_noalloc(const sp_params* p, int32_t H, int32_t W, const uint8_t*
   {
     Bump b;
     b.take<StreamDesc>(1);
-    layout_stream(sd, g, *p, b, 1, true);
+    layout_stream(sd, g, *p, b);
     std::vector<std::vector<Job>> parts;
     std::vector<int> kinds;
-    build_forward_jobs(parts, kinds, sd, g, 0, PROG_ALL, nc);
+    build_forward_jobs(parts, kinds, sd, g, 0, nc);
     for (const auto& v : parts) n_jobs += v.size();
     b.take<Job>(n_jobs);
     need = b.off;
@@ -1514,7 +1481,7 @@ int sp_saliency_noalloc(const sp_params* p, int32_t H, int32_t W, const uint8_t*
   Bump b;
   b.base = static_cast<char*>(base);
   StreamDesc* d_sd = b.take<StreamDesc>(1);
-  layout_stream(sd, g, *p, b, 1, true);
+  layout_stream(sd, g, *p, b);
   Job* d_jobs = b.take<Job>(n_jobs);
   if (b.off != need) return fail(SP_EINVAL, "scratch layout changed between its passes");
   JobStore js;
@@ -1705,23 +1672,15 @@ int saliency_backward(sp_ctx* c, const float* grad_prior, int32_t T, float* grad
       if (e != hipSuccess) return fail(SP_EHIP, "adjoint launch: %s", hipGetErrorString(e));
     }
   }
-  // conspicuity maps recomputed from the checkpoints, dotted with the saliency adjoint
-  for (int t0 = 0; t0 < T; t0 += c->CH) {
-    const int n = std::min(c->CH, T - t0);
-    const StepIO* ios = c->d_rio + t0;
-    for (const Phase& ph : c->rec) {
-      const int nj = ph.upto[n];
-      hipError_t e = timed(c, ph.kind, [&] {
-        if (ph.kind == JOB_CONSP_DOT) return sp_launch_consp_dot(c->jobs.dev + ph.off, nj, c->d_rsd, ios, c->stream);
-        return sp_launch(ph.kind, c->jobs.dev + ph.off, nj, c->d_rsd, ios, nullptr, ph.flag, nullptr, c->stream, ph.lds);
-      });
-      if (e != hipSuccess) return fail(SP_EHIP, "recompute launch: %s", hipGetErrorString(e));
-    }
-  }
+  // the recorded conspicuity maps dotted with the saliency adjoint
+  hipError_t e = timed(c, JOB_CONSP_DOT, [&] {
+    return sp_launch_consp_dot(c->jobs.dev + c->dot.off, c->dot.n, c->d_sd, c->d_rio, 1, T, c->stream);
+  });
+  if (e != hipSuccess) return fail(SP_EHIP, "conspicuity adjoint launch: %s", hipGetErrorString(e));
   const float* wdev = reinterpret_cast<const float*>(reinterpret_cast<const char*>(c->d_sd) + offsetof(StreamDesc, w));
   BwdFin fin{c->gk_part, c->dot_part, c->cx, c->ms_tape, wdev, c->gK_scratch, grad_w, grad_q, grad_r,
              c->n_lvl0_tiles, c->h_sd.n_cmax_tiles};
-  hipError_t e = timed(c, JOB_BWD_FINAL, [&] {
+  e = timed(c, JOB_BWD_FINAL, [&] {
     return sp_launch_bwd_final(nullptr, &fin, 1, T, c->K_tape, c->P_tape, c->p.q, c->p.r, c->p.flat_tol, c->stream);
   });
   if (e != hipSuccess) return fail(SP_EHIP, "adjoint reduction launch: %s", hipGetErrorString(e));
@@ -1999,31 +1958,24 @@ struct sp_batch {
   int ca_nc = 2;            // preferred channels per across-scale workgroup (one value per launch)
   // tape and adjoint (record_tape > 0): every stream records the same steps
   int cap = 0;              // frames each stream's tape holds
-  int CH = 0;               // frames of every stream per recompute chunk
   bool tape_ok = true;      // false once the weights changed after recorded steps
   long long tape_gen = 0;   // bumped whenever the recorded clip stops being the current one
   std::vector<BatchAdj> adj;                  // per stream: adjoint buffers
-  std::vector<StreamDesc> h_rsd;              // [CH * n] recompute streams (v = j * n + i)
-  StreamDesc* d_rsd = nullptr;
-  StepIO* d_rio = nullptr;                    // [cap][n] checkpoint and adjoint buffers of each frame
+  StepIO* d_rio = nullptr;                    // [cap][n] F-bar and adjoint buffers of each frame
   char* d_bstage = nullptr;                   // gains, variances, [cap][n] BwdIO, [n] BwdFin
   char* d_lstage = nullptr;                   // [n] LossIO
   HostStage bstage, lstage;                   // pinned host copies of the two tables
-  std::vector<Phase> bwd, rec;                // adjoint sweep (2 launches per step), recompute program
+  std::vector<Phase> bwd;                     // adjoint sweep (2 launches per step)
+  Phase dot;                                  // recorded conspicuity dotted with the saliency adjoint
   int loss_nblk = 1024;
 };
 
 namespace {
 
-// Job tables of the batched adjoint: the level-0 sweep and the up-sample transpose over
-// every stream (one launch each per reverse step), and the recompute program over the
-// CH * n recompute streams of a chunk (recompute stream v = j * n + i takes frame t0 + j of
-// stream i).  Each phase lists its jobs in recompute-stream order, so a chunk of rem < CH
-// frames launches the prefix of rem * n streams.  Streams of different sizes may have
-// different numbers of pyramid stages: middle stages are merged by index and every final
-// stage goes to one last pyramid launch (its kernel handles every pyramid job kind).
-void batch_adjoint_tables(sp_batch* b, int nc, size_t lds_a, size_t lds_g) {
-  const int n = b->n, nv = b->CH * n;
+// Job tables of the batched adjoint: the level-0 sweep, the up-sample transpose and the
+// conspicuity maps of every stream (one launch each; the first two per reverse step).
+void batch_adjoint_tables(sp_batch* b) {
+  const int n = b->n;
   std::vector<Job> nu, gs;
   for (int i = 0; i < n; ++i) {
     const Geo& g = b->geo[i];
@@ -2033,54 +1985,7 @@ void batch_adjoint_tables(sp_batch* b, int nc, size_t lds_a, size_t lds_g) {
   b->bwd.clear();
   b->bwd.push_back(b->jobs.add(JOB_BWD_NU, 0, nu, n));
   b->bwd.push_back(b->jobs.add(JOB_BWD_GS, 0, gs, n));
-  std::vector<std::vector<Job>> mids;
-  std::vector<Job> fin, css, csg, csf, csa, csm, dot;
-  bool any_tail = false;
-  int set = 1;
-  for (int v = 0; v < nv; ++v) {
-    const int i = v % n;
-    const Geo& g = b->geo[i];
-    std::vector<std::vector<Job>> parts;
-    std::vector<int> kinds;
-    build_forward_jobs(parts, kinds, b->h_rsd[v], g, v, PROG_RECOMPUTE, nc);
-    size_t np = 0;   // leading pyramid stages; the last of them is the final one
-    while (np < parts.size() && (kinds[np] == JOB_DOWN || kinds[np] == JOB_TAIL)) ++np;
-    for (size_t k = 0; k + 1 < np; ++k) {
-      if (mids.size() <= k) mids.resize(k + 1);
-      mids[k].insert(mids[k].end(), parts[k].begin(), parts[k].end());
-    }
-    if (np > 0) {
-      fin.insert(fin.end(), parts[np - 1].begin(), parts[np - 1].end());
-      any_tail |= kinds[np - 1] == JOB_TAIL;
-    }
-    for (size_t k = np; k < parts.size(); ++k) {
-      std::vector<Job>* dst = nullptr;
-      switch (kinds[k]) {
-        case JOB_CSSTATS: dst = &css; break;
-        case JOB_CSG: dst = &csg; set = std::min(set, csg_set(g)); break;
-        case JOB_CSFINAL: dst = &csf; break;
-        case JOB_CSAPPLY: dst = &csa; break;
-        case JOB_CSMIX: dst = &csm; break;
-        default: dst = &dot; break;
-      }
-      dst->insert(dst->end(), parts[k].begin(), parts[k].end());
-    }
-  }
-  b->rec.clear();
-  for (auto& m : mids) b->rec.push_back(b->jobs.add(JOB_DOWN, b->p.gabor_radius, m, nv));
-  if (!fin.empty()) b->rec.push_back(b->jobs.add(any_tail ? JOB_TAIL : JOB_DOWN, b->p.gabor_radius, fin, nv));
-  if (!css.empty()) b->rec.push_back(b->jobs.add(JOB_CSSTATS, 0, css, nv));
-  if (!csg.empty()) {
-    b->rec.push_back(b->jobs.add(JOB_CSG, nc | (set << 8), csg, nv));
-    b->rec.back().lds = nc * lds_g;
-  }
-  if (!csf.empty()) b->rec.push_back(b->jobs.add(JOB_CSFINAL, 0, csf, nv));
-  if (!csa.empty()) {
-    b->rec.push_back(b->jobs.add(JOB_CSAPPLY, nc, csa, nv));
-    b->rec.back().lds = nc * lds_a;
-  }
-  if (!csm.empty()) b->rec.push_back(b->jobs.add(JOB_CSMIX, 0, csm, nv));
-  b->rec.push_back(b->jobs.add(JOB_CONSP_DOT, 0, dot, nv));
+  b->dot = b->jobs.add(JOB_CONSP_DOT, 0, gs, n);
 }
 
 // Drops the graph of several steps (recaptured by the next sp_batch_steps).
@@ -2202,7 +2107,7 @@ int batch_build_tables(sp_batch* b) {
   if (!csm.empty()) b->phases.push_back(b->jobs.add(JOB_CSMIX, 0, order(csm), n));
   b->phases.push_back(b->jobs.add(JOB_CONSP, 0, order(cons), n));
   b->phases.push_back(b->jobs.add(JOB_KALMAN, 0, order(kal), n));
-  if (b->cap > 0) batch_adjoint_tables(b, nc, lds_a, lds_g);
+  if (b->cap > 0) batch_adjoint_tables(b);
   return upload_jobs(b->jobs, b->stream);
 }
 
@@ -2367,10 +2272,7 @@ int sp_batch_create(const sp_params* p, int32_t n, const int32_t* H, const int32
   b->h_sd.resize(n);
   b->h_st.resize(n);
   b->cap = p->record_tape;
-  // recompute chunks of about 64 recompute streams (at least one frame per stream)
-  b->CH = b->cap > 0 ? std::max(1, std::min({b->cap, 32, (64 + n - 1) / n})) : 0;
   b->adj.resize(b->cap > 0 ? n : 0);
-  b->h_rsd.resize((size_t)b->CH * n);
   const size_t bstage_bytes = b->cap > 0 ? 2 * sizeof(double) * b->cap + sizeof(BwdIO) * (size_t)b->cap * n +
                                                sizeof(BwdFin) * n : 0;
   const size_t lstage_bytes = b->cap > 0 ? sizeof(LossIO) * n : 0;
@@ -2380,7 +2282,7 @@ int sp_batch_create(const sp_params* p, int32_t n, const int32_t* H, const int32
     bm.base = b->arena;
     for (int i = 0; i < n; ++i) {
       // the colour-statistics launch holds every stream's tiles: aim at ~192 in total
-      layout_stream(b->h_sd[i], b->geo[i], *p, bm, 1, true, std::max(1, 192 / n));
+      layout_stream(b->h_sd[i], b->geo[i], *p, bm, std::max(1, 192 / n));
       const Geo& g = b->geo[i];
       BatchState& s = b->h_st[i];
       std::memset(&s, 0, sizeof s);
@@ -2396,7 +2298,8 @@ int sp_batch_create(const sp_params* p, int32_t n, const int32_t* H, const int32
       if (b->cap > 0) {
         const size_t cap = (size_t)b->cap, hw = (size_t)g.H * g.W, plane = (size_t)g.Hl[g.c_max] * g.Wl[g.c_max];
         s.tape_cap = b->cap;
-        s.tape_ckpt = bm.take<float>(cap * 4 * g.Hl[g.c_min] * g.Wl[g.c_min]);
+        s.tape_fbar = bm.take<float>(cap * SP_NCH * plane);
+        s.tape_np = bm.take<float>(cap * 4 * SP_NCH);
         s.tape_S = bm.take<float>(cap * plane);
         s.tape_f = bm.take<float>(cap * hw);
         s.tape_ms = bm.take<float>(cap * 2);
@@ -2418,14 +2321,9 @@ int sp_batch_create(const sp_params* p, int32_t n, const int32_t* H, const int32
     b->d_io = bm.take<StepIO>(n);
     b->d_st = bm.take<BatchState>(n);
     if (b->cap > 0) {
-      b->d_rsd = bm.take<StreamDesc>(b->h_rsd.size());
       b->d_rio = bm.take<StepIO>((size_t)b->cap * n);
       b->d_bstage = bm.take<char>(bstage_bytes);
       b->d_lstage = bm.take<char>(lstage_bytes);
-      for (size_t v = 0; v < b->h_rsd.size(); ++v) {
-        const Geo& g = b->geo[v % n];
-        layout_stream(b->h_rsd[v], g, *p, bm, g.c_min + 1, false);
-      }
     }
     if (pass == 0) {
       bytes = bm.off + 256;
@@ -2459,7 +2357,6 @@ int sp_batch_create(const sp_params* p, int32_t n, const int32_t* H, const int32
   hipError_t e = hipMemcpy(b->d_sd, b->h_sd.data(), sizeof(StreamDesc) * n, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(b->d_st, b->h_st.data(), sizeof(BatchState) * n, hipMemcpyHostToDevice);
   if (e == hipSuccess && b->cap > 0) {
-    e = hipMemcpy(b->d_rsd, b->h_rsd.data(), sizeof(StreamDesc) * b->h_rsd.size(), hipMemcpyHostToDevice);
     std::vector<StepIO> rio((size_t)b->cap * n);
     for (int t = 0; t < b->cap; ++t)
       for (int i = 0; i < n; ++i) {
@@ -2468,13 +2365,15 @@ int sp_batch_create(const sp_params* p, int32_t n, const int32_t* H, const int32
         const BatchAdj& a = b->adj[i];
         StepIO& io = rio[(size_t)t * n + i];
         std::memset(&io, 0, sizeof io);
-        io.ckpt = s.tape_ckpt + (size_t)t * 4 * g.Hl[g.c_min] * g.Wl[g.c_min];
-        io.gs = a.gs_all + (size_t)t * g.Hl[g.c_max] * g.Wl[g.c_max];
+        const size_t plane = (size_t)g.Hl[g.c_max] * g.Wl[g.c_max];
+        io.fbar = s.tape_fbar + (size_t)t * SP_NCH * plane;
+        io.np_tape = s.tape_np + (size_t)t * 4 * SP_NCH;
+        io.gs = a.gs_all + (size_t)t * plane;
         io.ms_tape = s.tape_ms + 2 * (size_t)t;
         io.dot = a.dot_part + (size_t)t * b->h_sd[i].n_cmax_tiles * SP_NCH;
         io.cx = a.cx + (size_t)t * SP_NCH;
       }
-    if (e == hipSuccess) e = hipMemcpy(b->d_rio, rio.data(), sizeof(StepIO) * rio.size(), hipMemcpyHostToDevice);
+    e = hipMemcpy(b->d_rio, rio.data(), sizeof(StepIO) * rio.size(), hipMemcpyHostToDevice);
   }
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking);
   if (e != hipSuccess) {
@@ -2743,11 +2642,7 @@ int sp_batch_set_weights(sp_batch* b, const float* w, double q, double r) {
   b->p.r = r;
   for (StreamDesc& sd : b->h_sd)
     for (int k = 0; k < SP_NCH; ++k) sd.w[k] = w[k];
-  for (StreamDesc& sd : b->h_rsd)
-    for (int k = 0; k < SP_NCH; ++k) sd.w[k] = w[k];
   HIPCHK(hipMemcpy(b->d_sd, b->h_sd.data(), sizeof(StreamDesc) * b->n, hipMemcpyHostToDevice));
-  if (b->d_rsd)
-    HIPCHK(hipMemcpy(b->d_rsd, b->h_rsd.data(), sizeof(StreamDesc) * b->h_rsd.size(), hipMemcpyHostToDevice));
   // each step's first node carries Q and R: point every one of them again at its next launch
   b->in_node = nullptr;
   for (auto& t : b->mtab) t = nullptr;
@@ -2865,21 +2760,12 @@ int sp_batch_backward(sp_batch* b, const float* const* grad_prior, int32_t T, fl
       });
       if (e != hipSuccess) return fail(SP_EHIP, "adjoint launch: %s", hipGetErrorString(e));
     }
-  // conspicuity maps recomputed from the checkpoints, CH frames of every stream at a time
-  for (int t0 = 0; t0 < T; t0 += b->CH) {
-    const int rem = std::min(b->CH, T - t0);
-    const StepIO* ios = b->d_rio + (size_t)t0 * n;
-    for (const Phase& ph : b->rec) {
-      const int nj = ph.upto[(size_t)rem * n];
-      hipError_t e = b->prof.timed(b->stream, ph.kind, [&] {
-        if (ph.kind == JOB_CONSP_DOT) return sp_launch_consp_dot(b->jobs.dev + ph.off, nj, b->d_rsd, ios, b->stream);
-        return sp_launch(ph.kind, b->jobs.dev + ph.off, nj, b->d_rsd, ios, nullptr, ph.flag, nullptr, b->stream,
-                         ph.lds);
-      });
-      if (e != hipSuccess) return fail(SP_EHIP, "recompute launch: %s", hipGetErrorString(e));
-    }
-  }
-  hipError_t e = b->prof.timed(b->stream, JOB_BWD_FINAL, [&] {
+  // the recorded conspicuity maps dotted with the saliency adjoint, every step at once
+  hipError_t e = b->prof.timed(b->stream, JOB_CONSP_DOT, [&] {
+    return sp_launch_consp_dot(b->jobs.dev + b->dot.off, b->dot.n, b->d_sd, b->d_rio, n, T, b->stream);
+  });
+  if (e != hipSuccess) return fail(SP_EHIP, "conspicuity adjoint launch: %s", hipGetErrorString(e));
+  e = b->prof.timed(b->stream, JOB_BWD_FINAL, [&] {
     return sp_launch_bwd_final(dfin, nullptr, n, T, dKd, dPd, b->p.q, b->p.r, b->p.flat_tol, b->stream);
   });
   if (e != hipSuccess) return fail(SP_EHIP, "adjoint reduction launch: %s", hipGetErrorString(e));

@@ -38,7 +38,7 @@ enum JobKind : int32_t {
   JOB_MRF,          // unary + pairwise capacities at level 0
   JOB_BWD_NU,       // adjoint sweep at level 0
   JOB_BWD_GS,       // upsample transpose at c_max
-  JOB_CONSP_DOT,    // recomputed conspicuity dotted with the saliency adjoint
+  JOB_CONSP_DOT,    // recorded conspicuity dotted with the saliency adjoint
   JOB_LOSS,         // masked MSE partials
   JOB_TAIL,         // one channel: every level above a small source level, in LDS
   JOB_TAILGAB,      // Gabor maps of one level above the tail source (intensity chain in LDS)
@@ -112,7 +112,8 @@ struct StepIO {
   const uint8_t* rgb_prev;   // frame t-1 (null: t = 0, motion is zero)
   float* S_out;              // [Hc][Wc]
   float* C_out;              // [8][Hc][Wc] or null
-  float* ckpt;               // base channels of level c_min: overrides base[c_min] when set
+  float* fbar;               // [8][Hc][Wc] F-bar of a recorded step: overrides the stream's fbar when set
+  float* np_tape;            // [8][4] its N(.) parameters (recorded steps, or null)
   float* S_tape;             // copy of S for the adjoint (or null)
   const float* S_in;         // saliency map read by the prior update
   const uint8_t* seg_prev;   // previous segmentation (null: use the previous prior)
@@ -124,7 +125,7 @@ struct StepIO {
   float* unary;              // [2][H][W]
   float* pairwise;           // [4][H][W]
   float* beta_out;           // [1] or null
-  // conspicuity recomputed for the adjoint (one recorded frame per stream of the launch)
+  // the recorded conspicuity maps dotted with the saliency adjoint
   const float* gs;           // [Hc][Wc] adjoint of S of the frame
   float* dot;                // [n_cmax_tiles][8] partial sums of gs * C_k
   float* cx;                 // [8] C_k at the frame's argmax of S (ms_tape: its max and argmax)
@@ -166,7 +167,8 @@ struct BatchState {
   const uint8_t* last_rgb;   // frame of the last step (next step's previous frame)
   int32_t cur;
   int32_t tape_cap;          // frames the tape holds (0: no tape); steps >= tape_cap record nothing
-  float* tape_ckpt;          // [tape_cap][4][H_cmin][W_cmin] base channels of level c_min
+  float* tape_fbar;          // [tape_cap][8][Hc][Wc] across-scale sums F-bar
+  float* tape_np;            // [tape_cap][8][4] their N(.) parameters
   float* tape_S;             // [tape_cap][Hc][Wc]
   float* tape_f;             // [tape_cap][H][W] prediction f_t
   float* tape_ms;            // [tape_cap][2] max S and its first argmax

@@ -8,9 +8,10 @@ hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, co
 hipError_t sp_csapply_reserve_lds(size_t bytes);
 hipError_t sp_launch_bwd(int kind, const Job* jobs, int n, const StreamDesc* sds, const BwdIO* bios,
                          const BwdIO* b0, hipStream_t st);
-// Conspicuity recomputed from checkpoints, dotted with each frame's saliency adjoint
-// (per-frame buffers named by ios[stream]: gs, dot, cx, ms_tape).
-hipError_t sp_launch_consp_dot(const Job* jobs, int n, const StreamDesc* sds, const StepIO* ios, hipStream_t st);
+// The recorded conspicuity maps of T steps dotted with each step's saliency adjoint (buffers
+// of step t and stream i named by ios[t * n_streams + i]: fbar, np_tape, gs, dot, cx, ms_tape).
+hipError_t sp_launch_consp_dot(const Job* jobs, int n, const StreamDesc* sds, const StepIO* ios, int n_streams, int T,
+                               hipStream_t st);
 // Adjoint reduction: one workgroup per stream of tab (or the single stream *one when tab
 // is null), shared gains Kd and variances Pd of T steps.
 hipError_t sp_launch_bwd_final(const BwdFin* tab, const BwdFin* one, int n_streams, int T, const double* Kd,

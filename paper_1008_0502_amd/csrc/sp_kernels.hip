@@ -18,17 +18,15 @@
 namespace {
 
 // ---------------------------------------------------------------- stream helpers
-__device__ __forceinline__ const float* base_ptr(const StreamDesc& sd, const float* ckpt, int l) {
-  return (l == sd.c_min && ckpt) ? ckpt : sd.base[l];
-}
+// F-bar of a step: its tape slot when the step is recorded, else the stream's own map.
+__device__ __forceinline__ float* fbar_ptr(const StreamDesc& sd, float* tape) { return tape ? tape : sd.fbar; }
 
 // Channel k (I, RG, BY, O0, O45, O90, O135, M) of level l.
-__device__ __forceinline__ const float* chan_ptr(const StreamDesc& sd, const float* ckpt, int k, int l) {
+__device__ __forceinline__ const float* chan_ptr(const StreamDesc& sd, int k, int l) {
   // selects rather than branches: every operand is a uniform scalar load
   const size_t plane = (size_t)sd.Hl[l] * sd.Wl[l];
   const float* b = sd.base[l];
   const float* g = sd.gab[l];
-  b = (l == sd.c_min && ckpt) ? ckpt : b;
   const bool gabor = (unsigned)(k - 3) < 4u;
   const int idx = k < 3 ? k : (k == 7 ? 3 : k - 3);
   return (gabor ? g : b) + idx * plane;
@@ -465,7 +463,6 @@ __global__ __launch_bounds__(SP_BLOCK) __attribute__((amdgpu_waves_per_eu(8))) v
   const StreamDesc& sd = sds[J.stream];
   const uint8_t* __restrict__ rgb = IOF(rgb);
   const uint8_t* __restrict__ prev = IOF(rgb_prev);
-  float* ckpt = IOF(ckpt);
   const gp<float> pairw = G(IOF(pairwise));
   const int H = sd.H, W = sd.W;
   const int Y0 = 2 * J.y0 - 2, X0 = 2 * J.x0 - 2;
@@ -551,7 +548,7 @@ __global__ __launch_bounds__(SP_BLOCK) __attribute__((amdgpu_waves_per_eu(8))) v
   }
   float beta = 0.f;
   const int H1 = sd.Hl[1], W1 = sd.Wl[1];
-  const gp<float> dst = G((sd.c_min == 1 && ckpt) ? ckpt : sd.base[1]);
+  const gp<float> dst = G(sd.base[1]);
   const size_t plane1 = (size_t)H1 * W1;
   for (int h = 0; h < 2; ++h) {
     if (h == 1 && J.th <= TH / 2) break;
@@ -644,10 +641,6 @@ constexpr int GAB_LDS = GRM * GCM + 4 * GT * (GCM + 1) + 4 * (2 * SP_MAXR + 1);
 constexpr int TAIL_LDS = SP_TAIL_SRC + SP_TAIL_ALT + SP_TAIL_HB + 4 * (2 * SP_MAXR + 1);
 static_assert(DOWN_LDS >= GAB_LDS, "LDS of the small pyramid kernel");
 
-__device__ __forceinline__ gp<float> level_dst(const StreamDesc& sd, float* ckpt, int l) {
-  return G((l == sd.c_min && ckpt) ? ckpt : sd.base[l]);
-}
-
 // The four 1-D Gabor factors in LDS as [4][2*SP_MAXR+1], zero beyond the n = 2R+1
 // taps: the tap loops below run over the full length, unrolled and without branches, so
 // all their LDS reads issue together; a zero tap adds exactly nothing.
@@ -660,11 +653,11 @@ __device__ __forceinline__ void load_taps(const StreamDesc& sd, int n, float* ta
 }
 
 // level a -> a+1 of the 4 base channels for one 16x16 tile of level a+1
-__device__ void down_job(const Job& J, const StreamDesc& sd, float* ckpt, float* smem) {
+__device__ void down_job(const Job& J, const StreamDesc& sd, float* smem) {
   float* F = smem;                 // [4][DR][DR]; then the row pass [4][DR][DT] in its place
   const int l = J.a;
   const int Hs = sd.Hl[l], Ws = sd.Wl[l];
-  const float* src = base_ptr(sd, ckpt, l);
+  const float* src = sd.base[l];
   const size_t splane = (size_t)Hs * Ws;
   const int Y0 = 2 * J.y0 - 2, X0 = 2 * J.x0 - 2;
   const int wf = wave_first();
@@ -700,7 +693,7 @@ __device__ void down_job(const Job& J, const StreamDesc& sd, float* ckpt, float*
   __syncthreads();
   const float* Hb = F;   // channel c's row pass at c * DR * DR, [DR][DT]
   const int Hd = sd.Hl[l + 1], Wd = sd.Wl[l + 1];
-  const gp<float> dst = level_dst(sd, ckpt, l + 1);
+  const gp<float> dst = G(sd.base[l + 1]);
   const size_t plane = (size_t)Hd * Wd;
   const int yy = threadIdx.x / DT, xx = threadIdx.x % DT;
   const int y = J.y0 + yy, x = J.x0 + xx;
@@ -720,14 +713,14 @@ __device__ void down_job(const Job& J, const StreamDesc& sd, float* ckpt, float*
 // RC > 0: built for radius RC (every extent and offset a compile-time constant); RC = 0:
 // any radius, loops unrolled over the zero-padded maximum of taps.
 template <int RC>
-__device__ void gabor_job(const Job& J, const StreamDesc& sd, const float* ckpt, float* smem) {
+__device__ void gabor_job(const Job& J, const StreamDesc& sd, float* smem) {
   constexpr int NT = RC > 0 ? 2 * RC + 1 : 2 * SP_MAXR + 1;
   float* Ir = smem;                            // [RRr][RRc] (flat)
   float* V = Ir + GRM * GCM;                   // [4][GT][GCM+1]
   float* taps = V + 4 * GT * (GCM + 1);        // [4][2*SP_MAXR+1]
   const int l = J.a, R = RC > 0 ? RC : sd.gr, n = 2 * R + 1, RRr = GT + 2 * R, RRc = GW + 2 * R;
   const int Hs = sd.Hl[l], Ws = sd.Wl[l];
-  const float* I = base_ptr(sd, ckpt, l);
+  const float* I = sd.base[l];
   load_taps(sd, n, taps);
   const gp<const float> gI = G(I);
   const int wf = wave_first();
@@ -861,7 +854,7 @@ __device__ void gabor_lds(const float* I, int h, int w, int y0, int nr, float* V
 // intensity chain up to level tid and store that level's Gabor maps for the row band
 // y0 .. y0+th-1, so the Gabor work of the small levels runs in parallel workgroups.
 template <int RC>
-__device__ void tail_job(const Job& J, const StreamDesc& sd, float* ckpt, float* smem) {
+__device__ void tail_job(const Job& J, const StreamDesc& sd, float* smem) {
   float* SA = smem;
   float* SB = SA + SP_TAIL_SRC;
   float* HB = SB + SP_TAIL_ALT;
@@ -872,7 +865,7 @@ __device__ void tail_job(const Job& J, const StreamDesc& sd, float* ckpt, float*
   if (gab) load_taps(sd, nt, taps);
   int cH = sd.Hl[L0], cW = sd.Wl[L0];
   {
-    const float* src = base_ptr(sd, ckpt, L0) + (size_t)ch * cH * cW;
+    const float* src = sd.base[L0] + (size_t)ch * cH * cW;
     const int wf = wave_first();
     for (int i0 = 0; i0 + (int)threadIdx.x < cH * cW; i0 += SP_BLOCK)
       lds_load_u(SA + i0 + wf, G(src), (uint32_t)(i0 + threadIdx.x) * 4u);
@@ -893,7 +886,7 @@ __device__ void tail_job(const Job& J, const StreamDesc& sd, float* ckpt, float*
       HB[i] = acc;
     }
     __syncthreads();
-    const gp<float> dst = gab ? nullptr : level_dst(sd, ckpt, l + 1) + (size_t)ch * nH * nW;
+    const gp<float> dst = gab ? nullptr : G(sd.base[l + 1]) + (size_t)ch * nH * nW;
     Walk2 wk2(threadIdx.x, nW);
     for (int i = threadIdx.x; i < nH * nW; i += SP_BLOCK, wk2.next()) {
       const int r = wk2.r, j = wk2.c;
@@ -923,13 +916,12 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pyr(
   __shared__ float smem[BIG ? TAIL_LDS : DOWN_LDS];
   const Job J = jobs[blockIdx.x];
   const StreamDesc& sd = sds[J.stream];
-  float* ckpt = IOF(ckpt);
   if (J.kind == JOB_DOWN) {
-    down_job(J, sd, ckpt, smem);
+    down_job(J, sd, smem);
   } else if (J.kind == JOB_GABOR) {
-    gabor_job<RC>(J, sd, ckpt, smem);
+    gabor_job<RC>(J, sd, smem);
   } else if (BIG && (J.kind == JOB_TAIL || J.kind == JOB_TAILGAB)) {
-    tail_job<RC>(J, sd, ckpt, smem);
+    tail_job<RC>(J, sd, smem);
   }
 }
 
@@ -969,13 +961,12 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csstats(const Job* __restrict__ jo
   __shared__ float sur[4][SP_NCH][CS_F * CS_F];
   const Job J = jobs[blockIdx.x];
   const StreamDesc& sd = sds[J.stream];
-  const float* ckpt = IOF(ckpt);
   const int c = J.a, Hc = sd.Hl[c], Wc = sd.Wl[c];
   const int lane = lane_id(), w = wave_id();
   // stage the centre tile of all channels
   const float* cptr[SP_NCH];
 #pragma unroll
-  for (int k = 0; k < SP_NCH; ++k) cptr[k] = chan_ptr(sd, ckpt, k, c);
+  for (int k = 0; k < SP_NCH; ++k) cptr[k] = chan_ptr(sd, k, c);
   for (int i = threadIdx.x; i < CS_T * CS_T; i += SP_BLOCK) {
     const int yy = i / CS_T, xx = i - yy * CS_T;
     const size_t o = (size_t)min(J.y0 + yy, Hc - 1) * Wc + min(J.x0 + xx, Wc - 1);
@@ -994,7 +985,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csstats(const Job* __restrict__ jo
     for (int i = threadIdx.x; i < SP_NCH * CS_F * CS_F; i += SP_BLOCK) {
       const int k = i / (CS_F * CS_F), r = i - k * (CS_F * CS_F), fy = r / CS_F, fx = r - fy * CS_F;
       if (fy < f.h && fx < f.w)
-        lds_load(&sur[q][0][0] + i, chan_ptr(sd, ckpt, k, s) + (size_t)(f.y0 + fy) * Ws + f.x0 + fx);
+        lds_load(&sur[q][0][0] + i, chan_ptr(sd, k, s) + (size_t)(f.y0 + fy) * Ws + f.x0 + fx);
     }
   }
   lds_wait();
@@ -1117,7 +1108,6 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
   __shared__ float wacc[4][NC][3];
   const Job J = jobs[blockIdx.x];
   const StreamDesc& sd = sds[J.stream];
-  const float* ckpt = IOF(ckpt);
   const int k0 = J.a, cm = sd.c_max;
   const int Hm = sd.Hl[cm], Wm = sd.Wl[cm];
   const CaLayout L = csapply_layout(sd.pc, sd.ps, sd.n_pairs, cm);
@@ -1144,7 +1134,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
     const int n = rr.n * cc.n;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const float* Xc = chan_ptr(sd, ckpt, k0 + j, c);
+      const float* Xc = chan_ptr(sd, k0 + j, c);
       float* X = dyn + j * CS + xoff;
       Walk2 wk(threadIdx.x, cc.n);
       for (int i = threadIdx.x; i < n; i += SP_BLOCK, wk.next())
@@ -1166,7 +1156,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
       const Foot f = footprint(rr.lo, rr.n, cc.lo, cc.n, s - c, sd.Hl[s], Ws);
 #pragma unroll
       for (int j = 0; j < NC; ++j) {
-        const float* Xs = chan_ptr(sd, ckpt, k0 + j, s);
+        const float* Xs = chan_ptr(sd, k0 + j, s);
         float* dst = dyn + j * CS + off;
         Walk2 wk(threadIdx.x, f.w);
         for (int i = threadIdx.x; i < f.h * f.w; i += SP_BLOCK, wk.next())
@@ -1312,7 +1302,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
     float wmn = INFINITY, wmx = -INFINITY;
     if (act) {
       const float v = valid ? fb[j][yy * CA_T + xx] : 0.f;
-      if (valid) G(sd.fbar)[(size_t)(k0 + j) * Hm * Wm + (size_t)(J.y0 + yy) * Wm + J.x0 + xx] = v;
+      if (valid) G(fbar_ptr(sd, IOF(fbar)))[(size_t)(k0 + j) * Hm * Wm + (size_t)(J.y0 + yy) * Wm + J.x0 + xx] = v;
       wmn = wave_reduce<OpMin>(valid ? v : INFINITY);
       wmx = wave_reduce<OpMax>(valid ? v : -INFINITY);
     }
@@ -1389,7 +1379,6 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg(const Job* __restrict__ jobs,
   __shared__ float4 rtap[2 * SP_CA_T + 3];       // per region row: two table offsets and a weight
   const Job J = jobs[blockIdx.x];
   const StreamDesc& sd = sds[J.stream];
-  const float* ckpt = IOF(ckpt);
   const int k0 = J.a, cm = sd.c_max;
   const int Hm = sd.Hl[cm], Wm = sd.Wl[cm];
   // the pairs as (r, d) = (c_max - c, s - c): compile-time constants for a known set
@@ -1441,7 +1430,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg(const Job* __restrict__ jobs,
     bool vec = (Wc & 3) == 0;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      Xc[j] = G(chan_ptr(sd, ckpt, k0 + j, c));
+      Xc[j] = G(chan_ptr(sd, k0 + j, c));
       vec = vec && (reinterpret_cast<uintptr_t>(Xc[j]) & 15) == 0;
     }
     if (vec) {
@@ -1474,7 +1463,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg(const Job* __restrict__ jobs,
       const int cap = csapply_foot_cap(r, d);
       gp<const float> Xs[NC];
 #pragma unroll
-      for (int j = 0; j < NC; ++j) Xs[j] = G(chan_ptr(sd, ckpt, k0 + j, s));
+      for (int j = 0; j < NC; ++j) Xs[j] = G(chan_ptr(sd, k0 + j, s));
       Walk2 wk(threadIdx.x, f.w);
       for (int i0 = 0; i0 + (int)threadIdx.x < f.h * f.w; i0 += SP_BLOCK, wk.next()) {
         const uint32_t ob = ((uint32_t)(f.y0 + wk.r) * (uint32_t)Ws + (uint32_t)(f.x0 + wk.c)) * 4u;
@@ -1735,7 +1724,6 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg1(const Job* __restrict__ jobs,
   __shared__ float wred[4][NC][3];
   const Job J = jobs[blockIdx.x];
   const StreamDesc& sd = sds[J.stream];
-  const float* ckpt = IOF(ckpt);
   const int k0 = J.a, cm = sd.c_max, c1 = cm - 1;
   const int Hm = sd.Hl[cm], Wm = sd.Wl[cm], H1 = sd.Hl[c1], W1 = sd.Wl[c1];
   const int y0 = J.y0, x0 = J.x0, ry0 = 2 * y0 - 2, rx0 = 2 * x0 - 2;
@@ -1751,7 +1739,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg1(const Job* __restrict__ jobs,
     bool vec = (W1 & 3) == 0 && rx0 >= 2 && rx0 + PW - 2 <= W1;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      Xc[j] = G(chan_ptr(sd, ckpt, k0 + j, c1));
+      Xc[j] = G(chan_ptr(sd, k0 + j, c1));
       vec = vec && (reinterpret_cast<uintptr_t>(Xc[j]) & 15) == 0;
     }
     if (vec) {
@@ -1785,7 +1773,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg1(const Job* __restrict__ jobs,
     bool vec = (Wm & 3) == 0 && x0 + T <= Wm;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      Xc[j] = G(chan_ptr(sd, ckpt, k0 + j, cm));
+      Xc[j] = G(chan_ptr(sd, k0 + j, cm));
       vec = vec && (reinterpret_cast<uintptr_t>(Xc[j]) & 15) == 0;
     }
     if (vec) {
@@ -1810,7 +1798,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg1(const Job* __restrict__ jobs,
       const int i = tid / fe(p), e = tid - i * fe(p);
       const uint32_t ob = ((uint32_t)clampi(oy + i, 0, Hs - 1) * (uint32_t)Ws + (uint32_t)clampi(ox + e, 0, Ws - 1)) * 4u;
 #pragma unroll
-      for (int j = 0; j < NC; ++j) lds_load_u(FP + j * FN + fo(p) + wf, G(chan_ptr(sd, ckpt, k0 + j, s)), ob);
+      for (int j = 0; j < NC; ++j) lds_load_u(FP + j * FN + fo(p) + wf, G(chan_ptr(sd, k0 + j, s)), ob);
     }
   }
   if (tid < 4 * N1) {
@@ -2137,7 +2125,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csmix(const Job* __restrict__ jobs
       }
     }
   }
-  const gp<float> fbar = G(sd.fbar);
+  const gp<float> fbar = G(fbar_ptr(sd, IOF(fbar)));
 #pragma unroll
   for (int k = 0; k < SP_NCH; ++k) {
     if (valid) fbar[(size_t)k * plane + o] = acc[k];
@@ -2215,8 +2203,11 @@ __global__ __launch_bounds__(SP_BLOCK) void k_consp(const Job* __restrict__ jobs
   const uint32_t ob = (uint32_t)o * 4u;
   float fv[SP_NCH];
 #pragma unroll
-  for (int k = 0; k < SP_NCH; ++k) fv[k] = *at_bytes(G((const float*)sd.fbar) + k * plane, ob);
+  for (int k = 0; k < SP_NCH; ++k) fv[k] = *at_bytes(G((const float*)fbar_ptr(sd, IOF(fbar))) + k * plane, ob);
   consp_nparams(sd, np);
+  // a recorded step keeps F-bar's N(.) parameters beside the map, for the adjoint
+  const gp<float> np_tape = G(IOF(np_tape));
+  if (np_tape && J.tid == 0 && (int)threadIdx.x < SP_NCH) store_np(np_tape + 4 * threadIdx.x, np[threadIdx.x]);
   float S = 0.f;
 #pragma unroll
   for (int k = 0; k < SP_NCH; ++k) {
@@ -2653,31 +2644,41 @@ __global__ __launch_bounds__(SP_BLOCK) void k_bwd_gs(const Job* __restrict__ job
   B.gs[(size_t)Y * Wm + X] = acc;
 }
 
-// Recomputed conspicuity maps dotted with the adjoint g_s of each frame (one recorded
-// frame per stream of the launch, its buffers named by the stream's StepIO): partial
-// sums of g_s * C_k per tile, and C_k at the frame's argmax.
+// The recorded conspicuity maps of step t0 + blockIdx.y dotted with that step's adjoint g_s
+// (ios: [T][n_streams]): partial sums of g_s * C_k per tile, and C_k at the step's argmax.
+// C_k = N(F-bar_k) from the tape's F-bar and N(.) parameters (the values the forward took, so
+// the same bits as a recomputation, which cost 9.7 of the 37.2 ms of 16 clips of 120 frames at
+// 640x480).  Memory-bound: 36 bytes per c_max pixel and step; the eight sums share one barrier.
 __global__ __launch_bounds__(SP_BLOCK) void k_consp_dot(const Job* __restrict__ jobs,
                                                         const StreamDesc* __restrict__ sds,
-                                                        const StepIO* __restrict__ ios) {
-  __shared__ float sh4[4];
-  __shared__ NParams np[SP_NCH];
+                                                        const StepIO* __restrict__ ios, int n_streams) {
+  __shared__ float wsum[4][SP_NCH];
   const Job J = jobs[blockIdx.x];
   const StreamDesc& sd = sds[J.stream];
-  const StepIO& io = ios[J.stream];
-  consp_nparams(sd, np);
+  const StepIO& io = ios[(size_t)blockIdx.y * n_streams + J.stream];
   const int cm = sd.c_max, Hm = sd.Hl[cm], Wm = sd.Wl[cm];
   const size_t plane = (size_t)Hm * Wm;
   const int yy = threadIdx.x / CA_T, xx = threadIdx.x % CA_T;
   const int y = J.y0 + yy, x = J.x0 + xx;
   const bool valid = yy < J.th && xx < J.tw && y < Hm && x < Wm;
-  const size_t o = (size_t)min(y, Hm - 1) * Wm + min(x, Wm - 1);
-  const float g = valid ? io.gs[o] : 0.f;
+  const uint32_t o = (uint32_t)min(y, Hm - 1) * (uint32_t)Wm + (uint32_t)min(x, Wm - 1);
+  const gp<const float> fbar = G((const float*)io.fbar), npt = G((const float*)io.np_tape);
+  float fv[SP_NCH];
+#pragma unroll
+  for (int k = 0; k < SP_NCH; ++k) fv[k] = *at_bytes(fbar + k * plane, o * 4u);
+  const float g = valid ? *at_bytes(G(io.gs), o * 4u) : 0.f;
   const int xs = __float_as_int(io.ms_tape[1]);
+#pragma unroll
   for (int k = 0; k < SP_NCH; ++k) {
-    const float Ck = napply(np[k], sd.fbar[k * plane + o]);
-    const float tot = block_reduce<OpSum>(valid ? g * Ck : 0.f, sh4);
-    if (threadIdx.x == 0) io.dot[(size_t)J.tid * SP_NCH + k] = tot;
+    const float Ck = napply(load_np(npt + 4 * k), fv[k]);
+    const float tot = wave_reduce<OpSum>(valid ? g * Ck : 0.f);
+    if (lane_id() == 0) wsum[wave_id()][k] = tot;
     if (valid && (int)o == xs) io.cx[k] = Ck;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < SP_NCH) {
+    const int k = threadIdx.x;
+    io.dot[(size_t)J.tid * SP_NCH + k] = (wsum[0][k] + wsum[1][k]) + (wsum[2][k] + wsum[3][k]);
   }
 }
 
@@ -2827,17 +2828,19 @@ __device__ void batch_begin_stream(int i, BatchState* __restrict__ st, const Str
   io->pi_prev = s.cur ? s.pi[1] : s.pi[0];
   io->pi_next = s.cur ? s.pi[0] : s.pi[1];
   if (s.t < s.tape_cap) {
-    // recorded step: level c_min goes straight to its checkpoint slot; S, f, (max S,
-    // argmax) and the prior are kept for the adjoint
+    // recorded step: F-bar goes straight to its tape slot, with its N(.) parameters; S, f,
+    // (max S, argmax) and the prior are kept for the adjoint
     const StreamDesc& sd = sds[i];
-    const size_t k = (size_t)s.t, hw = (size_t)sd.H * sd.W;
-    io->ckpt = s.tape_ckpt + k * 4 * (size_t)sd.Hl[sd.c_min] * sd.Wl[sd.c_min];
-    io->S_tape = s.tape_S + k * (size_t)sd.Hl[sd.c_max] * sd.Wl[sd.c_max];
+    const size_t k = (size_t)s.t, hw = (size_t)sd.H * sd.W, hwc = (size_t)sd.Hl[sd.c_max] * sd.Wl[sd.c_max];
+    io->fbar = s.tape_fbar + k * SP_NCH * hwc;
+    io->np_tape = s.tape_np + k * 4 * SP_NCH;
+    io->S_tape = s.tape_S + k * hwc;
     io->f_tape = s.tape_f + k * hw;
     io->ms_tape = s.tape_ms + 2 * k;
     io->prior_out = s.tape_pi + k * hw;
   } else {
-    io->ckpt = nullptr;
+    io->fbar = nullptr;
+    io->np_tape = nullptr;
     io->S_tape = nullptr;
     io->f_tape = nullptr;
     io->ms_tape = nullptr;
@@ -3004,10 +3007,17 @@ hipError_t sp_launch_bwd(int kind, const Job* jobs, int n, const StreamDesc* sds
   return chk();
 }
 
-hipError_t sp_launch_consp_dot(const Job* jobs, int n, const StreamDesc* sds, const StepIO* ios, hipStream_t st) {
+hipError_t sp_launch_consp_dot(const Job* jobs, int n, const StreamDesc* sds, const StepIO* ios, int n_streams, int T,
+                               hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_consp_dot, dim3(n), dim3(SP_BLOCK), 0, st, jobs, sds, ios);
-  return chk();
+  constexpr int MAXT = 32768;   // steps per launch (grid y)
+  for (int t0 = 0; t0 < T; t0 += MAXT) {
+    hipLaunchKernelGGL(k_consp_dot, dim3(n, T - t0 < MAXT ? T - t0 : MAXT), dim3(SP_BLOCK), 0, st, jobs, sds,
+                       ios + (size_t)t0 * n_streams, n_streams);
+    const hipError_t e = chk();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t sp_launch_bwd_final(const BwdFin* tab, const BwdFin* one, int n_streams, int T, const double* Kd,
