@@ -294,6 +294,22 @@ void pyramid_stages(const Geo& g, int s, int lo, std::vector<std::vector<Job>>& 
   if (g.used & (1u << L0)) add_tiles_wh(fin, s, L0, g.Hl[L0], g.Wl[L0], 16, 32, JOB_GABOR);
 }
 
+// Reverse steps of the adjoint: up to this c_max one launch sweeps level 0 and gathers dL/dS
+// (the strip of 2^c_max - 1 pixels a 32x32 tile computes besides its own stays below half the
+// tile); above it two launches on 16x16 tiles.
+constexpr int kSweepMax = 3;
+
+void add_sweep_tiles(std::vector<Job>& v, int stream, const Geo& g) {
+  if (g.c_max <= kSweepMax)
+    add_tiles_wh(v, stream, 0, g.H, g.W, SP_SWEEP_T, SP_SWEEP_T, JOB_BWD_NU);
+  else
+    add_tiles(v, stream, 0, g.H, g.W);
+}
+int n_sweep_tiles(const Geo& g) {
+  const int e = g.c_max <= kSweepMax ? SP_SWEEP_T : kTile;
+  return ((g.H + e - 1) / e) * ((g.W + e - 1) / e);
+}
+
 // ---------------------------------------------------------------- device memory layout
 struct Bump {
   char* base = nullptr;   // null during the sizing pass
@@ -1017,7 +1033,7 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
     return fail(SP_EHIP, "hipGetDevice failed (no GPU?)");
   }
   c->cap = p->record_tape;
-  c->n_lvl0_tiles = ntiles(H, W);
+  c->n_lvl0_tiles = n_sweep_tiles(g);
   const int Hc = g.Hl[g.c_max], Wc = g.Wl[g.c_max];
   const size_t HW = (size_t)H * W;
   // two passes over the layout: size, then place
@@ -1050,7 +1066,7 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
       c->P_tape = b.take<double>(c->cap);
       c->nu[0] = b.take<float>(HW);
       c->nu[1] = b.take<float>(HW);
-      c->gu = b.take<float>(HW);
+      if (g.c_max > kSweepMax) c->gu = b.take<float>(HW);
       c->gs_all = b.take<float>((size_t)c->cap * Hc * Wc);
       c->gk_part = b.take<float>((size_t)c->cap * c->n_lvl0_tiles);
       c->dot_part = b.take<float>((size_t)c->cap * c->h_sd.n_cmax_tiles * SP_NCH);
@@ -1146,11 +1162,11 @@ int ctx_build_tables(sp_ctx* c) {
     add_tiles_wh(v, 0, 0, H, W, SP_DT_T, SP_DT_T, JOB_DT);
     c->dt.push_back(c->jobs.add(JOB_DT, 0, order(v), 1));
     v.clear();
-    add_tiles(v, 0, 0, H, W);
-    c->bwd.push_back(c->jobs.add(JOB_BWD_NU, 0, v, 1));
+    add_sweep_tiles(v, 0, g);
+    c->bwd.push_back(c->jobs.add(JOB_BWD_NU, g.c_max <= kSweepMax ? g.c_max : 0, v, 1));
     v.clear();
     add_tiles(v, 0, 0, Hc, Wc);
-    c->bwd.push_back(c->jobs.add(JOB_BWD_GS, 0, v, 1));
+    if (g.c_max > kSweepMax) c->bwd.push_back(c->jobs.add(JOB_BWD_GS, 0, v, 1));
     c->dot = c->jobs.add(JOB_CONSP_DOT, 0, v, 1);
   }
   return upload_jobs(c->jobs, c->stream);
@@ -1667,7 +1683,7 @@ int saliency_backward(sp_ctx* c, const float* grad_prior, int32_t T, float* grad
     b.t = t;
     for (const Phase& ph : c->bwd) {
       hipError_t e = timed(c, ph.kind, [&] {
-        return sp_launch_bwd(ph.kind, c->jobs.dev + ph.off, ph.n, c->d_sd, nullptr, &b, c->stream);
+        return sp_launch_bwd(ph.kind, ph.flag, c->jobs.dev + ph.off, ph.n, c->d_sd, nullptr, &b, c->stream);
       });
       if (e != hipSuccess) return fail(SP_EHIP, "adjoint launch: %s", hipGetErrorString(e));
     }
@@ -1965,27 +1981,33 @@ struct sp_batch {
   char* d_bstage = nullptr;                   // gains, variances, [cap][n] BwdIO, [n] BwdFin
   char* d_lstage = nullptr;                   // [n] LossIO
   HostStage bstage, lstage;                   // pinned host copies of the two tables
-  std::vector<Phase> bwd;                     // adjoint sweep (2 launches per step)
+  std::vector<Phase> bwd;                     // reverse step
   Phase dot;                                  // recorded conspicuity dotted with the saliency adjoint
   int loss_nblk = 1024;
 };
 
 namespace {
 
-// Job tables of the batched adjoint: the level-0 sweep, the up-sample transpose and the
-// conspicuity maps of every stream (one launch each; the first two per reverse step).
+// Job tables of the batched adjoint: the reverse step (one launch per c_max up to kSweepMax
+// over its streams; the sweep and the up-sample transpose of the others) and the conspicuity
+// maps of every stream.
 void batch_adjoint_tables(sp_batch* b) {
   const int n = b->n;
-  std::vector<Job> nu, gs;
-  for (int i = 0; i < n; ++i) {
-    const Geo& g = b->geo[i];
-    add_tiles(nu, i, 0, g.H, g.W);
-    add_tiles(gs, i, 0, g.Hl[g.c_max], g.Wl[g.c_max]);
-  }
   b->bwd.clear();
-  b->bwd.push_back(b->jobs.add(JOB_BWD_NU, 0, nu, n));
-  b->bwd.push_back(b->jobs.add(JOB_BWD_GS, 0, gs, n));
-  b->dot = b->jobs.add(JOB_CONSP_DOT, 0, gs, n);
+  std::vector<Job> dot;
+  for (int i = 0; i < n; ++i) add_tiles(dot, i, 0, b->geo[i].Hl[b->geo[i].c_max], b->geo[i].Wl[b->geo[i].c_max]);
+  for (int cm = 0; cm <= kSweepMax; ++cm) {   // 0: the streams above kSweepMax
+    std::vector<Job> nu, gs;
+    for (int i = 0; i < n; ++i) {
+      const Geo& g = b->geo[i];
+      if ((g.c_max <= kSweepMax ? g.c_max : 0) != cm) continue;
+      add_sweep_tiles(nu, i, g);
+      if (cm == 0) add_tiles(gs, i, 0, g.Hl[g.c_max], g.Wl[g.c_max]);
+    }
+    if (!nu.empty()) b->bwd.push_back(b->jobs.add(JOB_BWD_NU, cm, nu, n));
+    if (!gs.empty()) b->bwd.push_back(b->jobs.add(JOB_BWD_GS, 0, gs, n));
+  }
+  b->dot = b->jobs.add(JOB_CONSP_DOT, 0, dot, n);
 }
 
 // Drops the graph of several steps (recaptured by the next sp_batch_steps).
@@ -2305,10 +2327,10 @@ int sp_batch_create(const sp_params* p, int32_t n, const int32_t* H, const int32
         s.tape_ms = bm.take<float>(cap * 2);
         s.tape_pi = bm.take<float>(cap * hw);
         BatchAdj& a = b->adj[i];
-        a.n_lvl0_tiles = ntiles(g.H, g.W);
+        a.n_lvl0_tiles = n_sweep_tiles(g);
         a.nu[0] = bm.take<float>(hw);
         a.nu[1] = bm.take<float>(hw);
-        a.gu = bm.take<float>(hw);
+        if (g.c_max > kSweepMax) a.gu = bm.take<float>(hw);
         a.gs_all = bm.take<float>(cap * plane);
         a.gk_part = bm.take<float>(cap * a.n_lvl0_tiles);
         a.dot_part = bm.take<float>(cap * b->h_sd[i].n_cmax_tiles * SP_NCH);
@@ -2751,12 +2773,11 @@ int sp_batch_backward(sp_batch* b, const float* const* grad_prior, int32_t T, fl
   const double* dPd = dKd + b->cap;
   const BwdIO* dbio = reinterpret_cast<const BwdIO*>(dPd + b->cap);
   const BwdFin* dfin = reinterpret_cast<const BwdFin*>(dbio + (size_t)b->cap * n);
-  // reverse sweep: per step one launch of the level-0 adjoint and one of the up-sample
-  // transpose, each over every stream
+  // reverse sweep, every stream side by side
   for (int t = T - 1; t >= 0; --t)
     for (const Phase& ph : b->bwd) {
       hipError_t e = b->prof.timed(b->stream, ph.kind, [&] {
-        return sp_launch_bwd(ph.kind, b->jobs.dev + ph.off, ph.n, b->d_sd, dbio + (size_t)t * n, nullptr, b->stream);
+        return sp_launch_bwd(ph.kind, ph.flag, b->jobs.dev + ph.off, ph.n, b->d_sd, dbio + (size_t)t * n, nullptr, b->stream);
       });
       if (e != hipSuccess) return fail(SP_EHIP, "adjoint launch: %s", hipGetErrorString(e));
     }

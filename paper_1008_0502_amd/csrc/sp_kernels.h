@@ -6,7 +6,7 @@
 hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, const StepIO* ios,
                      const StepIO* io0, int flag, const float* aux, hipStream_t st, size_t lds = 0);
 hipError_t sp_csapply_reserve_lds(size_t bytes);
-hipError_t sp_launch_bwd(int kind, const Job* jobs, int n, const StreamDesc* sds, const BwdIO* bios,
+hipError_t sp_launch_bwd(int kind, int flag, const Job* jobs, int n, const StreamDesc* sds, const BwdIO* bios,
                          const BwdIO* b0, hipStream_t st);
 // The recorded conspicuity maps of T steps dotted with each step's saliency adjoint (buffers
 // of step t and stream i named by ios[t * n_streams + i]: fbar, np_tape, gs, dot, cx, ms_tape).

@@ -2644,6 +2644,196 @@ __global__ __launch_bounds__(SP_BLOCK) void k_bwd_gs(const Job* __restrict__ job
   B.gs[(size_t)Y * Wm + X] = acc;
 }
 
+// One reverse step in one launch (c_max = CM <= 3): the level-0 adjoint of a 32x32 tile
+// and, from the same values held in LDS, the transposed up-sample of the c_max pixels the
+// tile owns.  A c_max pixel X gathers level-0 pixels sc X - sc + 1 .. sc X + sc - 1
+// (sc = 2^CM), so the tile also computes a strip of sc - 1 pixels above and to its left
+// (35x35 pixels for c_max 2, 1.20 of the tile); nothing of that strip is stored.
+// Bound by memory: 16 bytes per pixel (dL/dprior, f and nu_{t+1} read, nu_t written) against
+// 28 and a second launch when the observation's adjoint went through memory between a
+// 16x16-tile sweep and a gather of 49 taps per c_max pixel.  32x32 tiles: 300 workgroups for one
+// 640x480 stream (16-row tiles stage 1.6 times the pixels they own); at c_max 4 the strip makes
+// the region 2.2 times the tile, so the two launches above stay from there on.
+// Reverse step of 16 streams at 640x480: 76 us in two launches, 36 us here; of one stream
+// 16.9 us, 10.6 us here.
+constexpr int SW_T = SP_SWEEP_T;
+
+// Weights of the transposed clamp-to-edge binomial at output y: w[2 + d] for source y + d
+// (0 outside the frame); only the frame's first and last line differ from the plain taps.
+__device__ __forceinline__ void sweep_taps(int y, int n, float (&w)[5]) {
+#pragma unroll
+  for (int d = -2; d <= 2; ++d) w[d + 2] = (y + d >= 0 && y + d < n) ? binom(d) : 0.f;
+  if (y == 0) {
+    w[2] += kB1 + kB0;
+    w[3] += n > 1 ? kB0 : 0.f;
+  }
+  if (y == n - 1) {
+    w[2] += kB1 + kB0;
+    w[1] += n > 1 ? kB0 : 0.f;
+  }
+}
+
+template <int CM>
+__global__ __launch_bounds__(SP_BLOCK) void k_bwd_sweep(const Job* __restrict__ jobs,
+                                                        const StreamDesc* __restrict__ sds,
+                                                        const BwdIO* __restrict__ bios, BwdIO b0) {
+  constexpr int SC = 1 << CM, HL = SC - 1;
+  constexpr int N = SW_T + HL;                    // region edge
+  constexpr int NS = N + 4;                       // staged rows of nu_{t+1}
+  constexpr int XO = (HL + 2 + 3) & ~3;           // staged columns start at x0 - XO (whole quads)
+  constexpr int PW = (XO + SW_T + 2 + 3) & ~3;    // their row stride
+  constexpr int G_ = SP_BLOCK / N;                // a thread keeps one region column and steps G_ rows
+  constexpr int NR = (N + G_ - 1) / G_, NH = (NS + G_ - 1) / G_;
+  constexpr int XT = SW_T / SC, FE = XT + 2;      // c_max pixels of the tile; staged saliency edge
+  __shared__ __align__(16) float reg[NS * PW];    // nu_{t+1}, then the observation's adjoint [N][N]
+  __shared__ float hb[NS * N];                    // its row pass, then the up-sample's row sums [N][XT]
+  __shared__ float Sl[FE * FE];
+  __shared__ double shd[4];
+  static_assert(NS * PW >= N * N && N >= XT, "reused buffers");
+  const Job J = jobs[blockIdx.x];
+  const StreamDesc& sd = sds[J.stream];
+  const BwdIO& B = bios ? bios[J.stream] : b0;
+  const int H = sd.H, W = sd.W, Hm = sd.Hl[CM], Wm = sd.Wl[CM];
+  const gp<const float> nun = G(B.nu_next), grad = G(B.grad), f = G(B.f);
+  const bool carry = (B.nu_next != nullptr) && (B.carry != 0.f);
+  const int ys = J.y0 - HL - 2, xs = J.x0 - XO;
+  const int wf = wave_first();
+  if (carry) {
+    const bool quads = ys >= 0 && ys + NS <= H && xs >= 0 && xs + PW <= W && (W & 3) == 0 &&
+                       (reinterpret_cast<uintptr_t>(B.nu_next) & 15) == 0;
+    if (quads) {
+      constexpr int NQ = NS * (PW / 4);
+#pragma unroll
+      for (int q0 = 0; q0 < NQ; q0 += SP_BLOCK) {
+        const int q = q0 + (int)threadIdx.x;
+        if (q < NQ) {
+          const int r = q / (PW / 4), c = q - r * (PW / 4);
+          lds_load4_u(reg + 4 * (q0 + wf), nun, ((uint32_t)(ys + r) * (uint32_t)W + (uint32_t)(xs + 4 * c)) * 4u);
+        }
+      }
+    } else {
+      // pixels outside the frame are zero (not a clamped copy: 0 weights would turn an
+      // infinite gradient into NaN)
+      for (int i = threadIdx.x; i < NS * PW; i += SP_BLOCK) {
+        const int r = i / PW, c = i - r * PW, y = ys + r, x = xs + c;
+        const float v = *at_bytes(nun, ((uint32_t)clampi(y, 0, H - 1) * (uint32_t)W + (uint32_t)clampi(x, 0, W - 1)) * 4u);
+        reg[i] = ((unsigned)y < (unsigned)H && (unsigned)x < (unsigned)W) ? v : 0.f;
+      }
+    }
+  }
+  // saliency samples around the tile, rows J.y0 / SC - 1 .., clamped (a replicated row is what
+  // clamped sampling reads)
+  const int Y0 = J.y0 >> CM, X0 = J.x0 >> CM;
+  for (int i = threadIdx.x; i < FE * FE; i += SP_BLOCK) {
+    const int r = i / FE, c = i - r * FE;
+    Sl[i] = *at_bytes(G(B.S), ((uint32_t)clampi(Y0 - 1 + r, 0, Hm - 1) * (uint32_t)Wm +
+                               (uint32_t)clampi(X0 - 1 + c, 0, Wm - 1)) * 4u);
+  }
+  // the thread's column: its gradients (and f on owned pixels) are requested at once
+  const int g = threadIdx.x / N, j = threadIdx.x - g * N;
+  const int x = J.x0 - HL + j;
+  const bool col = g < G_ && (unsigned)x < (unsigned)W;
+  const uint32_t xc = (uint32_t)clampi(x, 0, W - 1);
+  float gr[NR], fv[NR];
+#pragma unroll
+  for (int k = 0; k < NR; ++k) {
+    const uint32_t ob = ((uint32_t)clampi(J.y0 - HL + g + G_ * k, 0, H - 1) * (uint32_t)W + xc) * 4u;
+    gr[k] = *at_bytes(grad, ob);
+    fv[k] = B.f ? *at_bytes(f, ob) : 0.f;
+  }
+  const float m = G(B.ms)[0];
+  lds_wait();
+  __syncthreads();
+  if (carry) {
+    if (g < G_) {
+      float w[5];
+      sweep_taps(x, W, w);
+#pragma unroll
+      for (int k = 0; k < NH; ++k) {
+        const int r = g + G_ * k;
+        if (r < NS) {
+          const float* p = reg + r * PW + (XO - HL) + j;
+          float acc = 0.f;
+#pragma unroll
+          for (int d = 0; d < 5; ++d) acc += p[d - 2] * w[d];
+          hb[r * N + j] = acc;
+        }
+      }
+    }
+    __syncthreads();
+  }
+  const bool flat = !(m > sd.flat_tol);
+  const float rm = 1.f / m;
+  const gp<float> nu_out = G(B.nu_out);
+  double contrib = 0.0;
+  const Tap tx = bilinear_tap(min(max(x, 0), W - 1), CM, Wm);
+#pragma unroll
+  for (int k = 0; k < NR; ++k) {
+    const int r = g + G_ * k, y = J.y0 - HL + r;
+    if (g >= G_ || r >= N) continue;
+    float gu = 0.f;
+    if (col && (unsigned)y < (unsigned)H) {
+      float nu = gr[k];
+      if (carry) {
+        float w[5];
+        sweep_taps(y, H, w);
+        float acc = 0.f;
+#pragma unroll
+        for (int d = 0; d < 5; ++d) acc += hb[(r + d) * N + j] * w[d];
+        nu += B.carry * acc;
+      }
+      const bool ring = on_border(y, x, H, W, sd.border);
+      const float nut = ring ? 0.f : nu;
+      float q = 0.5f;
+      if (!flat) {
+        const Tap ty = bilinear_tap(y, CM, Hm);
+        const float* r0 = Sl + (ty.i0 - (Y0 - 1)) * FE - (X0 - 1);
+        const float* r1 = Sl + (ty.i1 - (Y0 - 1)) * FE - (X0 - 1);
+        const float top = (1.f - tx.w) * r0[tx.i0] + tx.w * r0[tx.i1];
+        const float bot = (1.f - tx.w) * r1[tx.i0] + tx.w * r1[tx.i1];
+        const float u = ((1.f - ty.w) * top + ty.w * bot) * rm;
+        q = fminf(fmaxf(u, sd.eps), 1.f - sd.eps);
+        if (u > sd.eps && u < 1.f - sd.eps && !ring) gu = B.K * nut;
+      }
+      if (ring) q = sd.eps;
+      if (r >= HL && j >= HL) {   // owned
+        if (B.f) contrib += (double)(nut * (q - fv[k]));
+        *at_bytes(nu_out, ((uint32_t)y * (uint32_t)W + (uint32_t)x) * 4u) = nut;
+      }
+    }
+    reg[r * N + j] = gu;   // nu_{t+1} is no longer read
+  }
+  contrib = wave_sum_d(contrib);
+  if (lane_id() == 0) shd[wave_id()] = contrib;
+  __syncthreads();
+  if (threadIdx.x == 0) B.gk_part[J.tid] = (float)((shd[0] + shd[1]) + (shd[2] + shd[3]));
+  // transposed up-sample: pixel sc X + k weighs (sc - |k|) / sc, or 1 beyond the last sample
+  for (int i = threadIdx.x; i < N * XT; i += SP_BLOCK) {
+    const int r = i / XT, X = i - r * XT;
+    const bool last = X0 + X == Wm - 1;
+    const float* p = reg + r * N + SC * X;
+    float acc = 0.f;
+#pragma unroll
+    for (int k = 0; k < 2 * SC - 1; ++k) {
+      const float w = (float)(k < SC ? k + 1 : 2 * SC - 1 - k) * (1.f / SC);
+      acc += (last && k >= SC ? 1.f : w) * p[k];
+    }
+    hb[r * XT + X] = acc;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < XT * XT) {
+    const int Y = threadIdx.x / XT, X = threadIdx.x - Y * XT;
+    const bool last = Y0 + Y == Hm - 1;
+    float acc = 0.f;
+#pragma unroll
+    for (int k = 0; k < 2 * SC - 1; ++k) {
+      const float w = (float)(k < SC ? k + 1 : 2 * SC - 1 - k) * (1.f / SC);
+      acc += (last && k >= SC ? 1.f : w) * hb[(SC * Y + k) * XT + X];
+    }
+    if (Y0 + Y < Hm && X0 + X < Wm) G(B.gs)[(size_t)(Y0 + Y) * Wm + X0 + X] = acc;
+  }
+}
+
 // The recorded conspicuity maps of step t0 + blockIdx.y dotted with that step's adjoint g_s
 // (ios: [T][n_streams]): partial sums of g_s * C_k per tile, and C_k at the step's argmax.
 // C_k = N(F-bar_k) from the tape's F-bar and N(.) parameters (the values the forward took, so
@@ -2994,13 +3184,22 @@ hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, co
   return chk();
 }
 
-hipError_t sp_launch_bwd(int kind, const Job* jobs, int n, const StreamDesc* sds, const BwdIO* bios,
+hipError_t sp_launch_bwd(int kind, int flag, const Job* jobs, int n, const StreamDesc* sds, const BwdIO* bios,
                          const BwdIO* b0, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   BwdIO z{};
   const BwdIO& b = b0 ? *b0 : z;
   switch (kind) {
-    case JOB_BWD_NU: hipLaunchKernelGGL(k_bwd_nu, dim3(n), dim3(SP_BLOCK), 0, st, jobs, sds, bios, b); break;
+    case JOB_BWD_NU:   // flag: c_max of every stream of a one-launch reverse step, 0: the sweep alone
+      if (flag == 1)
+        hipLaunchKernelGGL(k_bwd_sweep<1>, dim3(n), dim3(SP_BLOCK), 0, st, jobs, sds, bios, b);
+      else if (flag == 2)
+        hipLaunchKernelGGL(k_bwd_sweep<2>, dim3(n), dim3(SP_BLOCK), 0, st, jobs, sds, bios, b);
+      else if (flag == 3)
+        hipLaunchKernelGGL(k_bwd_sweep<3>, dim3(n), dim3(SP_BLOCK), 0, st, jobs, sds, bios, b);
+      else
+        hipLaunchKernelGGL(k_bwd_nu, dim3(n), dim3(SP_BLOCK), 0, st, jobs, sds, bios, b);
+      break;
     case JOB_BWD_GS: hipLaunchKernelGGL(k_bwd_gs, dim3(n), dim3(SP_BLOCK), 0, st, jobs, sds, bios, b); break;
     default: return hipErrorInvalidValue;
   }
