@@ -229,6 +229,18 @@ int sp_mincut(sp_cut* cut, const float* unary, const float* pairwise, float scal
 int sp_step(sp_ctx* ctx, const uint8_t* rgb_t, const uint8_t* rgb_prev, const uint8_t* seg_prev, float* S_out,
             float* C_out, float* prior_out, float* unary_out, float* pairwise_out, float* beta_out);
 
+/* A whole clip: sp_reset, then the steps sp_step would run on its T frames, with the same
+ * results.  A context with a tape computes the saliency maps of several frames side by side
+ * (they do not depend on each other), then the prior of one frame after the other.
+ *   frames    HOST array of T device pointers, each [H][W][3] uint8.
+ *   seg_prev  HOST array of T device pointers ([H][W] uint8, or NULL for the previous prior),
+ *             or NULL.
+ *   S_out [T][Hc][Wc]; C_out [T][8][Hc][Wc], prior_out [T][H][W], unary_out [T][2][H][W],
+ *   pairwise_out [T][4][H][W] and beta_out [T] may be NULL (unary and pairwise together).
+ * The host arrays are read during the call.  SP_ESTATE when a tape is too short for T. */
+int sp_run_clip(sp_ctx* ctx, const uint8_t* const* frames, int32_t T, const uint8_t* const* seg_prev, float* S_out,
+                float* C_out, float* prior_out, float* unary_out, float* pairwise_out, float* beta_out);
+
 /* Adjoint of the clip recorded since sp_reset (requires record_tape >= T and exactly T
  * prior updates since the reset).
  *   grad_prior [T][H][W] float: dL/d prior_t for every recorded step.

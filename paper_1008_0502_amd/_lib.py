@@ -85,6 +85,8 @@ SIGNATURES = [
     ("sp_mincut", c_int32, [c_void_p, c_void_p, c_void_p, c_float, c_void_p, c_void_p]),
     ("sp_step", c_int32, [c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p,
                           c_void_p, c_void_p]),
+    ("sp_run_clip", c_int32, [c_void_p, ctypes.POINTER(c_void_p), c_int32, ctypes.POINTER(c_void_p), c_void_p,
+                              c_void_p, c_void_p, c_void_p, c_void_p, c_void_p]),
     ("saliency_backward", c_int32, [c_void_p, c_void_p, c_int32, c_void_p, c_void_p, c_void_p]),
     ("saliency_backward_frames", c_int32, [c_void_p, c_void_p, c_int32, c_void_p]),
     ("sp_mse_mask_loss", c_int32, [c_void_p, c_void_p, c_void_p, c_int32, c_void_p, c_void_p]),

@@ -366,7 +366,6 @@ class Context:
         collects the stochastic saliency means of every step (key "mu")."""
         T = frames.shape[0]
         g = self.geometry
-        self.reset()
         MU = torch.empty((T, g.Hc, g.Wc), dtype=torch.float32, device=self.device) if want_ssm else None
         S = torch.empty((T, g.Hc, g.Wc), dtype=torch.float32, device=self.device)
         C = torch.empty((T, 8, g.Hc, g.Wc), dtype=torch.float32, device=self.device) if want_C else None
@@ -374,6 +373,20 @@ class Context:
         U = torch.empty((T, 2, g.H, g.W), dtype=torch.float32, device=self.device) if with_mrf else None
         PW = torch.empty((T, 4, g.H, g.W), dtype=torch.float32, device=self.device) if with_mrf else None
         B = torch.empty((T, 1), dtype=torch.float32, device=self.device) if with_mrf else None
+        if T and manual is None and MU is None:
+            _need(frames[0], "frames[0]", torch.uint8, (g.H, g.W, 3), self.device)   # every frame has its strides
+            ptrs = (c_void_p * T)(*[frames.data_ptr() + t * frames.stride(0) for t in range(T)])
+            sp = None
+            if segs is not None:
+                for t in range(T):
+                    if segs[t] is not None:
+                        _need(segs[t], "seg_prev", torch.uint8, (g.H, g.W), self.device)
+                sp = (c_void_p * T)(*[_ptr(segs[t]) for t in range(T)])
+            self._bind_stream()
+            check(self.lib.sp_run_clip(self._handle, ptrs, T, sp, _ptr(S), _ptr(C), _ptr(P), _ptr(U), _ptr(PW), _ptr(B)),
+                  "sp_run_clip")
+            return {"S": S, "C": C, "pi": P, "unary": U, "pairwise": PW, "beta": B, "mu": MU}
+        self.reset()
         for t in range(T):
             self.saliency_forward(frames[t], frames[t - 1] if t > 0 else None, S[t], None if C is None else C[t])
             seg = None if segs is None else segs[t]

@@ -310,6 +310,19 @@ int n_sweep_tiles(const Geo& g) {
   return ((g.H + e - 1) / e) * ((g.W + e - 1) / e);
 }
 
+// Frames of a recorded clip whose saliency maps are computed side by side.  One 640x480 frame
+// leaves the chip idle (its nine launches hold 20 to 360 workgroups and take 5 to 9 us each,
+// 52 us a frame; 16 frames in one launch per phase take 8.4 us a frame), and the launches stop
+// gaining at about 16 such frames, so the slots hold that many pixels, at least 4 frames and at
+// most 64; the clip is split evenly.
+int clip_slots(const Geo& g, int cap) {
+  if (cap <= 0) return 0;
+  const long long px = (long long)g.H * g.W;
+  const int most = (int)std::min<long long>(64, std::max<long long>(4, (16LL * 640 * 480 + px - 1) / px));
+  const int chunks = (cap + most - 1) / most;
+  return (cap + chunks - 1) / chunks;
+}
+
 // ---------------------------------------------------------------- device memory layout
 struct Bump {
   char* base = nullptr;   // null during the sizing pass
@@ -552,6 +565,42 @@ struct Profiler {
   }
 };
 
+// Pinned host buffer for a table uploaded asynchronously.  Refilling waits for the event
+// recorded after the last upload, so the copy engine has consumed it first.
+struct HostStage {
+  char* host = nullptr;
+  size_t bytes = 0;
+  hipEvent_t done = nullptr;
+  bool pending = false;
+  int init(size_t n) {
+    if (hipHostMalloc((void**)&host, std::max<size_t>(n, 256), 0) != hipSuccess) {
+      (void)hipGetLastError();
+      host = nullptr;
+      return fail(SP_ENOMEM, "hipHostMalloc of %zu bytes failed", n);
+    }
+    bytes = n;
+    HIPCHK(hipEventCreateWithFlags(&done, hipEventDisableTiming));
+    return SP_OK;
+  }
+  int acquire() {
+    if (pending) HIPCHK(hipEventSynchronize(done));
+    pending = false;
+    return SP_OK;
+  }
+  int upload(void* dev, size_t n, hipStream_t st) {
+    HIPCHK(hipMemcpyAsync(dev, host, n, hipMemcpyHostToDevice, st));
+    HIPCHK(hipEventRecord(done, st));
+    pending = true;
+    return SP_OK;
+  }
+  void destroy() {
+    if (done) (void)hipEventDestroy(done);
+    if (host) (void)hipHostFree(host);
+    done = nullptr;
+    host = nullptr;
+  }
+};
+
 // ---------------------------------------------------------------- context
 struct sp_ctx {
   sp_params p{};
@@ -561,7 +610,7 @@ struct sp_ctx {
   char* arena = nullptr;
   size_t arena_bytes = 0;
   StreamDesc h_sd{};
-  StreamDesc* d_sd = nullptr;
+  StreamDesc* d_sd = nullptr;     // the stream, followed by the CH clip slots
   JobStore jobs;
   std::vector<Phase> fwd, prior, mrf, bwd;
   Phase dot;                      // recorded conspicuity dotted with the saliency adjoint
@@ -594,6 +643,14 @@ struct sp_ctx {
   double* gK_scratch = nullptr;   // [cap] dL/dK_t, then [cap][8] the steps' shares of dL/dw
   int n_lvl0_tiles = 0;
   StepIO* d_rio = nullptr;        // [cap] io of every tape frame (F-bar and adjoint buffers)
+  // a clip's frames side by side (contexts with a tape): CH frame slots, each with a pyramid,
+  // maps and partials of its own
+  int CH = 0;
+  std::vector<StreamDesc> h_slots;
+  std::vector<Phase> clip_full;   // the forward of CH frames, jobs in XCD order
+  std::vector<Phase> clip_part;   // the same, slot by slot: a prefix serves fewer frames
+  StepIO* d_cio = nullptr;        // [cap] io of the clip's frames
+  HostStage cstage;               // its pinned host copy
   float* S_scratch = nullptr;     // [Hc][Wc] saliency map of the autotuner's steps
   // variants of the prior
   float* f_map = nullptr;         // [H][W] distance-transform prediction (f_mode 1)
@@ -665,9 +722,9 @@ int run_phase(sp_ctx* c, const Phase& ph, const StreamDesc* sds, const StepIO* i
   return SP_OK;
 }
 
-// Tape slots of the step about to run that the saliency kernels fill.
-void tape_forward(const sp_ctx* c, StepIO& io) {
-  const size_t t = (size_t)c->t, plane = (size_t)c->g.Hl[c->g.c_max] * c->g.Wl[c->g.c_max];
+// Tape slots of step t that the saliency kernels fill.
+void tape_forward(const sp_ctx* c, int64_t step, StepIO& io) {
+  const size_t t = (size_t)step, plane = (size_t)c->g.Hl[c->g.c_max] * c->g.Wl[c->g.c_max];
   io.fbar = c->fbar_tape + t * SP_NCH * plane;
   io.np_tape = c->np_tape + t * 4 * SP_NCH;
   io.S_tape = c->S_tape + t * plane;
@@ -1008,6 +1065,7 @@ int sp_destroy(sp_ctx* c) {
   if (!c) return SP_OK;
   if (c->stream || c->arena) (void)hipStreamSynchronize(c->stream);
   c->prof.destroy();
+  c->cstage.destroy();
   if (c->arena) (void)hipFree(c->arena);
   if (c->jobs.dev) (void)hipFree(c->jobs.dev);
   delete c;
@@ -1036,12 +1094,14 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
   c->n_lvl0_tiles = n_sweep_tiles(g);
   const int Hc = g.Hl[g.c_max], Wc = g.Wl[g.c_max];
   const size_t HW = (size_t)H * W;
+  c->CH = clip_slots(g, c->cap);
+  c->h_slots.resize(c->CH);
   // two passes over the layout: size, then place
   for (int pass = 0; pass < 2; ++pass) {
     Bump b;
     b.base = c->arena;
     layout_stream(c->h_sd, g, *p, b);
-    c->d_sd = b.take<StreamDesc>(1);
+    c->d_sd = b.take<StreamDesc>(1 + c->CH);
     c->pi_state[0] = b.take<float>(HW);
     c->pi_state[1] = b.take<float>(HW);
     c->loss_part = b.take<float>(c->loss_nblk);
@@ -1073,6 +1133,8 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
       c->cx = b.take<float>((size_t)c->cap * SP_NCH);
       c->gK_scratch = b.take<double>((size_t)c->cap * (1 + SP_NCH));
       c->d_rio = b.take<StepIO>(c->cap);
+      c->d_cio = b.take<StepIO>(c->cap);
+      for (StreamDesc& sd : c->h_slots) layout_stream(sd, g, *p, b, std::max(1, 192 / c->CH));
       pixadj_layout(c, b);
     }
     if (pass == 0) {
@@ -1086,6 +1148,7 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
       // upload static tables
       hipError_t e = hipMemcpyAsync(c->d_sd, &c->h_sd, sizeof(StreamDesc), hipMemcpyHostToDevice, c->stream);
       if (e == hipSuccess && c->cap > 0) {
+        e = hipMemcpyAsync(c->d_sd + 1, c->h_slots.data(), sizeof(StreamDesc) * c->CH, hipMemcpyHostToDevice, c->stream);
         std::vector<StepIO> rio(c->cap);
         const size_t plane = (size_t)Hc * Wc;
         for (int t = 0; t < c->cap; ++t) {
@@ -1097,7 +1160,8 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
           rio[t].dot = c->dot_part + (size_t)t * c->h_sd.n_cmax_tiles * SP_NCH;
           rio[t].cx = c->cx + (size_t)t * SP_NCH;
         }
-        e = hipMemcpyAsync(c->d_rio, rio.data(), sizeof(StepIO) * c->cap, hipMemcpyHostToDevice, c->stream);
+        if (e == hipSuccess)
+          e = hipMemcpyAsync(c->d_rio, rio.data(), sizeof(StepIO) * c->cap, hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         if (e == hipSuccess) e = pixadj_upload(c);
       }
@@ -1113,7 +1177,8 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
     return fail(SP_EHIP, "cannot reserve %zu bytes of LDS for the across-scale sum", csapply_lds_bytes(g));
   }
   c->tune = cached_tune(H, W);
-  int rc2 = ctx_build_tables(c);
+  int rc2 = c->cap > 0 ? c->cstage.init(sizeof(StepIO) * c->cap) : SP_OK;
+  if (!rc2) rc2 = ctx_build_tables(c);
   if (rc2) {
     std::string msg = g_err;
     sp_destroy(c);
@@ -1128,6 +1193,41 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
 
 namespace {
 
+// The forward phases over the clip slots: slot by slot (a prefix serves a shorter chunk), and
+// for whole chunks in XCD order with the longer jobs of a pyramid launch (Gabor tiles, small
+// levels) first, as in the batched step.
+void clip_tables(sp_ctx* c, int nc) {
+  const Geo& g = c->g;
+  std::vector<std::vector<Job>> all;
+  std::vector<int> kinds;
+  for (int s = 0; s < c->CH; ++s) {
+    std::vector<std::vector<Job>> parts;
+    std::vector<int> ks;
+    build_forward_jobs(parts, ks, c->h_slots[s], g, s, nc);
+    if (all.empty()) {
+      all.resize(parts.size());
+      kinds = ks;
+    }
+    for (size_t i = 0; i < parts.size(); ++i) all[i].insert(all[i].end(), parts[i].begin(), parts[i].end());
+  }
+  const size_t lds = nc * (gpath_ok(g) ? csg_lds_bytes(g) : csapply_lds_bytes(g));
+  for (size_t i = 0; i < all.size(); ++i) {
+    const bool grp = kinds[i] == JOB_CSAPPLY || kinds[i] == JOB_CSG;
+    const bool pyr = kinds[i] == JOB_DOWN || kinds[i] == JOB_TAIL;
+    const int flag = grp ? nc | (kinds[i] == JOB_CSG ? csg_set(g) << 8 : 0) : (pyr ? c->p.gabor_radius : 0);
+    c->clip_part.push_back(c->jobs.add(kinds[i], flag, all[i], c->CH));
+    std::vector<Job> first, rest;
+    for (const Job& jb : all[i])
+      (jb.kind == JOB_GABOR ? kinds[i] == JOB_DOWN : jb.kind == JOB_TAIL || jb.kind == JOB_TAILGAB) ? first.push_back(jb)
+                                                                                                   : rest.push_back(jb);
+    xcd_order(first);
+    xcd_order(rest);
+    first.insert(first.end(), rest.begin(), rest.end());
+    c->clip_full.push_back(c->jobs.add(kinds[i], flag, first, c->CH));
+    if (grp) c->clip_part.back().lds = c->clip_full.back().lds = lds;
+  }
+}
+
 // (Re)builds every job table of a context from its geometry and tuning knobs.
 int ctx_build_tables(sp_ctx* c) {
   const Geo& g = c->g;
@@ -1138,6 +1238,8 @@ int ctx_build_tables(sp_ctx* c) {
   c->mrf.clear();
   c->bwd.clear();
   c->dt.clear();
+  c->clip_full.clear();
+  c->clip_part.clear();
   {
     int nc = 0;
     int rc = forward_phases(g, c->p, c->h_sd, c->tune, c->jobs, c->fwd, &nc);
@@ -1168,6 +1270,7 @@ int ctx_build_tables(sp_ctx* c) {
     add_tiles(v, 0, 0, Hc, Wc);
     if (g.c_max > kSweepMax) c->bwd.push_back(c->jobs.add(JOB_BWD_GS, 0, v, 1));
     c->dot = c->jobs.add(JOB_CONSP_DOT, 0, v, 1);
+    if (c->CH > 0) clip_tables(c, nc);
   }
   return upload_jobs(c->jobs, c->stream);
 }
@@ -1218,6 +1321,7 @@ int sp_set_weights(sp_ctx* c, const float* w, double q, double r) {
   for (int k = 0; k < SP_NCH; ++k) {
     c->p.weights[k] = w[k];
     c->h_sd.w[k] = w[k];
+    for (StreamDesc& sd : c->h_slots) sd.w[k] = w[k];
   }
   c->p.q = q;
   c->p.r = r;
@@ -1226,6 +1330,8 @@ int sp_set_weights(sp_ctx* c, const float* w, double q, double r) {
   if (c->t > 0) c->tape_ok = false;
   c->tape_gen += 1;
   HIPCHK(hipMemcpyAsync(c->d_sd, &c->h_sd, sizeof(StreamDesc), hipMemcpyHostToDevice, c->stream));
+  if (c->CH > 0)
+    HIPCHK(hipMemcpyAsync(c->d_sd + 1, c->h_slots.data(), sizeof(StreamDesc) * c->CH, hipMemcpyHostToDevice, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   return SP_OK;
 }
@@ -1323,7 +1429,7 @@ int saliency_forward(sp_ctx* c, const uint8_t* rgb_t, const uint8_t* rgb_prev, f
   if (c->cap > 0) {
     if (c->t >= c->cap) return fail(SP_ESTATE, "tape holds %d frames; call sp_reset before frame %lld", c->cap,
                                     (long long)c->t);
-    tape_forward(c, io);
+    tape_forward(c, c->t, io);
   }
   for (const Phase& ph : c->fwd) {
     int rc = run_phase(c, ph, c->d_sd, nullptr, &io, ph.n);
@@ -1438,7 +1544,7 @@ int sp_step(sp_ctx* c, const uint8_t* rgb_t, const uint8_t* rgb_prev, const uint
   io.K = (float)K;
   io.t = (int32_t)std::min<int64_t>(c->t, 0x7fffffff);
   if (c->cap > 0) {
-    tape_forward(c, io);
+    tape_forward(c, c->t, io);
     io.f_tape = c->f_tape + (size_t)c->t * g.H * g.W;
     io.ms_tape = c->ms_tape + (size_t)c->t * 2;
   }
@@ -1459,6 +1565,83 @@ int sp_step(sp_ctx* c, const uint8_t* rgb_t, const uint8_t* rgb_prev, const uint
   c->P = Pn;
   c->cur ^= 1;
   c->t += 1;
+  return SP_OK;
+}
+
+int sp_run_clip(sp_ctx* c, const uint8_t* const* frames, int32_t T, const uint8_t* const* seg_prev, float* S_out,
+                float* C_out, float* prior_out, float* unary_out, float* pairwise_out, float* beta_out) {
+  g_err.clear();
+  if (!c || !frames || !S_out) return fail(SP_EINVAL, "ctx, frames and S_out must not be NULL");
+  if (T < 1) return fail(SP_EINVAL, "T must be >= 1");
+  for (int t = 0; t < T; ++t)
+    if (!frames[t]) return fail(SP_EINVAL, "frame %d is NULL", t);
+  if ((unary_out == nullptr) != (pairwise_out == nullptr))
+    return fail(SP_EINVAL, "unary_out and pairwise_out must be given together");
+  if (c->cap > 0 && T > c->cap)
+    return fail(SP_ESTATE, "tape holds %d frames; the clip has %d", c->cap, T);
+  const Geo& g = c->g;
+  const size_t HW = (size_t)g.H * g.W, plane = (size_t)g.Hl[g.c_max] * g.Wl[g.c_max];
+  auto at = [](float* p, size_t off) { return p ? p + off : nullptr; };
+  int rc = sp_reset(c);
+  if (rc) return rc;
+  // no frame slots, or a graph under capture (a captured upload would read the host table at
+  // replay): one step after the other
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (c->CH > 0) HIPCHK(hipStreamIsCapturing(c->stream, &cap));
+  if (c->CH == 0 || cap != hipStreamCaptureStatusNone) {
+    for (size_t t = 0; t < (size_t)T && !rc; ++t)
+      rc = sp_step(c, frames[t], t ? frames[t - 1] : nullptr, seg_prev ? seg_prev[t] : nullptr, S_out + t * plane,
+                   at(C_out, t * SP_NCH * plane), at(prior_out, t * HW), at(unary_out, t * 2 * HW),
+                   at(pairwise_out, t * 4 * HW), at(beta_out, t));
+    return rc;
+  }
+  // the io of every step (a context with a tape runs the default prior: no variants)
+  rc = c->cstage.acquire();
+  if (rc) return rc;
+  StepIO* io = reinterpret_cast<StepIO*>(c->cstage.host);
+  double P = 0.0;
+  for (size_t t = 0; t < (size_t)T; ++t) {
+    StepIO& o = io[t];
+    std::memset(&o, 0, sizeof o);
+    o.rgb = frames[t];
+    o.rgb_prev = t ? frames[t - 1] : nullptr;
+    o.S_out = S_out + t * plane;
+    o.S_in = o.S_out;
+    o.C_out = at(C_out, t * SP_NCH * plane);
+    o.seg_prev = seg_prev ? seg_prev[t] : nullptr;
+    o.pi_prev = c->pi_state[(c->cur + t) & 1];
+    o.pi_next = c->pi_state[(c->cur + t + 1) & 1];
+    o.prior_out = at(prior_out, t * HW);
+    o.unary = at(unary_out, t * 2 * HW);
+    o.pairwise = at(pairwise_out, t * 4 * HW);
+    o.beta_out = unary_out ? at(beta_out, t) : nullptr;
+    const double K = now_gain((int64_t)t, P, c->p.q, c->p.r, &P);
+    o.K = (float)K;
+    o.t = (int32_t)t;
+    tape_forward(c, (int64_t)t, o);
+    o.f_tape = c->f_tape + t * HW;
+    o.ms_tape = c->ms_tape + t * 2;
+  }
+  rc = c->cstage.upload(c->d_cio, sizeof(StepIO) * (size_t)T, c->stream);
+  if (rc) return rc;
+  for (int t0 = 0; t0 < T; t0 += c->CH) {
+    const int n = std::min(c->CH, T - t0);
+    for (const Phase& ph0 : n == c->CH ? c->clip_full : c->clip_part) {
+      Phase ph = ph0;
+      if (ph.kind == JOB_RGB) ph.flag = unary_out ? 1 : 0;
+      rc = run_phase(c, ph, c->d_sd + 1, c->d_cio + t0, nullptr, ph.upto[n]);
+      if (rc) return rc;
+    }
+    for (int t = t0; t < t0 + n; ++t) {
+      rc = run_phase(c, c->prior.back(), c->d_sd + 1 + (t - t0), nullptr, &io[t], c->prior.back().n);
+      if (rc) return rc;
+      c->Kf.push_back(io[t].K);
+      c->uses_pi.push_back(io[t].seg_prev == nullptr && t > 0);
+    }
+  }
+  c->P = P;
+  c->cur = (c->cur + T) & 1;
+  c->t = T;
   return SP_OK;
 }
 
@@ -1901,42 +2084,6 @@ struct BatchAdj {
   double* gK;          // [cap]
   float* loss_part;    // [loss_nblk]
   int n_lvl0_tiles;
-};
-
-// Pinned host buffer for a table uploaded asynchronously.  Refilling waits for the event
-// recorded after the last upload, so the copy engine has consumed it first.
-struct HostStage {
-  char* host = nullptr;
-  size_t bytes = 0;
-  hipEvent_t done = nullptr;
-  bool pending = false;
-  int init(size_t n) {
-    if (hipHostMalloc((void**)&host, std::max<size_t>(n, 256), 0) != hipSuccess) {
-      (void)hipGetLastError();
-      host = nullptr;
-      return fail(SP_ENOMEM, "hipHostMalloc of %zu bytes failed", n);
-    }
-    bytes = n;
-    HIPCHK(hipEventCreateWithFlags(&done, hipEventDisableTiming));
-    return SP_OK;
-  }
-  int acquire() {
-    if (pending) HIPCHK(hipEventSynchronize(done));
-    pending = false;
-    return SP_OK;
-  }
-  int upload(void* dev, size_t n, hipStream_t st) {
-    HIPCHK(hipMemcpyAsync(dev, host, n, hipMemcpyHostToDevice, st));
-    HIPCHK(hipEventRecord(done, st));
-    pending = true;
-    return SP_OK;
-  }
-  void destroy() {
-    if (done) (void)hipEventDestroy(done);
-    if (host) (void)hipHostFree(host);
-    done = nullptr;
-    host = nullptr;
-  }
 };
 
 struct sp_batch {
