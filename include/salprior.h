@@ -253,7 +253,7 @@ int saliency_backward(sp_ctx* ctx, const float* grad_prior, int32_t T, float* gr
  * (N(.), the across-scale sum, centre-surround, the Gabor maps, the pyramid and the level-0
  * features of Section 3 / Section 7.2); the motion feature also carries gradient to the
  * previous frame.  Run saliency_backward for the clip first: this call continues from its
- * dL/dS of every frame.  The frames' maps are recomputed from the frames.
+ * dL/dS of every frame.  The frames' pyramids are recomputed from the frames.
  *   frames       [T][H][W][3] uint8 (device): the clip the forward ran, in order.
  *   grad_frames  [T][H][W][3] float (device): receives dL/d(frame value), per unit of the
  *                0..255 scale (the frames taken as real numbers).

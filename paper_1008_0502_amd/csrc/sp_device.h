@@ -208,6 +208,17 @@ __device__ __forceinline__ gp<T> G(T* p) {
   return (gp<T>)p;
 }
 
+// Channel k (I, RG, BY, O0, O45, O90, O135, M) of level l.
+__device__ __forceinline__ const float* chan_ptr(const StreamDesc& sd, int k, int l) {
+  // selects rather than branches: every operand is a uniform scalar load
+  const size_t plane = (size_t)sd.Hl[l] * sd.Wl[l];
+  const float* b = sd.base[l];
+  const float* g = sd.gab[l];
+  const bool gabor = (unsigned)(k - 3) < 4u;
+  const int idx = k < 3 ? k : (k == 7 ? 3 : k - 3);
+  return (gabor ? g : b) + idx * plane;
+}
+
 // base + a 32-bit byte offset, which the compiler addresses as a scalar base plus one
 // vector register (no 64-bit vector add per access).  Frames hold at most 2^28 pixels,
 // so byte offsets into a plane stay below 2^30.

@@ -659,39 +659,11 @@ struct sp_ctx {
   int ssm_cur = 0;
   int64_t ssm_t = 0;              // maps filtered since the reset
   double ssm_P = 0.0;             // variance of the stochastic map
-  // pixel-level adjoint (contexts with a tape): workspace planes and static launch tables
-  struct PixAdj {
-    float* gS = nullptr;                 // [Hc][Wc] dL/dS of the frame
-    float* gfbar = nullptr;              // [8][Hc][Wc]
-    double* gs_part = nullptr;           // per-workgroup partials of sum gs S
-    float* gN[SP_MAXL] = {};             // [8][H_l][W_l] dL/dN(F) at centre levels below c_max
-    float* F[SP_MAXP] = {};              // [8][H_c][W_c] per pair: F, then dL/dF, then sign(D) dL/dF
-    float* gX[SP_MAXL] = {};             // [8][H_l][W_l] dL/d(channel maps) per level 0..top
-    size_t gX_floats = 0;                // floats of gX, followed by amax
-    uint32_t* amax = nullptr;            // [n_pairs][8][SP_PA_AMAX] scale of each centre-surround pair (float bits)
-    float* taps = nullptr;               // [4][2R+1][2R+1] Gabor taps
-    PaMap* maps_fbar = nullptr;          // [8]
-    PaMap* maps_F = nullptr;             // [8 n_pairs]
-    PaPlane* tab_gn[SP_MAXL] = {};       // [8] per centre level below c_max
-    PaPlane* tab_cs[SP_MAXP] = {};       // [8] per pair: centre-surround map and adjoint
-    PaPlane* tab_up[SP_MAXP] = {};       // [8] per pair: up-sample transpose
-    PaPlane* tab_gab[SP_MAXL] = {};      // [1] per used level
-    PaPlane* tab_pyr[SP_MAXL] = {};      // [4] per level 1..top: to the level below
-    float** gc[SP_MAXP] = {};            // [8] per pair: dL/dX(c) planes
-    // pairs grouped so that no two of a group share a centre level (cs: the adjoint adds to
-    // dL/dX(c)) or a surround level (up: the transpose adds to dL/dX(s)); each group's
-    // tables are contiguous, the cs groups one after another, so one launch covers a group
-    // (cs maps: every pair)
-    int cs_first[SP_MAXP] = {}, cs_count[SP_MAXP] = {}, n_cs = 0;   // pair index of the first table, pairs
-    int up_first[SP_MAXP] = {}, up_count[SP_MAXP] = {}, n_up = 0;
-    int cs_order[SP_MAXP] = {}, up_order[SP_MAXP] = {};              // pairs in table order
-    int64_t gen = -1;                    // tape generation of the last saliency_backward
-    int T = 0;                           // and its clip length
-  } pa;
-  int32_t* pa_bpos = nullptr;     // block-maximum positions of every N(.) adjoint map
-  float* pa_sc = nullptr;         // [maps][8] scalars of every N(.) adjoint map
-  float2* pa_mm = nullptr;        // [maps][mm] (min, max) partials of every N(.) adjoint map
-  PaStrip* pa_strip = nullptr;    // [maps][strips] strip partials of every N(.) adjoint map
+  // pixel-level adjoint (contexts with a tape): the workspace of pa_slots frames
+  PaDesc pa{};
+  int pa_slots = 0;
+  int64_t pa_gen = -1;            // tape generation of the last saliency_backward
+  int pa_T = 0;                   // and its clip length
   // colour likelihood
   GmmState* gmm_state = nullptr;
   double* gmm_part = nullptr;     // [2 M 10][gmm_tiles] FP64 moments per tile
@@ -779,223 +751,49 @@ void build_forward_jobs(std::vector<std::vector<Job>>& parts, std::vector<int>& 
   push(JOB_CONSP, v);
 }
 
-// 8x8 blocks of every map of the N(.) adjoint: the 8 across-scale sums and every pair's 8
-// centre-surround maps.
-size_t pixadj_nblocks(const Geo& g) {
-  auto nblk = [&](int l) { return (size_t)((g.Hl[l] + 7) / 8) * ((g.Wl[l] + 7) / 8); };
-  size_t n = SP_NCH * nblk(g.c_max);
-  for (int p = 0; p < g.n_pairs; ++p) n += SP_NCH * nblk(g.pc[p]);
-  return n;
-}
-
-// Largest N(.) adjoint map (pixels, rows) and the partials each map gets.
-struct PaDims {
-  int maxn, maxh;
-  size_t mm, strips;
-};
-PaDims pixadj_dims(const Geo& g) {
-  PaDims D{g.Hl[g.c_max] * g.Wl[g.c_max], g.Hl[g.c_max], 0, 0};
-  for (int p = 0; p < g.n_pairs; ++p) {
-    D.maxn = std::max(D.maxn, g.Hl[g.pc[p]] * g.Wl[g.pc[p]]);
-    D.maxh = std::max(D.maxh, g.Hl[g.pc[p]]);
-  }
-  D.mm = (size_t)(D.maxn + SP_PA_MMT - 1) / SP_PA_MMT;
-  D.strips = (size_t)(D.maxh + 7) / 8;
-  return D;
-}
-
-// Workspace of the pixel-level adjoint, taken from the context's arena (both layout passes).
+// Workspace of the pixel-level adjoint, taken from the context's arena (both layout passes):
+// one frame slot laid out, the others at the same distance from each other.
 void pixadj_layout(sp_ctx* c, Bump& b) {
   const Geo& g = c->g;
-  auto& A = c->pa;
+  PaDesc& A = c->pa;
+  A = PaDesc{};
   auto n_l = [&](int l) { return (size_t)g.Hl[l] * g.Wl[l]; };
-  const int Hc = g.Hl[g.c_max], Wc = g.Wl[g.c_max];
-  A.gS = b.take<float>((size_t)Hc * Wc);
-  A.gs_part = b.take<double>(((size_t)Hc * Wc + SP_BLOCK - 1) / SP_BLOCK);
-  A.gfbar = b.take<float>((size_t)SP_NCH * Hc * Wc);
-  for (int l = g.c_min; l < g.c_max; ++l) A.gN[l] = b.take<float>(SP_NCH * n_l(l));
-  for (int p = 0; p < g.n_pairs; ++p) A.F[p] = b.take<float>(SP_NCH * n_l(g.pc[p]));
-  A.gX_floats = 0;
-  for (int l = 0; l <= g.top; ++l) A.gX_floats += SP_NCH * n_l(l);
-  float* gx = b.take<float>(A.gX_floats + (size_t)SP_NCH * g.n_pairs * SP_PA_AMAX);
-  for (int l = 0; l <= g.top; ++l) {
-    A.gX[l] = gx;
-    if (gx) gx += SP_NCH * n_l(l);
-  }
-  A.amax = reinterpret_cast<uint32_t*>(gx);
-  const int K = 2 * SP_PA_R + 1;
-  A.taps = b.take<float>((size_t)4 * K * K);
-  A.maps_fbar = b.take<PaMap>(SP_NCH);
-  A.maps_F = b.take<PaMap>((size_t)SP_NCH * g.n_pairs);
-  for (int l = g.c_min; l < g.c_max; ++l) A.tab_gn[l] = b.take<PaPlane>(SP_NCH);
-  {
-    // group round r: the pairs that are the r-th of their centre (surround) level
-    auto groups = [&](bool by_surround, int* order, int* first, int* count, int& ng) {
-      int round[SP_MAXP], nr = 0, k = 0;
-      for (int p = 0; p < g.n_pairs; ++p) {
-        int r = 0;
-        for (int q = 0; q < p; ++q) r += (by_surround ? g.ps[q] == g.ps[p] : g.pc[q] == g.pc[p]) ? 1 : 0;
-        round[p] = r;
-        nr = std::max(nr, r + 1);
-      }
-      ng = nr;
-      for (int r = 0; r < nr; ++r) {
-        first[r] = k;
-        count[r] = 0;
-        for (int p = 0; p < g.n_pairs; ++p)
-          if (round[p] == r) {
-            order[k++] = p;
-            ++count[r];
-          }
-      }
-    };
-    groups(false, A.cs_order, A.cs_first, A.cs_count, A.n_cs);
-    groups(true, A.up_order, A.up_first, A.up_count, A.n_up);
-    PaPlane* cs = b.take<PaPlane>((size_t)SP_NCH * g.n_pairs);
-    PaPlane* up = b.take<PaPlane>((size_t)SP_NCH * g.n_pairs);
-    float** gc = b.take<float*>((size_t)SP_NCH * g.n_pairs);
-    for (int k = 0; k < g.n_pairs; ++k) {
-      const int pc = A.cs_order[k], pu = A.up_order[k];
-      A.tab_cs[pc] = cs ? cs + (size_t)k * SP_NCH : nullptr;
-      A.gc[pc] = gc ? gc + (size_t)k * SP_NCH : nullptr;
-      A.tab_up[pu] = up ? up + (size_t)k * SP_NCH : nullptr;
-    }
-  }
-  for (int l = 1; l <= g.top; ++l) {
-    if (g.used & (1u << l)) A.tab_gab[l] = b.take<PaPlane>(1);
-    A.tab_pyr[l] = b.take<PaPlane>(4);
-  }
-  c->pa_bpos = b.take<int32_t>(pixadj_nblocks(g) + 64);
-  c->pa_sc = b.take<float>((size_t)SP_PA_SC * SP_NCH * (1 + g.n_pairs));
-  const size_t nmaps = (size_t)SP_NCH * (1 + g.n_pairs);
-  const PaDims D = pixadj_dims(g);
-  c->pa_mm = b.take<float2>(nmaps * D.mm);
-  c->pa_strip = b.take<PaStrip>(nmaps * D.strips);
-}
-
-// Static launch tables of the pixel-level adjoint (pointers into the forward's own maps and
-// the workspace; every frame reuses them).
-hipError_t pixadj_upload(sp_ctx* c) {
-  const Geo& g = c->g;
-  const StreamDesc& sd = c->h_sd;
-  auto& A = c->pa;
-  auto n_l = [&](int l) { return (size_t)g.Hl[l] * g.Wl[l]; };
-  const int cm = g.c_max;
-  // channel k of level l in the forward's maps (I, RG, BY, O0..O135, M)
-  auto chan = [&](int k, int l) -> const float* {
-    if (k == 0) return sd.base[l];
-    if (k == 1 || k == 2) return sd.base[l] + (size_t)k * n_l(l);
-    if (k == 7) return sd.base[l] + (size_t)BASE_M * n_l(l);
-    return sd.gab[l] + (size_t)(k - 3) * n_l(l);
-  };
-  std::vector<char> blob;
-  std::vector<std::pair<void*, std::vector<char>>> ups;
-  auto put = [&](void* dst, const void* src, size_t bytes) {
-    ups.emplace_back(dst, std::vector<char>((const char*)src, (const char*)src + bytes));
-  };
-  // Gabor taps, the 2-D kernel of each orientation in FP64, stored FP32
-  {
-    const int R = c->p.gabor_radius, K = 2 * SP_PA_R + 1;
-    std::vector<float> taps((size_t)4 * K * K, 0.f);
-    const double s2 = 2.0 * (double)c->p.gabor_sigma * (double)c->p.gabor_sigma;
-    for (int th = 0; th < 4; ++th) {
-      const double a = th * M_PI / 4.0;
-      double se = 0, sec = 0;
-      for (int v = -R; v <= R; ++v)
-        for (int u = -R; u <= R; ++u) {
-          const double e = std::exp(-(double)(u * u + v * v) / s2);
-          se += e;
-          sec += e * std::cos(2.0 * M_PI * (u * std::cos(a) + v * std::sin(a)) / (double)c->p.gabor_lambda);
-        }
-      const double c0 = sec / se;
-      for (int v = -R; v <= R; ++v)
-        for (int u = -R; u <= R; ++u) {
-          const double e = std::exp(-(double)(u * u + v * v) / s2);
-          const double h = e * std::cos(2.0 * M_PI * (u * std::cos(a) + v * std::sin(a)) / (double)c->p.gabor_lambda) - c0 * e;
-          taps[((size_t)th * K + (v + R)) * K + (u + R)] = (float)h;
-        }
-    }
-    put(A.taps, taps.data(), taps.size() * sizeof(float));
-  }
-  // N(.) adjoint maps: the 8 across-scale sums, then every pair's 8 centre-surround maps
-  int32_t* bpos = c->pa_bpos;
-  float* sc = c->pa_sc;
-  float2* mm = c->pa_mm;
-  PaStrip* strip = c->pa_strip;
-  const PaDims D = pixadj_dims(g);
-  auto nblk = [&](int l) { return ((g.Hl[l] + 7) / 8) * ((g.Wl[l] + 7) / 8); };
-  {
-    std::vector<PaMap> m(SP_NCH);
-    const size_t pl = n_l(cm);
-    for (int k = 0; k < SP_NCH; ++k) {
-      m[k] = PaMap{sd.fbar + k * pl, A.gS, A.gfbar + k * pl, bpos, sc, mm, strip, g.Hl[cm], g.Wl[cm], c->p.weights[k], 0};
-      bpos += nblk(cm);
-      sc += SP_PA_SC;
-      mm += D.mm;
-      strip += D.strips;
-    }
-    put(A.maps_fbar, m.data(), m.size() * sizeof(PaMap));
-  }
-  {
-    std::vector<PaMap> m((size_t)SP_NCH * g.n_pairs);
-    for (int p = 0; p < g.n_pairs; ++p) {
-      const int cl = g.pc[p];
-      const size_t pl = n_l(cl);
-      for (int k = 0; k < SP_NCH; ++k) {
-        const float* gn = cl == cm ? A.gfbar + k * pl : A.gN[cl] + k * pl;
-        m[(size_t)p * SP_NCH + k] = PaMap{A.F[p] + k * pl, gn, A.F[p] + k * pl, bpos, sc, mm, strip, g.Hl[cl], g.Wl[cl],
-                                          1.f, 0};
-        bpos += nblk(cl);
-        sc += SP_PA_SC;
-        mm += D.mm;
-        strip += D.strips;
-      }
-    }
-    put(A.maps_F, m.data(), m.size() * sizeof(PaMap));
-  }
-  // dL/dN at centre levels below c_max: pyramid-step transposes from c_max down
-  for (int l = cm - 1; l >= g.c_min; --l) {
-    std::vector<PaPlane> t(SP_NCH);
-    for (int k = 0; k < SP_NCH; ++k) {
-      const float* src = (l + 1 == cm) ? A.gfbar + k * n_l(cm) : A.gN[l + 1] + k * n_l(l + 1);
-      t[k] = PaPlane{src, nullptr, A.gN[l] + k * n_l(l), nullptr, g.Hl[l], g.Wl[l], g.Hl[l + 1], g.Wl[l + 1], 0, 0};
-    }
-    put(A.tab_gn[l], t.data(), t.size() * sizeof(PaPlane));
-  }
-  // centre-surround maps, their adjoint and the up-sample transpose, per pair
+  const size_t plc = n_l(g.c_max), maps = (size_t)SP_NCH * (1 + g.n_pairs);
+  size_t maxn = plc, maxh = g.Hl[g.c_max], maxb = (size_t)((g.Hl[g.c_max] + 7) / 8) * ((g.Wl[g.c_max] + 7) / 8);
   for (int p = 0; p < g.n_pairs; ++p) {
-    const int cl = g.pc[p], sl = g.ps[p];
-    std::vector<PaPlane> cs(SP_NCH), up(SP_NCH);
-    std::vector<float*> gc(SP_NCH);
-    for (int k = 0; k < SP_NCH; ++k) {
-      float* Fk = A.F[p] + k * n_l(cl);
-      cs[k] = PaPlane{chan(k, cl), chan(k, sl), Fk, A.amax + ((size_t)p * SP_NCH + k) * SP_PA_AMAX, g.Hl[cl], g.Wl[cl],
-                      g.Hl[sl], g.Wl[sl], sl - cl, 0};
-      up[k] = PaPlane{Fk, nullptr, A.gX[sl] + k * n_l(sl), nullptr, g.Hl[cl], g.Wl[cl], g.Hl[sl], g.Wl[sl], sl - cl, 0};
-      gc[k] = A.gX[cl] + k * n_l(cl);
-    }
-    put(A.tab_cs[p], cs.data(), cs.size() * sizeof(PaPlane));
-    put(A.tab_up[p], up.data(), up.size() * sizeof(PaPlane));
-    put(A.gc[p], gc.data(), gc.size() * sizeof(float*));
+    const int cl = g.pc[p];
+    maxn = std::max(maxn, n_l(cl));
+    maxh = std::max(maxh, (size_t)g.Hl[cl]);
+    maxb = std::max(maxb, (size_t)((g.Hl[cl] + 7) / 8) * ((g.Wl[cl] + 7) / 8));
   }
-  // Gabor transposes at the used levels; pyramid-step transposes of the base channels
+  A.mm_n = (int)((maxn + SP_PA_TILE - 1) / SP_PA_TILE);
+  A.strip_n = (int)((maxh + 7) / 8);
+  A.nb_n = (int)maxb;
+  b.off = (b.off + 255) & ~size_t(255);
+  const size_t from = b.off;
+  A.gS = b.take<float>(plc);
+  A.gs_part = b.take<double>((plc + SP_BLOCK - 1) / SP_BLOCK);
+  A.gfbar = b.take<float>(SP_NCH * plc);
+  for (int l = g.c_min; l < g.c_max; ++l) A.gN[l] = b.take<float>(SP_NCH * n_l(l));
+  for (int p = 0; p < g.n_pairs; ++p) A.D[p] = b.take<float>(SP_NCH * n_l(g.pc[p]));
+  for (int l = 1; l <= g.top; ++l) A.gX[l] = b.take<float>(SP_NCH * n_l(l));
+  A.bpos = b.take<int32_t>(maps * A.nb_n);
+  A.sc = b.take<float>(maps * SP_PA_SC);
+  A.mm = b.take<PaMM>(maps * A.mm_n);
+  A.strip = b.take<PaStrip>(maps * A.strip_n);
+  A.stride = ((b.off - from) + 255) & ~size_t(255);
+  c->pa_slots = std::min(c->CH, SP_PA_SLOTS);
+  b.off = from + A.stride * c->pa_slots;
+  unsigned sur = 0;
+  for (int p = 0; p < g.n_pairs; ++p) {
+    A.centres |= 1u << g.pc[p];
+    sur |= 1u << g.ps[p];
+  }
   for (int l = 1; l <= g.top; ++l) {
-    if (A.tab_gab[l]) {
-      PaPlane t{A.gX[l] + 3 * n_l(l), nullptr, A.gX[l], nullptr, g.Hl[l], g.Wl[l], 0, 0, c->p.gabor_radius, 0};
-      put(A.tab_gab[l], &t, sizeof t);
-    }
-    const int ks[4] = {0, 1, 2, 7};
-    std::vector<PaPlane> t(4);
-    for (int j = 0; j < 4; ++j)
-      t[j] = PaPlane{A.gX[l] + ks[j] * n_l(l), nullptr, A.gX[l - 1] + ks[j] * n_l(l - 1), nullptr, g.Hl[l - 1],
-                     g.Wl[l - 1], g.Hl[l], g.Wl[l], 0, 0};
-    put(A.tab_pyr[l], t.data(), t.size() * sizeof(PaPlane));
+    if ((A.centres >> l) & 1u) A.cl[A.n_cl++] = l;
+    if ((sur >> l) & 1u) A.sl[A.n_sl++] = l;
+    if ((g.used >> l) & 1u) A.ul[A.n_ul++] = l;
   }
-  for (auto& u : ups) {
-    const hipError_t e = hipMemcpyAsync(u.first, u.second.data(), u.second.size(), hipMemcpyHostToDevice, c->stream);
-    if (e != hipSuccess) return e;
-  }
-  return hipStreamSynchronize(c->stream);
 }
 
 // Phases of one stream's forward saliency map (stream index 0), appended to `js` with
@@ -1162,8 +960,6 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
         }
         if (e == hipSuccess)
           e = hipMemcpyAsync(c->d_rio, rio.data(), sizeof(StepIO) * c->cap, hipMemcpyHostToDevice, c->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        if (e == hipSuccess) e = pixadj_upload(c);
       }
       if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
       if (e != hipSuccess) {
@@ -1883,8 +1679,8 @@ int saliency_backward(sp_ctx* c, const float* grad_prior, int32_t T, float* grad
     return sp_launch_bwd_final(nullptr, &fin, 1, T, c->K_tape, c->P_tape, c->p.q, c->p.r, c->p.flat_tol, c->stream);
   });
   if (e != hipSuccess) return fail(SP_EHIP, "adjoint reduction launch: %s", hipGetErrorString(e));
-  c->pa.gen = c->tape_gen;
-  c->pa.T = T;
+  c->pa_gen = c->tape_gen;
+  c->pa_T = T;
   return SP_OK;
 }
 
@@ -1892,85 +1688,51 @@ int saliency_backward_frames(sp_ctx* c, const uint8_t* frames, int32_t T, float*
   g_err.clear();
   if (!c || !frames || !grad_frames) return fail(SP_EINVAL, "NULL argument");
   if (c->cap <= 0) return fail(SP_ESTATE, "context was created without a tape (record_tape = 0)");
-  if (c->pa.gen != c->tape_gen || c->pa.T != T || T != c->t)
+  if (c->pa_gen != c->tape_gen || c->pa_T != T || T != c->t)
     return fail(SP_ESTATE, "saliency_backward of this %d-step clip must run first", T);
   const Geo& g = c->g;
-  auto& A = c->pa;
-  const size_t HW = (size_t)g.H * g.W, HW3 = 3 * HW;
-  const int cm = g.c_max;
-  const size_t plc = (size_t)g.Hl[cm] * g.Wl[cm];
-  auto n_l = [&](int l) { return (int)((size_t)g.Hl[l] * g.Wl[l]); };
-  auto ok = [&](hipError_t e, const char* what) -> int {
-    if (e != hipSuccess) return fail(SP_EHIP, "pixel adjoint (%s): %s", what, hipGetErrorString(e));
-    return SP_OK;
-  };
-  int maxF = 0;
-  for (int p = 0; p < g.n_pairs; ++p) maxF = std::max(maxF, n_l(g.pc[p]));
-  for (int t = 0; t < T; ++t) {
-    // the frame's forward maps, recomputed into the context's buffers
+  const size_t HW3 = 3 * (size_t)g.H * g.W, plc = (size_t)g.Hl[g.c_max] * g.Wl[g.c_max];
+  auto frame_io = [&](int t) {
     StepIO io;
     std::memset(&io, 0, sizeof io);
     io.rgb = frames + (size_t)t * HW3;
     io.rgb_prev = t ? frames + (size_t)(t - 1) * HW3 : nullptr;
-    io.S_out = c->S_scratch;
-    for (const Phase& ph0 : c->fwd) {
+    return io;
+  };
+  // the frames' pyramids and Gabor maps, recomputed into the slots from a table of their
+  // inputs (under capture, where an upload would read the host table at replay, slot by slot)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  HIPCHK(hipStreamIsCapturing(c->stream, &cap));
+  const bool table = cap == hipStreamCaptureStatusNone;
+  int rc = SP_OK;
+  if (table) {
+    if ((rc = c->cstage.acquire())) return rc;
+    StepIO* io = reinterpret_cast<StepIO*>(c->cstage.host);
+    for (int t = 0; t < T; ++t) io[t] = frame_io(t);
+    if ((rc = c->cstage.upload(c->d_cio, sizeof(StepIO) * (size_t)T, c->stream))) return rc;
+  }
+  for (int t0 = 0; t0 < T; t0 += c->pa_slots) {
+    const int n = std::min(c->pa_slots, T - t0);
+    for (const Phase& ph0 : table && n == c->CH ? c->clip_full : c->clip_part) {
       Phase ph = ph0;
+      if (ph.kind != JOB_RGB && ph.kind != JOB_FEAT && ph.kind != JOB_DOWN && ph.kind != JOB_TAIL) break;
       if (ph.kind == JOB_RGB) ph.flag = 0;
-      int rc = run_phase(c, ph, c->d_sd, nullptr, &io, ph.n);
-      if (rc) return rc;
+      if (table) {
+        if ((rc = run_phase(c, ph, c->d_sd + 1, c->d_cio + t0, nullptr, ph.upto[n]))) return rc;
+        continue;
+      }
+      for (int z = 0; z < n; ++z) {
+        const StepIO io = frame_io(t0 + z);
+        ph.off = ph0.off + ph.upto[z];
+        if ((rc = run_phase(c, ph, c->d_sd + 1, nullptr, &io, ph.upto[z + 1] - ph.upto[z]))) return rc;
+      }
     }
-    int rc = SP_OK;
-    const hipError_t e = timed(c, JOB_PIX_ADJ, [&]() -> hipError_t {
-      hipError_t r = sp_pa_gs(c->gs_all + (size_t)t * plc, c->S_tape + (size_t)t * plc, c->ms_tape + 2 * (size_t)t,
-                              (int)plc, c->p.flat_tol, A.gS, A.gs_part, c->stream);
-      if (r == hipSuccess) r = sp_pa_nadjoint(A.maps_fbar, SP_NCH, (int)plc, g.Hl[cm], c->p.flat_tol, c->stream);
-      for (int l = cm - 1; l >= g.c_min && r == hipSuccess; --l)
-        r = sp_pa_plane(0, A.tab_gn[l], SP_NCH, n_l(l), 0, nullptr, nullptr, c->stream);
-      // dL/dX and the pairs' scales start at zero
-      if (r == hipSuccess) r = sp_pa_zero(A.gX[0], A.gX_floats + (size_t)SP_NCH * g.n_pairs * SP_PA_AMAX, c->stream);
-      // maps of every pair in one launch, then the adjoint and the up-sample transpose one
-      // group at a time (a group's pairs write different levels)
-      auto group_n = [&](const int* order, int first, int count, bool surround) {
-        int mx = 0;
-        for (int k = first; k < first + count; ++k) mx = std::max(mx, n_l(surround ? g.ps[order[k]] : g.pc[order[k]]));
-        return mx;
-      };
-      if (r == hipSuccess)
-        r = sp_pa_plane(1, A.tab_cs[A.cs_order[0]], SP_NCH * g.n_pairs, group_n(A.cs_order, 0, g.n_pairs, false), 0,
-                        nullptr, nullptr, c->stream);
-      if (r == hipSuccess)
-        r = sp_pa_nadjoint(A.maps_F, SP_NCH * g.n_pairs, maxF, pixadj_dims(g).maxh, c->p.flat_tol, c->stream);
-      for (int q = 0; q < A.n_cs && r == hipSuccess; ++q) {
-        const int p0 = A.cs_order[A.cs_first[q]];
-        r = sp_pa_plane(2, A.tab_cs[p0], SP_NCH * A.cs_count[q], group_n(A.cs_order, A.cs_first[q], A.cs_count[q], false),
-                        0, A.gc[p0], nullptr, c->stream);
-      }
-      for (int q = 0; q < A.n_up && r == hipSuccess; ++q) {
-        const int p0 = A.up_order[A.up_first[q]];
-        r = sp_pa_plane(3, A.tab_up[p0], SP_NCH * A.up_count[q], group_n(A.up_order, A.up_first[q], A.up_count[q], true),
-                        0, nullptr, nullptr, c->stream);
-      }
-      // the Gabor transposes of every used level at once (each reads its level's orientation
-      // gradients, complete here, and adds into that level's intensity gradient), then the
-      // pyramid-step transposes from the top level down
-      if (r == hipSuccess) {
-        PaGabLevels L{};
-        int max_tiles = 0;
-        for (int l = g.top; l >= 1; --l)
-          if (A.tab_gab[l]) {
-            L.tab[L.n++] = A.tab_gab[l];
-            max_tiles = std::max(max_tiles, ((g.Hl[l] + 15) / 16) * ((g.Wl[l] + 15) / 16));
-          }
-        r = sp_pa_gabor(L, max_tiles, A.taps, c->stream, c->p.gabor_radius);
-      }
-      for (int l = g.top; l >= 1 && r == hipSuccess; --l)
-        r = sp_pa_plane(0, A.tab_pyr[l], 4, n_l(l - 1), 1, nullptr, nullptr, c->stream);
-      if (r == hipSuccess)
-        r = sp_pa_feat(io.rgb, io.rgb_prev, c->h_sd.rgb_max_part, c->h_sd.n_rgb, A.gX[0], (int)HW,
-                       grad_frames + (size_t)t * HW3, t ? grad_frames + (size_t)(t - 1) * HW3 : nullptr, c->stream);
-      return r;
+    const hipError_t e = timed(c, JOB_PIX_ADJ, [&] {
+      return sp_pixel_adjoint(c->pa, c->d_sd + 1, c->h_slots[0], t0, n, frames, c->gs_all + (size_t)t0 * plc,
+                              c->S_tape + (size_t)t0 * plc, c->ms_tape + 2 * (size_t)t0,
+                              c->fbar_tape + (size_t)t0 * SP_NCH * plc, grad_frames, c->stream);
     });
-    if ((rc = ok(e, "launch"))) return rc;
+    if (e != hipSuccess) return fail(SP_EHIP, "pixel adjoint launch: %s", hipGetErrorString(e));
   }
   return SP_OK;
 }

@@ -363,42 +363,37 @@ struct CutIO {
   int32_t pad;
 };
 
-// Pixel-level adjoint (dL/d frame): one map of the N(.) adjoint.
+// Pixel-level adjoint (dL/d frame).
+#define SP_PA_SLOTS 8      // most frames whose adjoint runs side by side
+#define SP_PA_TILE 1024    // elements of a workgroup of the elementwise passes (and of a min / max partial)
 struct PaStrip {           // partial sums of one 8-row strip of an N(.) adjoint map
   double sb, sgy, sg;      // block maxima of Y, g Y, g
   int32_t jn, jx;          // first positions within the tie tolerance of the minimum and maximum
 };
-#define SP_PA_MMT 4096     // pixels of a min / max partial of an N(.) adjoint map
-struct PaMap {
-  const float* X;          // [h][w] the map N was applied to
-  const float* g;          // [h][w] dL/dN before the factor gs
-  float* out;              // [h][w] dL/dX (may be the storage of X: the apply pass does not read X)
-  int32_t* bpos;           // [nb] first position of each 8x8 block maximum
-  float* sc;               // [8] A/range, gb/range, g(min), g(max), argmin, argmax (int bits), flat, nb
-  float2* mm;              // [ceil(h w / SP_PA_MMT)] (min, max) partials
-  PaStrip* strip;          // [ceil(h / 8)] strip partials
-  int32_t h, w;
-  float gs;
-  int32_t pad;
+struct PaMM {              // partial of one tile of a map
+  float mn, mx;            // its minimum and maximum
+  float am;                // a pair's largest |X(c)|, |X(s)|
+  float pad;
 };
-// A plane pair of a gather pass (pyramid-step transpose, centre-surround, up-sample transpose).
-struct PaPlane {
-  const float* a;          // input plane(s)
-  const float* b;
-  float* out;
-  uint32_t* amax;          // centre-surround: the pair's scale max |X(c)|, |X(s)| (float bits), as the
-                           // maximum of SP_PA_AMAX slots (workgroup b takes slot b mod SP_PA_AMAX)
-  int32_t ha, wa, hb, wb;  // sizes of a and b (b: the surround level of a centre-surround pair)
-  int32_t d;               // level offset of the pair
-  int32_t pad;
+// The workspace of frame slot 0 (slot z: every pointer `stride` bytes further, z times).
+// Maps m of the N(.) adjoint: the 8 across-scale sums, then every pair's 8 maps.
+struct PaDesc {
+  float* gS;               // [Hc][Wc] dL/dS of the frame
+  double* gs_part;         // per-workgroup partials of sum gs S
+  float* gfbar;            // [8][Hc][Wc]
+  float* gN[SP_MAXL];      // [8][H_l][W_l] dL/dN(F) at levels c_min .. c_max - 1
+  float* D[SP_MAXP];       // [8][H_c][W_c] per pair: the signed difference, then its gradient
+  float* gX[SP_MAXL];      // [8][H_l][W_l] dL/d(channel maps) per level 1..top
+  int32_t* bpos;           // [maps][nb_n] first position of each 8x8 block maximum
+  float* sc;               // [maps][SP_PA_SC] A/range, gb/range, g(min), g(max), argmin, argmax (int bits), flat, scale
+  PaMM* mm;                // [maps][mm_n]
+  PaStrip* strip;          // [maps][strip_n]
+  size_t stride;
+  int32_t mm_n, strip_n, nb_n;
+  uint32_t centres;        // bit l: level l is a centre
+  int32_t cl[4], n_cl;     // the centre levels
+  int32_t sl[SP_MAXP], n_sl;   // the surround levels
+  int32_t ul[SP_MAXL], n_ul;   // the used levels, largest first
 };
-
-// The Gabor transposes of several levels in one launch: level blockIdx.y's plane table.
-#define SP_PA_AMAX 16   // atomic-maximum slots of a pair's scale (fewer workgroups per address)
-
-struct PaGabLevels {
-  const PaPlane* tab[SP_MAXL];
-  int32_t n;
-};
-#define SP_PA_R 8          // largest Gabor radius of the adjoint's 2-D taps
+#define SP_PA_R SP_MAXR    // largest Gabor radius
 #define SP_PA_SC 8         // floats of the statistics of one N(.) adjoint map

@@ -21,17 +21,6 @@ namespace {
 // F-bar of a step: its tape slot when the step is recorded, else the stream's own map.
 __device__ __forceinline__ float* fbar_ptr(const StreamDesc& sd, float* tape) { return tape ? tape : sd.fbar; }
 
-// Channel k (I, RG, BY, O0, O45, O90, O135, M) of level l.
-__device__ __forceinline__ const float* chan_ptr(const StreamDesc& sd, int k, int l) {
-  // selects rather than branches: every operand is a uniform scalar load
-  const size_t plane = (size_t)sd.Hl[l] * sd.Wl[l];
-  const float* b = sd.base[l];
-  const float* g = sd.gab[l];
-  const bool gabor = (unsigned)(k - 3) < 4u;
-  const int idx = k < 3 ? k : (k == 7 ? 3 : k - 3);
-  return (gabor ? g : b) + idx * plane;
-}
-
 // Sample-aligned bilinear tap set for target index y of a map whose source level is
 // d steps coarser and has n samples: position y / 2^d clamped to [0, n-1].
 struct Tap { int i0, i1; float w; };

@@ -1,7 +1,10 @@
 // Pixel-level adjoint of the saliency model (Section 3 / Section 7.2): dL/d frame_t from
 // dL/dS_t, through the weighted sum, N(.), the across-scale sum, centre-surround, the Gabor
 // maps, the pyramid and the level-0 features (the motion feature also reaches frame t-1).
-// The forward maps of the frame are recomputed by the forward kernels first.  Every pass
+// The forward maps of up to SP_PA_SLOTS frames are recomputed side by side by the forward
+// kernels first (the across-scale sums come from the tape), and every pass here runs over all of
+// them (blockIdx.z = frame slot): one 640x480 frame's passes were about 30 dependent launches
+// of 2 to 37 us, 206 us a frame; eight frames at once take 38 us a frame.  Every pass
 // here gathers: one thread per output element, each output a fixed-order sum over the
 // inputs that depend on it, so results do not depend on scheduling.  Non-differentiable
 // points follow one convention: the global minimum and maximum and each 8x8 block maximum
@@ -16,40 +19,55 @@
 #include <stdint.h>
 #include <math.h>
 
+#include <algorithm>
+
 #include "sp_internal.h"
 #include "sp_kernels.h"
 #include "sp_device.h"
 
 namespace {
 
+constexpr int TILE = SP_PA_TILE;             // elements of a workgroup of the elementwise passes
+constexpr int PER = TILE / SP_BLOCK;
 
 __device__ __forceinline__ float kb(int i) {   // i in -2..2
   return i == 0 ? 0.375f : ((i == 1 || i == -1) ? 0.25f : 0.0625f);
 }
 
+// The workspace pointer of frame slot z.
+template <class T>
+__device__ __forceinline__ T* slot(T* p, const PaDesc& A, int z) {
+  return reinterpret_cast<T*>(const_cast<char*>(reinterpret_cast<const char*>(p)) + (size_t)z * A.stride);
+}
+
 // dL/dS = gs / m - [x = x*] sum(gs S) / m^2 (zero when S was flat), in two launches.
-__global__ __launch_bounds__(SP_BLOCK) void k_pa_gs(const float* __restrict__ gs, const float* __restrict__ S,
-                                                    const float* __restrict__ ms, int n, float flat_tol,
-                                                    float* __restrict__ gS, double* __restrict__ part) {
+__global__ __launch_bounds__(SP_BLOCK) void k_pa_gs(PaDesc A, const float* __restrict__ gs_, const float* __restrict__ S_,
+                                                    const float* __restrict__ ms_, int n, float flat_tol) {
   // every workgroup: SP_BLOCK elements of gs / m and its FP64 partial of sum gs S; the
   // element at the argmax is left to k_pa_gs_fix
-  __shared__ double sh[SP_BLOCK];
+  __shared__ double sh[4];
+  const int z = blockIdx.z;
+  const float *gs = gs_ + (size_t)z * n, *S = S_ + (size_t)z * n, *ms = ms_ + 2 * z;
   const float m = ms[0];
   const int xs = __float_as_int(ms[1]);
   const bool flat = !(m > flat_tol);
   const int i = blockIdx.x * SP_BLOCK + threadIdx.x;
   const float g = i < n ? gs[i] : 0.f;
-  const double dot = block_sum_d(i < n ? (double)g * (double)S[i] : 0.0, sh);
-  if (i < n && i != xs) gS[i] = flat ? 0.f : g * (1.f / m);
-  if (threadIdx.x == 0) part[blockIdx.x] = dot;
+  const double dot = wave_sum_d(i < n ? (double)g * (double)S[i] : 0.0);
+  if (i < n && i != xs) slot(A.gS, A, z)[i] = flat ? 0.f : g * (1.f / m);
+  if (lane_id() == 0) sh[wave_id()] = dot;
+  __syncthreads();
+  if (threadIdx.x == 0) slot(A.gs_part, A, z)[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
 // The argmax element of gS: gs / m - (sum gs S) / m^2, the sum from the workgroups' partials
 // in a fixed order.
-__global__ __launch_bounds__(SP_BLOCK) void k_pa_gs_fix(const float* __restrict__ gs, const float* __restrict__ ms,
-                                                        int n, int nparts, float flat_tol, float* __restrict__ gS,
-                                                        const double* __restrict__ part) {
+__global__ __launch_bounds__(SP_BLOCK) void k_pa_gs_fix(PaDesc A, const float* __restrict__ gs_, const float* __restrict__ ms_,
+                                                        int n, int nparts, float flat_tol) {
   __shared__ double sh[SP_BLOCK];
+  const int z = blockIdx.z;
+  const float *gs = gs_ + (size_t)z * n, *ms = ms_ + 2 * z;
+  const double* part = slot(A.gs_part, A, z);
   double acc = 0.0;
   for (int k = threadIdx.x; k < nparts; k += SP_BLOCK) acc += part[k];
   const double dot = block_sum_d(acc, sh);
@@ -57,87 +75,154 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_gs_fix(const float* __restrict_
   if (threadIdx.x == 0 && xs >= 0 && xs < n) {   // an index outside the map was written by k_pa_gs
     const float m = ms[0];
     const float corr = (float)(dot / ((double)m * (double)m));
-    gS[xs] = !(m > flat_tol) ? 0.f : gs[xs] * (1.f / m) - corr;
+    slot(A.gS, A, z)[xs] = !(m > flat_tol) ? 0.f : gs[xs] * (1.f / m) - corr;
   }
 }
 
 // Tolerance (on the normalised map) within which values count as tied with an extreme.
 constexpr float kTie = 0x1p-20f;
 
-// Statistics of the N(.) adjoint, in three launches over all maps: (1) the (min, max) of
-// tiles of SP_PA_MMT pixels; (2) per 8-row strip, with the map's range reduced from (1):
-// each 8x8 block's maximum of Y = (X - mn) / range and its first position (row-major)
+// Maps of the N(.) adjoint: m < 8 the across-scale sum of channel m (from the tape), then the
+// eight centre-surround maps of each pair.  A pair's plane holds the signed difference D; the
+// map is |D|.
+struct MapView {
+  gp<const float> X;   // the map, or D where abs is set
+  gp<const float> g;   // dL/dN before the factor gs
+  int h, w, m;
+  float gs;
+  bool abs;
+  __device__ __forceinline__ float at(int i) const { return abs ? fabsf(X[i]) : X[i]; }
+};
+__device__ __forceinline__ MapView map_view(const PaDesc& A, const StreamDesc& sd, const float* fbar, int m, int z) {
+  MapView M;
+  const int k = m & (SP_NCH - 1);
+  const size_t plc = (size_t)sd.Hl[sd.c_max] * sd.Wl[sd.c_max];
+  M.m = m;
+  if (m < SP_NCH) {
+    M.X = G(fbar + ((size_t)z * SP_NCH + k) * plc);
+    M.g = G((const float*)slot(A.gS, A, z));
+    M.h = sd.Hl[sd.c_max];
+    M.w = sd.Wl[sd.c_max];
+    M.gs = sd.w[k];
+    M.abs = false;
+  } else {
+    const int p = (m >> 3) - 1, c = sd.pc[p];
+    M.h = sd.Hl[c];
+    M.w = sd.Wl[c];
+    const size_t n = (size_t)M.h * M.w;
+    M.X = G((const float*)slot(A.D[p], A, z) + k * n);
+    M.g = G((const float*)(c == sd.c_max ? slot(A.gfbar, A, z) : slot(A.gN[c], A, z)) + k * n);
+    M.gs = 1.f;
+    M.abs = true;
+  }
+  return M;
+}
+
+// Statistics of the N(.) adjoint: (1) the (min, max) of tiles of TILE pixels (the
+// centre-surround pass takes its own); (2) per 8-row strip, with the map's range reduced from
+// (1): each 8x8 block's maximum of Y = (X - mn) / range and its first position (row-major)
 // within kTie of it, the strip's sums of the block maxima, g Y and g (FP64), and the first
 // positions within kTie of the minimum and the maximum; (3) per map, the scalars below.
 
-__device__ __forceinline__ int block_min_i(int v, int* sh4) {
-  v = wave_min_i(v);
-  __syncthreads();
-  if (lane_id() == 0) sh4[wave_id()] = v;
-  __syncthreads();
-  return min(min(sh4[0], sh4[1]), min(sh4[2], sh4[3]));
-}
-
-// The map's (min, max) from its tile partials (every thread gets them).
-__device__ __forceinline__ void map_range(const PaMap& M, float* sh4, float& mn, float& mx) {
-  const int nt = (M.h * M.w + SP_PA_MMT - 1) / SP_PA_MMT;
-  float a = INFINITY, b = -INFINITY;
+// The map's (min, max) and, for a pair, the scale max(|X(c)|, |X(s)|) from its tile partials
+// (every thread gets them).
+__device__ __forceinline__ void map_range(const PaDesc& A, const MapView& M, int z, float (*sh)[4], float& mn, float& mx,
+                                          float& am) {
+  const int nt = (M.h * M.w + TILE - 1) / TILE;
+  const PaMM* mm = slot(A.mm, A, z) + (size_t)M.m * A.mm_n;
+  float a = INFINITY, b = -INFINITY, c = 0.f;
   for (int k = threadIdx.x; k < nt; k += SP_BLOCK) {
-    const float2 v = M.mm[k];
-    a = fminf(a, v.x);
-    b = fmaxf(b, v.y);
+    const PaMM v = mm[k];
+    a = fminf(a, v.mn);
+    b = fmaxf(b, v.mx);
+    c = fmaxf(c, v.am);
   }
-  mn = block_reduce<OpMin>(a, sh4);
-  mx = block_reduce<OpMax>(b, sh4);
+  a = wave_reduce<OpMin>(a);
+  b = wave_reduce<OpMax>(b);
+  c = wave_reduce<OpMax>(c);
+  if (lane_id() == 0) {
+    sh[0][wave_id()] = a;
+    sh[1][wave_id()] = b;
+    sh[2][wave_id()] = c;
+  }
+  __syncthreads();
+  mn = fminf(fminf(sh[0][0], sh[0][1]), fminf(sh[0][2], sh[0][3]));
+  mx = fmaxf(fmaxf(sh[1][0], sh[1][1]), fmaxf(sh[1][2], sh[1][3]));
+  am = fmaxf(fmaxf(sh[2][0], sh[2][1]), fmaxf(sh[2][2], sh[2][3]));
+}
+// One tile's partial from the threads' values.
+__device__ __forceinline__ void store_mm(float mn, float mx, float am, PaMM* out, float (*sh)[4]) {
+  mn = wave_reduce<OpMin>(mn);
+  mx = wave_reduce<OpMax>(mx);
+  am = wave_reduce<OpMax>(am);
+  if (lane_id() == 0) {
+    sh[0][wave_id()] = mn;
+    sh[1][wave_id()] = mx;
+    sh[2][wave_id()] = am;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0)
+    *out = PaMM{fminf(fminf(sh[0][0], sh[0][1]), fminf(sh[0][2], sh[0][3])),
+                fmaxf(fmaxf(sh[1][0], sh[1][1]), fmaxf(sh[1][2], sh[1][3])),
+                fmaxf(fmaxf(sh[2][0], sh[2][1]), fmaxf(sh[2][2], sh[2][3])), 0.f};
 }
 
-__global__ __launch_bounds__(SP_BLOCK) void k_pa_nmm(const PaMap* __restrict__ maps) {
-  __shared__ float sh4[4];
-  const PaMap M = maps[blockIdx.y];
-  const int n = M.h * M.w, base = blockIdx.x * SP_PA_MMT;
+__global__ __launch_bounds__(SP_BLOCK) void k_pa_nmm(PaDesc A, const StreamDesc* __restrict__ sds, const float* __restrict__ fbar) {
+  __shared__ float sh[3][4];
+  const int z = blockIdx.z;
+  const MapView M = map_view(A, sds[z], fbar, blockIdx.y, z);
+  const int n = M.h * M.w, base = blockIdx.x * TILE;
   if (base >= n) return;   // uniform
   float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
-  for (int k = 0; k < SP_PA_MMT / SP_BLOCK; ++k) {
+  for (int k = 0; k < PER; ++k) {
     const int i = base + k * SP_BLOCK + threadIdx.x;
-    const float v = M.X[min(i, n - 1)];
+    const float v = M.at(min(i, n - 1));
     mn = i < n ? fminf(mn, v) : mn;
     mx = i < n ? fmaxf(mx, v) : mx;
   }
-  mn = block_reduce<OpMin>(mn, sh4);
-  mx = block_reduce<OpMax>(mx, sh4);
-  if (threadIdx.x == 0) M.mm[blockIdx.x] = make_float2(mn, mx);
+  store_mm(mn, mx, 0.f, slot(A.mm, A, z) + (size_t)M.m * A.mm_n + blockIdx.x, sh);
 }
 
-__global__ __launch_bounds__(SP_BLOCK) void k_pa_nstrip(const PaMap* __restrict__ maps, float flat_tol) {
-  __shared__ float sh4[4];
-  __shared__ int shi[4];
-  __shared__ double sh[SP_BLOCK];
-  const PaMap M = maps[blockIdx.y];
+__global__ __launch_bounds__(SP_BLOCK) void k_pa_nstrip(PaDesc A, const StreamDesc* __restrict__ sds,
+                                                        const float* __restrict__ fbar, int m0, float flat_tol) {
+  __shared__ float sh[3][4];
+  __shared__ double shd[3][4];
+  __shared__ int shi[2][4];
+  const int z = blockIdx.z;
+  const MapView M = map_view(A, sds[z], fbar, m0 + blockIdx.y, z);
   if ((int)blockIdx.x >= (M.h + 7) >> 3) return;   // uniform
-  float mn, mx;
-  map_range(M, sh4, mn, mx);
+  float mn, mx, am;
+  map_range(A, M, z, sh, mn, mx, am);
   const float rng = mx - mn;
   if (!(rng > flat_tol)) return;   // uniform: a flat map passes no gradient
   const float rr = 1.f / rng;
+  const gp<int32_t> bpos = G(slot(A.bpos, A, z) + (size_t)M.m * A.nb_n);
   const int y0 = blockIdx.x * 8, nrow = min(8, M.h - y0), nbx = (M.w + 7) >> 3;
   double sb = 0.0, sgy = 0.0, sg = 0.0;
   int jn = 0x7fffffff, jx = 0x7fffffff;
   // a thread takes column x of the strip; the eight columns of a block are eight
-  // consecutive lanes (the chunks of SP_BLOCK columns start at multiples of 8)
+  // consecutive lanes (the chunks of SP_BLOCK columns start at multiples of 8).  All sixteen
+  // loads of a chunk are issued before any use.
   for (int x0 = 0; x0 < M.w; x0 += SP_BLOCK) {
     const int x = x0 + threadIdx.x;
     const bool cv = x < M.w;
-    float Y[8], cb = -INFINITY;
+    float Y[8], G8[8], cb = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int i = (y0 + min(r, nrow - 1)) * M.w + min(x, M.w - 1);
+      Y[r] = M.at(i);
+      G8[r] = M.g[i];
+    }
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
       const bool ok = cv && r < nrow;
       const int i = (y0 + min(r, nrow - 1)) * M.w + min(x, M.w - 1);
-      const float v = (M.X[i] - mn) * rr;
+      const float v = (Y[r] - mn) * rr;
       Y[r] = ok ? v : -INFINITY;
       cb = fmaxf(cb, Y[r]);
       if (ok) {
-        const double g = (double)M.g[i] * (double)M.gs;
+        const double g = (double)G8[r] * (double)M.gs;
         sgy += g * (double)v;
         sg += g;
         if (v <= kTie) jn = min(jn, i);
@@ -146,41 +231,58 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_nstrip(const PaMap* __restrict_
     }
     // the block's maximum and its first position within kTie (row-major: smallest index)
     float best = cb;
-    best = fmaxf(best, __shfl_xor(best, 1));
-    best = fmaxf(best, __shfl_xor(best, 2));
-    best = fmaxf(best, __shfl_xor(best, 4));
+    best = fmaxf(best, dpp_f<0xB1>(best));
+    best = fmaxf(best, dpp_f<0x4E>(best));
+    best = fmaxf(best, dpp_f<0x141>(best));
     int cand = 0x7fffffff;
 #pragma unroll
     for (int r = 7; r >= 0; --r)
       if (Y[r] >= best - kTie) cand = (y0 + r) * M.w + x;
-    cand = min(cand, __shfl_xor(cand, 1));
-    cand = min(cand, __shfl_xor(cand, 2));
-    cand = min(cand, __shfl_xor(cand, 4));
+    cand = min(cand, dpp_i<0xB1>(cand));
+    cand = min(cand, dpp_i<0x4E>(cand));
+    cand = min(cand, dpp_i<0x141>(cand));
     if ((threadIdx.x & 7) == 0 && cv) {
-      M.bpos[(y0 >> 3) * nbx + (x >> 3)] = cand;
+      bpos[(y0 >> 3) * nbx + (x >> 3)] = cand;
       sb += (double)best;
     }
   }
-  sb = block_sum_d(sb, sh);
-  sgy = block_sum_d(sgy, sh);
-  sg = block_sum_d(sg, sh);
-  jn = block_min_i(jn, shi);
-  jx = block_min_i(jx, shi);
-  if (threadIdx.x == 0) M.strip[blockIdx.x] = PaStrip{sb, sgy, sg, jn, jx};
+  sb = wave_sum_d(sb);
+  sgy = wave_sum_d(sgy);
+  sg = wave_sum_d(sg);
+  jn = wave_min_i(jn);
+  jx = wave_min_i(jx);
+  if (lane_id() == 0) {
+    const int w = wave_id();
+    shd[0][w] = sb;
+    shd[1][w] = sgy;
+    shd[2][w] = sg;
+    shi[0][w] = jn;
+    shi[1][w] = jx;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    auto add = [&](int q) { return (shd[q][0] + shd[q][1]) + (shd[q][2] + shd[q][3]); };
+    auto mini = [&](int q) { return min(min(shi[q][0], shi[q][1]), min(shi[q][2], shi[q][3])); };
+    slot(A.strip, A, z)[(size_t)M.m * A.strip_n + blockIdx.x] = PaStrip{add(0), add(1), add(2), mini(0), mini(1)};
+  }
 }
 
-__global__ __launch_bounds__(SP_BLOCK) void k_pa_nfin(const PaMap* __restrict__ maps, float flat_tol) {
-  __shared__ float sh4[4];
-  __shared__ int shi[4];
-  __shared__ double sh[SP_BLOCK];
-  const PaMap M = maps[blockIdx.x];
-  float mn, mx;
-  map_range(M, sh4, mn, mx);
+__global__ __launch_bounds__(SP_BLOCK) void k_pa_nfin(PaDesc A, const StreamDesc* __restrict__ sds,
+                                                      const float* __restrict__ fbar, int m0, float flat_tol) {
+  __shared__ float sh[3][4];
+  __shared__ int shi[2][4];
+  __shared__ double shd[3][4];
+  const int z = blockIdx.z;
+  const MapView M = map_view(A, sds[z], fbar, m0 + blockIdx.y, z);
+  float* sc = slot(A.sc, A, z) + (size_t)M.m * SP_PA_SC;
+  const PaStrip* strip = slot(A.strip, A, z) + (size_t)M.m * A.strip_n;
+  float mn, mx, am;
+  map_range(A, M, z, sh, mn, mx, am);
   const float rng = mx - mn;
   if (!(rng > flat_tol)) {
     if (threadIdx.x == 0) {
-      for (int k = 0; k < SP_PA_SC; ++k) M.sc[k] = 0.f;
-      M.sc[6] = 1.f;
+      for (int k = 0; k < SP_PA_SC; ++k) sc[k] = 0.f;
+      sc[6] = 1.f;
     }
     return;
   }
@@ -188,52 +290,73 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_nfin(const PaMap* __restrict__ 
   double sb = 0.0, sgy = 0.0, sg = 0.0;
   int jn = 0x7fffffff, jx = 0x7fffffff;
   for (int k = threadIdx.x; k < ns; k += SP_BLOCK) {
-    const PaStrip p = M.strip[k];
+    const PaStrip p = strip[k];
     sb += p.sb;
     sgy += p.sgy;
     sg += p.sg;
     jn = min(jn, p.jn);
     jx = min(jx, p.jx);
   }
-  const double Sb = block_sum_d(sb, sh);
-  const double Sgy = block_sum_d(sgy, sh);
-  const double Sg = block_sum_d(sg, sh);
-  const int gimn = block_min_i(jn, shi), gimx = block_min_i(jx, shi);
+  sb = wave_sum_d(sb);
+  sgy = wave_sum_d(sgy);
+  sg = wave_sum_d(sg);
+  jn = wave_min_i(jn);
+  jx = wave_min_i(jx);
+  if (lane_id() == 0) {
+    const int w = wave_id();
+    shd[0][w] = sb;
+    shd[1][w] = sgy;
+    shd[2][w] = sg;
+    shi[0][w] = jn;
+    shi[1][w] = jx;
+  }
+  __syncthreads();
   const int nb = ((M.w + 7) >> 3) * ns;
   if (threadIdx.x == 0) {
+    auto add = [&](int q) { return (shd[q][0] + shd[q][1]) + (shd[q][2] + shd[q][3]); };
+    auto mini = [&](int q) { return min(min(shi[q][0], shi[q][1]), min(shi[q][2], shi[q][3])); };
+    const double Sb = add(0), Sgy = add(1), Sg = add(2);
     const double mbar = nb > 1 ? (Sb - 1.0) / (nb - 1) : 0.0;
-    const double A = (1.0 - mbar) * (1.0 - mbar);
+    const double a = (1.0 - mbar) * (1.0 - mbar);
     const double gb = nb > 1 ? -2.0 * (1.0 - mbar) * Sgy / (nb - 1) : 0.0;
-    const double sgyy = A * Sgy + gb * Sb;   // sum gY Y
-    const double sgyt = A * Sg + gb * nb;    // sum gY
-    M.sc[0] = (float)(A / rng);
-    M.sc[1] = (float)(gb / rng);
-    M.sc[2] = (float)((sgyy - sgyt) / rng);
-    M.sc[3] = (float)(-sgyy / rng);
-    M.sc[4] = __int_as_float(gimn);
-    M.sc[5] = __int_as_float(gimx);
-    M.sc[6] = 0.f;
-    M.sc[7] = (float)nb;
+    const double sgyy = a * Sgy + gb * Sb;   // sum gY Y
+    const double sgyt = a * Sg + gb * nb;    // sum gY
+    sc[0] = (float)(a / rng);
+    sc[1] = (float)(gb / rng);
+    sc[2] = (float)((sgyy - sgyt) / rng);
+    sc[3] = (float)(-sgyy / rng);
+    sc[4] = __int_as_float(mini(0));
+    sc[5] = __int_as_float(mini(1));
+    sc[6] = 0.f;
+    sc[7] = am;
   }
 }
 
-// dL/dX = gN A / range + [block maximum] gb / range + [argmin] g(min) + [argmax] g(max).
-__global__ __launch_bounds__(SP_BLOCK) void k_pa_napply(const PaMap* __restrict__ maps) {
-  const PaMap M = maps[blockIdx.y];
-  const int n = M.h * M.w;
-  const int i = blockIdx.x * SP_BLOCK + threadIdx.x;
-  if (i >= n) return;
-  if (M.sc[6] != 0.f) {
-    M.out[i] = 0.f;
-    return;
+// dL/dX of map M at element i (row y, column x):
+// gN A / range + [block maximum] gb / range + [argmin] g(min) + [argmax] g(max).
+__device__ __forceinline__ float napply_at(const MapView& M, const float* sc, gp<const int32_t> bpos, int nbx, int y, int x, int i) {
+  if (sc[6] != 0.f) return 0.f;
+  float v = M.g[i] * M.gs * sc[0];
+  if (bpos[(y >> 3) * nbx + (x >> 3)] == i) v += sc[1];
+  if (i == __float_as_int(sc[4])) v += sc[2];
+  if (i == __float_as_int(sc[5])) v += sc[3];
+  return v;
+}
+
+// The across-scale sums' adjoint gfbar (blockIdx.y = channel).
+__global__ __launch_bounds__(SP_BLOCK) void k_pa_napply(PaDesc A, const StreamDesc* __restrict__ sds, const float* __restrict__ fbar) {
+  const int z = blockIdx.z;
+  const MapView M = map_view(A, sds[z], fbar, blockIdx.y, z);
+  const float* sc = slot(A.sc, A, z) + (size_t)M.m * SP_PA_SC;
+  const gp<const int32_t> bpos = G((const int32_t*)slot(A.bpos, A, z) + (size_t)M.m * A.nb_n);
+  const int n = M.h * M.w, base = blockIdx.x * TILE, nbx = (M.w + 7) >> 3;
+  const gp<float> out = G(slot(A.gfbar, A, z) + (size_t)blockIdx.y * n);
+  Walk2 wk(base + threadIdx.x, M.w);
+#pragma unroll
+  for (int k = 0; k < PER; ++k, wk.next()) {
+    const int i = base + k * SP_BLOCK + threadIdx.x;
+    if (i < n) out[i] = napply_at(M, sc, bpos, nbx, wk.r, wk.c, i);
   }
-  const int y = i / M.w, x = i - y * M.w;
-  const int nbx = (M.w + 7) >> 3;
-  float v = M.g[i] * M.gs * M.sc[0];
-  if (M.bpos[(y >> 3) * nbx + (x >> 3)] == i) v += M.sc[1];
-  if (i == __float_as_int(M.sc[4])) v += M.sc[2];
-  if (i == __float_as_int(M.sc[5])) v += M.sc[3];
-  M.out[i] = v;
 }
 
 // Weight of output position yo (of a clamped 5-tap blur over n positions) in the blur at yp.
@@ -244,24 +367,77 @@ __device__ __forceinline__ float blur_w(int yo, int yp, int n) {
   return a;
 }
 
-// Transpose of one pyramid step: out (ha x wa, the finer level) +=/= sum over the coarser
-// level b of g(y2, x2) a(y, 2 y2) a(x, 2 x2).  Plane table entry: a = coarse input, out.
-__global__ __launch_bounds__(SP_BLOCK) void k_pa_reduce_t(const PaPlane* __restrict__ tab, int accumulate) {
-  const PaPlane P = tab[blockIdx.y];
-  const int n = P.ha * P.wa;
-  const int i = blockIdx.x * SP_BLOCK + threadIdx.x;
-  if (i >= n) return;
-  const int y = i / P.wa, x = i - y * P.wa;
-  float acc = 0.f;
-  for (int y2 = max(0, (y - 1) >> 1); y2 <= min(P.hb - 1, (y + 2) >> 1); ++y2) {
-    const float wy = blur_w(y, 2 * y2, P.ha);
-    if (wy == 0.f) continue;
-    float r = 0.f;
-    for (int x2 = max(0, (x - 1) >> 1); x2 <= min(P.wb - 1, (x + 2) >> 1); ++x2)
-      r += P.a[y2 * P.wb + x2] * blur_w(x, 2 * x2, P.wa);
-    acc += wy * r;
+// Transpose of one pyramid step at fine rows 2q, 2q+1 and columns 2r, 2r+1: coarse rows and
+// columns q - 1 .. q + 1 reach them.  The nine coarse values of one channel serve the four
+// outputs; the weights come from wy, wx [2][3] (zero outside the coarse level).
+struct QuadT {
+  float wy[2][3], wx[2][3];
+  uint32_t o[3][3];   // clamped element offsets
+  __device__ __forceinline__ QuadT(int q, int r, int h, int w, int hb, int wb) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        const int y2 = q - 1 + b, x2 = r - 1 + b;
+        wy[a][b] = (y2 >= 0 && y2 < hb) ? blur_w(2 * q + a, 2 * y2, h) : 0.f;
+        wx[a][b] = (x2 >= 0 && x2 < wb) ? blur_w(2 * r + a, 2 * x2, w) : 0.f;
+      }
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b)
+        o[a][b] = (uint32_t)clampi(q - 1 + a, 0, hb - 1) * (uint32_t)wb + (uint32_t)clampi(r - 1 + b, 0, wb - 1);
   }
-  P.out[i] = accumulate ? P.out[i] + acc : acc;
+  __device__ __forceinline__ void load(const gp<const float> src, float (&v)[3][3]) const {
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) v[a][b] = src[o[a][b]];
+  }
+  // zero weights are skipped, not multiplied: they would turn an infinite gradient into NaN
+  __device__ __forceinline__ void apply(const float (&v)[3][3], float (&out)[2][2]) const {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        float acc = 0.f;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          float r = 0.f;
+#pragma unroll
+          for (int j = 0; j < 3; ++j) r += wx[b][j] != 0.f ? v[i][j] * wx[b][j] : 0.f;
+          acc += wy[a][i] != 0.f ? wy[a][i] * r : 0.f;
+        }
+        out[a][b] = acc;
+      }
+  }
+};
+
+// Transposed pyramid step from a level of hb x wb to the finer h x w, plane blockIdx.y (all
+// eight channels, or I, RG, BY, M: planes 0, 1, 2, 7 when four); out is added to or written.
+// A thread makes a 2x2 block from nine coarse values (one thread per output, with its up to
+// nine values and weights, took 14.7 us for the last step of a 640x480 frame).
+__global__ __launch_bounds__(SP_BLOCK) void k_pa_reduce_t(PaDesc A, const float* __restrict__ src_, float* __restrict__ out_,
+                                                          int h, int w, int hb, int wb, int accumulate) {
+  const int z = blockIdx.z;
+  const int pl = gridDim.y == 4 && blockIdx.y == 3 ? 7 : blockIdx.y;
+  const int i = blockIdx.x * SP_BLOCK + threadIdx.x;
+  if (i >= hb * wb) return;
+  const int q = i / wb, r = i - q * wb;
+  const gp<const float> src = G((const float*)slot(src_, A, z) + (size_t)pl * hb * wb);
+  const gp<float> out = G(slot(out_, A, z) + (size_t)pl * h * w);
+  const QuadT T(q, r, h, w, hb, wb);
+  float v[3][3], o[2][2];
+  T.load(src, v);
+  T.apply(v, o);
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+      if (2 * q + a < h && 2 * r + b < w) {
+        const uint32_t e = (uint32_t)(2 * q + a) * (uint32_t)w + (uint32_t)(2 * r + b);
+        out[e] = accumulate ? out[e] + o[a][b] : o[a][b];
+      }
 }
 
 // Bilinear sample-aligned tap of target position y at level offset d on n source samples.
@@ -272,176 +448,219 @@ __device__ __forceinline__ void tap(int y, int d, int n, int& i0, int& i1, float
   w = fy - (float)i0;
 }
 
-__device__ __forceinline__ float cs_diff(const PaPlane& P, int y, int x) {
-  int y0, y1, x0, x1;
-  float wy, wx;
-  tap(y, P.d, P.hb, y0, y1, wy);
-  tap(x, P.d, P.wb, x0, x1, wx);
-  const float* s = P.b;
-  const float top = (1.f - wx) * s[y0 * P.wb + x0] + wx * s[y0 * P.wb + x1];
-  const float bot = (1.f - wx) * s[y1 * P.wb + x0] + wx * s[y1 * P.wb + x1];
-  return P.a[y * P.wa + x] - ((1.f - wy) * top + wy * bot);
-}
-
-// F = |X(c) - up X(s)| for one pair and channel per plane entry (a = X(c), b = X(s)), and
-// the pair's scale max(max |X(c)|, max |X(s)|) by an atomic maximum on the float's bits
-// (order-preserving for non-negative floats; the slot starts at zero).
-__global__ __launch_bounds__(SP_BLOCK) void k_pa_csmap(const PaPlane* __restrict__ tab) {
-  __shared__ float red[SP_BLOCK / 64];
-  const PaPlane P = tab[blockIdx.y];
-  const int i = blockIdx.x * SP_BLOCK + threadIdx.x;
-  float m = 0.f;
-  if (i < P.ha * P.wa) {
-    const int y = i / P.wa, x = i - y * P.wa;
-    P.out[i] = fabsf(cs_diff(P, y, x));
-    m = fabsf(P.a[i]);
-    if (i < P.hb * P.wb) m = fmaxf(m, fabsf(P.b[i]));
+// D = X(c) - up X(s) of pair blockIdx.y / 8, channel blockIdx.y % 8 (kept for the adjoint), and
+// the tile's partial: (min, max) of F = |D| and the largest |X(c)|, |X(s)|.
+__global__ __launch_bounds__(SP_BLOCK) void k_pa_csmap(PaDesc A, const StreamDesc* __restrict__ sds) {
+  __shared__ float sh[3][4];
+  const int z = blockIdx.z, p = blockIdx.y >> 3, k = blockIdx.y & 7;
+  const StreamDesc& sd = sds[z];
+  const int c = sd.pc[p], s = sd.ps[p], d = s - c;
+  const int h = sd.Hl[c], w = sd.Wl[c], hb = sd.Hl[s], wb = sd.Wl[s], n = h * w, base = blockIdx.x * TILE;
+  if (base >= n) return;   // uniform
+  const gp<const float> a = G(chan_ptr(sd, k, c)), b = G(chan_ptr(sd, k, s));
+  const gp<float> out = G(slot(A.D[p], A, z) + (size_t)k * n);
+  float mn = INFINITY, mx = -INFINITY, am = 0.f;
+  Walk2 wk(base + threadIdx.x, w);
+#pragma unroll
+  for (int q = 0; q < PER; ++q, wk.next()) {
+    const int i = base + q * SP_BLOCK + threadIdx.x;
+    if (i < n) {
+      int y0, y1, x0, x1;
+      float wy, wx;
+      tap(wk.r, d, hb, y0, y1, wy);
+      tap(wk.c, d, wb, x0, x1, wx);
+      const float top = (1.f - wx) * b[y0 * wb + x0] + wx * b[y0 * wb + x1];
+      const float bot = (1.f - wx) * b[y1 * wb + x0] + wx * b[y1 * wb + x1];
+      const float X = a[i], D = X - ((1.f - wy) * top + wy * bot);
+      out[i] = D;
+      mn = fminf(mn, fabsf(D));
+      mx = fmaxf(mx, fabsf(D));
+      am = fmaxf(am, fabsf(X));
+      if (i < hb * wb) am = fmaxf(am, fabsf(b[i]));
+    }
   }
-  // the workgroup's maximum, then one atomic per workgroup
-  m = wave_reduce<OpMax>(m);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float t = red[0];
-    for (int k = 1; k < SP_BLOCK / 64; ++k) t = fmaxf(t, red[k]);
-    atomicMax(P.amax + (blockIdx.x & (SP_PA_AMAX - 1)), __float_as_uint(t));
-  }
+  store_mm(mn, mx, am, slot(A.mm, A, z) + (size_t)(SP_NCH + blockIdx.y) * A.mm_n + blockIdx.x, sh);
 }
 
 // Derivative of |D| taken as 0 within this fraction of the pair's scale: there the sign of
 // D is below what FP32 maps resolve (D vanishes identically on flat regions of both levels).
 constexpr float kSignBand = 0x1p-16f;
 
-// gD = sign(D) dL/dF outside the band (0 inside), in place in the plane of F (out), added
-// to dL/dX(c) (gc).
-__global__ __launch_bounds__(SP_BLOCK) void k_pa_csadj(const PaPlane* __restrict__ tab, float* const* __restrict__ gc) {
-  const PaPlane P = tab[blockIdx.y];
-  const int i = blockIdx.x * SP_BLOCK + threadIdx.x;
-  if (i >= P.ha * P.wa) return;
-  const int y = i / P.wa, x = i - y * P.wa;
-  const float D = cs_diff(P, y, x);
-  uint32_t am = 0;   // the pair's scale: the largest of its slots (all >= 0, compared as bits)
+// gD = sign(D) dL/dF outside the band (0 inside) in the place of D, for every pair of centre
+// level A.cl[blockIdx.y / 8] in pair order, and their sum as that level's dL/dX.
+__global__ __launch_bounds__(SP_BLOCK) void k_pa_csadj(PaDesc A, const StreamDesc* __restrict__ sds) {
+  const int z = blockIdx.z, c = A.cl[blockIdx.y >> 3], k = blockIdx.y & 7;
+  const StreamDesc& sd = sds[z];
+  const int w = sd.Wl[c], n = sd.Hl[c] * w, base = blockIdx.x * TILE, nbx = (w + 7) >> 3;
+  if (base >= n) return;   // uniform
+  float acc[PER];
 #pragma unroll
-  for (int k = 0; k < SP_PA_AMAX; ++k) am = max(am, P.amax[k]);
-  const float band = kSignBand * __uint_as_float(am);
-  const float gd = D > band ? P.out[i] : (D < -band ? -P.out[i] : 0.f);
-  P.out[i] = gd;
-  gc[blockIdx.y][i] += gd;
+  for (int q = 0; q < PER; ++q) acc[q] = 0.f;
+  for (int p = 0; p < sd.n_pairs; ++p) {
+    if (sd.pc[p] != c) continue;
+    const MapView M = map_view(A, sd, nullptr, SP_NCH * (1 + p) + k, z);
+    const float* sc = slot(A.sc, A, z) + (size_t)M.m * SP_PA_SC;
+    const gp<const int32_t> bpos = G((const int32_t*)slot(A.bpos, A, z) + (size_t)M.m * A.nb_n);
+    const gp<float> D = G(slot(A.D[p], A, z) + (size_t)k * n);
+    const float band = kSignBand * sc[7];
+    Walk2 wk(base + threadIdx.x, w);
+#pragma unroll
+    for (int q = 0; q < PER; ++q, wk.next()) {
+      const int i = base + q * SP_BLOCK + threadIdx.x;
+      if (i < n) {
+        const float gf = napply_at(M, sc, bpos, nbx, wk.r, wk.c, i), v = D[i];
+        const float gd = v > band ? gf : (v < -band ? -gf : 0.f);
+        D[i] = gd;
+        acc[q] += gd;
+      }
+    }
+  }
+  const gp<float> out = G(slot(A.gX[c], A, z) + (size_t)k * n);
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int i = base + q * SP_BLOCK + threadIdx.x;
+    if (i < n) out[i] = acc[q];
+  }
 }
 
-// dL/dX(s) += up^T(-gD): the level-s element gathers every level-c element whose bilinear
-// taps read it, a window of at most 2^(d+1) + 1 rows and columns.  Plane entry: a = gD
-// (level c, ha x wa), out = dL/dX(s) (hb x wb).  Sixteen lanes (one DPP row) per level-s
-// element: lane j takes the window's rows j, j + 16, ..., each as the tap-weighted sum of
-// its columns, and the row adds the lanes' sums in a fixed order.
+// dL/dX(s) of surround level A.sl[blockIdx.y / 8]: up^T(-gD) of every pair with that
+// surround, added to the level's centre part when it has one.  A level-s element gathers the
+// level-c elements xs 2^d + k, |k| < 2^d, weight (2^d - |k|) / 2^d (1 beyond the last sample).
+// Sixteen lanes (one DPP row) per level-s element: lane j takes the window's rows j, j + 16,
+// ..., each as the weighted sum of its columns, and the row adds the lanes' sums in a fixed order.
 constexpr int UPT_L = 16;   // lanes per level-s element
-__global__ __launch_bounds__(SP_BLOCK) void k_pa_up_t(const PaPlane* __restrict__ tab) {
-  const PaPlane P = tab[blockIdx.y];
-  const int e = blockIdx.x * (SP_BLOCK / UPT_L) + (int)(threadIdx.x / UPT_L);
+__global__ __launch_bounds__(SP_BLOCK) void k_pa_up_t(PaDesc A, const StreamDesc* __restrict__ sds) {
+  const int z = blockIdx.z, s = A.sl[blockIdx.y >> 3], ch = blockIdx.y & 7;
+  const StreamDesc& sd = sds[z];
+  const int hb = sd.Hl[s], wb = sd.Wl[s];
+  const int e0 = blockIdx.x * (SP_BLOCK / UPT_L);
+  if (e0 >= hb * wb) return;   // uniform
+  const int e = e0 + (int)(threadIdx.x / UPT_L);
   const int j = threadIdx.x & (UPT_L - 1);
-  const bool valid = e < P.hb * P.wb;   // every lane stays for the row's sum
+  const bool valid = e < hb * wb;   // every lane stays for the row's sum
   const int i = valid ? e : 0;
-  const int ys = i / P.wb, xs = i - ys * P.wb;
-  const int st = 1 << P.d;
-  const int x_lo = max(0, (xs - 1) * st), x_hi = min(P.wa - 1, (xs + 1) * st);
-  float acc = 0.f;
-  if (valid)
-    for (int y = max(0, (ys - 1) * st) + j; y <= min(P.ha - 1, (ys + 1) * st); y += UPT_L) {
-      int y0, y1;
-      float wy;
-      tap(y, P.d, P.hb, y0, y1, wy);
-      const float ay = (y0 == ys ? 1.f - wy : 0.f) + (y1 == ys ? wy : 0.f);
-      if (ay == 0.f) continue;
-      float r = 0.f;
-      for (int x = x_lo; x <= x_hi; ++x) {
-        int x0, x1;
-        float wx;
-        tap(x, P.d, P.wb, x0, x1, wx);
-        const float ax = (x0 == xs ? 1.f - wx : 0.f) + (x1 == xs ? wx : 0.f);
-        r += ax * P.a[y * P.wa + x];
+  const int ys = i / wb, xs = i - ys * wb;
+  const gp<float> out = G(slot(A.gX[s], A, z) + (size_t)ch * hb * wb);
+  float tot = valid && j == 0 && ((A.centres >> s) & 1u) ? out[e] : 0.f;
+  for (int p = 0; p < sd.n_pairs; ++p) {
+    if (sd.ps[p] != s) continue;
+    const int c = sd.pc[p], d = s - c, st = 1 << d, ha = sd.Hl[c], wa = sd.Wl[c];
+    const float inv = __int_as_float((127 - d) << 23);   // 2^-d
+    const gp<const float> a = G((const float*)slot(A.D[p], A, z) + (size_t)ch * ha * wa);
+    const int xc = xs * st, x_lo = max(0, xc - st + 1), x_hi = min(wa - 1, xc + st - 1);
+    float acc = 0.f;
+    if (valid)
+      for (int ky = j - st + 1; ky < st; ky += UPT_L) {
+        const int y = ys * st + ky;
+        if (y < 0 || y >= ha) continue;
+        const float ay = ys == hb - 1 && ky > 0 ? 1.f : (float)(st - abs(ky)) * inv;
+        const gp<const float> row = a + (uint32_t)y * (uint32_t)wa;
+        float r = 0.f;
+#pragma unroll 4
+        for (int x = x_lo; x <= x_hi; ++x) {
+          const int kx = x - xc;
+          const float ax = xs == wb - 1 && kx > 0 ? 1.f : (float)(st - abs(kx)) * inv;
+          r += ax * row[x];
+        }
+        acc += ay * r;
       }
-      acc += ay * r;
-    }
-  // the sixteen lanes' sums: pairs, quads, halves, the row (every lane ends with the total)
-  acc += dpp_f<0xB1>(acc);
-  acc += dpp_f<0x4E>(acc);
-  acc += dpp_f<0x141>(acc);
-  acc += dpp_f<0x140>(acc);
-  if (valid && j == 0) P.out[e] -= acc;
+    // the sixteen lanes' sums: pairs, quads, halves, the row (every lane ends with the total)
+    acc += dpp_f<0xB1>(acc);
+    acc += dpp_f<0x4E>(acc);
+    acc += dpp_f<0x141>(acc);
+    acc += dpp_f<0x140>(acc);
+    tot -= acc;
+  }
+  if (valid && j == 0) out[e] = tot;
 }
 
 // dL/dI(l) += sum over the four orientations of the clamped Gabor correlation's transpose.
 // With E(q) = sum_{v,u} h(v, u) gO(q - (v, u)) on the plane extended by the radius (gO zero
 // outside the level), the transpose at p is the sum of E(q) over the q that clamp to p: q = p
-// inside the level, the outside strip folded onto its border row or column.  One 16x16 tile
-// of p per workgroup: the four orientation gradients of the tile plus twice the radius are
-// staged in LDS (orientations interleaved), with the taps; E is computed once for each q the
-// tile's outputs need (the tile, plus the outside strips of a tile on the border), then each
-// output sums its fold set.  a: the four orientation gradients at a plane stride of ha * wa;
-// out: dL/dI(l); taps [4][2 SP_PA_R + 1]^2, tap (v, u) of radius R = d at row v + R and
-// column u + R of each.  RC: the radius when known at compile time (0: read from d).
+// inside the level, the outside strip folded onto its border row or column.
+// The kernels are sums of separable ones (h0 = gm(u) g(v), h90 = g(u) gm(v), h45 and h135 =
+// gc gc -+ gs gs - c45 g g), so with P = gO45 + gO135 and Q = gO135 - gO45
+//   E = H[gm] V[g] gO0 + H[g] (V[gm] gO90 - c45 V[g] P) + H[gc] V[gc] P + H[gs] V[gs] Q:
+// 117 multiply-adds per position instead of the 676 of four 13x13 kernels, whose LDS reads
+// (two 16-byte reads a tap) bound the launch: 37 us for one 640x480 frame, 38 us for eight of them here.
+// One 16x16 tile of p per workgroup: gO0, gO90, P and Q of the tile plus twice the radius
+// interleaved in LDS, the vertical pass over the rows of q the tile needs (its own, and the
+// outside strips of a tile on the border), the horizontal pass, then the fold.
+// RC: the radius when known at compile time (0: read from the stream description, with
+// zero-padded taps).
 constexpr int GT = 16;
-constexpr int GN = GT + 4 * SP_PA_R;
-constexpr int GQ = GT + 2 * SP_PA_R;
 template <int RC>
-__global__ __launch_bounds__(SP_BLOCK) void k_pa_gabor_t(PaGabLevels L, const float* __restrict__ taps) {
-  __shared__ float4 go[GN * GN];
-  __shared__ float4 tp[(2 * SP_PA_R + 1) * (2 * SP_PA_R + 1)];
-  __shared__ float eq[GQ * GQ];
-  const PaPlane P = *L.tab[blockIdx.y];   // the level of this workgroup (one launch for every level)
-  const int h = P.ha, w = P.wa, R = RC ? RC : P.d, K = 2 * R + 1;
-  const size_t n = (size_t)h * w;
+__global__ __launch_bounds__(SP_BLOCK) void k_pa_gabor_t(PaDesc A, const StreamDesc* __restrict__ sds) {
+  constexpr int RM = RC ? RC : SP_PA_R, NS = GT + 4 * RM, NQ = GT + 2 * RM;
+  __shared__ float4 st[NS * NS];   // gO0, gO90, P, Q; then E [NQ][NQ]
+  __shared__ float4 vp[NQ * NS];   // V[g] gO0, V[gm] gO90 - c45 V[g] P, V[gc] P, V[gs] Q
+  const int z = blockIdx.z, l = A.ul[blockIdx.y];
+  const StreamDesc& sd = sds[z];
+  const int h = sd.Hl[l], w = sd.Wl[l], R = RC ? RC : sd.gr;
+  const uint32_t n = (uint32_t)h * (uint32_t)w;
   const int ntx = (w + GT - 1) / GT;
   if ((int)blockIdx.x >= ntx * ((h + GT - 1) / GT)) return;   // the level has fewer tiles
   const int ty0 = (blockIdx.x / ntx) * GT, tx0 = (blockIdx.x % ntx) * GT;
   const int E = GT + 4 * R, oy = ty0 - 2 * R, ox = tx0 - 2 * R;
-  for (int i = threadIdx.x; i < E * E; i += SP_BLOCK) {
-    const int r = i / E, c = i - r * E, y = oy + r, x = ox + c;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (y >= 0 && y < h && x >= 0 && x < w) {
-      const size_t o = (size_t)y * w + x;
-      v = make_float4(P.a[o], P.a[n + o], P.a[2 * n + o], P.a[3 * n + o]);
+  float* gI = slot(A.gX[l], A, z);
+  const gp<const float> gO = G((const float*)gI + 3 * (size_t)n);
+  {
+    Walk2 wk(threadIdx.x, E);
+    for (int i = threadIdx.x; i < E * E; i += SP_BLOCK, wk.next()) {
+      const int y = oy + wk.r, x = ox + wk.c;
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (y >= 0 && y < h && x >= 0 && x < w) {
+        const uint32_t o = (uint32_t)y * (uint32_t)w + (uint32_t)x;
+        const float o45 = gO[n + o], o135 = gO[3 * n + o];
+        v = make_float4(gO[o], gO[2 * n + o], o45 + o135, o135 - o45);
+      }
+      st[wk.r * NS + wk.c] = v;
     }
-    go[r * GN + c] = v;
-  }
-  constexpr int KT = 2 * SP_PA_R + 1;   // row stride of the global tap table
-  for (int i = threadIdx.x; i < K * K; i += SP_BLOCK) {
-    const int v = i / K, u = i - v * K;
-    const int o = v * KT + u;
-    tp[i] = make_float4(taps[o], taps[KT * KT + o], taps[2 * KT * KT + o], taps[3 * KT * KT + o]);
   }
   __syncthreads();
   // the q the tile needs: its own positions, and the outside strips on the level's borders
   const int th = min(GT, h - ty0), tw = min(GT, w - tx0);
   const int qy0 = ty0 == 0 ? -R : ty0, qy1 = ty0 + th - 1 + (ty0 + th == h ? R : 0);
   const int qx0 = tx0 == 0 ? -R : tx0, qx1 = tx0 + tw - 1 + (tx0 + tw == w ? R : 0);
-  const int nqx = qx1 - qx0 + 1, nq = (qy1 - qy0 + 1) * nqx;
-  for (int i = threadIdx.x; i < nq; i += SP_BLOCK) {
-    const int qy = qy0 + i / nqx, qx = qx0 + i % nqx;
-    const float4* g0 = go + (qy + R - oy) * GN + (qx + R - ox);   // q - (v - R, u - R) at g0 - v GN - u
-    float e = 0.f;
+  const int nqx = qx1 - qx0 + 1, nqy = qy1 - qy0 + 1;
+  const int cx0 = qx0 - R, ncx = nqx + 2 * R;   // columns of the vertical pass
+  // tap t of the 1-D factors g, gm, gc, gs: uniform scalars; position q reads q - (t - R).  For a
+  // run-time radius the table is zero beyond 2 R + 1 and the position stays in the staged region.
+  constexpr int NT = 2 * RM + 1;
+  const float c45 = sd.c45;
+  {
+    Walk2 wk(threadIdx.x, ncx);
+    for (int i = threadIdx.x; i < nqy * ncx; i += SP_BLOCK, wk.next()) {
+      const float4* col = st + (qy0 + wk.r + R - oy) * NS + (cx0 + wk.c - ox);
+      float a = 0.f, b = 0.f, gP = 0.f, c = 0.f, e = 0.f;
 #pragma unroll
-    for (int v = 0; v < (RC ? 2 * RC + 1 : 1); ++v) {
-      if (!RC) break;
-      const float4* gr = g0 - v * GN;
-      const float4* tr = tp + v * K;
+      for (int t = 0; t < NT; ++t) {
+        if (RC == 0 && t > 2 * R) break;
+        const float4 v = col[-t * NS];
+        a = fmaf(sd.gf[0][t], v.x, a);
+        b = fmaf(sd.gf[1][t], v.y, b);
+        gP = fmaf(sd.gf[0][t], v.z, gP);
+        c = fmaf(sd.gf[2][t], v.z, c);
+        e = fmaf(sd.gf[3][t], v.w, e);
+      }
+      vp[wk.r * NS + wk.c] = make_float4(a, b - c45 * gP, c, e);
+    }
+  }
+  __syncthreads();
+  float* eq = reinterpret_cast<float*>(st);   // the staged gradients are no longer read
+  {
+    Walk2 wk(threadIdx.x, nqx);
+    for (int i = threadIdx.x; i < nqy * nqx; i += SP_BLOCK, wk.next()) {
+      const float4* row = vp + wk.r * NS + wk.c + 2 * R;
+      float e = 0.f;
 #pragma unroll
-      for (int u = 0; u < 2 * RC + 1; ++u) {
-        const float4 g = gr[-u], t = tr[u];
-        e = fmaf(t.x, g.x, fmaf(t.y, g.y, fmaf(t.z, g.z, fmaf(t.w, g.w, e))));
+      for (int t = 0; t < NT; ++t) {
+        if (RC == 0 && t > 2 * R) break;
+        const float4 v = row[-t];
+        e = fmaf(sd.gf[1][t], v.x, fmaf(sd.gf[0][t], v.y, fmaf(sd.gf[2][t], v.z, fmaf(sd.gf[3][t], v.w, e))));
       }
+      eq[wk.r * NQ + wk.c] = e;
     }
-    if (!RC) {
-      for (int v = 0; v < K; ++v) {
-        const float4* gr = g0 - v * GN;
-        const float4* tr = tp + v * K;
-        for (int u = 0; u < K; ++u) {
-          const float4 g = gr[-u], t = tr[u];
-          e = fmaf(t.x, g.x, fmaf(t.y, g.y, fmaf(t.z, g.z, fmaf(t.w, g.w, e))));
-        }
-      }
-    }
-    eq[(qy - qy0) * GQ + (qx - qx0)] = e;
   }
   __syncthreads();
   const int py = ty0 + (int)(threadIdx.x >> 4), px = tx0 + (int)(threadIdx.x & 15);
@@ -450,116 +669,153 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_gabor_t(PaGabLevels L, const fl
   const int fx0 = px == 0 ? -R : px, fx1 = px == w - 1 ? w - 1 + R : px;
   float acc = 0.f;
   for (int qy = fy0; qy <= fy1; ++qy)
-    for (int qx = fx0; qx <= fx1; ++qx) acc += eq[(qy - qy0) * GQ + (qx - qx0)];
-  P.out[(size_t)py * w + px] += acc;
+    for (int qx = fx0; qx <= fx1; ++qx) acc += eq[(qy - qy0) * NQ + (qx - qx0)];
+  gI[(size_t)py * w + px] += acc;
 }
 
-// Level-0 features back to the frame: g_frame[t] = own part; g_frame[t-1] += motion part.
-__global__ __launch_bounds__(SP_BLOCK) void k_pa_feat(const uint8_t* __restrict__ rgb, const uint8_t* __restrict__ prev,
-                                                      const uint32_t* __restrict__ maxp, int nmax,
-                                                      const float* __restrict__ g0, int n,
-                                                      float* __restrict__ gout, float* __restrict__ gprev) {
+// Level 1 back to the frames: the last transposed pyramid step (2x2 pixels per thread from nine
+// level-1 values a channel, never stored) and the level-0 features.  Frame t0 + z gets its own
+// part and the motion part of frame t0 + z + 1 when that frame is in the launch; the first
+// frame adds its motion part to frame t0 - 1, finished by the launch before.  Storing the four
+// level-0 planes took two more passes over 16 bytes a pixel (14.7 + 4.8 us a 640x480 frame).
+__global__ __launch_bounds__(SP_BLOCK) void k_pa_feat(PaDesc A, const StreamDesc* __restrict__ sds,
+                                                      const uint8_t* __restrict__ frames, float* __restrict__ grad, int t0, int nz) {
   __shared__ float sh4[4];
+  const int z = blockIdx.z, t = t0 + z;
+  const StreamDesc& sd = sds[z];
+  const int H = sd.H, W = sd.W, h1 = sd.Hl[1], w1 = sd.Wl[1];
+  const size_t hw3 = 3 * (size_t)H * W;
   // the frame's colour maximum from the partials (integers below 2^24: exact as floats)
   uint32_t m = 0;
-  for (int k = threadIdx.x; k < nmax; k += SP_BLOCK) m = max(m, maxp[k]);
+  for (int k = threadIdx.x; k < sd.n_rgb; k += SP_BLOCK) m = max(m, sd.rgb_max_part[k]);
   const uint32_t smax = (uint32_t)block_reduce<OpMax>((float)m, sh4);
   const int i = blockIdx.x * SP_BLOCK + threadIdx.x;
-  if (i >= n) return;
-  // channels of the level-0 block: I, RG, BY at planes 0-2, M at plane 7
-  const float gI = g0[i], gRG = g0[(size_t)n + i], gBY = g0[2 * (size_t)n + i], gM = g0[7 * (size_t)n + i];
-  const uint32_t R8 = rgb[3 * i], G8 = rgb[3 * i + 1], B8 = rgb[3 * i + 2];
-  const float r = R8 * (1.f / 255.f), g = G8 * (1.f / 255.f), b = B8 * (1.f / 255.f);
-  const float I = (r + g + b) / 3.f;
-  const bool chrom = 10u * (R8 + G8 + B8) > smax;
-  float gIt = gI;
-  if (prev) {
-    // the sign of I_t - I_{t-1}, exact from the byte sums
-    const int dm = (int)(R8 + G8 + B8) - (int)(prev[3 * i] + prev[3 * i + 1] + prev[3 * i + 2]);
-    const float sg = dm > 0 ? gM : (dm < 0 ? -gM : 0.f);
-    gIt += sg;
-    const float gp = -sg / 3.f / 255.f;
-    gprev[3 * i] += gp;
-    gprev[3 * i + 1] += gp;
-    gprev[3 * i + 2] += gp;
+  if (i >= h1 * w1) return;
+  const int q = i / w1, r = i - q * w1;
+  const QuadT Q(q, r, H, W, h1, w1);
+  const size_t n1 = (size_t)h1 * w1;
+  const float* g1 = slot(A.gX[1], A, z);
+  float gI[2][2], gRG[2][2], gBY[2][2], gM[2][2], gN[2][2];
+  const bool next = z + 1 < nz;   // uniform
+  {
+    float v[5][3][3];
+    Q.load(G(g1), v[0]);
+    Q.load(G(g1 + n1), v[1]);
+    Q.load(G(g1 + 2 * n1), v[2]);
+    Q.load(G(g1 + 7 * n1), v[3]);
+    if (next) Q.load(G((const float*)slot(A.gX[1], A, z + 1) + 7 * n1), v[4]);
+    Q.apply(v[0], gI);
+    Q.apply(v[1], gRG);
+    Q.apply(v[2], gBY);
+    Q.apply(v[3], gM);
+    if (next) Q.apply(v[4], gN);
   }
-  float gr = 0.f, gg = 0.f, gb = 0.f;
-  if (chrom) {
-    const float ri = 1.f / I;
-    // the branches of the opponent channels, exact from the bytes (r' = R / I with I > 0)
-    const int r8 = (int)R8, g8 = (int)G8, b8 = (int)B8;
-    const float guR = 2 * r8 - g8 - b8 > 0 ? gRG : 0.f, guG = 2 * g8 - r8 - b8 > 0 ? -gRG : 0.f;
-    const float guB = 2 * b8 - r8 - g8 > 0 ? gBY : 0.f, guY = min(r8, g8) - b8 > 0 ? -gBY : 0.f;
-    float grp = guR - 0.5f * guG - 0.5f * guB;
-    float ggp = -0.5f * guR + guG - 0.5f * guB;
-    const float gbp = -0.5f * guR - 0.5f * guG + guB - guY;
-    if (r8 <= g8) grp += guY;
-    else ggp += guY;
-    gr = grp * ri;
-    gg = ggp * ri;
-    gb = gbp * ri;
-    gIt -= (grp * r + ggp * g + gbp * b) * ri * ri;
-  }
-  gr += gIt / 3.f;
-  gg += gIt / 3.f;
-  gb += gIt / 3.f;
-  gout[3 * i] = gr / 255.f;
-  gout[3 * i + 1] = gg / 255.f;
-  gout[3 * i + 2] = gb / 255.f;
+  const gp<const uint8_t> rgb = G(frames + (size_t)t * hw3);
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int y = 2 * q + a, x = 2 * r + b;
+      if (y >= H || x >= W) continue;
+      const size_t o = 3 * ((size_t)y * W + x);
+      const uint32_t R8 = rgb[o], G8 = rgb[o + 1], B8 = rgb[o + 2];
+      const int s8 = (int)(R8 + G8 + B8);
+      const float rr = R8 * (1.f / 255.f), gg_ = G8 * (1.f / 255.f), bb = B8 * (1.f / 255.f);
+      const float I = (rr + gg_ + bb) / 3.f;
+      const bool chrom = 10u * (R8 + G8 + B8) > smax;
+      float gIt = gI[a][b];
+      if (t > 0) {
+        // the sign of I_t - I_{t-1}, exact from the byte sums
+        const gp<const uint8_t> prev = rgb - hw3;
+        const int dm = s8 - (int)(prev[o] + prev[o + 1] + prev[o + 2]);
+        const float sg = dm > 0 ? gM[a][b] : (dm < 0 ? -gM[a][b] : 0.f);
+        gIt += sg;
+        if (z == 0) {
+          const gp<float> gp_ = G(grad + (size_t)(t - 1) * hw3 + o);
+          const float gpv = -sg / 3.f / 255.f;
+          gp_[0] += gpv;
+          gp_[1] += gpv;
+          gp_[2] += gpv;
+        }
+      }
+      float gr = 0.f, gg = 0.f, gb = 0.f;
+      if (chrom) {
+        const float ri = 1.f / I;
+        // the branches of the opponent channels, exact from the bytes (r' = R / I with I > 0)
+        const int r8 = (int)R8, g8 = (int)G8, b8 = (int)B8;
+        const float vRG = gRG[a][b], vBY = gBY[a][b];
+        const float guR = 2 * r8 - g8 - b8 > 0 ? vRG : 0.f, guG = 2 * g8 - r8 - b8 > 0 ? -vRG : 0.f;
+        const float guB = 2 * b8 - r8 - g8 > 0 ? vBY : 0.f, guY = min(r8, g8) - b8 > 0 ? -vBY : 0.f;
+        float grp = guR - 0.5f * guG - 0.5f * guB;
+        float ggp = -0.5f * guR + guG - 0.5f * guB;
+        const float gbp = -0.5f * guR - 0.5f * guG + guB - guY;
+        if (r8 <= g8) grp += guY;
+        else ggp += guY;
+        gr = grp * ri;
+        gg = ggp * ri;
+        gb = gbp * ri;
+        gIt -= (grp * rr + ggp * gg_ + gbp * bb) * ri * ri;
+      }
+      gr = (gr + gIt / 3.f) / 255.f;
+      gg = (gg + gIt / 3.f) / 255.f;
+      gb = (gb + gIt / 3.f) / 255.f;
+      if (next) {
+        const gp<const uint8_t> nx = rgb + hw3;
+        const int dm = (int)(nx[o] + nx[o + 1] + nx[o + 2]) - s8;
+        const float sg = dm > 0 ? gN[a][b] : (dm < 0 ? -gN[a][b] : 0.f);
+        const float gpv = -sg / 3.f / 255.f;
+        gr += gpv;
+        gg += gpv;
+        gb += gpv;
+      }
+      const gp<float> go = G(grad + (size_t)t * hw3 + o);
+      go[0] = gr;
+      go[1] = gg;
+      go[2] = gb;
+    }
 }
 
-__global__ void k_pa_zero(float* __restrict__ p, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * SP_BLOCK + threadIdx.x; i < n; i += (size_t)gridDim.x * SP_BLOCK) p[i] = 0.f;
-}
-
-inline int blocks(long long n) { return (int)((n + SP_BLOCK - 1) / SP_BLOCK); }
+inline int blocks(long long n, int per = SP_BLOCK) { return (int)((n + per - 1) / per); }
 
 }  // namespace
 
-hipError_t sp_pa_gs(const float* gs, const float* S, const float* ms, int n, float flat_tol, float* gS,
-                    double* part, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pa_gs, dim3(blocks(n)), dim3(SP_BLOCK), 0, st, gs, S, ms, n, flat_tol, gS, part);
-  hipLaunchKernelGGL(k_pa_gs_fix, dim3(1), dim3(SP_BLOCK), 0, st, gs, ms, n, blocks(n), flat_tol, gS, part);
-  return hipGetLastError();
-}
-hipError_t sp_pa_nadjoint(const PaMap* maps, int nmaps, int maxn, int maxh, float flat_tol, hipStream_t st) {
-  if (nmaps <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pa_nmm, dim3((maxn + SP_PA_MMT - 1) / SP_PA_MMT, nmaps), dim3(SP_BLOCK), 0, st, maps);
-  hipLaunchKernelGGL(k_pa_nstrip, dim3((maxh + 7) / 8, nmaps), dim3(SP_BLOCK), 0, st, maps, flat_tol);
-  hipLaunchKernelGGL(k_pa_nfin, dim3(nmaps), dim3(SP_BLOCK), 0, st, maps, flat_tol);
-  hipLaunchKernelGGL(k_pa_napply, dim3(blocks(maxn), nmaps), dim3(SP_BLOCK), 0, st, maps);
-  return hipGetLastError();
-}
-hipError_t sp_pa_plane(int kind, const PaPlane* tab, int nplanes, int maxn, int flag, float* const* gc,
-                       const float* taps, hipStream_t st, int gabor_r) {
-  if (nplanes <= 0 || maxn <= 0) return hipSuccess;
-  const dim3 g(blocks(maxn), nplanes);
-  switch (kind) {
-    case 0: hipLaunchKernelGGL(k_pa_reduce_t, g, dim3(SP_BLOCK), 0, st, tab, flag); break;
-    case 1: hipLaunchKernelGGL(k_pa_csmap, g, dim3(SP_BLOCK), 0, st, tab); break;
-    case 2: hipLaunchKernelGGL(k_pa_csadj, g, dim3(SP_BLOCK), 0, st, tab, gc); break;
-    case 3: hipLaunchKernelGGL(k_pa_up_t, dim3(blocks(maxn * UPT_L), nplanes), dim3(SP_BLOCK), 0, st, tab); break;
-    default: return hipErrorInvalidValue;
+hipError_t sp_pixel_adjoint(const PaDesc& A, const StreamDesc* sds, const StreamDesc& g, int t0, int nz,
+                            const uint8_t* frames, const float* gs, const float* S, const float* ms, const float* fbar,
+                            float* grad, hipStream_t st) {
+  if (nz <= 0) return hipSuccess;
+  const dim3 b(SP_BLOCK);
+  auto n_l = [&](int l) { return g.Hl[l] * g.Wl[l]; };
+  auto grid = [&](int x, int y) { return dim3(x, y, nz); };
+  const int cm = g.c_max, nc = n_l(cm), nF = SP_NCH * g.n_pairs;
+  int maxc = 0, maxh = 0, maxs = 0, maxt = 0;
+  for (int p = 0; p < g.n_pairs; ++p) {
+    maxc = std::max(maxc, n_l(g.pc[p]));
+    maxh = std::max(maxh, g.Hl[g.pc[p]]);
+    maxs = std::max(maxs, n_l(g.ps[p]));
   }
-  return hipGetLastError();
-}
-hipError_t sp_pa_gabor(const PaGabLevels& L, int max_tiles, const float* taps, hipStream_t st, int gabor_r) {
-  if (L.n <= 0 || max_tiles <= 0) return hipSuccess;
-  const dim3 grid(max_tiles, L.n);
-  if (gabor_r == 6)
-    hipLaunchKernelGGL(k_pa_gabor_t<6>, grid, dim3(SP_BLOCK), 0, st, L, taps);
+  for (int q = 0; q < A.n_ul; ++q) maxt = std::max(maxt, blocks(g.Hl[A.ul[q]], GT) * blocks(g.Wl[A.ul[q]], GT));
+  hipLaunchKernelGGL(k_pa_gs, grid(blocks(nc), 1), b, 0, st, A, gs, S, ms, nc, g.flat_tol);
+  hipLaunchKernelGGL(k_pa_gs_fix, grid(1, 1), b, 0, st, A, gs, ms, nc, blocks(nc), g.flat_tol);
+  hipLaunchKernelGGL(k_pa_nmm, grid(blocks(nc, TILE), SP_NCH), b, 0, st, A, sds, fbar);
+  hipLaunchKernelGGL(k_pa_nstrip, grid(blocks(g.Hl[cm], 8), SP_NCH), b, 0, st, A, sds, fbar, 0, g.flat_tol);
+  hipLaunchKernelGGL(k_pa_nfin, grid(1, SP_NCH), b, 0, st, A, sds, fbar, 0, g.flat_tol);
+  hipLaunchKernelGGL(k_pa_napply, grid(blocks(nc, TILE), SP_NCH), b, 0, st, A, sds, fbar);
+  for (int l = cm - 1; l >= g.c_min; --l)
+    hipLaunchKernelGGL(k_pa_reduce_t, grid(blocks(n_l(l + 1)), SP_NCH), b, 0, st, A,
+                       (const float*)(l + 1 == cm ? A.gfbar : A.gN[l + 1]), A.gN[l], g.Hl[l], g.Wl[l], g.Hl[l + 1],
+                       g.Wl[l + 1], 0);
+  hipLaunchKernelGGL(k_pa_csmap, grid(blocks(maxc, TILE), nF), b, 0, st, A, sds);
+  hipLaunchKernelGGL(k_pa_nstrip, grid(blocks(maxh, 8), nF), b, 0, st, A, sds, fbar, SP_NCH, g.flat_tol);
+  hipLaunchKernelGGL(k_pa_nfin, grid(1, nF), b, 0, st, A, sds, fbar, SP_NCH, g.flat_tol);
+  hipLaunchKernelGGL(k_pa_csadj, grid(blocks(maxc, TILE), SP_NCH * A.n_cl), b, 0, st, A, sds);
+  hipLaunchKernelGGL(k_pa_up_t, grid(blocks((long long)maxs * UPT_L), SP_NCH * A.n_sl), b, 0, st, A, sds);
+  if (g.gr == 6)
+    hipLaunchKernelGGL(k_pa_gabor_t<6>, grid(maxt, A.n_ul), b, 0, st, A, sds);
   else
-    hipLaunchKernelGGL(k_pa_gabor_t<0>, grid, dim3(SP_BLOCK), 0, st, L, taps);
-  return hipGetLastError();
-}
-hipError_t sp_pa_feat(const uint8_t* rgb, const uint8_t* prev, const uint32_t* maxp, int nmax, const float* g0, int n,
-                      float* gout, float* gprev, hipStream_t st) {
-  hipLaunchKernelGGL(k_pa_feat, dim3(blocks(n)), dim3(SP_BLOCK), 0, st, rgb, prev, maxp, nmax, g0, n, gout, gprev);
-  return hipGetLastError();
-}
-hipError_t sp_pa_zero(float* p, size_t n, hipStream_t st) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pa_zero, dim3((int)std::min<size_t>((n + SP_BLOCK - 1) / SP_BLOCK, 4096)), dim3(SP_BLOCK), 0, st, p, n);
+    hipLaunchKernelGGL(k_pa_gabor_t<0>, grid(maxt, A.n_ul), b, 0, st, A, sds);
+  for (int l = g.top; l >= 2; --l)   // a level no pair uses starts from the level above
+    hipLaunchKernelGGL(k_pa_reduce_t, grid(blocks(n_l(l)), 4), b, 0, st, A, (const float*)A.gX[l], A.gX[l - 1], g.Hl[l - 1],
+                       g.Wl[l - 1], g.Hl[l], g.Wl[l], (int)((g.used >> (l - 1)) & 1u));
+  hipLaunchKernelGGL(k_pa_feat, grid(blocks(n_l(1)), 1), b, 0, st, A, sds, frames, grad, t0, nz);
   return hipGetLastError();
 }
