@@ -344,6 +344,10 @@ struct GmmIO {
 // the sink cannot be reached) and the residual capacity to the sink.
 #define SP_CUT_INF (1 << 30)
 #define SP_CUT_T 32        // tile edge of the relabel pass
+#define SP_CUT_PT 16       // tile edge of the push launches
+#define SP_CUT_CTL 64      // counter slots of the relabel passes (a power of two)
+#define SP_CUT_FLOW 64     // partial sums of the flow pushed into the sink
+#define SP_CUT_PARTS 4096  // most workgroups of the capacity pass
 #define SP_CUT_CAPMAX (1 << 24)
 struct CutIO {
   const float* unary;      // [2][n] U0 (cost of the background), U1 (cost of the object)
@@ -353,14 +357,20 @@ struct CutIO {
   int32_t* h;              // [n]
   int32_t* rt;             // [n]
   uint8_t* labels;         // [n] 1 = object (source side)
-  unsigned long long* flow;   // [2] flow through the t-links at the start, flow pushed into the sink
-  int32_t* flags;          // [2] heights lowered by a relabel pass, pixels with excess that reach the sink
+  unsigned long long* flow_part;   // [SP_CUT_PARTS] flow through the t-links at the start
+  unsigned long long* flow;   // [SP_CUT_FLOW] flow pushed into the sink
+  int32_t* ctl;            // [2][SP_CUT_CTL] per relabel pass: heights lowered (0 / 1), pixels with excess
+                           // that reach the sink
+  int32_t* tile;           // [push tiles] nonzero: the tile holds such pixels
+  int32_t* status;         // [2] host memory: the last pass's counters
   int64_t* flow_out;       // caller's, or null
   int32_t H, W;
   float scale;
   int32_t cycles;          // push / relabel cycles per thread and launch
+  int32_t pass;            // relabel passes enqueued so far
   int32_t reset;           // relabel pass: start from the sink's neighbours (1) or from the heights (0)
-  int32_t pad;
+  int32_t first;           // relabel pass: the first of a sequence (runs whatever the pass before did);
+                           // push: no relabel has set the tile flags yet
 };
 
 // Pixel-level adjoint (dL/d frame).
