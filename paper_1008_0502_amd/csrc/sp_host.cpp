@@ -1724,7 +1724,7 @@ int saliency_backward_frames(sp_ctx* c, const uint8_t* frames, int32_t T, float*
       for (int z = 0; z < n; ++z) {
         const StepIO io = frame_io(t0 + z);
         ph.off = ph0.off + ph.upto[z];
-        if ((rc = run_phase(c, ph, c->d_sd + 1, nullptr, &io, ph.upto[z + 1] - ph.upto[z]))) return rc;
+        if ((rc = run_phase(c, ph, c->d_sd + 1 + z, nullptr, &io, ph.upto[z + 1] - ph.upto[z]))) return rc;
       }
     }
     const hipError_t e = timed(c, JOB_PIX_ADJ, [&] {

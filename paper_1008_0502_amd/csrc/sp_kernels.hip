@@ -171,7 +171,13 @@ __device__ __forceinline__ bool on_border(int y, int x, int H, int W, int b) {
   return y < b || y >= H - b || x < b || x >= W - b;
 }
 
-#define IOF(field) (ios ? ios[J.stream].field : io0.field)
+// Kernels of the step are built twice.  ONE: the launch serves one stream, sds[0], with its io
+// by value.  Such a launch is a chain of dependent reads (job, description, data), and knowing
+// the description before the job is read takes one of them out: 40.3 -> 39.2 us for a 160x120
+// step, 50.0 -> 48.7 for 320x240 with capacities.  (A run-time test of the io table in its place
+// made the compiler fetch the description with vector loads: 44.5 us.)  Otherwise the job names
+// the stream and the io table holds every stream's.
+#define IOF(field) (ONE ? io0.field : ios[J.stream].field)
 
 // ---------------------------------------------------------------- colour statistics
 // Colours packed as R | G << 8 | B << 16 are byte vectors with a zero fourth byte, so
@@ -216,6 +222,7 @@ __device__ void batch_begin_stream(int i, BatchState* __restrict__ st, const Str
                                    const uint8_t* const* __restrict__ in_ptrs, StepIO* __restrict__ ios, double Q,
                                    double R);
 
+template <bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_rgb(const Job* __restrict__ jobs,
                                                   const StreamDesc* __restrict__ sds,
                                                   const StepIO* __restrict__ ios, StepIO io0, int want_d2,
@@ -223,7 +230,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_rgb(const Job* __restrict__ jobs,
   __shared__ unsigned long long sh[4];
   __shared__ uint32_t shm[4];
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   // a batched step: this launch also starts the step (the other launches read the step's
   // inputs after it completes); its own frames come from the caller's table
   if (bb.in_ptrs && blockIdx.x == 0)
@@ -435,7 +442,7 @@ __device__ __forceinline__ float d2_norms(uint32_t a, uint32_t na, uint32_t b, u
 // registers at once (no branch between the loads); the features then go through LDS
 // in two halves of the tile (TH/2 output rows, TH+3 region rows each), which keeps the
 // launch at 8 workgroups per CU.
-template <int TH, int TW>
+template <int TH, int TW, bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void k_feat(const Job* __restrict__ jobs,
                                                    const StreamDesc* __restrict__ sds,
                                                    const StepIO* __restrict__ ios, StepIO io0) {
@@ -449,7 +456,7 @@ __global__ __launch_bounds__(SP_BLOCK) __attribute__((amdgpu_waves_per_eu(8))) v
   static_assert(4 * HR * TW >= HR * RW, "packed colours fit in the row-blur buffer");
   uint32_t* Pk = reinterpret_cast<uint32_t*>(&Hb[0][0][0]);  // packed colours until the blur
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const uint8_t* __restrict__ rgb = IOF(rgb);
   const uint8_t* __restrict__ prev = IOF(rgb_prev);
   const gp<float> pairw = G(IOF(pairwise));
@@ -899,12 +906,12 @@ __device__ void tail_job(const Job& J, const StreamDesc& sd, float* smem) {
 
 // RC: the Gabor radius the launch is built for (every stream of a launch shares it), or
 // 0 for any radius.  The default radius keeps 8 workgroups per CU.
-template <bool BIG, int RC>
+template <bool BIG, int RC, bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_pyr(
     const Job* __restrict__ jobs, const StreamDesc* __restrict__ sds, const StepIO* __restrict__ ios, StepIO io0) {
   __shared__ float smem[BIG ? TAIL_LDS : DOWN_LDS];
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   if (J.kind == JOB_DOWN) {
     down_job(J, sd, smem);
   } else if (J.kind == JOB_GABOR) {
@@ -943,13 +950,14 @@ __device__ __forceinline__ float bilinear_lds(const float* X, int ld, const Tap&
   return fmaf(ty.w, bot, (1.f - ty.w) * top);
 }
 
+template <bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_csstats(const Job* __restrict__ jobs,
                                                       const StreamDesc* __restrict__ sds,
                                                       const StepIO* __restrict__ ios, StepIO io0) {
   __shared__ float cen[SP_NCH][CS_T * CS_T];
   __shared__ float sur[4][SP_NCH][CS_F * CS_F];
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const int c = J.a, Hc = sd.Hl[c], Wc = sd.Wl[c];
   const int lane = lane_id(), w = wave_id();
   // stage the centre tile of all channels
@@ -1041,11 +1049,12 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csstats(const Job* __restrict__ jo
 }
 
 // N(.) parameters of the 8 maps of one pair (job a = pair), two maps per wavefront.
+template <bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_csfinal(const Job* __restrict__ jobs,
                                                       const StreamDesc* __restrict__ sds,
                                                       const StepIO* __restrict__ ios, StepIO io0) {
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const int p = J.a, c = sd.pc[p], nt = sd.cs_nt[p], nb = nblocks8(sd.Hl[c], sd.Wl[c]);
   static_assert(SP_NCH == 8, "two maps per wavefront");
   const int k = wave_id();
@@ -1085,7 +1094,7 @@ struct CaPair {
 // to every channel.  Each channel owns a block of L.total floats of dynamic LDS with the
 // layout of csapply_layout.  A flat map has zero N parameters (inv = scale = 0), which
 // adds exactly 0.
-template <int NC>
+template <int NC, bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jobs,
                                                       const StreamDesc* __restrict__ sds,
                                                       const StepIO* __restrict__ ios, StepIO io0) {
@@ -1096,7 +1105,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
   __shared__ float fb[NC][CA_T * CA_T];
   __shared__ float wacc[4][NC][3];
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const int k0 = J.a, cm = sd.c_max;
   const int Hm = sd.Hl[cm], Wm = sd.Wl[cm];
   const CaLayout L = csapply_layout(sd.pc, sd.ps, sd.n_pairs, cm);
@@ -1359,7 +1368,7 @@ __device__ __forceinline__ void lds_putv(float* p, const float (&v)[NC]) {
 // The pair loops carry an unroll request that only the compile-time pair set can meet.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Wpass-failed"
-template <int NC, int SET>
+template <int NC, int SET, bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_csg(const Job* __restrict__ jobs,
                                                   const StreamDesc* __restrict__ sds,
                                                   const StepIO* __restrict__ ios, StepIO io0) {
@@ -1367,7 +1376,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg(const Job* __restrict__ jobs,
   __shared__ float wred[4][NC][3];
   __shared__ float4 rtap[2 * SP_CA_T + 3];       // per region row: two table offsets and a weight
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const int k0 = J.a, cm = sd.c_max;
   const int Hm = sd.Hl[cm], Wm = sd.Wl[cm];
   // the pairs as (r, d) = (c_max - c, s - c): compile-time constants for a known set
@@ -1702,7 +1711,7 @@ __host__ __device__ constexpr int fe(int p) { return p == 0 ? 11 : (p == 1 ? 7 :
 __host__ __device__ constexpr int fo(int p) { return p == 0 ? 0 : (p == 1 ? 121 : (p == 2 ? 170 : 195)); }
 }  // namespace cg1
 
-template <int NC>
+template <int NC, bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_csg1(const Job* __restrict__ jobs,
                                                    const StreamDesc* __restrict__ sds,
                                                    const StepIO* __restrict__ ios, StepIO io0) {
@@ -1712,7 +1721,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg1(const Job* __restrict__ jobs,
   __shared__ float4 rtab[2][N1], ctab[2][N1];   // pairs 0, 1: taps (i0, i1 as offsets, w, 1 - w)
   __shared__ float wred[4][NC][3];
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const int k0 = J.a, cm = sd.c_max, c1 = cm - 1;
   const int Hm = sd.Hl[cm], Wm = sd.Wl[cm], H1 = sd.Hl[c1], W1 = sd.Wl[c1];
   const int y0 = J.y0, x0 = J.x0, ry0 = 2 * y0 - 2, rx0 = 2 * x0 - 2;
@@ -2053,13 +2062,14 @@ struct PairNp {
 
 // F-bar_k on a 16x16 c_max tile = sum over pairs of N(reduced map), all 8 channels; then
 // its partial statistics (one 8x8 block per wavefront).
+template <bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_csmix(const Job* __restrict__ jobs,
                                                     const StreamDesc* __restrict__ sds,
                                                     const StepIO* __restrict__ ios, StepIO io0) {
   __shared__ float nps[SP_MAXP][SP_NCH][3];
   __shared__ float wacc[4][SP_NCH][3];
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const int cm = sd.c_max, Hm = sd.Hl[cm], Wm = sd.Wl[cm];
   const size_t plane = (size_t)Hm * Wm;
   const int lane = lane_id(), w = wave_id();
@@ -2172,6 +2182,7 @@ __device__ void smax_partial(float v, int idx, bool valid, gp<float> out, float*
   }
 }
 
+template <bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_consp(const Job* __restrict__ jobs,
                                                     const StreamDesc* __restrict__ sds,
                                                     const StepIO* __restrict__ ios, StepIO io0) {
@@ -2179,7 +2190,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_consp(const Job* __restrict__ jobs
   __shared__ int shi4[4];
   __shared__ NParams np[SP_NCH];
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const gp<float> S_out = G(IOF(S_out));
   const gp<float> C_out = G(IOF(C_out));
   const gp<float> S_tape = G(IOF(S_tape));
@@ -2211,13 +2222,14 @@ __global__ __launch_bounds__(SP_BLOCK) void k_consp(const Job* __restrict__ jobs
   smax_partial(S, (int)o, valid, G(sd.s_part) + 2 * (size_t)J.tid, sh4, shi4);
 }
 
+template <bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_smax(const Job* __restrict__ jobs,
                                                    const StreamDesc* __restrict__ sds,
                                                    const StepIO* __restrict__ ios, StepIO io0) {
   __shared__ float sh4[4];
   __shared__ int shi4[4];
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const float* S_in = IOF(S_in);
   const int cm = sd.c_max, Hm = sd.Hl[cm], Wm = sd.Wl[cm];
   const int yy = threadIdx.x / CA_T, xx = threadIdx.x % CA_T;
@@ -2242,6 +2254,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_smax(const Job* __restrict__ jobs,
 constexpr int KT = 16;        // tile edge of the level-0 adjoint sweep
 constexpr int KTR = SP_KAL_ROWS;   // tile rows of the level-0 update
 constexpr int KTW_MAX = 64;   // widest tile (the width is chosen per stream by the host)
+template <bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_kalman(const Job* __restrict__ jobs,
                                                      const StreamDesc* __restrict__ sds,
                                                      const StepIO* __restrict__ ios, StepIO io0) {
@@ -2251,7 +2264,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_kalman(const Job* __restrict__ job
   __shared__ float sh4[4];
   __shared__ int shi4[4];
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const gp<const uint8_t> seg = G(IOF(seg_prev));
   const float* pprev = IOF(pi_prev);
   const gp<float> pnext = G(IOF(pi_next));
@@ -2387,13 +2400,14 @@ __global__ __launch_bounds__(SP_BLOCK) void k_kalman(const Job* __restrict__ job
 constexpr int DT_N = SP_DT_T + 2 * SP_DT_RMAX;
 constexpr int DT_W = (DT_N + 31) / 32;   // 32-bit words of a region column or row mask
 constexpr int DT_INF = 1 << 30;
+template <bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_dt(const Job* __restrict__ jobs, const StreamDesc* __restrict__ sds,
                                                  const StepIO* __restrict__ ios, StepIO io0) {
   __shared__ uint32_t cmask[DT_N][DT_W];       // per region column: bit r = object at region row r
   __shared__ uint32_t rmask[SP_DT_T][DT_W];    // per tile row: bit c = an object within R in column c
   __shared__ int vd[SP_DT_T * DT_N];           // squared column distance (or DT_INF) per tile row and region column
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const gp<const uint8_t> seg = G(IOF(seg_prev));
   const gp<const float> pprev = G(IOF(pi_prev));
   const gp<float> fout = G(IOF(f_map));
@@ -2501,13 +2515,14 @@ __global__ __launch_bounds__(SP_BLOCK) void k_manual(const uint8_t* __restrict__
 }
 
 // ---------------------------------------------------------------- MRF capacities
+template <bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_mrf(const Job* __restrict__ jobs,
                                                   const StreamDesc* __restrict__ sds,
                                                   const StepIO* __restrict__ ios, StepIO io0,
                                                   const float* __restrict__ prior) {
   __shared__ unsigned long long sh[4];
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const uint8_t* rgb = IOF(rgb);
   float* unary = IOF(unary);
   float* pairw = IOF(pairwise);
@@ -3105,6 +3120,15 @@ __global__ __launch_bounds__(SP_BLOCK) void k_calib(const float* __restrict__ sr
 // ---------------------------------------------------------------- launchers
 static inline hipError_t chk() { return hipGetLastError(); }
 
+// A kernel over the job table, built for one stream (no io table) or for many.
+#define SP_STEP_KERNEL(...)                                                                     \
+  do {                                                                                          \
+    if (ios)                                                                                    \
+      hipLaunchKernelGGL((__VA_ARGS__, false>), g, b, lds, st, jobs, sds, ios, io);             \
+    else                                                                                        \
+      hipLaunchKernelGGL((__VA_ARGS__, true>), g, b, lds, st, jobs, sds, ios, io);              \
+  } while (0)
+
 hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, const StepIO* ios,
                      const StepIO* io0, int flag, const float* aux, hipStream_t st, size_t lds) {
   if (n <= 0) return hipSuccess;
@@ -3112,62 +3136,107 @@ hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, co
   StepIO z{};
   const StepIO& io = io0 ? *io0 : z;
   switch (kind) {
-    case JOB_RGB: hipLaunchKernelGGL(k_rgb, g, b, 0, st, jobs, sds, ios, io, flag, BatchBegin{}); break;
-    case JOB_FEAT: hipLaunchKernelGGL((k_feat<16, 16>), g, b, 0, st, jobs, sds, ios, io); break;
+    case JOB_RGB:
+      if (ios)
+        hipLaunchKernelGGL(k_rgb<false>, g, b, 0, st, jobs, sds, ios, io, flag, BatchBegin{});
+      else
+        hipLaunchKernelGGL(k_rgb<true>, g, b, 0, st, jobs, sds, ios, io, flag, BatchBegin{});
+      break;
+    case JOB_FEAT: SP_STEP_KERNEL(k_feat<16, 16); break;
     case JOB_DOWN:   // pyramid launch without tail jobs (DOWN and GABOR jobs)
     case JOB_GABOR:   // flag: the Gabor radius of the launch
       if (flag == 6)
-        hipLaunchKernelGGL((k_pyr<false, 6>), g, b, 0, st, jobs, sds, ios, io);
+        SP_STEP_KERNEL(k_pyr<false, 6);
       else
-        hipLaunchKernelGGL((k_pyr<false, 0>), g, b, 0, st, jobs, sds, ios, io);
+        SP_STEP_KERNEL(k_pyr<false, 0);
       break;
     case JOB_TAIL:
       if (flag == 6)
-        hipLaunchKernelGGL((k_pyr<true, 6>), g, b, 0, st, jobs, sds, ios, io);
+        SP_STEP_KERNEL(k_pyr<true, 6);
       else
-        hipLaunchKernelGGL((k_pyr<true, 0>), g, b, 0, st, jobs, sds, ios, io);
+        SP_STEP_KERNEL(k_pyr<true, 0);
       break;
-    case JOB_CSSTATS: hipLaunchKernelGGL(k_csstats, g, b, 0, st, jobs, sds, ios, io); break;
-    case JOB_CSFINAL: hipLaunchKernelGGL(k_csfinal, g, b, 0, st, jobs, sds, ios, io); break;
+    case JOB_CSSTATS:
+      if (ios)
+        hipLaunchKernelGGL(k_csstats<false>, g, b, 0, st, jobs, sds, ios, io);
+      else
+        hipLaunchKernelGGL(k_csstats<true>, g, b, 0, st, jobs, sds, ios, io);
+      break;
+    case JOB_CSFINAL:
+      if (ios)
+        hipLaunchKernelGGL(k_csfinal<false>, g, b, 0, st, jobs, sds, ios, io);
+      else
+        hipLaunchKernelGGL(k_csfinal<true>, g, b, 0, st, jobs, sds, ios, io);
+      break;
     case JOB_CSG: {   // flag: channels per workgroup | pair set << 8
       const int nc = flag & 0xff, set = flag >> 8;
       if (set == 1) {
         if (nc == 8)
-          hipLaunchKernelGGL((k_csg1<8>), g, b, lds, st, jobs, sds, ios, io);
+          SP_STEP_KERNEL(k_csg1<8);
         else if (nc == 4)
-          hipLaunchKernelGGL((k_csg1<4>), g, b, lds, st, jobs, sds, ios, io);
+          SP_STEP_KERNEL(k_csg1<4);
         else if (nc == 2)
-          hipLaunchKernelGGL((k_csg1<2>), g, b, lds, st, jobs, sds, ios, io);
+          SP_STEP_KERNEL(k_csg1<2);
         else
-          hipLaunchKernelGGL((k_csg1<1>), g, b, lds, st, jobs, sds, ios, io);
+          SP_STEP_KERNEL(k_csg1<1);
       } else {
         if (nc == 8)
-          hipLaunchKernelGGL((k_csg<8, 0>), g, b, lds, st, jobs, sds, ios, io);
+          SP_STEP_KERNEL(k_csg<8, 0);
         else if (nc == 4)
-          hipLaunchKernelGGL((k_csg<4, 0>), g, b, lds, st, jobs, sds, ios, io);
+          SP_STEP_KERNEL(k_csg<4, 0);
         else if (nc == 2)
-          hipLaunchKernelGGL((k_csg<2, 0>), g, b, lds, st, jobs, sds, ios, io);
+          SP_STEP_KERNEL(k_csg<2, 0);
         else
-          hipLaunchKernelGGL((k_csg<1, 0>), g, b, lds, st, jobs, sds, ios, io);
+          SP_STEP_KERNEL(k_csg<1, 0);
       }
       break;
     }
-    case JOB_CSMIX: hipLaunchKernelGGL(k_csmix, g, b, 0, st, jobs, sds, ios, io); break;
+    case JOB_CSMIX:
+      if (ios)
+        hipLaunchKernelGGL(k_csmix<false>, g, b, 0, st, jobs, sds, ios, io);
+      else
+        hipLaunchKernelGGL(k_csmix<true>, g, b, 0, st, jobs, sds, ios, io);
+      break;
     case JOB_CSAPPLY:   // flag: channels per workgroup
       if (flag == 8)
-        hipLaunchKernelGGL(k_csapply<8>, g, b, lds, st, jobs, sds, ios, io);
+        SP_STEP_KERNEL(k_csapply<8);
       else if (flag == 4)
-        hipLaunchKernelGGL(k_csapply<4>, g, b, lds, st, jobs, sds, ios, io);
+        SP_STEP_KERNEL(k_csapply<4);
       else if (flag == 2)
-        hipLaunchKernelGGL(k_csapply<2>, g, b, lds, st, jobs, sds, ios, io);
+        SP_STEP_KERNEL(k_csapply<2);
       else
-        hipLaunchKernelGGL(k_csapply<1>, g, b, lds, st, jobs, sds, ios, io);
+        SP_STEP_KERNEL(k_csapply<1);
       break;
-    case JOB_CONSP: hipLaunchKernelGGL(k_consp, g, b, 0, st, jobs, sds, ios, io); break;
-    case JOB_SMAX: hipLaunchKernelGGL(k_smax, g, b, 0, st, jobs, sds, ios, io); break;
-    case JOB_KALMAN: hipLaunchKernelGGL(k_kalman, g, b, 0, st, jobs, sds, ios, io); break;
-    case JOB_MRF: hipLaunchKernelGGL(k_mrf, g, b, 0, st, jobs, sds, ios, io, aux); break;
-    case JOB_DT: hipLaunchKernelGGL(k_dt, g, b, 0, st, jobs, sds, ios, io); break;
+    case JOB_CONSP:
+      if (ios)
+        hipLaunchKernelGGL(k_consp<false>, g, b, 0, st, jobs, sds, ios, io);
+      else
+        hipLaunchKernelGGL(k_consp<true>, g, b, 0, st, jobs, sds, ios, io);
+      break;
+    case JOB_SMAX:
+      if (ios)
+        hipLaunchKernelGGL(k_smax<false>, g, b, 0, st, jobs, sds, ios, io);
+      else
+        hipLaunchKernelGGL(k_smax<true>, g, b, 0, st, jobs, sds, ios, io);
+      break;
+    case JOB_KALMAN:
+      if (ios)
+        hipLaunchKernelGGL(k_kalman<false>, g, b, 0, st, jobs, sds, ios, io);
+      else
+        hipLaunchKernelGGL(k_kalman<true>, g, b, 0, st, jobs, sds, ios, io);
+      break;
+    case JOB_MRF:
+      if (ios)
+        hipLaunchKernelGGL(k_mrf<false>, g, b, 0, st, jobs, sds, ios, io, aux);
+      else
+        hipLaunchKernelGGL(k_mrf<true>, g, b, 0, st, jobs, sds, ios, io, aux);
+      break;
+    case JOB_DT:
+      if (ios)
+        hipLaunchKernelGGL(k_dt<false>, g, b, 0, st, jobs, sds, ios, io);
+      else
+        hipLaunchKernelGGL(k_dt<true>, g, b, 0, st, jobs, sds, ios, io);
+      break;
     default: return hipErrorInvalidValue;
   }
   return chk();
@@ -3234,7 +3303,7 @@ hipError_t sp_launch_loss(const LossIO* tab, const LossIO* one, int n_streams, i
 
 hipError_t sp_launch_batch_rgb(const Job* jobs, int n_jobs, const StreamDesc* sds, StepIO* ios, int want_d2,
                                const BatchBegin& bb, hipStream_t stream) {
-  hipLaunchKernelGGL(k_rgb, dim3(n_jobs), dim3(SP_BLOCK), 0, stream, jobs, sds, ios, StepIO{}, want_d2, bb);
+  hipLaunchKernelGGL(k_rgb<false>, dim3(n_jobs), dim3(SP_BLOCK), 0, stream, jobs, sds, ios, StepIO{}, want_d2, bb);
   return chk();
 }
 
@@ -3246,7 +3315,7 @@ void sp_batch_rgb_node_params(RgbNodeArgs* a, int n_jobs, hipKernelNodeParams* p
   a->argv[4] = &a->want_d2;
   a->argv[5] = &a->bb;
   *p = hipKernelNodeParams{};
-  p->func = reinterpret_cast<void*>(&k_rgb);
+  p->func = reinterpret_cast<void*>(&k_rgb<false>);
   p->gridDim = dim3(n_jobs);
   p->blockDim = dim3(SP_BLOCK);
   p->sharedMemBytes = 0;
@@ -3267,12 +3336,12 @@ hipError_t sp_launch_batch_copy_out(int n, const BatchState* st, const StreamDes
 
 hipError_t sp_csapply_reserve_lds(size_t bytes) {
   if (bytes <= 65536) return hipSuccess;
-  const void* fns[12] = {reinterpret_cast<const void*>(&k_csapply<1>), reinterpret_cast<const void*>(&k_csapply<2>),
-                         reinterpret_cast<const void*>(&k_csapply<4>), reinterpret_cast<const void*>(&k_csapply<8>),
-                         reinterpret_cast<const void*>(&k_csg<1, 0>),  reinterpret_cast<const void*>(&k_csg<2, 0>),
-                         reinterpret_cast<const void*>(&k_csg<4, 0>),  reinterpret_cast<const void*>(&k_csg<8, 0>),
-                         reinterpret_cast<const void*>(&k_csg1<1>),    reinterpret_cast<const void*>(&k_csg1<2>),
-                         reinterpret_cast<const void*>(&k_csg1<4>),    reinterpret_cast<const void*>(&k_csg1<8>)};
+  const void* fns[] = {
+#define SP_BOTH(...) reinterpret_cast<const void*>(&__VA_ARGS__, false>), reinterpret_cast<const void*>(&__VA_ARGS__, true>)
+      SP_BOTH(k_csapply<1), SP_BOTH(k_csapply<2), SP_BOTH(k_csapply<4), SP_BOTH(k_csapply<8),
+      SP_BOTH(k_csg<1, 0),  SP_BOTH(k_csg<2, 0),  SP_BOTH(k_csg<4, 0),  SP_BOTH(k_csg<8, 0),
+      SP_BOTH(k_csg1<1),    SP_BOTH(k_csg1<2),    SP_BOTH(k_csg1<4),    SP_BOTH(k_csg1<8)};
+#undef SP_BOTH
   for (const void* f : fns) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (e != hipSuccess) return e;
