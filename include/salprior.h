@@ -402,7 +402,8 @@ int sp_autotune(sp_ctx* ctx, const uint8_t* rgb_t, const uint8_t* rgb_prev, int3
 int sp_set_tune(sp_ctx* ctx, int32_t kalman_tw, int32_t xcd_order, int32_t channels);
 int sp_batch_set_tune(sp_batch* b, int32_t kalman_tw, int32_t xcd_order, int32_t channels);
 /* Forgets every autotuner choice recorded in this process (contexts and batches created
- * later start from the defaults: tile width 32, no XCD order, 2 channels). */
+ * later start from the defaults: a tile width and 1 or 2 channels by the number of tiles, XCD
+ * order on). */
 int sp_tune_cache_clear(void);
 
 /* Allocation-free form of saliency_forward, for callers that cannot allocate device

@@ -184,12 +184,32 @@ void add_tiles_wh(std::vector<Job>& v, int stream, int a, int h, int w, int th, 
       v.push_back(Job{stream, a, y0, x0, std::min(th, h - y0), std::min(tw, w - x0), tid++, kind});
 }
 
-// Tuning knobs that never change results: the width of the level-0 update tiles and
-// the XCD-aware order of the job tables.
+// Tuning knobs that never change results: the width of the level-0 update tiles, the XCD-aware
+// order of the job tables and the channels per across-scale workgroup.
 struct Tune {
   int kalman_tw = 32;   // 16, 32 or 64
-  bool xcd = false;
+  bool xcd = true;
   int ca_nc = 2;        // channels per workgroup of the across-scale sum: 1, 2, 4 or 8
+};
+
+// Launch shapes where the autotuner has made no choice, from the tiles the launch holds.  Wide
+// update tiles read less of each other's borders, narrow ones give a small launch more
+// workgroups: 16 while 32-wide tiles would number below 512 (160x120 step 40.3 -> 39.6 us,
+// 640x480 with variants 78.5 -> 77.8), 64 from 1024 of them on (16 streams of 640x480, 0.160 ->
+// 0.153 ms a step).  Two channels share the sampling geometry of an across-scale workgroup
+// once five workgroups per CU remain; below, one channel each (1920x1080 step 97.6 -> 89.5 us,
+// 640x480 78.5 -> 77.6; 16 streams 0.158 against 0.153 ms with two).  The XCD order is kept on: 0.187 ->
+// 0.167 ms for 16 streams, 103.4 -> 97.6 us for 1920x1080, nothing lost below.
+struct TileCount {
+  long long upd32 = 0, upd64 = 0, cmax = 0;
+  void add(const Geo& g) {
+    const long long rows = (g.H + SP_KAL_ROWS - 1) / SP_KAL_ROWS;
+    upd32 += rows * ((g.W + 31) / 32);
+    upd64 += rows * ((g.W + 63) / 64);
+    cmax += (long long)((g.Hl[g.c_max] + kTile - 1) / kTile) * ((g.Wl[g.c_max] + kTile - 1) / kTile);
+  }
+  int tw() const { return upd32 < 512 ? 16 : (upd64 >= 1024 ? 64 : 32); }
+  int nc() const { return cmax * (SP_NCH / 2) >= 5 * 256 ? 2 : 1; }
 };
 
 // Choices of the autotuner per resolution, reused by later contexts and batches.
@@ -197,25 +217,25 @@ std::map<std::pair<int, int>, int>& tune_cache_tw() {
   static std::map<std::pair<int, int>, int> m;
   return m;
 }
-bool& tune_cache_xcd() {
-  static bool x = false;
+int& tune_cache_xcd() {   // -1: none made
+  static int x = -1;
   return x;
 }
-int& tune_cache_nc() {
-  static int nc = 2;
+int& tune_cache_nc() {    // 0: none made
+  static int nc = 0;
   return nc;
 }
 std::mutex& tune_mutex() {
   static std::mutex m;
   return m;
 }
-Tune cached_tune(int H, int W) {
+Tune cached_tune(int H, int W, const TileCount& n) {
   std::lock_guard<std::mutex> lk(tune_mutex());
   Tune t;
   auto it = tune_cache_tw().find({H, W});
-  if (it != tune_cache_tw().end()) t.kalman_tw = it->second;
-  t.xcd = tune_cache_xcd();
-  t.ca_nc = tune_cache_nc();
+  t.kalman_tw = it != tune_cache_tw().end() ? it->second : n.tw();
+  t.xcd = tune_cache_xcd() != 0;
+  t.ca_nc = tune_cache_nc() > 0 ? tune_cache_nc() : n.nc();
   return t;
 }
 
@@ -972,7 +992,9 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
     sp_destroy(c);
     return fail(SP_EHIP, "cannot reserve %zu bytes of LDS for the across-scale sum", csapply_lds_bytes(g));
   }
-  c->tune = cached_tune(H, W);
+  TileCount tiles;
+  tiles.add(g);
+  c->tune = cached_tune(H, W, tiles);
   int rc2 = c->cap > 0 ? c->cstage.init(sizeof(StepIO) * c->cap) : SP_OK;
   if (!rc2) rc2 = ctx_build_tables(c);
   if (rc2) {
@@ -992,8 +1014,11 @@ namespace {
 // The forward phases over the clip slots: slot by slot (a prefix serves a shorter chunk), and
 // for whole chunks in XCD order with the longer jobs of a pyramid launch (Gabor tiles, small
 // levels) first, as in the batched step.
-void clip_tables(sp_ctx* c, int nc) {
+int clip_tables(sp_ctx* c) {
   const Geo& g = c->g;
+  TileCount tiles;
+  for (int s = 0; s < c->CH; ++s) tiles.add(g);
+  const int nc = csapply_nc(g, tiles.nc());
   std::vector<std::vector<Job>> all;
   std::vector<int> kinds;
   for (int s = 0; s < c->CH; ++s) {
@@ -1007,6 +1032,8 @@ void clip_tables(sp_ctx* c, int nc) {
     for (size_t i = 0; i < parts.size(); ++i) all[i].insert(all[i].end(), parts[i].begin(), parts[i].end());
   }
   const size_t lds = nc * (gpath_ok(g) ? csg_lds_bytes(g) : csapply_lds_bytes(g));
+  if (sp_csapply_reserve_lds(lds) != hipSuccess)
+    return fail(SP_EHIP, "cannot reserve %zu bytes of LDS for the across-scale sum", lds);
   for (size_t i = 0; i < all.size(); ++i) {
     const bool grp = kinds[i] == JOB_CSAPPLY || kinds[i] == JOB_CSG;
     const bool pyr = kinds[i] == JOB_DOWN || kinds[i] == JOB_TAIL;
@@ -1022,6 +1049,7 @@ void clip_tables(sp_ctx* c, int nc) {
     c->clip_full.push_back(c->jobs.add(kinds[i], flag, first, c->CH));
     if (grp) c->clip_part.back().lds = c->clip_full.back().lds = lds;
   }
+  return SP_OK;
 }
 
 // (Re)builds every job table of a context from its geometry and tuning knobs.
@@ -1066,7 +1094,7 @@ int ctx_build_tables(sp_ctx* c) {
     add_tiles(v, 0, 0, Hc, Wc);
     if (g.c_max > kSweepMax) c->bwd.push_back(c->jobs.add(JOB_BWD_GS, 0, v, 1));
     c->dot = c->jobs.add(JOB_CONSP_DOT, 0, v, 1);
-    if (c->CH > 0) clip_tables(c, nc);
+    if (c->CH > 0 && (rc = clip_tables(c))) return rc;
   }
   return upload_jobs(c->jobs, c->stream);
 }
@@ -1450,7 +1478,9 @@ int sp_saliency_noalloc(const sp_params* p, int32_t H, int32_t W, const uint8_t*
   Geo g;
   rc = make_geo(*p, H, W, g);
   if (rc) return rc;
-  const Tune tune = cached_tune(H, W);
+  TileCount tiles;
+  tiles.add(g);
+  const Tune tune = cached_tune(H, W, tiles);
   const int nc = csapply_nc(g, tune.ca_nc);
   // sizing pass (no device call): stream description, job table, then the stream's
   // pyramid, maps and partials, in the order the placing pass takes them
@@ -1572,7 +1602,7 @@ int sp_autotune(sp_ctx* c, const uint8_t* rgb_t, const uint8_t* rgb_prev, int32_
   {
     std::lock_guard<std::mutex> lk(tune_mutex());
     tune_cache_tw()[{g.H, g.W}] = bt.kalman_tw;
-    tune_cache_xcd() = bt.xcd;
+    tune_cache_xcd() = bt.xcd ? 1 : 0;
     tune_cache_nc() = bt.ca_nc;
   }
   if (report && report_len) {
@@ -1600,8 +1630,8 @@ int sp_tune_cache_clear(void) {
   g_err.clear();
   std::lock_guard<std::mutex> lk(tune_mutex());
   tune_cache_tw().clear();
-  tune_cache_xcd() = false;
-  tune_cache_nc() = 2;
+  tune_cache_xcd() = -1;
+  tune_cache_nc() = 0;
   return SP_OK;
 }
 
@@ -2267,9 +2297,11 @@ int sp_batch_create(const sp_params* p, int32_t n, const int32_t* H, const int32
   }
   b->mrf = mrf;
   b->tune.resize(n);
-  for (int i = 0; i < n; ++i) b->tune[i] = cached_tune(H[i], W[i]);
-  b->xcd = n > 0 ? b->tune[0].xcd : false;
-  b->ca_nc = n > 0 ? b->tune[0].ca_nc : 2;
+  TileCount tiles;
+  for (const Geo& g : b->geo) tiles.add(g);
+  for (int i = 0; i < n; ++i) b->tune[i] = cached_tune(H[i], W[i], tiles);
+  b->xcd = b->tune[0].xcd;
+  b->ca_nc = b->tune[0].ca_nc;
   {
     size_t lds = 0;
     for (const Geo& g : b->geo) lds = std::max(lds, csapply_lds_bytes(g));
@@ -2527,7 +2559,7 @@ int sp_batch_autotune(sp_batch* b, const uint8_t* const* rgb_ptrs, int32_t steps
   if (rc) return rc;
   {
     std::lock_guard<std::mutex> lk(tune_mutex());
-    tune_cache_xcd() = b->xcd;
+    tune_cache_xcd() = b->xcd ? 1 : 0;
     tune_cache_nc() = b->ca_nc;
     for (int i = 0; i < b->n; ++i) tune_cache_tw()[{b->geo[i].H, b->geo[i].W}] = b->tune[i].kalman_tw;
   }
