@@ -2394,113 +2394,141 @@ __global__ __launch_bounds__(SP_BLOCK) void k_kalman(const Job* __restrict__ job
 // f(A, x) = exp(-d(x)^2 / (2 sigma^2)), d the Euclidean distance from x to the nearest
 // object pixel of the previous segmentation (or of prior > 1/2 without one).  The search
 // radius R has exp(-R^2 / (2 sigma^2)) below FP32's normal range, so a pixel with no object
-// within R gets 0 and every other pixel its exact squared distance: a column pass gives the
-// distance to the nearest object in the pixel's column within R, a row pass the minimum of
-// v(x')^2 + (x - x')^2 over |x - x'| <= R.
+// within R gets 0 and every other pixel its exact squared distance: a row pass gives the
+// distance to the nearest object in each row of the tile's region within R, a column pass the
+// minimum of v(y')^2 + (y - y')^2 over |y - y'| <= R.
+// The region of a 32x32 tile (86x86 pixels for a decay length of 2) is read four pixels a load
+// into row bit masks; a tile with no object in it, most of a frame, writes its zeros and ends.
+// Latency-bound: one 1024-thread workgroup per tile has one pixel per thread in the last pass
+// and two loads per thread in the first, where 256 threads with a byte per load, a column mask
+// built by atomics and 32 rows of masks searched per tile took 19.8 us a 640x480 frame, 8.0 us
+// here.
 constexpr int DT_N = SP_DT_T + 2 * SP_DT_RMAX;
-constexpr int DT_W = (DT_N + 31) / 32;   // 32-bit words of a region column or row mask
+constexpr int DT_W = (DT_N + 3 + 31) / 32;   // 32-bit words of a region row (starting at a multiple of 4)
 constexpr int DT_INF = 1 << 30;
+constexpr int DT_B = SP_DT_T * SP_DT_T;      // threads: one per pixel of the tile
 template <bool ONE>
-__global__ __launch_bounds__(SP_BLOCK) void k_dt(const Job* __restrict__ jobs, const StreamDesc* __restrict__ sds,
-                                                 const StepIO* __restrict__ ios, StepIO io0) {
-  __shared__ uint32_t cmask[DT_N][DT_W];       // per region column: bit r = object at region row r
-  __shared__ uint32_t rmask[SP_DT_T][DT_W];    // per tile row: bit c = an object within R in column c
-  __shared__ int vd[SP_DT_T * DT_N];           // squared column distance (or DT_INF) per tile row and region column
+__global__ __launch_bounds__(DT_B) void k_dt(const Job* __restrict__ jobs, const StreamDesc* __restrict__ sds,
+                                             const StepIO* __restrict__ ios, StepIO io0) {
+  __shared__ uint32_t mask[DT_N][DT_W];     // per region row: bit b = object at column xa + b
+  __shared__ int hd[DT_N * SP_DT_T];        // squared distance along the row (or DT_INF) per region row and tile column
+  __shared__ int found;
   const Job J = jobs[blockIdx.x];
   const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const gp<const uint8_t> seg = G(IOF(seg_prev));
-  const gp<const float> pprev = G(IOF(pi_prev));
+  const float* prior = IOF(pi_prev);
+  const gp<const float> pprev = G(prior);
   const gp<float> fout = G(IOF(f_map));
   const int H = sd.H, W = sd.W, R = sd.dt_r;
-  const int nr = J.th + 2 * R, nc = J.tw + 2 * R;
-  const int ry0 = J.y0 - R, rx0 = J.x0 - R;
   const int tid = threadIdx.x;
-  for (int i = tid; i < DT_N * DT_W; i += SP_BLOCK) (&cmask[0][0])[i] = 0u;
-  for (int i = tid; i < SP_DT_T * DT_W; i += SP_BLOCK) (&rmask[0][0])[i] = 0u;
+  const int nr = J.th + 2 * R, ry0 = J.y0 - R;
+  const int xa = (J.x0 - R) & ~3, nq = (J.x0 + J.tw + R - xa + 3) >> 2;   // quads of a row
+  for (int i = tid; i < DT_N * DT_W; i += DT_B) (&mask[0][0])[i] = 0u;
+  if (tid == 0) found = 0;
   __syncthreads();
-  // the object pixels of the region (outside the frame: none), eight loads in flight per
-  // thread (unconditional, from clamped addresses, then selected); the source (segmentation
-  // bytes or the previous prior) is chosen outside the loop, so no branch splits a batch
-  auto stage = [&](auto is_obj) {
-    const int n = nr * nc;
-    Walk2 wk(tid, nc);
-    for (int i0 = 0; i0 < n; i0 += 8 * SP_BLOCK) {
-      int r[8], c[8], in[8], ob[8];
-      uint32_t a[8];
+  // the object pixels of the region (outside the frame: none), two quads in flight per thread;
+  // the source (segmentation bytes or the previous prior) is chosen outside the loop.  Quads of
+  // a width that is a multiple of 4 lie wholly inside or outside the frame.
+  auto stage = [&](auto quad) {
+    const int n = nr * nq;
+    for (int i0 = tid; i0 < n; i0 += 2 * DT_B) {
+      uint32_t nib[2];
+      int r[2], c[2];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        r[k] = wk.r;
-        c[k] = wk.c;
-        wk.next();
-        const int y = ry0 + r[k], x = rx0 + c[k];
-        a[k] = (uint32_t)clampi(y, 0, H - 1) * (uint32_t)W + (uint32_t)clampi(x, 0, W - 1);
-        // in the region and in the frame, as an integer (no short-circuit branch)
-        in[k] = (int)(i0 + k * SP_BLOCK + tid < n) & (int)((unsigned)y < (unsigned)H) & (int)((unsigned)x < (unsigned)W);
+      for (int k = 0; k < 2; ++k) {
+        const int i = min(i0 + k * DT_B, n - 1);   // past the end: the last quad again (the same bits)
+        r[k] = i / nq;
+        c[k] = i - r[k] * nq;
+        nib[k] = quad(ry0 + r[k], xa + 4 * c[k]);
       }
 #pragma unroll
-      for (int k = 0; k < 8; ++k) ob[k] = is_obj(a[k]);   // all eight loads issued before any use
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (in[k] & ob[k]) atomicOr(&cmask[c[k]][r[k] >> 5], 1u << (r[k] & 31));
+      for (int k = 0; k < 2; ++k)
+        if (nib[k]) {
+          atomicOr(&mask[r[k]][c[k] >> 3], nib[k] << ((4 * c[k]) & 31));
+          found = 1;
+        }
     }
   };
-  if (seg)
-    stage([&](uint32_t a) { return (int)(seg[a] != 0); });
-  else
-    stage([&](uint32_t a) { return (int)(pprev[a] > 0.5f); });
-  __syncthreads();
-  // column pass: the nearest object row at or above / at or below each tile row, from the
-  // column's mask (clz / ctz on the word holding the row, then the words before / after)
-  const int R2 = R * R;
-  for (int q = tid; q < J.th * nc; q += SP_BLOCK) {
-    const int t = q / nc, c = q - t * nc, rr = t + R;
-    const int w = rr >> 5, b = rr & 31;
-    uint32_t cm[DT_W];
+  const bool w4 = (W & 3) == 0;
+  if (seg) {
+    if (w4 && (reinterpret_cast<uintptr_t>(IOF(seg_prev)) & 3) == 0)
+      stage([&](int y, int x) -> uint32_t {
+        const bool in = (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)W;
+        const uint32_t v = *(gp<const uint32_t>)at_bytes(seg, (uint32_t)clampi(y, 0, H - 1) * (uint32_t)W + (uint32_t)clampi(x, 0, W - 4));
+        const uint32_t b = ((v & 0xffu) ? 1u : 0u) | ((v & 0xff00u) ? 2u : 0u) | ((v & 0xff0000u) ? 4u : 0u) | ((v >> 24) ? 8u : 0u);
+        return in ? b : 0u;
+      });
+    else
+      stage([&](int y, int x) -> uint32_t {
+        const uint32_t row = (uint32_t)clampi(y, 0, H - 1) * (uint32_t)W;
+        uint32_t b = 0u;
 #pragma unroll
-    for (int k = 0; k < DT_W; ++k) cm[k] = cmask[c][k];   // all words read together
-    const uint32_t lo = b == 31 ? 0xffffffffu : ((2u << b) - 1u), hi = ~((1u << b) - 1u);
-    // the highest object row at or above rr (the last nonzero word upward wins) and the
-    // lowest at or below (the last nonzero word downward wins), without data-dependent loops
-    int up = -DT_INF, dn = DT_INF;
+        for (int k = 0; k < 4; ++k)
+          b |= (seg[row + (uint32_t)clampi(x + k, 0, W - 1)] != 0 && (unsigned)(x + k) < (unsigned)W) ? 1u << k : 0u;
+        return (unsigned)y < (unsigned)H ? b : 0u;
+      });
+  } else if (w4 && (reinterpret_cast<uintptr_t>(prior) & 15) == 0) {
+    typedef float v4f __attribute__((ext_vector_type(4)));
+    stage([&](int y, int x) -> uint32_t {
+      const bool in = (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)W;
+      const v4f v = *(gp<const v4f>)at_bytes(pprev, ((uint32_t)clampi(y, 0, H - 1) * (uint32_t)W + (uint32_t)clampi(x, 0, W - 4)) * 4u);
+      const uint32_t b = (v.x > 0.5f ? 1u : 0u) | (v.y > 0.5f ? 2u : 0u) | (v.z > 0.5f ? 4u : 0u) | (v.w > 0.5f ? 8u : 0u);
+      return in ? b : 0u;
+    });
+  } else {
+    stage([&](int y, int x) -> uint32_t {
+      const uint32_t row = (uint32_t)clampi(y, 0, H - 1) * (uint32_t)W;
+      uint32_t b = 0u;
 #pragma unroll
-    for (int k = 0; k < DT_W; ++k) {
-      const uint32_t m = k < w ? cm[k] : (k == w ? cm[k] & lo : 0u);
-      up = m ? 32 * k + 31 - __clz(m) : up;
-    }
-#pragma unroll
-    for (int k = DT_W - 1; k >= 0; --k) {
-      const uint32_t m = k > w ? cm[k] : (k == w ? cm[k] & hi : 0u);
-      dn = m ? 32 * k + __ffs(m) - 1 : dn;
-    }
-    const int d = min(rr - up, dn - rr);
-    const bool near = d <= R;
-    vd[t * nc + c] = near ? d * d : DT_INF;
-    if (near) atomicOr(&rmask[t][c >> 5], 1u << (c & 31));
+      for (int k = 0; k < 4; ++k)
+        b |= (pprev[row + (uint32_t)clampi(x + k, 0, W - 1)] > 0.5f && (unsigned)(x + k) < (unsigned)W) ? 1u << k : 0u;
+      return (unsigned)y < (unsigned)H ? b : 0u;
+    });
   }
   __syncthreads();
-  // row pass: min over |k| <= R of vd(x + k) + k^2 (exact squared distance within R), the
-  // search skipped when no column within R holds an object
-  const float k2 = sd.dt_k;
-  Walk2 wk(tid, J.tw);
-  for (int i0 = 0; i0 + tid < J.th * J.tw; i0 += SP_BLOCK, wk.next()) {
-    const int* row = vd + wk.r * nc + wk.c + R;
-    // columns wk.c .. wk.c + 2R of the region (the window around the pixel)
-    const int lo = wk.c, hi = wk.c + 2 * R;
-    bool any = false;
-    for (int k = lo >> 5; k <= hi >> 5; ++k) {
-      uint32_t m = rmask[wk.r][k];
-      if (k == lo >> 5) m &= ~((1u << (lo & 31)) - 1u);
-      if (k == hi >> 5 && (hi & 31) != 31) m &= (2u << (hi & 31)) - 1u;
-      any |= m != 0;
+  const int ty = tid / SP_DT_T, tx = tid % SP_DT_T;
+  const bool own = ty < J.th && tx < J.tw;
+  const uint32_t oo = (uint32_t)(J.y0 + ty) * (uint32_t)W + (uint32_t)(J.x0 + tx);
+  if (!found) {   // uniform
+    if (own) fout[oo] = 0.f;
+    return;
+  }
+  // row pass: the nearest object column at or before / at or after each tile column, from the
+  // row's mask (clz / ctz on the word holding the column, then the words before / after)
+  for (int r = ty; r < nr; r += SP_DT_T) {
+    uint32_t cm[DT_W], any = 0u;
+#pragma unroll
+    for (int k = 0; k < DT_W; ++k) {   // all words read together
+      cm[k] = mask[r][k];
+      any |= cm[k];
     }
-    int best = DT_INF;
+    int v = DT_INF;
     if (any) {
-      best = row[0];
-      for (int k = 1; k <= R && k * k < best; ++k) best = min(best, min(row[-k], row[k]) + k * k);
+      const int p = J.x0 + tx - xa, w = p >> 5, b = p & 31;
+      const uint32_t lo = b == 31 ? 0xffffffffu : ((2u << b) - 1u), hi = ~((1u << b) - 1u);
+      int up = -DT_INF, dn = DT_INF;
+#pragma unroll
+      for (int k = 0; k < DT_W; ++k) {
+        const uint32_t m = k < w ? cm[k] : (k == w ? cm[k] & lo : 0u);
+        up = m ? 32 * k + 31 - __clz(m) : up;
+      }
+#pragma unroll
+      for (int k = DT_W - 1; k >= 0; --k) {
+        const uint32_t m = k > w ? cm[k] : (k == w ? cm[k] & hi : 0u);
+        dn = m ? 32 * k + __ffs(m) - 1 : dn;
+      }
+      const int d = min(p - up, dn - p);
+      v = d <= R ? d * d : DT_INF;
     }
-    const float f = best <= R2 ? __builtin_amdgcn_exp2f((float)best * k2) : 0.f;
-    fout[(uint32_t)(J.y0 + wk.r) * (uint32_t)W + (uint32_t)(J.x0 + wk.c)] = f;
+    hd[r * SP_DT_T + tx] = v;
   }
+  __syncthreads();
+  // column pass: min over |k| <= R of hd(y + k) + k^2 (exact squared distance within R)
+  if (!own) return;
+  const int* col = hd + (ty + R) * SP_DT_T + tx;
+  int best = col[0];
+  for (int k = 1; k <= R && k * k < best; ++k) best = min(best, min(col[-k * SP_DT_T], col[k * SP_DT_T]) + k * k);
+  fout[oo] = best <= R * R ? __builtin_amdgcn_exp2f((float)best * sd.dt_k) : 0.f;
 }
 
 // Prior of the first frame from manual labels: 1 -> 1, 0 -> eps, anything else -> 0.5.
@@ -3233,9 +3261,9 @@ hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, co
       break;
     case JOB_DT:
       if (ios)
-        hipLaunchKernelGGL(k_dt<false>, g, b, 0, st, jobs, sds, ios, io);
+        hipLaunchKernelGGL(k_dt<false>, g, dim3(DT_B), 0, st, jobs, sds, ios, io);
       else
-        hipLaunchKernelGGL(k_dt<true>, g, b, 0, st, jobs, sds, ios, io);
+        hipLaunchKernelGGL(k_dt<true>, g, dim3(DT_B), 0, st, jobs, sds, ios, io);
       break;
     default: return hipErrorInvalidValue;
   }
