@@ -245,16 +245,17 @@ __device__ __forceinline__ void lds_load4_u(float* wave_dst, gp<const float> bas
 // read again within the step.
 __device__ __forceinline__ void st_stream(gp<float> p, float v) { __builtin_nontemporal_store(v, p); }
 
-// Row and column of the flat index i = threadIdx.x + k * SP_BLOCK over rows of length
-// w, advanced by SP_BLOCK per step: the quotient and remainder of the start and of the
+// Row and column of the flat index i = threadIdx.x + k * B over rows of length
+// w, advanced by B (the workgroup) per step: the quotient and remainder of the start and of the
 // stride are taken once, so a staging loop does no integer division per element.
-struct Walk2 {
+template <int B>
+struct WalkB {
   int r, c, dr, dc, w;
-  __device__ __forceinline__ Walk2(int start, int w_) : w(max(w_, 1)) {
+  __device__ __forceinline__ WalkB(int start, int w_) : w(max(w_, 1)) {
     r = start / w;
     c = start - r * w;
-    dr = SP_BLOCK / w;
-    dc = SP_BLOCK - dr * w;
+    dr = B / w;
+    dc = B - dr * w;
   }
   __device__ __forceinline__ void next() {
     r += dr;
@@ -265,5 +266,6 @@ struct Walk2 {
     }
   }
 };
+typedef WalkB<SP_BLOCK> Walk2;
 
 }  // namespace

@@ -649,6 +649,7 @@ __device__ __forceinline__ void load_taps(const StreamDesc& sd, int n, float* ta
 }
 
 // level a -> a+1 of the 4 base channels for one 16x16 tile of level a+1
+template <int NT_>
 __device__ void down_job(const Job& J, const StreamDesc& sd, float* smem) {
   float* F = smem;                 // [4][DR][DR]; then the row pass [4][DR][DT] in its place
   const int l = J.a;
@@ -657,7 +658,7 @@ __device__ void down_job(const Job& J, const StreamDesc& sd, float* smem) {
   const size_t splane = (size_t)Hs * Ws;
   const int Y0 = 2 * J.y0 - 2, X0 = 2 * J.x0 - 2;
   const int wf = wave_first();
-  for (int i0 = 0; i0 + (int)threadIdx.x < DR * DR; i0 += SP_BLOCK) {
+  for (int i0 = 0; i0 + (int)threadIdx.x < DR * DR; i0 += NT_) {
     const int i = i0 + threadIdx.x, ry = i / DR, rx = i - ry * DR;
     const uint32_t ob = ((uint32_t)clampi(Y0 + ry, 0, Hs - 1) * (uint32_t)Ws + (uint32_t)clampi(X0 + rx, 0, Ws - 1)) * 4u;
 #pragma unroll
@@ -667,13 +668,13 @@ __device__ void down_job(const Job& J, const StreamDesc& sd, float* smem) {
   __syncthreads();
   // row pass of every channel into registers, then (after one barrier) into the start of
   // that channel's own staged region, no longer read: the launch keeps 8 workgroups per CU
-  constexpr int NH = (DR * DT + SP_BLOCK - 1) / SP_BLOCK;
+  constexpr int NH = (DR * DT + NT_ - 1) / NT_;
   float hv[4][NH];
 #pragma unroll
   for (int c = 0; c < 4; ++c)
 #pragma unroll
     for (int k = 0; k < NH; ++k) {
-      const int i = threadIdx.x + k * SP_BLOCK;
+      const int i = threadIdx.x + k * NT_;
       const int r = min(i / DT, DR - 1), j = i % DT;
       const float* row = F + (c * DR + r) * DR + 2 * j;
       hv[c][k] = kB0 * row[0] + kB1 * row[1] + kB2 * row[2] + kB1 * row[3] + kB0 * row[4];
@@ -683,7 +684,7 @@ __device__ void down_job(const Job& J, const StreamDesc& sd, float* smem) {
   for (int c = 0; c < 4; ++c)
 #pragma unroll
     for (int k = 0; k < NH; ++k) {
-      const int i = threadIdx.x + k * SP_BLOCK;
+      const int i = threadIdx.x + k * NT_;
       if (i < DR * DT) F[c * DR * DR + i] = hv[c][k];
     }
   __syncthreads();
@@ -693,7 +694,7 @@ __device__ void down_job(const Job& J, const StreamDesc& sd, float* smem) {
   const size_t plane = (size_t)Hd * Wd;
   const int yy = threadIdx.x / DT, xx = threadIdx.x % DT;
   const int y = J.y0 + yy, x = J.x0 + xx;
-  if (yy < J.th && xx < J.tw && y < Hd && x < Wd) {
+  if (yy < DT && yy < J.th && xx < J.tw && y < Hd && x < Wd) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const float* col = Hb + c * DR * DR + 2 * yy * DT + xx;
@@ -708,7 +709,7 @@ __device__ void down_job(const Job& J, const StreamDesc& sd, float* smem) {
 //   O45 = H[gc] V[gc] - H[gs] V[gs] - c45 H[g] V[g], O135 = same with + H[gs] V[gs].
 // RC > 0: built for radius RC (every extent and offset a compile-time constant); RC = 0:
 // any radius, loops unrolled over the zero-padded maximum of taps.
-template <int RC>
+template <int RC, int NT_>
 __device__ void gabor_job(const Job& J, const StreamDesc& sd, float* smem) {
   constexpr int NT = RC > 0 ? 2 * RC + 1 : 2 * SP_MAXR + 1;
   float* Ir = smem;                            // [RRr][RRc] (flat)
@@ -720,8 +721,8 @@ __device__ void gabor_job(const Job& J, const StreamDesc& sd, float* smem) {
   load_taps(sd, n, taps);
   const gp<const float> gI = G(I);
   const int wf = wave_first();
-  Walk2 wk(threadIdx.x, RRc);
-  for (int i0 = 0; i0 + (int)threadIdx.x < RRr * RRc; i0 += SP_BLOCK, wk.next()) {
+  WalkB<NT_> wk(threadIdx.x, RRc);
+  for (int i0 = 0; i0 + (int)threadIdx.x < RRr * RRc; i0 += NT_, wk.next()) {
     const int y = clampi(J.y0 - R + wk.r, 0, Hs - 1), x = clampi(J.x0 - R + wk.c, 0, Ws - 1);
     lds_load_u(Ir + i0 + wf, gI, ((uint32_t)y * (uint32_t)Ws + (uint32_t)x) * 4u);
   }
@@ -737,9 +738,9 @@ __device__ void gabor_job(const Job& J, const StreamDesc& sd, float* smem) {
       return taps[f * (2 * SP_MAXR + 1) + v];
   };
   // vertical pass: the four factors of one (row, column) from one read of its column
-  Walk2 wk2(threadIdx.x, RRc);
+  WalkB<NT_> wk2(threadIdx.x, RRc);
 #pragma unroll 1
-  for (int i = threadIdx.x; i < GT * RRc; i += SP_BLOCK, wk2.next()) {
+  for (int i = threadIdx.x; i < GT * RRc; i += NT_, wk2.next()) {
     const int yy = wk2.r, xr = wk2.c;
     float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
 #pragma unroll
@@ -759,7 +760,7 @@ __device__ void gabor_job(const Job& J, const StreamDesc& sd, float* smem) {
   const size_t plane = (size_t)Hs * Ws;
   const gp<float> Go = G(sd.gab[l]);
 #pragma unroll 1
-  for (int i = threadIdx.x; i < GT * GW; i += SP_BLOCK) {
+  for (int i = threadIdx.x; i < GT * GW; i += NT_) {
     const int yy = i / GW, xx = i % GW;
     const int y = J.y0 + yy, x = J.x0 + xx;
     const float* V0 = V + (0 * GT + yy) * (GCM + 1) + xx;
@@ -792,7 +793,7 @@ __device__ void gabor_job(const Job& J, const StreamDesc& sd, float* smem) {
 // LDS), so a band needs no halo of its own.
 // SC: the taps are the NT = 2R + 1 leading values of the stream's factor table gf, read as
 // uniform scalars; otherwise the zero-padded LDS table taps.
-template <int NT, bool SC>
+template <int NT, bool SC, int NT_>
 __device__ void gabor_lds(const float* I, int h, int w, int y0, int nr, float* V, const float* taps,
                           const float (*gf)[2 * SP_MAXR + 1], int R, float c45, gp<float> out) {
   auto tap = [&](int f, int v) -> float {
@@ -803,8 +804,8 @@ __device__ void gabor_lds(const float* I, int h, int w, int y0, int nr, float* V
   };
   const int n = nr * w, plane = h * w;
   {
-    Walk2 wk(threadIdx.x, w);
-    for (int pix = threadIdx.x; pix < n; pix += SP_BLOCK, wk.next()) {
+    WalkB<NT_> wk(threadIdx.x, w);
+    for (int pix = threadIdx.x; pix < n; pix += NT_, wk.next()) {
       const int y = y0 + wk.r, x = wk.c;
       float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
 #pragma unroll
@@ -822,8 +823,8 @@ __device__ void gabor_lds(const float* I, int h, int w, int y0, int nr, float* V
     }
   }
   __syncthreads();
-  Walk2 wk(threadIdx.x, w);
-  for (int pix = threadIdx.x; pix < n; pix += SP_BLOCK, wk.next()) {
+  WalkB<NT_> wk(threadIdx.x, w);
+  for (int pix = threadIdx.x; pix < n; pix += NT_, wk.next()) {
     const int y = wk.r, x = wk.c;   // y relative to the band
     float A = 0.f, B = 0.f, C = 0.f, D = 0.f, E = 0.f;
 #pragma unroll
@@ -849,7 +850,7 @@ __device__ void gabor_lds(const float* I, int h, int w, int y0, int nr, float* V
 // (channel tid) compute and store every level up to the top; TAILGAB jobs rebuild the
 // intensity chain up to level tid and store that level's Gabor maps for the row band
 // y0 .. y0+th-1, so the Gabor work of the small levels runs in parallel workgroups.
-template <int RC>
+template <int RC, int NT_>
 __device__ void tail_job(const Job& J, const StreamDesc& sd, float* smem) {
   float* SA = smem;
   float* SB = SA + SP_TAIL_SRC;
@@ -863,7 +864,7 @@ __device__ void tail_job(const Job& J, const StreamDesc& sd, float* smem) {
   {
     const float* src = sd.base[L0] + (size_t)ch * cH * cW;
     const int wf = wave_first();
-    for (int i0 = 0; i0 + (int)threadIdx.x < cH * cW; i0 += SP_BLOCK)
+    for (int i0 = 0; i0 + (int)threadIdx.x < cH * cW; i0 += NT_)
       lds_load_u(SA + i0 + wf, G(src), (uint32_t)(i0 + threadIdx.x) * 4u);
     lds_wait();
   }
@@ -872,8 +873,8 @@ __device__ void tail_job(const Job& J, const StreamDesc& sd, float* smem) {
   for (int l = L0; l < last; ++l) {
     const int nH = sd.Hl[l + 1], nW = sd.Wl[l + 1];
     __syncthreads();
-    Walk2 wk(threadIdx.x, nW);
-    for (int i = threadIdx.x; i < cH * nW; i += SP_BLOCK, wk.next()) {
+    WalkB<NT_> wk(threadIdx.x, nW);
+    for (int i = threadIdx.x; i < cH * nW; i += NT_, wk.next()) {
       const int r = wk.r, j = wk.c;
       const float* row = cur + r * cW;
       float acc = 0.f;
@@ -883,8 +884,8 @@ __device__ void tail_job(const Job& J, const StreamDesc& sd, float* smem) {
     }
     __syncthreads();
     const gp<float> dst = gab ? nullptr : G(sd.base[l + 1]) + (size_t)ch * nH * nW;
-    Walk2 wk2(threadIdx.x, nW);
-    for (int i = threadIdx.x; i < nH * nW; i += SP_BLOCK, wk2.next()) {
+    WalkB<NT_> wk2(threadIdx.x, nW);
+    for (int i = threadIdx.x; i < nH * nW; i += NT_, wk2.next()) {
       const int r = wk2.r, j = wk2.c;
       float acc = 0.f;
 #pragma unroll
@@ -894,7 +895,7 @@ __device__ void tail_job(const Job& J, const StreamDesc& sd, float* smem) {
     }
     __syncthreads();
     if (gab && l + 1 == last)   // its vertical passes go to the buffer of level l, now free
-      gabor_lds<(RC > 0 ? 2 * RC + 1 : 2 * SP_MAXR + 1), (RC > 0)>(nxt, nH, nW, J.y0, J.th, cur, taps, sd.gf, R,
+      gabor_lds<(RC > 0 ? 2 * RC + 1 : 2 * SP_MAXR + 1), (RC > 0), NT_>(nxt, nH, nW, J.y0, J.th, cur, taps, sd.gf, R,
                                                                sd.c45, G(sd.gab[l + 1]));
     float* tmp = cur;
     cur = nxt;
@@ -906,18 +907,21 @@ __device__ void tail_job(const Job& J, const StreamDesc& sd, float* smem) {
 
 // RC: the Gabor radius the launch is built for (every stream of a launch shares it), or
 // 0 for any radius.  The default radius keeps 8 workgroups per CU.
-template <bool BIG, int RC, bool ONE>
-__global__ __launch_bounds__(SP_BLOCK) void k_pyr(
+// NT_: its threads.  A launch of at most one workgroup per CU (one frame) takes 1024, which run
+// the serial passes of a job in a quarter of the steps: the final launch of a 160x120 step
+// 8.3 -> 6.8 us, a 640x480 frame's 8.0 -> 6.5; with more workgroups 256 keep several on a CU.
+template <bool BIG, int RC, int NT_, bool ONE>
+__global__ __launch_bounds__(NT_) void k_pyr(
     const Job* __restrict__ jobs, const StreamDesc* __restrict__ sds, const StepIO* __restrict__ ios, StepIO io0) {
   __shared__ float smem[BIG ? TAIL_LDS : DOWN_LDS];
   const Job J = jobs[blockIdx.x];
   const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   if (J.kind == JOB_DOWN) {
-    down_job(J, sd, smem);
+    down_job<NT_>(J, sd, smem);
   } else if (J.kind == JOB_GABOR) {
-    gabor_job<RC>(J, sd, smem);
+    gabor_job<RC, NT_>(J, sd, smem);
   } else if (BIG && (J.kind == JOB_TAIL || J.kind == JOB_TAILGAB)) {
-    tail_job<RC>(J, sd, smem);
+    tail_job<RC, NT_>(J, sd, smem);
   }
 }
 
@@ -3149,13 +3153,14 @@ __global__ __launch_bounds__(SP_BLOCK) void k_calib(const float* __restrict__ sr
 static inline hipError_t chk() { return hipGetLastError(); }
 
 // A kernel over the job table, built for one stream (no io table) or for many.
-#define SP_STEP_KERNEL(...)                                                                     \
+#define SP_STEP_KERNEL_B(threads, ...)                                                          \
   do {                                                                                          \
     if (ios)                                                                                    \
-      hipLaunchKernelGGL((__VA_ARGS__, false>), g, b, lds, st, jobs, sds, ios, io);             \
+      hipLaunchKernelGGL((__VA_ARGS__, false>), g, dim3(threads), lds, st, jobs, sds, ios, io); \
     else                                                                                        \
-      hipLaunchKernelGGL((__VA_ARGS__, true>), g, b, lds, st, jobs, sds, ios, io);              \
+      hipLaunchKernelGGL((__VA_ARGS__, true>), g, dim3(threads), lds, st, jobs, sds, ios, io);  \
   } while (0)
+#define SP_STEP_KERNEL(...) SP_STEP_KERNEL_B(SP_BLOCK, __VA_ARGS__)
 
 hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, const StepIO* ios,
                      const StepIO* io0, int flag, const float* aux, hipStream_t st, size_t lds) {
@@ -3173,16 +3178,20 @@ hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, co
     case JOB_FEAT: SP_STEP_KERNEL(k_feat<16, 16); break;
     case JOB_DOWN:   // pyramid launch without tail jobs (DOWN and GABOR jobs)
     case JOB_GABOR:   // flag: the Gabor radius of the launch
-      if (flag == 6)
-        SP_STEP_KERNEL(k_pyr<false, 6);
+      if (flag == 6 && n <= SP_CUS)
+        SP_STEP_KERNEL_B(1024, k_pyr<false, 6, 1024);
+      else if (flag == 6)
+        SP_STEP_KERNEL(k_pyr<false, 6, SP_BLOCK);
       else
-        SP_STEP_KERNEL(k_pyr<false, 0);
+        SP_STEP_KERNEL(k_pyr<false, 0, SP_BLOCK);
       break;
     case JOB_TAIL:
-      if (flag == 6)
-        SP_STEP_KERNEL(k_pyr<true, 6);
+      if (flag == 6 && n <= SP_CUS)
+        SP_STEP_KERNEL_B(1024, k_pyr<true, 6, 1024);
+      else if (flag == 6)
+        SP_STEP_KERNEL(k_pyr<true, 6, SP_BLOCK);
       else
-        SP_STEP_KERNEL(k_pyr<true, 0);
+        SP_STEP_KERNEL(k_pyr<true, 0, SP_BLOCK);
       break;
     case JOB_CSSTATS:
       if (ios)
