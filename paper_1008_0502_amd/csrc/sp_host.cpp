@@ -685,9 +685,9 @@ struct sp_ctx {
   int64_t pa_gen = -1;            // tape generation of the last saliency_backward
   int pa_T = 0;                   // and its clip length
   // colour likelihood
-  GmmState* gmm_state = nullptr;
-  double* gmm_part = nullptr;     // [2 M 10][gmm_tiles] FP64 moments per tile
-  int gmm_tiles = 0;
+  GmmState* gmm_state = nullptr;  // [2]: the mixtures of a fit and of the one before
+  double* gmm_part = nullptr;     // [2][gmm_tiles][2 M 10] FP64 moments per tile, of a pass and the one before
+  int gmm_tile = 0, gmm_tiles = 0;   // pixels of a workgroup, and how many of them
   // loss helper
   float* loss_part = nullptr;
   int loss_nblk = 1024;
@@ -926,9 +926,11 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
     c->S_scratch = b.take<float>((size_t)Hc * Wc);
     if (p->f_mode == 1) c->f_map = b.take<float>(HW);
     if (p->gmm_components > 0) {
-      c->gmm_tiles = (int)((HW + SP_GMM_TILE - 1) / SP_GMM_TILE);
-      c->gmm_state = b.take<GmmState>(1);
-      c->gmm_part = b.take<double>((size_t)2 * p->gmm_components * 10 * c->gmm_tiles);
+      const size_t per_cu = (HW + (size_t)SP_BLOCK * SP_CUS - 1) / ((size_t)SP_BLOCK * SP_CUS);
+      c->gmm_tile = SP_BLOCK * (int)std::min<size_t>(per_cu, SP_GMM_GPX);
+      c->gmm_tiles = (int)((HW + c->gmm_tile - 1) / c->gmm_tile);
+      c->gmm_state = b.take<GmmState>(2);
+      c->gmm_part = b.take<double>((size_t)2 * 2 * p->gmm_components * 10 * c->gmm_tiles);
     }
     if (p->ssm_r > 0) {
       c->ssm[0] = b.take<float>((size_t)Hc * Wc);
@@ -1209,25 +1211,34 @@ int sp_colour_likelihood(sp_ctx* c, const uint8_t* rgb_t, const float* prior, fl
   io.unary = unary_inout;
   io.n = c->g.H * c->g.W;
   io.ntiles = c->gmm_tiles;
+  io.tile = c->gmm_tile;
   io.reg = c->p.gmm_reg;
   const int iters = c->p.gmm_iters;
-  io.part_out = c->gmm_part;
-  io.part_in = c->gmm_part;
-  io.st_prev = c->gmm_state;
-  io.st_next = c->gmm_state;
-  auto launch = [&](int phase, int kind, float* out) -> int {
+  // Every launch that fits reads the moments and the mixtures of the one before and writes the
+  // other of the two buffers.
+  const size_t part_n = (size_t)2 * M * 10 * c->gmm_tiles;
+  const bool fused = c->gmm_tiles <= SP_GMM_FUSE;
+  int moments = 0, mix = 0;   // the buffers last written
+  auto launch = [&](int pass, int fit, int kind, float* out) -> int {
     io.out = out;
-    const hipError_t e = c->prof.timed(c->stream, kind, [&] { return sp_launch_gmm(phase, M, io, c->stream); });
-    if (e != hipSuccess) return fail(SP_EHIP, "colour likelihood launch (phase %d): %s", phase, hipGetErrorString(e));
+    io.part_in = c->gmm_part + (size_t)moments * part_n;
+    io.part_out = c->gmm_part + (size_t)(moments ^ 1) * part_n;
+    io.st_prev = c->gmm_state + mix;
+    io.st_next = c->gmm_state + (mix ^ 1);
+    const hipError_t e = c->prof.timed(c->stream, kind, [&] { return sp_launch_gmm(pass, fit, M, io, c->stream); });
+    if (e != hipSuccess)
+      return fail(SP_EHIP, "colour likelihood launch (pass %d, fit %d): %s", pass, fit, hipGetErrorString(e));
+    if (fit) mix ^= 1;
+    if (pass == 0 || pass == 1) moments ^= 1;
     return SP_OK;
   };
-  int rc = launch(0, JOB_GMM_ACC, nullptr);
-  if (!rc) rc = launch(1, JOB_GMM_FIT, iters == 0 ? gmm_out : nullptr);
-  for (int it = 0; it < iters && !rc; ++it) {
-    rc = launch(2, JOB_GMM_ACC, nullptr);
-    if (!rc) rc = launch(3, JOB_GMM_FIT, it == iters - 1 ? gmm_out : nullptr);
+  int rc = launch(0, 0, JOB_GMM_ACC, nullptr);
+  for (int it = 0; it <= iters && !rc; ++it) {
+    const int pass = it < iters ? 1 : 2, fit = it == 0 ? 1 : 2;
+    float* const out = it == iters ? gmm_out : nullptr;
+    if (!fused) rc = launch(-1, fit, JOB_GMM_FIT, out);
+    if (!rc) rc = launch(pass, fused ? fit : 0, pass == 1 ? JOB_GMM_ACC : JOB_GMM_PSI, fused ? out : nullptr);
   }
-  if (!rc) rc = launch(4, JOB_GMM_PSI, nullptr);
   return rc;
 }
 

@@ -310,7 +310,14 @@ __host__ __device__ constexpr int cg_set1_d(int p) { return 2 + (p & 1); }
 // Colour likelihood of the t-links: per label (0 background, 1 object) a mixture of up to
 // SP_GMM_MAXM Gaussians over RGB in [0, 1].
 #define SP_GMM_MAXM 4
-#define SP_GMM_TILE 1024   // pixels of an accumulation workgroup (4 per thread)
+// Pixels of an accumulation workgroup: SP_BLOCK times as many as keep the launch at one workgroup
+// per CU (two on some of them take twice as long), from 1 to SP_GMM_GPX per thread and label.
+#define SP_GMM_GPX 8
+// Most tiles with the fit inside the next pixel pass: every workgroup reads the moments of all of
+// them (2 M 10 doubles each) from L2, against one workgroup and a launch of its own.  Ten steps with
+// three components, one launch a step against two: 160x120 (75 tiles) 81 against 97 us, 640x480 (240)
+// 116 against 133, 1280x720 (450) 207 against 203, 1920x1080 (1013) 484 against 334.
+#define SP_GMM_FUSE SP_CUS
 struct GmmComp {           // E-step form of one component (FP32)
   float mu[3];             // mean, also the centre of the moments accumulated for it
   float P[6];              // precision: xx, xy, xz, yy, yz, zz
@@ -329,14 +336,14 @@ struct GmmIO {
   const uint8_t* rgb;      // [n][3]
   const float* prior;      // [n] p(A = 1): the object's sample weights (1 - p: the background's)
   const GmmState* st_prev; // mixtures the launch reads (the E-step's; the M-step's centres)
-  GmmState* st_next;       // mixtures a fit stores (may be st_prev: read before written)
-  const double* part_in;   // [values][ntiles] FP64 moments per tile, read by a fit
-  double* part_out;        // [values][ntiles] written by the moment passes
+  GmmState* st_next;       // mixtures a fit stores (not st_prev)
+  const double* part_in;   // [ntiles][values] FP64 moments per tile, read by a fit
+  double* part_out;        // [ntiles][values] written by the moment passes (not part_in)
   float* unary;            // [2][n], psi added in place
   float* out;              // [2][M][10] alpha, mu, cov (xx, xy, xz, yy, yz, zz) or null
   int32_t n, ntiles;
   float reg;               // added to the covariance diagonals
-  int32_t pad;
+  int32_t tile;            // pixels of a workgroup
 };
 
 // Minimum cut of the MRF on the pixel grid: integer residual capacities of the 8 n-links

@@ -45,9 +45,10 @@ hipError_t sp_launch_calib(const float* src, float* dst, size_t n16, int mode, h
 hipError_t sp_noalloc_scratch(void** ptr);
 // Prior of the first frame from manual labels (n pixels).
 hipError_t sp_launch_manual(const uint8_t* labels, float* pnext, float* pout, size_t n, float eps, hipStream_t st);
-// Colour likelihood phases: 0 start moments, 1 start fit, 2 E-step moments, 3 M-step fit,
-// 4 psi added to the unary costs (M = components per label, 1..SP_GMM_MAXM).
-hipError_t sp_launch_gmm(int phase, int M, const GmmIO& io, hipStream_t st);
+// Colour likelihood: pass 0 the start's moments, 1 the E-step's, 2 psi added to the unary costs, -1 no
+// pixels (the fit alone); fit 0 the mixtures of io.st_prev, 1 the start and 2 the M-step from
+// io.part_in, stored in io.st_next (M = components per label, 1..SP_GMM_MAXM).
+hipError_t sp_launch_gmm(int pass, int fit, int M, const GmmIO& io, hipStream_t st);
 // Minimum cut phases: 0 counters + capacities, 1 relabel pass, 2 push / relabel cycles,
 // 3 labels, the flow value and the last pass's counters.
 hipError_t sp_launch_cut(int phase, const CutIO& io, hipStream_t st);
