@@ -92,8 +92,8 @@ __device__ __forceinline__ int label_of() { return __builtin_amdgcn_readfirstlan
 __device__ __forceinline__ uint32_t slot_of() { return threadIdx.x % SP_BLOCK; }
 
 // The workgroup's pixels in LDS: colour in [0, 1] and the prior, loaded once for both labels, all
-// loads in flight together.  The pixel loops below are rolled: a launch finds no instruction of its
-// kernel in the cache, and fetching the code of several pixels costs more than running it.
+// loads in flight together.  The pixel loops below are rolled: unrolled over a thread's pixels they
+// take more registers and are no faster (9.0 against 8.2 us a pass at 640x480).
 template <bool PRIOR>
 struct Staged {
   uint32_t c[GPX / 2][3];
@@ -467,8 +467,8 @@ __device__ __forceinline__ void mixtures(const GmmIO& io, GmmState& S, Put put) 
 }
 
 // The moments of every tile: the start's (EM = false) or the E-step's under the launch's
-// mixtures.  A pass bounded by its chain (pixels, mixtures, E-step, workgroup sum, and the fetch of
-// its code), not by its 7 bytes a pixel: at 640x480 with three components 9.2 us with both labels on
+// mixtures.  A pass bounded by its chain (pixels, mixtures, E-step, workgroup sum), not by its
+// 7 bytes a pixel: at 640x480 with three components 9.2 us with both labels on
 // a thread and four pixels unrolled on 300 workgroups, 6.6 us so; with the fit in the same launch
 // 10.4 us against 6.6 + 5.2 for the two.
 template <int M, bool EM, int FIT>

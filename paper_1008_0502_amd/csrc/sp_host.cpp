@@ -1091,7 +1091,7 @@ int ctx_build_tables(sp_ctx* c) {
     c->dt.push_back(c->jobs.add(JOB_DT, 0, order(v), 1));
     v.clear();
     add_sweep_tiles(v, 0, g);
-    c->bwd.push_back(c->jobs.add(JOB_BWD_NU, g.c_max <= kSweepMax ? g.c_max : 0, v, 1));
+    c->bwd.push_back(c->jobs.add(JOB_BWD_NU, g.c_max <= kSweepMax ? g.c_max : 0, order(v), 1));
     v.clear();
     add_tiles(v, 0, 0, Hc, Wc);
     if (g.c_max > kSweepMax) c->bwd.push_back(c->jobs.add(JOB_BWD_GS, 0, v, 1));
@@ -1954,6 +1954,7 @@ void batch_adjoint_tables(sp_batch* b) {
       add_sweep_tiles(nu, i, g);
       if (cm == 0) add_tiles(gs, i, 0, g.Hl[g.c_max], g.Wl[g.c_max]);
     }
+    if (b->xcd) xcd_order(nu);
     if (!nu.empty()) b->bwd.push_back(b->jobs.add(JOB_BWD_NU, cm, nu, n));
     if (!gs.empty()) b->bwd.push_back(b->jobs.add(JOB_BWD_GS, 0, gs, n));
   }

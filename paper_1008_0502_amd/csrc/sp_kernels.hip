@@ -9,6 +9,8 @@
 #include <stdint.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include <mutex>
 
 #include "sp_internal.h"
@@ -2591,7 +2593,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_bwd_nu(const Job* __restrict__ job
   __shared__ float sh4[4];
   const Job J = jobs[blockIdx.x];
   const StreamDesc& sd = sds[J.stream];
-  const BwdIO& B = bios ? bios[J.stream] : b0;
+  const BwdIO B = bios ? bios[J.stream] : b0;
   const int H = sd.H, W = sd.W, cm = sd.c_max, Hm = sd.Hl[cm], Wm = sd.Wl[cm];
   const bool carry = (B.nu_next != nullptr) && (B.carry != 0.f);
   if (carry) {
@@ -2656,7 +2658,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_bwd_gs(const Job* __restrict__ job
                                                      const BwdIO* __restrict__ bios, BwdIO b0) {
   const Job J = jobs[blockIdx.x];
   const StreamDesc& sd = sds[J.stream];
-  const BwdIO& B = bios ? bios[J.stream] : b0;
+  const BwdIO B = bios ? bios[J.stream] : b0;
   const int H = sd.H, W = sd.W, cm = sd.c_max, Hm = sd.Hl[cm], Wm = sd.Wl[cm];
   const int yy = threadIdx.x / CA_T, xx = threadIdx.x % CA_T;
   const int Y = J.y0 + yy, X = J.x0 + xx;
@@ -2690,8 +2692,9 @@ __global__ __launch_bounds__(SP_BLOCK) void k_bwd_gs(const Job* __restrict__ job
 // 16x16-tile sweep and a gather of 49 taps per c_max pixel.  32x32 tiles: 300 workgroups for one
 // 640x480 stream (16-row tiles stage 1.6 times the pixels they own); at c_max 4 the strip makes
 // the region 2.2 times the tile, so the two launches above stay from there on.
-// Reverse step of 16 streams at 640x480: 76 us in two launches, 36 us here; of one stream
-// 16.9 us, 10.6 us here.
+// Reverse step of 16 streams at 640x480: 76 us in two launches, 28 us here; of one stream
+// 16.9 us, 9.0 us here (36 and 10.4 us with the row pass through LDS, the frame's edge tested per
+// pixel and tiles in no order over the XCDs).
 constexpr int SW_T = SP_SWEEP_T;
 
 // Weights of the transposed clamp-to-edge binomial at output y: w[2 + d] for source y + d
@@ -2709,7 +2712,7 @@ __device__ __forceinline__ void sweep_taps(int y, int n, float (&w)[5]) {
   }
 }
 
-template <int CM>
+template <int CM, bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_bwd_sweep(const Job* __restrict__ jobs,
                                                         const StreamDesc* __restrict__ sds,
                                                         const BwdIO* __restrict__ bios, BwdIO b0) {
@@ -2718,17 +2721,20 @@ __global__ __launch_bounds__(SP_BLOCK) void k_bwd_sweep(const Job* __restrict__ 
   constexpr int NS = N + 4;                       // staged rows of nu_{t+1}
   constexpr int XO = (HL + 2 + 3) & ~3;           // staged columns start at x0 - XO (whole quads)
   constexpr int PW = (XO + SW_T + 2 + 3) & ~3;    // their row stride
-  constexpr int G_ = SP_BLOCK / N;                // a thread keeps one region column and steps G_ rows
-  constexpr int NR = (N + G_ - 1) / G_, NH = (NS + G_ - 1) / G_;
+  constexpr int G_ = SP_BLOCK / N;                // a thread takes one region column and NR rows of it
+  constexpr int NR = (N + G_ - 1) / G_;
+  constexpr int RS = (N + 3) & ~3;                // row stride of the region's values
   constexpr int XT = SW_T / SC, FE = XT + 2;      // c_max pixels of the tile; staged saliency edge
-  __shared__ __align__(16) float reg[NS * PW];    // nu_{t+1}, then the observation's adjoint [N][N]
-  __shared__ float hb[NS * N];                    // its row pass, then the up-sample's row sums [N][XT]
-  __shared__ float Sl[FE * FE];
+  constexpr int NL = G_ * NR + 4 > NS ? G_ * NR + 4 : NS;   // rows read (those past NS for no output)
+  __shared__ __align__(16) float reg[NL * PW];    // nu_{t+1}, then the observation's adjoint [N][RS]
+  __shared__ float hb[N * XT];                    // the up-sample's row sums
+  __shared__ float Sl[FE * FE], Us[FE * RS];      // saliency samples; the same at the region's columns
+  __shared__ float4 rtab[N];                      // per region row: its two rows of Us, the weights
   __shared__ double shd[4];
-  static_assert(NS * PW >= N * N && N >= XT, "reused buffers");
+  static_assert(NL * PW >= N * RS && G_ * NR >= N, "reused buffer, all rows taken");
   const Job J = jobs[blockIdx.x];
-  const StreamDesc& sd = sds[J.stream];
-  const BwdIO& B = bios ? bios[J.stream] : b0;
+  const StreamDesc& sd = sds[ONE ? 0 : J.stream];
+  const BwdIO B = ONE ? b0 : bios[J.stream];   // by value: a reference is read again after every store
   const int H = sd.H, W = sd.W, Hm = sd.Hl[CM], Wm = sd.Wl[CM];
   const gp<const float> nun = G(B.nu_next), grad = G(B.grad), f = G(B.f);
   const bool carry = (B.nu_next != nullptr) && (B.carry != 0.f);
@@ -2765,80 +2771,103 @@ __global__ __launch_bounds__(SP_BLOCK) void k_bwd_sweep(const Job* __restrict__ 
     Sl[i] = *at_bytes(G(B.S), ((uint32_t)clampi(Y0 - 1 + r, 0, Hm - 1) * (uint32_t)Wm +
                                (uint32_t)clampi(X0 - 1 + c, 0, Wm - 1)) * 4u);
   }
-  // the thread's column: its gradients (and f on owned pixels) are requested at once
-  const int g = threadIdx.x / N, j = threadIdx.x - g * N;
-  const int x = J.x0 - HL + j;
-  const bool col = g < G_ && (unsigned)x < (unsigned)W;
-  const uint32_t xc = (uint32_t)clampi(x, 0, W - 1);
+  if ((int)threadIdx.x < N) {
+    const Tap ty = bilinear_tap(clampi(J.y0 - HL + (int)threadIdx.x, 0, H - 1), CM, Hm);
+    rtab[threadIdx.x] = make_float4(__int_as_float((ty.i0 - (Y0 - 1)) * RS), __int_as_float((ty.i1 - (Y0 - 1)) * RS),
+                                    ty.w, 1.f - ty.w);
+  }
+  // the thread's rows of its column: the gradients (and f) are requested at once
+  const int g = threadIdx.x / N, j = threadIdx.x - g * N, r0 = g * NR;
+  const int x = J.x0 - HL + j, ya = J.y0 - HL + r0;
+  const bool act = g < G_;
   float gr[NR], fv[NR];
+  {
+    const uint32_t xc = (uint32_t)clampi(x, 0, W - 1);
 #pragma unroll
-  for (int k = 0; k < NR; ++k) {
-    const uint32_t ob = ((uint32_t)clampi(J.y0 - HL + g + G_ * k, 0, H - 1) * (uint32_t)W + xc) * 4u;
-    gr[k] = *at_bytes(grad, ob);
-    fv[k] = B.f ? *at_bytes(f, ob) : 0.f;
+    for (int k = 0; k < NR; ++k) {
+      const uint32_t ob = ((uint32_t)clampi(ya + k, 0, H - 1) * (uint32_t)W + xc) * 4u;
+      gr[k] = *at_bytes(grad, ob);
+      fv[k] = B.f ? *at_bytes(f, ob) : 0.f;
+    }
   }
   const float m = G(B.ms)[0];
+  // Tiles whose region and its taps lie inside the frame and off its border ring take the plain
+  // binomial and no test per pixel.
+  const int off = max(2, sd.border);
+  const bool inner = J.th == SW_T && J.tw == SW_T && J.y0 - HL >= off && J.y0 + SW_T + off <= H &&
+                     J.x0 - HL >= off && J.x0 + SW_T + off <= W;
   lds_wait();
   __syncthreads();
-  if (carry) {
-    if (g < G_) {
-      float w[5];
-      sweep_taps(x, W, w);
-#pragma unroll
-      for (int k = 0; k < NH; ++k) {
-        const int r = g + G_ * k;
-        if (r < NS) {
-          const float* p = reg + r * PW + (XO - HL) + j;
-          float acc = 0.f;
-#pragma unroll
-          for (int d = 0; d < 5; ++d) acc += p[d - 2] * w[d];
-          hb[r * N + j] = acc;
-        }
-      }
-    }
-    __syncthreads();
-  }
   const bool flat = !(m > sd.flat_tol);
-  const float rm = 1.f / m;
+  const float rm = 1.f / m, eps = sd.eps, hi = 1.f - sd.eps;
   const gp<float> nu_out = G(B.nu_out);
   double contrib = 0.0;
-  const Tap tx = bilinear_tap(min(max(x, 0), W - 1), CM, Wm);
+  auto body = [&](auto in_c) {
+    constexpr bool IN = decltype(in_c)::value;
+    // the row pass of the blur for the thread's rows and the four after stays in registers
+    float hv[NR + 4];
+    if (carry && act) {
+      float w[5] = {kB0, kB1, kB2, kB1, kB0};
+      if (!IN) sweep_taps(x, W, w);
+      const float* p = reg + r0 * PW + (XO - HL) + j;
 #pragma unroll
-  for (int k = 0; k < NR; ++k) {
-    const int r = g + G_ * k, y = J.y0 - HL + r;
-    if (g >= G_ || r >= N) continue;
-    float gu = 0.f;
-    if (col && (unsigned)y < (unsigned)H) {
-      float nu = gr[k];
-      if (carry) {
-        float w[5];
-        sweep_taps(y, H, w);
+      for (int k = 0; k < NR + 4; ++k) {
         float acc = 0.f;
 #pragma unroll
-        for (int d = 0; d < 5; ++d) acc += hb[(r + d) * N + j] * w[d];
-        nu += B.carry * acc;
-      }
-      const bool ring = on_border(y, x, H, W, sd.border);
-      const float nut = ring ? 0.f : nu;
-      float q = 0.5f;
-      if (!flat) {
-        const Tap ty = bilinear_tap(y, CM, Hm);
-        const float* r0 = Sl + (ty.i0 - (Y0 - 1)) * FE - (X0 - 1);
-        const float* r1 = Sl + (ty.i1 - (Y0 - 1)) * FE - (X0 - 1);
-        const float top = (1.f - tx.w) * r0[tx.i0] + tx.w * r0[tx.i1];
-        const float bot = (1.f - tx.w) * r1[tx.i0] + tx.w * r1[tx.i1];
-        const float u = ((1.f - ty.w) * top + ty.w * bot) * rm;
-        q = fminf(fmaxf(u, sd.eps), 1.f - sd.eps);
-        if (u > sd.eps && u < 1.f - sd.eps && !ring) gu = B.K * nut;
-      }
-      if (ring) q = sd.eps;
-      if (r >= HL && j >= HL) {   // owned
-        if (B.f) contrib += (double)(nut * (q - fv[k]));
-        *at_bytes(nu_out, ((uint32_t)y * (uint32_t)W + (uint32_t)x) * 4u) = nut;
+        for (int d = 0; d < 5; ++d) acc += p[k * PW + d - 2] * w[d];
+        hv[k] = acc;
       }
     }
-    reg[r * N + j] = gu;   // nu_{t+1} is no longer read
-  }
+    if (act) {
+      const Tap tx = bilinear_tap(IN ? x : clampi(x, 0, W - 1), CM, Wm);
+      const float* s0 = Sl + tx.i0 - (X0 - 1);
+      const float* s1 = Sl + tx.i1 - (X0 - 1);
+      for (int i = g; i < FE; i += G_) Us[i * RS + j] = (1.f - tx.w) * s0[i * FE] + tx.w * s1[i * FE];
+    }
+    __syncthreads();
+    if (act) {
+      const bool col = IN || (unsigned)x < (unsigned)W;
+      const bool xring = !IN && (x < sd.border || x >= W - sd.border);
+      const uint32_t ob0 = ((uint32_t)ya * (uint32_t)W + (uint32_t)x) * 4u;
+#pragma unroll
+      for (int k = 0; k < NR; ++k) {
+        const int r = r0 + k, y = ya + k;
+        if (G_ * NR > N && r >= N) continue;
+        float gu = 0.f;
+        if (IN || (col && (unsigned)y < (unsigned)H)) {
+          float nu = gr[k];
+          if (carry) {
+            float w[5] = {kB0, kB1, kB2, kB1, kB0};
+            if (!IN) sweep_taps(y, H, w);
+            float acc = 0.f;
+#pragma unroll
+            for (int d = 0; d < 5; ++d) acc += hv[k + d] * w[d];
+            nu += B.carry * acc;
+          }
+          const bool ring = !IN && (xring || y < sd.border || y >= H - sd.border);
+          const float nut = ring ? 0.f : nu;
+          float q = 0.5f;
+          if (!flat) {
+            const float4 rt = rtab[r];
+            const float top = Us[__float_as_int(rt.x) + j], bot = Us[__float_as_int(rt.y) + j];
+            const float u = (rt.w * top + rt.z * bot) * rm;
+            q = fminf(fmaxf(u, eps), hi);
+            if (u > eps && u < hi && !ring) gu = B.K * nut;
+          }
+          if (ring) q = eps;
+          if (r >= HL && j >= HL) {   // owned
+            if (B.f) contrib += (double)(nut * (q - fv[k]));
+            *at_bytes(nu_out, ob0 + (uint32_t)(k * W) * 4u) = nut;
+          }
+        }
+        reg[r * RS + j] = gu;   // nu_{t+1} is no longer read
+      }
+    }
+  };
+  if (inner)
+    body(std::true_type{});
+  else
+    body(std::false_type{});
   contrib = wave_sum_d(contrib);
   if (lane_id() == 0) shd[wave_id()] = contrib;
   __syncthreads();
@@ -2847,7 +2876,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_bwd_sweep(const Job* __restrict__ 
   for (int i = threadIdx.x; i < N * XT; i += SP_BLOCK) {
     const int r = i / XT, X = i - r * XT;
     const bool last = X0 + X == Wm - 1;
-    const float* p = reg + r * N + SC * X;
+    const float* p = reg + r * RS + SC * X;
     float acc = 0.f;
 #pragma unroll
     for (int k = 0; k < 2 * SC - 1; ++k) {
@@ -3284,14 +3313,21 @@ hipError_t sp_launch_bwd(int kind, int flag, const Job* jobs, int n, const Strea
   if (n <= 0) return hipSuccess;
   BwdIO z{};
   const BwdIO& b = b0 ? *b0 : z;
+#define SP_BWD_SWEEP(CM)                                                                                     \
+  do {                                                                                                       \
+    if (bios)                                                                                                \
+      hipLaunchKernelGGL((k_bwd_sweep<CM, false>), dim3(n), dim3(SP_BLOCK), 0, st, jobs, sds, bios, b);      \
+    else                                                                                                     \
+      hipLaunchKernelGGL((k_bwd_sweep<CM, true>), dim3(n), dim3(SP_BLOCK), 0, st, jobs, sds, bios, b);       \
+  } while (0)
   switch (kind) {
     case JOB_BWD_NU:   // flag: c_max of every stream of a one-launch reverse step, 0: the sweep alone
       if (flag == 1)
-        hipLaunchKernelGGL(k_bwd_sweep<1>, dim3(n), dim3(SP_BLOCK), 0, st, jobs, sds, bios, b);
+        SP_BWD_SWEEP(1);
       else if (flag == 2)
-        hipLaunchKernelGGL(k_bwd_sweep<2>, dim3(n), dim3(SP_BLOCK), 0, st, jobs, sds, bios, b);
+        SP_BWD_SWEEP(2);
       else if (flag == 3)
-        hipLaunchKernelGGL(k_bwd_sweep<3>, dim3(n), dim3(SP_BLOCK), 0, st, jobs, sds, bios, b);
+        SP_BWD_SWEEP(3);
       else
         hipLaunchKernelGGL(k_bwd_nu, dim3(n), dim3(SP_BLOCK), 0, st, jobs, sds, bios, b);
       break;
