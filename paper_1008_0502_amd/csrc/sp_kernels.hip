@@ -2943,61 +2943,107 @@ __global__ __launch_bounds__(SP_BLOCK) void k_consp_dot(const Job* __restrict__ 
 // variances Pd are shared.
 // One step t (blockIdx.x) of stream blockIdx.y: dL/dK_t from its tile partials, and the
 // step's share of dL/dw (zero-weight steps, where max S is flat, have none), each sum in a
-// fixed order.  The steps are independent, so they run side by side.
+// fixed order.  The steps are independent, so they run side by side.  Latency-bound: a thread sums
+// one weight's partials (the block is a multiple of the weights, which lie together per tile) and
+// all nine sums meet in one barrier: 10.0 -> 5.0 us for 120 steps at 640x480 against a block
+// reduction for each.
 __global__ __launch_bounds__(SP_BLOCK) void k_bwd_step(const BwdFin* __restrict__ tab, BwdFin one, int T,
                                                        float flat_tol) {
-  __shared__ double sh256[SP_BLOCK];
+  static_assert(SP_NCH == 8 && SP_BLOCK % SP_NCH == 0, "a thread keeps its weight");
+  __shared__ double red[4][SP_NCH + 1], A[SP_NCH];
   const BwdFin F = tab ? tab[blockIdx.y] : one;
-  const int t = blockIdx.x;
-  double s = 0.0;
-  for (int i = threadIdx.x; i < F.n_lvl0_tiles; i += SP_BLOCK) s += (double)F.gk_part[(size_t)t * F.n_lvl0_tiles + i];
-  s = block_sum_d(s, sh256);
-  if (threadIdx.x == 0) F.gK[t] = s;
-  double A[SP_NCH];
-  for (int k = 0; k < SP_NCH; ++k) {
-    double a = 0.0;
-    for (int i = threadIdx.x; i < F.n_cmax_tiles; i += SP_BLOCK)
-      a += (double)F.dot_part[((size_t)t * F.n_cmax_tiles + i) * SP_NCH + k];
-    A[k] = block_sum_d(a, sh256);
+  const int t = blockIdx.x, lane = lane_id(), w = wave_id();
+  const gp<const float> gk = G((const float*)F.gk_part) + (size_t)t * F.n_lvl0_tiles;
+  const gp<const float> dp = G((const float*)F.dot_part) + (size_t)t * F.n_cmax_tiles * SP_NCH;
+  double s = 0.0, a = 0.0;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < F.n_lvl0_tiles; i += SP_BLOCK) s += (double)gk[i];
+#pragma unroll 4
+  for (int i = threadIdx.x; i < F.n_cmax_tiles * SP_NCH; i += SP_BLOCK) a += (double)dp[i];
+  s = wave_sum_d(s);
+#pragma unroll
+  for (int d = SP_NCH; d < 64; d *= 2) a += __shfl_xor(a, d);
+  if (lane < SP_NCH) red[w][lane] = a;
+  if (lane == 0) red[w][SP_NCH] = s;
+  __syncthreads();
+  if ((int)threadIdx.x <= SP_NCH) {
+    const double v = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+    if (threadIdx.x == SP_NCH)
+      F.gK[t] = v;
+    else
+      A[threadIdx.x] = v;
   }
+  __syncthreads();
   const double m = (double)F.ms[2 * t];
-  if (threadIdx.x == 0 && m > (double)flat_tol) {
+  if ((int)threadIdx.x < SP_NCH && m > (double)flat_tol) {
     double Bs = 0.0;
     for (int k = 0; k < SP_NCH; ++k) Bs += (double)F.w[k] * A[k];
-    double* gw = F.gK + T + (size_t)t * SP_NCH;
-    for (int k = 0; k < SP_NCH; ++k) gw[k] = A[k] / m - (double)F.cx[(size_t)t * SP_NCH + k] * Bs / (m * m);
+    const int k = threadIdx.x;
+    F.gK[T + (size_t)t * SP_NCH + k] = A[k] / m - (double)F.cx[(size_t)t * SP_NCH + k] * Bs / (m * m);
   }
 }
 
 // Per stream (blockIdx.x): dL/dw as the sum of the steps' shares in step order (a thread
 // per weight), and the reverse sweep of the scalar gain recursion for dL/dQ and dL/dR
-// (FP64, one thread).
-__global__ void k_bwd_final(const BwdFin* __restrict__ tab, BwdFin one, int T, const double* __restrict__ Kd,
-                            const double* __restrict__ Pd, double Q, double R, float flat_tol) {
+// (FP64, one thread).  Both are serial, so what they read is staged FC steps at a time, with the
+// recursion's factors (a division each) formed beside it: for 120 steps 54 -> 7.3 us against a
+// read and a division in every step of the chain.
+constexpr int BF_FC = 256;
+__global__ __launch_bounds__(SP_BLOCK) void k_bwd_final(const BwdFin* __restrict__ tab, BwdFin one, int T,
+                                                        const double* __restrict__ Kd, const double* __restrict__ Pd,
+                                                        double Q, double R, float flat_tol) {
+  __shared__ double gk[BF_FC], kd[BF_FC], cq[BF_FC], cr[BF_FC], sw[BF_FC][SP_NCH];
+  static_assert(BF_FC == SP_BLOCK, "a thread stages one step");
   const BwdFin F = tab ? tab[blockIdx.x] : one;
-  if ((int)threadIdx.x < SP_NCH) {   // thread k: dL/dw_k over the steps in order
-    const int k = threadIdx.x;
-    double gw = 0.0;
-    for (int t = 0; t < T; ++t)
-      if ((double)F.ms[2 * t] > (double)flat_tol) gw += F.gK[T + (size_t)t * SP_NCH + k];
-    F.grad_w[k] = (float)gw;
+  const gp<const double> gK = G((const double*)F.gK);
+  const gp<const float> ms = G((const float*)F.ms);
+  const int w = wave_id(), lane = lane_id(), nc = (T + BF_FC - 1) / BF_FC;
+  double gw = 0.0, gQ = 0.0, gR = 0.0, gP = 0.0;
+  for (int c = 0; c < nc; ++c) {
+    const int r0 = (nc - 1 - c) * BF_FC, rn = min(BF_FC, T - r0);   // the recursion runs backward
+    const int w0 = c * BF_FC, wn = min(BF_FC, T - w0);
+    if ((int)threadIdx.x < rn) {
+      const int t = r0 + threadIdx.x;
+      gk[threadIdx.x] = gK[t];
+      if (t > 0) {
+        const double a = Pd[t - 1] + Q, den = (a + R) * (a + R);
+        kd[threadIdx.x] = Kd[t];
+        cq[threadIdx.x] = R / den;
+        cr[threadIdx.x] = a / den;
+      }
+    }
+#pragma unroll
+    for (int i = threadIdx.x; i < BF_FC * SP_NCH; i += SP_BLOCK) {
+      const int t = i / SP_NCH;
+      double v = 0.0;
+      if (t < wn) {
+        const double x = gK[T + (size_t)w0 * SP_NCH + i];
+        v = (double)ms[2 * (w0 + t)] > (double)flat_tol ? x : 0.0;
+      }
+      sw[t][i % SP_NCH] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll 4
+      for (int i = rn - 1; i >= (r0 == 0 ? 1 : 0); --i) {
+        const double g = gk[i] + R * gP;
+        gR += kd[i] * gP;
+        gR -= g * cr[i];
+        gP = g * cq[i];
+        gQ += gP;
+      }
+    } else if (w == 1 && lane < SP_NCH) {
+#pragma unroll 8
+      for (int i = 0; i < wn; ++i) gw += sw[i][lane];
+    }
+    __syncthreads();
   }
   if (threadIdx.x == 0) {
-    double gQ = 0.0, gR = 0.0, gP = 0.0;
-    for (int t = T - 1; t >= 1; --t) {
-      const double g = F.gK[t] + R * gP;
-      gR += Kd[t] * gP;
-      const double a = Pd[t - 1] + Q;
-      const double den = (a + R) * (a + R);
-      const double ga = g * R / den;
-      gR -= g * a / den;
-      gQ += ga;
-      gP = ga;
-    }
     gR += gP;
     *F.grad_q = (float)gQ;
     *F.grad_r = (float)gR;
   }
+  if (w == 1 && lane < SP_NCH) F.grad_w[lane] = (float)gw;
 }
 
 // ---------------------------------------------------------------- masked MSE loss helper
@@ -3359,7 +3405,7 @@ hipError_t sp_launch_bwd_final(const BwdFin* tab, const BwdFin* one, int n_strea
   hipLaunchKernelGGL(k_bwd_step, dim3(T, n_streams), dim3(SP_BLOCK), 0, st, tab, o, T, flat_tol);
   hipError_t e = chk();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_bwd_final, dim3(n_streams), dim3(64), 0, st, tab, o, T, Kd, Pd, Q, R, flat_tol);
+  hipLaunchKernelGGL(k_bwd_final, dim3(n_streams), dim3(SP_BLOCK), 0, st, tab, o, T, Kd, Pd, Q, R, flat_tol);
   return chk();
 }
 
