@@ -4,7 +4,7 @@
 // The forward maps of up to SP_PA_SLOTS frames are recomputed side by side by the forward
 // kernels first (the across-scale sums come from the tape), and every pass here runs over all of
 // them (blockIdx.z = frame slot): one 640x480 frame's passes were about 30 dependent launches
-// of 2 to 37 us, 206 us a frame; eight frames at once take 38 us a frame.  Every pass
+// of 2 to 37 us, 206 us a frame; eight frames at once take 31 us a frame.  Every pass
 // here gathers: one thread per output element, each output a fixed-order sum over the
 // inputs that depend on it, so results do not depend on scheduling.  Non-differentiable
 // points follow one convention: the global minimum and maximum and each 8x8 block maximum
@@ -29,6 +29,9 @@ namespace {
 
 constexpr int TILE = SP_PA_TILE;             // elements of a workgroup of the elementwise passes
 constexpr int PER = TILE / SP_BLOCK;
+
+typedef float Quad __attribute__((ext_vector_type(4)));   // a 16-byte access of global memory
+typedef float Pair __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float kb(int i) {   // i in -2..2
   return i == 0 ? 0.375f : ((i == 1 || i == -1) ? 0.25f : 0.0625f);
@@ -369,19 +372,25 @@ __device__ __forceinline__ float blur_w(int yo, int yp, int n) {
 
 // Transpose of one pyramid step at fine rows 2q, 2q+1 and columns 2r, 2r+1: coarse rows and
 // columns q - 1 .. q + 1 reach them.  The nine coarse values of one channel serve the four
-// outputs; the weights come from wy, wx [2][3] (zero outside the coarse level).
+// outputs; the weights come from wy, wx [2][3] (zero outside the coarse level).  A wavefront
+// wholly off the levels' borders has the same weights in every lane, constants then: the weights
+// and the tests for zero were most of the instructions.
 struct QuadT {
   float wy[2][3], wx[2][3];
   uint32_t o[3][3];   // clamped element offsets
+  bool inner;         // uniform over the wavefront
   __device__ __forceinline__ QuadT(int q, int r, int h, int w, int hb, int wb) {
+    inner = __all(q >= 2 && r >= 2 && q + 2 < hb && r + 2 < wb);
+    if (!inner) {
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+      for (int a = 0; a < 2; ++a)
 #pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        const int y2 = q - 1 + b, x2 = r - 1 + b;
-        wy[a][b] = (y2 >= 0 && y2 < hb) ? blur_w(2 * q + a, 2 * y2, h) : 0.f;
-        wx[a][b] = (x2 >= 0 && x2 < wb) ? blur_w(2 * r + a, 2 * x2, w) : 0.f;
-      }
+        for (int b = 0; b < 3; ++b) {
+          const int y2 = q - 1 + b, x2 = r - 1 + b;
+          wy[a][b] = (y2 >= 0 && y2 < hb) ? blur_w(2 * q + a, 2 * y2, h) : 0.f;
+          wx[a][b] = (x2 >= 0 && x2 < wb) ? blur_w(2 * r + a, 2 * x2, w) : 0.f;
+        }
+    }
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
@@ -396,6 +405,28 @@ struct QuadT {
   }
   // zero weights are skipped, not multiplied: they would turn an infinite gradient into NaN
   __device__ __forceinline__ void apply(const float (&v)[3][3], float (&out)[2][2]) const {
+    if (inner) {
+      // fine position 2q hears kb(2), kb(0), kb(2) of the three, 2q + 1 the last two's kb(1)
+      float e[3], f[3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        e[i] = kb(2) * v[i][0];
+        e[i] += kb(0) * v[i][1];
+        e[i] += kb(2) * v[i][2];
+        f[i] = kb(1) * v[i][1];
+        f[i] += kb(1) * v[i][2];
+      }
+      auto col = [](const float (&c)[3], float& top, float& bot) {
+        top = kb(2) * c[0];
+        top += kb(0) * c[1];
+        top += kb(2) * c[2];
+        bot = kb(1) * c[1];
+        bot += kb(1) * c[2];
+      };
+      col(e, out[0][0], out[1][0]);
+      col(f, out[0][1], out[1][1]);
+      return;
+    }
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -460,6 +491,41 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_csmap(PaDesc A, const StreamDes
   const gp<const float> a = G(chan_ptr(sd, k, c)), b = G(chan_ptr(sd, k, s));
   const gp<float> out = G(slot(A.D[p], A, z) + (size_t)k * n);
   float mn = INFINITY, mx = -INFINITY, am = 0.f;
+  // Four elements of a row a thread where rows are whole aligned quads and d >= 2, so that the four
+  // share the rows and columns they sample: one load and store of the map for four, and four
+  // surround values for sixteen (31 -> 23 us for eight 640x480 frames).
+  const bool quad = (w & 3) == 0 && d >= 2 && ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
+  if (quad) {
+    static_assert(PER == 4, "a quad per thread");
+    const int i = base + 4 * (int)threadIdx.x;
+    if (i < n) {
+      const int y = i / w, x = i - y * w;
+      int y0, y1, x0[4], x1[4];
+      float wy, wx[4];
+      tap(y, d, hb, y0, y1, wy);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) tap(x + q, d, wb, x0[q], x1[q], wx[q]);
+      // the four positions lie between the same two samples
+      const float b00 = b[y0 * wb + x0[0]], b01 = b[y0 * wb + x1[0]];
+      const float b10 = b[y1 * wb + x0[0]], b11 = b[y1 * wb + x1[0]];
+      const Quad X4 = *(gp<const Quad>)(a + i);
+      const float X[4] = {X4.x, X4.y, X4.z, X4.w};
+      float D[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float top = (1.f - wx[q]) * b00 + wx[q] * b01;
+        const float bot = (1.f - wx[q]) * b10 + wx[q] * b11;
+        D[q] = X[q] - ((1.f - wy) * top + wy * bot);
+        mn = fminf(mn, fabsf(D[q]));
+        mx = fmaxf(mx, fabsf(D[q]));
+        am = fmaxf(am, fabsf(X[q]));
+        if (i + q < hb * wb) am = fmaxf(am, fabsf(b[i + q]));
+      }
+      *(gp<Quad>)(out + i) = Quad{D[0], D[1], D[2], D[3]};
+    }
+    store_mm(mn, mx, am, slot(A.mm, A, z) + (size_t)(SP_NCH + blockIdx.y) * A.mm_n + blockIdx.x, sh);
+    return;
+  }
   Walk2 wk(base + threadIdx.x, w);
 #pragma unroll
   for (int q = 0; q < PER; ++q, wk.next()) {
@@ -493,6 +559,43 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_csadj(PaDesc A, const StreamDes
   const StreamDesc& sd = sds[z];
   const int w = sd.Wl[c], n = sd.Hl[c] * w, base = blockIdx.x * TILE, nbx = (w + 7) >> 3;
   if (base >= n) return;   // uniform
+  const gp<float> out = G(slot(A.gX[c], A, z) + (size_t)k * n);
+  // Four elements of a row a thread where rows are whole aligned quads: they lie in one 8x8 block,
+  // whose position is read once, and every other access is 16 bytes (50 -> 23 us for eight 640x480
+  // frames; 170 MB, 33 us from memory, part of which stays on the chip).
+  if ((w & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
+    static_assert(PER == 4, "a quad per thread");
+    const int i = base + 4 * (int)threadIdx.x;
+    if (i >= n) return;
+    const int y = i / w, x = i - y * w;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int p = 0; p < sd.n_pairs; ++p) {
+      if (sd.pc[p] != c) continue;
+      const MapView M = map_view(A, sd, nullptr, SP_NCH * (1 + p) + k, z);
+      const float* sc = slot(A.sc, A, z) + (size_t)M.m * SP_PA_SC;
+      const gp<float> D = G(slot(A.D[p], A, z) + (size_t)k * n);
+      const int bp = G((const int32_t*)slot(A.bpos, A, z))[(size_t)M.m * A.nb_n + (uint32_t)((y >> 3) * nbx + (x >> 3))];
+      const Quad g4 = *(gp<const Quad>)(M.g + i), d4 = *(gp<const Quad>)(D + i);
+      const float g[4] = {g4.x, g4.y, g4.z, g4.w}, v[4] = {d4.x, d4.y, d4.z, d4.w};
+      const float band = kSignBand * sc[7], s0 = sc[0], s1 = sc[1], s2 = sc[2], s3 = sc[3];
+      const int jn = __float_as_int(sc[4]), jx = __float_as_int(sc[5]);
+      const bool flat = sc[6] != 0.f;
+      float gd[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float gf = g[q] * M.gs * s0;
+        if (bp == i + q) gf += s1;
+        if (jn == i + q) gf += s2;
+        if (jx == i + q) gf += s3;
+        gf = flat ? 0.f : gf;
+        gd[q] = v[q] > band ? gf : (v[q] < -band ? -gf : 0.f);
+        acc[q] += gd[q];
+      }
+      *(gp<Quad>)(D + i) = Quad{gd[0], gd[1], gd[2], gd[3]};
+    }
+    *(gp<Quad>)(out + i) = Quad{acc[0], acc[1], acc[2], acc[3]};
+    return;
+  }
   float acc[PER];
 #pragma unroll
   for (int q = 0; q < PER; ++q) acc[q] = 0.f;
@@ -515,7 +618,6 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_csadj(PaDesc A, const StreamDes
       }
     }
   }
-  const gp<float> out = G(slot(A.gX[c], A, z) + (size_t)k * n);
 #pragma unroll
   for (int q = 0; q < PER; ++q) {
     const int i = base + q * SP_BLOCK + threadIdx.x;
@@ -526,52 +628,77 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_csadj(PaDesc A, const StreamDes
 // dL/dX(s) of surround level A.sl[blockIdx.y / 8]: up^T(-gD) of every pair with that
 // surround, added to the level's centre part when it has one.  A level-s element gathers the
 // level-c elements xs 2^d + k, |k| < 2^d, weight (2^d - |k|) / 2^d (1 beyond the last sample).
-// Sixteen lanes (one DPP row) per level-s element: lane j takes the window's rows j, j + 16,
-// ..., each as the weighted sum of its columns, and the row adds the lanes' sums in a fixed order.
-constexpr int UPT_L = 16;   // lanes per level-s element
+// Eight lanes per level-s element: lane j takes the window's rows j, j + 8, ..., each as the
+// weighted sum of its columns (16 bytes a load where rows allow), and the lanes' sums are added in a
+// fixed order.  A workgroup takes 128 elements: with sixteen elements and sixteen lanes each the
+// launch of eight 640x480 frames was 57600 workgroups and 54 us, 41 us here.
+static_assert(SP_BLOCK % 64 == 0, "whole wavefronts");
+constexpr int UPT_L = 8;    // lanes per level-s element
+constexpr int UPT_E = 128;  // level-s elements of a workgroup
 __global__ __launch_bounds__(SP_BLOCK) void k_pa_up_t(PaDesc A, const StreamDesc* __restrict__ sds) {
   const int z = blockIdx.z, s = A.sl[blockIdx.y >> 3], ch = blockIdx.y & 7;
   const StreamDesc& sd = sds[z];
   const int hb = sd.Hl[s], wb = sd.Wl[s];
-  const int e0 = blockIdx.x * (SP_BLOCK / UPT_L);
+  const int e0 = blockIdx.x * UPT_E;
   if (e0 >= hb * wb) return;   // uniform
-  const int e = e0 + (int)(threadIdx.x / UPT_L);
-  const int j = threadIdx.x & (UPT_L - 1);
-  const bool valid = e < hb * wb;   // every lane stays for the row's sum
-  const int i = valid ? e : 0;
-  const int ys = i / wb, xs = i - ys * wb;
+  // neighbouring lanes take neighbouring elements of the same window row, which lie in the same
+  // cache lines; lanes 8 apart the rows
+  const int j = lane_id() >> 3, own = wave_id() * (64 / UPT_L) + (lane_id() & 7);
   const gp<float> out = G(slot(A.gX[s], A, z) + (size_t)ch * hb * wb);
-  float tot = valid && j == 0 && ((A.centres >> s) & 1u) ? out[e] : 0.f;
-  for (int p = 0; p < sd.n_pairs; ++p) {
-    if (sd.ps[p] != s) continue;
-    const int c = sd.pc[p], d = s - c, st = 1 << d, ha = sd.Hl[c], wa = sd.Wl[c];
-    const float inv = __int_as_float((127 - d) << 23);   // 2^-d
-    const gp<const float> a = G((const float*)slot(A.D[p], A, z) + (size_t)ch * ha * wa);
-    const int xc = xs * st, x_lo = max(0, xc - st + 1), x_hi = min(wa - 1, xc + st - 1);
-    float acc = 0.f;
-    if (valid)
-      for (int ky = j - st + 1; ky < st; ky += UPT_L) {
-        const int y = ys * st + ky;
-        if (y < 0 || y >= ha) continue;
-        const float ay = ys == hb - 1 && ky > 0 ? 1.f : (float)(st - abs(ky)) * inv;
-        const gp<const float> row = a + (uint32_t)y * (uint32_t)wa;
-        float r = 0.f;
+  const bool centre = (A.centres >> s) & 1u;
+#pragma unroll 1
+  for (int b = e0; b < min(e0 + UPT_E, hb * wb); b += SP_BLOCK / UPT_L) {
+    const int e = b + own;
+    const bool valid = e < hb * wb;   // every lane stays for the sum
+    const int i = valid ? e : 0;
+    const int ys = i / wb, xs = i - ys * wb;
+    float tot = valid && j == 0 && centre ? out[e] : 0.f;
+    for (int p = 0; p < sd.n_pairs; ++p) {
+      if (sd.ps[p] != s) continue;
+      const int c = sd.pc[p], d = s - c, st = 1 << d, ha = sd.Hl[c], wa = sd.Wl[c];
+      const float inv = __int_as_float((127 - d) << 23);   // 2^-d
+      const gp<const float> a = G((const float*)slot(A.D[p], A, z) + (size_t)ch * ha * wa);
+      const bool quad = st >= 4 && (wa & 3) == 0 && (reinterpret_cast<uintptr_t>(a) & 15) == 0;   // uniform
+      const int xc = xs * st, x_lo = max(0, xc - st + 1), x_hi = min(wa - 1, xc + st - 1);
+      float acc = 0.f;
+      if (valid)
+        for (int ky = j - st + 1; ky < st; ky += UPT_L) {
+          const int y = ys * st + ky;
+          if (y < 0 || y >= ha) continue;
+          const float ay = ys == hb - 1 && ky > 0 ? 1.f : (float)(st - abs(ky)) * inv;
+          const gp<const float> row = a + (uint32_t)y * (uint32_t)wa;
+          float r = 0.f;
+          if (quad) {   // whole quads of columns from xc - st on; column xc - st itself is not in the window
 #pragma unroll 4
-        for (int x = x_lo; x <= x_hi; ++x) {
-          const int kx = x - xc;
-          const float ax = xs == wb - 1 && kx > 0 ? 1.f : (float)(st - abs(kx)) * inv;
-          r += ax * row[x];
+            for (int x = xc - st; x < xc + st; x += 4) {
+              if (x < 0 || x >= wa) continue;
+              const Quad v4 = *(gp<const Quad>)(row + x);
+              const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                const int kx = x + q - xc;
+                const float ax = xs == wb - 1 && kx > 0 ? 1.f : (float)(st - abs(kx)) * inv;
+                if (q > 0 || kx > -st) r += ax * v[q];
+              }
+            }
+          } else {
+#pragma unroll 4
+            for (int x = x_lo; x <= x_hi; ++x) {
+              const int kx = x - xc;
+              const float ax = xs == wb - 1 && kx > 0 ? 1.f : (float)(st - abs(kx)) * inv;
+              r += ax * row[x];
+            }
+          }
+          acc += ay * r;
         }
-        acc += ay * r;
-      }
-    // the sixteen lanes' sums: pairs, quads, halves, the row (every lane ends with the total)
-    acc += dpp_f<0xB1>(acc);
-    acc += dpp_f<0x4E>(acc);
-    acc += dpp_f<0x141>(acc);
-    acc += dpp_f<0x140>(acc);
-    tot -= acc;
+      // the eight lanes' sums: pairs, quads, halves (every lane ends with the total)
+      acc += __shfl_xor(acc, 8);
+      acc += __shfl_xor(acc, 16);
+      acc += __shfl_xor(acc, 32);
+      tot -= acc;
+    }
+    if (valid && j == 0) out[e] = tot;
   }
-  if (valid && j == 0) out[e] = tot;
 }
 
 // dL/dI(l) += sum over the four orientations of the clamped Gabor correlation's transpose.
@@ -582,7 +709,8 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_up_t(PaDesc A, const StreamDesc
 // gc gc -+ gs gs - c45 g g), so with P = gO45 + gO135 and Q = gO135 - gO45
 //   E = H[gm] V[g] gO0 + H[g] (V[gm] gO90 - c45 V[g] P) + H[gc] V[gc] P + H[gs] V[gs] Q:
 // 117 multiply-adds per position instead of the 676 of four 13x13 kernels, whose LDS reads
-// (two 16-byte reads a tap) bound the launch: 37 us for one 640x480 frame, 38 us for eight of them here.
+// (two 16-byte reads a tap) bound the launch: 37 us for one 640x480 frame, 33 us for eight of them here (38 with
+// one output a thread and the staging loads waited for one at a time).
 // One 16x16 tile of p per workgroup: gO0, gO90, P and Q of the tile plus twice the radius
 // interleaved in LDS, the vertical pass over the rows of q the tile needs (its own, and the
 // outside strips of a tile on the border), the horizontal pass, then the fold.
@@ -592,8 +720,9 @@ constexpr int GT = 16;
 template <int RC>
 __global__ __launch_bounds__(SP_BLOCK) void k_pa_gabor_t(PaDesc A, const StreamDesc* __restrict__ sds) {
   constexpr int RM = RC ? RC : SP_PA_R, NS = GT + 4 * RM, NQ = GT + 2 * RM;
-  __shared__ float4 st[NS * NS];   // gO0, gO90, P, Q; then E [NQ][NQ]
-  __shared__ float4 vp[NQ * NS];   // V[g] gO0, V[gm] gO90 - c45 V[g] P, V[gc] P, V[gs] Q
+  // three rows and one value more than staged: read for outputs past the last, which are not stored
+  __shared__ float4 st[(NS + 3) * NS];   // gO0, gO90, P, Q; then E [NQ][NQ]
+  __shared__ float4 vp[NQ * NS + 1];     // V[g] gO0, V[gm] gO90 - c45 V[g] P, V[gc] P, V[gs] Q
   const int z = blockIdx.z, l = A.ul[blockIdx.y];
   const StreamDesc& sd = sds[z];
   const int h = sd.Hl[l], w = sd.Wl[l], R = RC ? RC : sd.gr;
@@ -604,18 +733,28 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_gabor_t(PaDesc A, const StreamD
   const int E = GT + 4 * R, oy = ty0 - 2 * R, ox = tx0 - 2 * R;
   float* gI = slot(A.gX[l], A, z);
   const gp<const float> gO = G((const float*)gI + 3 * (size_t)n);
+  const int py = ty0 + (int)(threadIdx.x >> 4), px = tx0 + (int)(threadIdx.x & 15);
+  const float base = G((const float*)gI)[(uint32_t)min(py, h - 1) * (uint32_t)w + (uint32_t)min(px, w - 1)];   // added to last
   {
+    // every load of the tile in flight at once: one at a time their latency was most of the launch
+    constexpr int NI = (NS * NS + SP_BLOCK - 1) / SP_BLOCK;
+    float v[NI][4];
+    bool in[NI];
     Walk2 wk(threadIdx.x, E);
-    for (int i = threadIdx.x; i < E * E; i += SP_BLOCK, wk.next()) {
+#pragma unroll
+    for (int k = 0; k < NI; ++k, wk.next()) {
       const int y = oy + wk.r, x = ox + wk.c;
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (y >= 0 && y < h && x >= 0 && x < w) {
-        const uint32_t o = (uint32_t)y * (uint32_t)w + (uint32_t)x;
-        const float o45 = gO[n + o], o135 = gO[3 * n + o];
-        v = make_float4(gO[o], gO[2 * n + o], o45 + o135, o135 - o45);
-      }
-      st[wk.r * NS + wk.c] = v;
+      in[k] = y >= 0 && y < h && x >= 0 && x < w;
+      const uint32_t o = (uint32_t)clampi(y, 0, h - 1) * (uint32_t)w + (uint32_t)clampi(x, 0, w - 1);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[k][q] = gO[q * n + o];
     }
+    Walk2 wl(threadIdx.x, E);
+#pragma unroll
+    for (int k = 0; k < NI; ++k, wl.next())
+      if (k * SP_BLOCK + (int)threadIdx.x < E * E)
+        st[wl.r * NS + wl.c] = in[k] ? make_float4(v[k][0], v[k][2], v[k][1] + v[k][3], v[k][3] - v[k][1])
+                                     : make_float4(0.f, 0.f, 0.f, 0.f);
   }
   __syncthreads();
   // the q the tile needs: its own positions, and the outside strips on the level's borders
@@ -628,49 +767,73 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_gabor_t(PaDesc A, const StreamD
   // run-time radius the table is zero beyond 2 R + 1 and the position stays in the staged region.
   constexpr int NT = 2 * RM + 1;
   const float c45 = sd.c45;
+  // vertical pass, VB consecutive rows of a column per thread: VB + 2 R reads for VB outputs
+  constexpr int VB = 4, HB = 2;
   {
+    const int ng = (nqy + VB - 1) / VB;
     Walk2 wk(threadIdx.x, ncx);
-    for (int i = threadIdx.x; i < nqy * ncx; i += SP_BLOCK, wk.next()) {
-      const float4* col = st + (qy0 + wk.r + R - oy) * NS + (cx0 + wk.c - ox);
-      float a = 0.f, b = 0.f, gP = 0.f, c = 0.f, e = 0.f;
+    for (int i = threadIdx.x; i < ng * ncx; i += SP_BLOCK, wk.next()) {
+      const int q0 = wk.r * VB;
+      // output row q0 + u, tap t reads column row q0 + u + R - t; m = u + 2 R - t runs over what they share
+      const float4* col = st + (qy0 + q0 - R - oy) * NS + (cx0 + wk.c - ox);
+      float a[VB], b[VB], gP[VB], c[VB], e[VB];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        if (RC == 0 && t > 2 * R) break;
-        const float4 v = col[-t * NS];
-        a = fmaf(sd.gf[0][t], v.x, a);
-        b = fmaf(sd.gf[1][t], v.y, b);
-        gP = fmaf(sd.gf[0][t], v.z, gP);
-        c = fmaf(sd.gf[2][t], v.z, c);
-        e = fmaf(sd.gf[3][t], v.w, e);
+      for (int u = 0; u < VB; ++u) a[u] = b[u] = gP[u] = c[u] = e[u] = 0.f;
+#pragma unroll
+      for (int m = NT + VB - 2; m >= 0; --m) {   // taps in increasing order for every output
+        if (RC == 0 && m > 2 * R + VB - 1) continue;
+        const float4 v = col[m * NS];
+#pragma unroll
+        for (int u = 0; u < VB; ++u) {
+          const int t = u + 2 * R - m;
+          if (t < 0 || t > 2 * R) continue;
+          a[u] = fmaf(sd.gf[0][t], v.x, a[u]);
+          b[u] = fmaf(sd.gf[1][t], v.y, b[u]);
+          gP[u] = fmaf(sd.gf[0][t], v.z, gP[u]);
+          c[u] = fmaf(sd.gf[2][t], v.z, c[u]);
+          e[u] = fmaf(sd.gf[3][t], v.w, e[u]);
+        }
       }
-      vp[wk.r * NS + wk.c] = make_float4(a, b - c45 * gP, c, e);
+#pragma unroll
+      for (int u = 0; u < VB; ++u)
+        if (q0 + u < nqy) vp[(q0 + u) * NS + wk.c] = make_float4(a[u], b[u] - c45 * gP[u], c[u], e[u]);
     }
   }
   __syncthreads();
   float* eq = reinterpret_cast<float*>(st);   // the staged gradients are no longer read
   {
-    Walk2 wk(threadIdx.x, nqx);
-    for (int i = threadIdx.x; i < nqy * nqx; i += SP_BLOCK, wk.next()) {
-      const float4* row = vp + wk.r * NS + wk.c + 2 * R;
-      float e = 0.f;
+    const int ng = (nqx + HB - 1) / HB;
+    Walk2 wk(threadIdx.x, ng);
+    for (int i = threadIdx.x; i < nqy * ng; i += SP_BLOCK, wk.next()) {
+      const int q0 = wk.c * HB;
+      const float4* row = vp + wk.r * NS + q0;
+      float e[HB];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        if (RC == 0 && t > 2 * R) break;
-        const float4 v = row[-t];
-        e = fmaf(sd.gf[1][t], v.x, fmaf(sd.gf[0][t], v.y, fmaf(sd.gf[2][t], v.z, fmaf(sd.gf[3][t], v.w, e))));
+      for (int u = 0; u < HB; ++u) e[u] = 0.f;
+#pragma unroll
+      for (int m = NT + HB - 2; m >= 0; --m) {
+        if (RC == 0 && m > 2 * R + HB - 1) continue;
+        const float4 v = row[m];
+#pragma unroll
+        for (int u = 0; u < HB; ++u) {
+          const int t = u + 2 * R - m;
+          if (t < 0 || t > 2 * R) continue;
+          e[u] = fmaf(sd.gf[1][t], v.x, fmaf(sd.gf[0][t], v.y, fmaf(sd.gf[2][t], v.z, fmaf(sd.gf[3][t], v.w, e[u]))));
+        }
       }
-      eq[wk.r * NQ + wk.c] = e;
+#pragma unroll
+      for (int u = 0; u < HB; ++u)
+        if (q0 + u < nqx) eq[wk.r * NQ + q0 + u] = e[u];
     }
   }
   __syncthreads();
-  const int py = ty0 + (int)(threadIdx.x >> 4), px = tx0 + (int)(threadIdx.x & 15);
   if (py >= h || px >= w) return;
   const int fy0 = py == 0 ? -R : py, fy1 = py == h - 1 ? h - 1 + R : py;
   const int fx0 = px == 0 ? -R : px, fx1 = px == w - 1 ? w - 1 + R : px;
   float acc = 0.f;
   for (int qy = fy0; qy <= fy1; ++qy)
     for (int qx = fx0; qx <= fx1; ++qx) acc += eq[(qy - qy0) * NQ + (qx - qx0)];
-  gI[(size_t)py * w + px] += acc;
+  G(gI)[(uint32_t)py * (uint32_t)w + (uint32_t)px] = base + acc;
 }
 
 // Level 1 back to the frames: the last transposed pyramid step (2x2 pixels per thread from nine
@@ -685,40 +848,82 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_feat(PaDesc A, const StreamDesc
   const StreamDesc& sd = sds[z];
   const int H = sd.H, W = sd.W, h1 = sd.Hl[1], w1 = sd.Wl[1];
   const size_t hw3 = 3 * (size_t)H * W;
-  // the frame's colour maximum from the partials (integers below 2^24: exact as floats)
-  uint32_t m = 0;
-  for (int k = threadIdx.x; k < sd.n_rgb; k += SP_BLOCK) m = max(m, sd.rgb_max_part[k]);
-  const uint32_t smax = (uint32_t)block_reduce<OpMax>((float)m, sh4);
   const int i = blockIdx.x * SP_BLOCK + threadIdx.x;
-  if (i >= h1 * w1) return;
-  const int q = i / w1, r = i - q * w1;
+  const bool act = i < h1 * w1;
+  const int q = min(i, h1 * w1 - 1) / w1, r = min(i, h1 * w1 - 1) - q * w1;
   const QuadT Q(q, r, H, W, h1, w1);
   const size_t n1 = (size_t)h1 * w1;
   const float* g1 = slot(A.gX[1], A, z);
-  float gI[2][2], gRG[2][2], gBY[2][2], gM[2][2], gN[2][2];
   const bool next = z + 1 < nz;   // uniform
-  {
-    float v[5][3][3];
-    Q.load(G(g1), v[0]);
-    Q.load(G(g1 + n1), v[1]);
-    Q.load(G(g1 + 2 * n1), v[2]);
-    Q.load(G(g1 + 7 * n1), v[3]);
-    if (next) Q.load(G((const float*)slot(A.gX[1], A, z + 1) + 7 * n1), v[4]);
-    Q.apply(v[0], gI);
-    Q.apply(v[1], gRG);
-    Q.apply(v[2], gBY);
-    Q.apply(v[3], gM);
-    if (next) Q.apply(v[4], gN);
-  }
+  // every gradient and byte is requested before the colour maximum is reduced; two pixels of a row
+  // are six bytes, three 2-byte loads and three 8-byte stores where rows allow
+  float v[5][3][3];
+  Q.load(G(g1), v[0]);
+  Q.load(G(g1 + n1), v[1]);
+  Q.load(G(g1 + 2 * n1), v[2]);
+  Q.load(G(g1 + 7 * n1), v[3]);
+  if (next) Q.load(G((const float*)slot(A.gX[1], A, z + 1) + 7 * n1), v[4]);
+  const bool pairs = (W & 1) == 0 && (reinterpret_cast<uintptr_t>(frames) & 1) == 0 && (reinterpret_cast<uintptr_t>(grad) & 7) == 0;
   const gp<const uint8_t> rgb = G(frames + (size_t)t * hw3);
+  uint32_t c0[2][2][3], cp[2][2], cn[2][2];   // the frame's bytes, the sums of the previous and the next
+  {
+    auto two = [&](gp<const uint8_t> f, int y, uint32_t (&c)[2][3]) {
+      const uint32_t o = 3u * ((uint32_t)min(y, H - 1) * (uint32_t)W + (uint32_t)(2 * r));
+      if (pairs) {
+        uint32_t u[3];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+        for (int k = 0; k < 3; ++k) u[k] = ((gp<const uint16_t>)(f + o))[k];
+        c[0][0] = u[0] & 255u;
+        c[0][1] = u[0] >> 8;
+        c[0][2] = u[1] & 255u;
+        c[1][0] = u[1] >> 8;
+        c[1][1] = u[2] & 255u;
+        c[1][2] = u[2] >> 8;
+      } else {
+        const uint32_t o1 = 2 * r + 1 < W ? o + 3u : o;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          c[0][k] = f[o + k];
+          c[1][k] = f[o1 + k];
+        }
+      }
+    };
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      two(rgb, 2 * q + a, c0[a]);
+      uint32_t c[2][3];
+      cp[a][0] = cp[a][1] = cn[a][0] = cn[a][1] = 0u;
+      if (t > 0) {
+        two(rgb - hw3, 2 * q + a, c);
+        cp[a][0] = c[0][0] + c[0][1] + c[0][2];
+        cp[a][1] = c[1][0] + c[1][1] + c[1][2];
+      }
+      if (next) {
+        two(rgb + hw3, 2 * q + a, c);
+        cn[a][0] = c[0][0] + c[0][1] + c[0][2];
+        cn[a][1] = c[1][0] + c[1][1] + c[1][2];
+      }
+    }
+  }
+  // the frame's colour maximum from the partials (integers below 2^24: exact as floats)
+  uint32_t m = 0;
+  for (int k = threadIdx.x; k < sd.n_rgb; k += SP_BLOCK) m = max(m, G((const uint32_t*)sd.rgb_max_part)[k]);
+  const uint32_t smax = (uint32_t)block_reduce<OpMax>((float)m, sh4);
+  if (!act) return;
+  float gI[2][2], gRG[2][2], gBY[2][2], gM[2][2], gN[2][2];
+  Q.apply(v[0], gI);
+  Q.apply(v[1], gRG);
+  Q.apply(v[2], gBY);
+  Q.apply(v[3], gM);
+  if (next) Q.apply(v[4], gN);
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    const int y = 2 * q + a;
+    if (y >= H) continue;
+    float g6[2][3];
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      const int y = 2 * q + a, x = 2 * r + b;
-      if (y >= H || x >= W) continue;
-      const size_t o = 3 * ((size_t)y * W + x);
-      const uint32_t R8 = rgb[o], G8 = rgb[o + 1], B8 = rgb[o + 2];
+      const uint32_t R8 = c0[a][b][0], G8 = c0[a][b][1], B8 = c0[a][b][2];
       const int s8 = (int)(R8 + G8 + B8);
       const float rr = R8 * (1.f / 255.f), gg_ = G8 * (1.f / 255.f), bb = B8 * (1.f / 255.f);
       const float I = (rr + gg_ + bb) / 3.f;
@@ -726,12 +931,11 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_feat(PaDesc A, const StreamDesc
       float gIt = gI[a][b];
       if (t > 0) {
         // the sign of I_t - I_{t-1}, exact from the byte sums
-        const gp<const uint8_t> prev = rgb - hw3;
-        const int dm = s8 - (int)(prev[o] + prev[o + 1] + prev[o + 2]);
+        const int dm = s8 - (int)cp[a][b];
         const float sg = dm > 0 ? gM[a][b] : (dm < 0 ? -gM[a][b] : 0.f);
         gIt += sg;
-        if (z == 0) {
-          const gp<float> gp_ = G(grad + (size_t)(t - 1) * hw3 + o);
+        if (z == 0 && 2 * r + b < W) {
+          const gp<float> gp_ = G(grad + (size_t)(t - 1) * hw3 + 3 * ((size_t)y * W + 2 * r + b));
           const float gpv = -sg / 3.f / 255.f;
           gp_[0] += gpv;
           gp_[1] += gpv;
@@ -760,19 +964,33 @@ __global__ __launch_bounds__(SP_BLOCK) void k_pa_feat(PaDesc A, const StreamDesc
       gg = (gg + gIt / 3.f) / 255.f;
       gb = (gb + gIt / 3.f) / 255.f;
       if (next) {
-        const gp<const uint8_t> nx = rgb + hw3;
-        const int dm = (int)(nx[o] + nx[o + 1] + nx[o + 2]) - s8;
+        const int dm = (int)cn[a][b] - s8;
         const float sg = dm > 0 ? gN[a][b] : (dm < 0 ? -gN[a][b] : 0.f);
         const float gpv = -sg / 3.f / 255.f;
         gr += gpv;
         gg += gpv;
         gb += gpv;
       }
-      const gp<float> go = G(grad + (size_t)t * hw3 + o);
-      go[0] = gr;
-      go[1] = gg;
-      go[2] = gb;
+      g6[b][0] = gr;
+      g6[b][1] = gg;
+      g6[b][2] = gb;
     }
+    const gp<float> go = G(grad + (size_t)t * hw3 + 3 * ((size_t)y * W + 2 * r));
+    if (pairs) {
+      const gp<Pair> go2 = (gp<Pair>)go;
+      go2[0] = Pair{g6[0][0], g6[0][1]};
+      go2[1] = Pair{g6[0][2], g6[1][0]};
+      go2[2] = Pair{g6[1][1], g6[1][2]};
+    } else {
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+        if (2 * r + b < W) {
+          go[3 * b] = g6[b][0];
+          go[3 * b + 1] = g6[b][1];
+          go[3 * b + 2] = g6[b][2];
+        }
+    }
+  }
 }
 
 inline int blocks(long long n, int per = SP_BLOCK) { return (int)((n + per - 1) / per); }
@@ -808,7 +1026,7 @@ hipError_t sp_pixel_adjoint(const PaDesc& A, const StreamDesc* sds, const Stream
   hipLaunchKernelGGL(k_pa_nstrip, grid(blocks(maxh, 8), nF), b, 0, st, A, sds, fbar, SP_NCH, g.flat_tol);
   hipLaunchKernelGGL(k_pa_nfin, grid(1, nF), b, 0, st, A, sds, fbar, SP_NCH, g.flat_tol);
   hipLaunchKernelGGL(k_pa_csadj, grid(blocks(maxc, TILE), SP_NCH * A.n_cl), b, 0, st, A, sds);
-  hipLaunchKernelGGL(k_pa_up_t, grid(blocks((long long)maxs * UPT_L), SP_NCH * A.n_sl), b, 0, st, A, sds);
+  hipLaunchKernelGGL(k_pa_up_t, grid(blocks(maxs, UPT_E), SP_NCH * A.n_sl), b, 0, st, A, sds);
   if (g.gr == 6)
     hipLaunchKernelGGL(k_pa_gabor_t<6>, grid(maxt, A.n_ul), b, 0, st, A, sds);
   else
