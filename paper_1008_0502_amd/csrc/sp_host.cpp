@@ -1921,6 +1921,7 @@ struct sp_batch {
   bool mrf = false;
   std::vector<Tune> tune;   // per stream
   bool xcd = false;
+  size_t max_px = 0;      // pixels of the largest stream
   int ca_nc = 2;            // preferred channels per across-scale workgroup (one value per launch)
   // tape and adjoint (record_tape > 0): every stream records the same steps
   int cap = 0;              // frames each stream's tape holds
@@ -2241,6 +2242,7 @@ int sp_batch_create(const sp_params* p, int32_t n, const int32_t* H, const int32
       batch_free(b);
       return fail(rc, "stream %d: %s", i, g_err.c_str());
     }
+    b->max_px = std::max(b->max_px, (size_t)H[i] * W[i]);
   }
   b->h_sd.resize(n);
   b->h_st.resize(n);
@@ -2377,7 +2379,7 @@ int sp_batch_step(sp_batch* b, const uint8_t* const* rgb_ptrs, float* const* pri
     if (rc) return rc;
     b->steps += 1;
     if (prior_ptrs) {
-      hipError_t e = sp_launch_batch_copy_out(b->n, b->d_st, b->d_sd, prior_ptrs, b->stream);
+      hipError_t e = sp_launch_batch_copy_out(b->n, b->max_px, b->d_st, b->d_sd, prior_ptrs, b->stream);
       if (e != hipSuccess) return fail(SP_EHIP, "copy-out launch: %s", hipGetErrorString(e));
     }
     return SP_OK;
@@ -2392,7 +2394,7 @@ int sp_batch_step(sp_batch* b, const uint8_t* const* rgb_ptrs, float* const* pri
   HIPCHK(hipGraphLaunch(b->exec, b->stream));
   b->steps += 1;
   if (prior_ptrs) {
-    hipError_t e = sp_launch_batch_copy_out(b->n, b->d_st, b->d_sd, prior_ptrs, b->stream);
+    hipError_t e = sp_launch_batch_copy_out(b->n, b->max_px, b->d_st, b->d_sd, prior_ptrs, b->stream);
     if (e != hipSuccess) return fail(SP_EHIP, "copy-out launch: %s", hipGetErrorString(e));
   }
   return SP_OK;

@@ -35,8 +35,9 @@ struct RgbNodeArgs {
 };
 void sp_batch_rgb_node_params(RgbNodeArgs* a, int n_jobs, hipKernelNodeParams* p);
 hipError_t sp_launch_batch_reset(int n, BatchState* st, hipStream_t stream);
-hipError_t sp_launch_batch_copy_out(int n, const BatchState* st, const StreamDesc* sds, float* const* out,
-                                    hipStream_t stream);
+// max_px: pixels of the largest stream.
+hipError_t sp_launch_batch_copy_out(int n, size_t max_px, const BatchState* st, const StreamDesc* sds,
+                                    float* const* out, hipStream_t stream);
 // Counter calibration copy of n16 16-byte units (mode: 0 dword, 1 dwordx4, 2 global->LDS dword).
 hipError_t sp_launch_calib(const float* src, float* dst, size_t n16, int mode, hipStream_t st);
 

@@ -3172,15 +3172,33 @@ __global__ void k_batch_reset(int n, BatchState* __restrict__ st) {
   st[i].last_rgb = nullptr;
 }
 
-// Copies each stream's current prior to the caller's buffers (blockIdx.y = stream).
-__global__ void k_batch_copy_out(const BatchState* __restrict__ st, const StreamDesc* __restrict__ sds,
-                                 float* const* __restrict__ out) {
+// Copies each stream's current prior to the caller's buffers (blockIdx.y = stream, blockIdx.x =
+// CO_PX pixels of it).  Memory-bound: four 16-byte accesses a thread, all in flight, where both sides
+// are aligned; 32 streams of 160x120 to 1280x720 (9.9 Mpixel, 79 MB, 15 us at the rate of a large copy)
+// COPY_OLD us with 64 workgroups a stream of any size and 4-byte flat accesses, COPY_NEW us here.
+constexpr int CO_PX = 16 * SP_BLOCK;
+__global__ __launch_bounds__(SP_BLOCK) void k_batch_copy_out(const BatchState* __restrict__ st,
+                                                             const StreamDesc* __restrict__ sds,
+                                                             float* const* __restrict__ out) {
+  typedef float v4f __attribute__((ext_vector_type(4)));
   const int s = blockIdx.y;
-  const size_t n = (size_t)sds[s].H * sds[s].W;
+  const uint32_t n = (uint32_t)sds[s].H * (uint32_t)sds[s].W, i0 = blockIdx.x * CO_PX;
+  if (i0 >= n) return;   // uniform
   const float* src = st[s].cur ? st[s].pi[1] : st[s].pi[0];
   float* dst = out[s];
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    dst[i] = src[i];
+  const gp<const float> gs = G(src);
+  const gp<float> gd = G(dst);
+  const bool quads = ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0;
+  if (quads && i0 + CO_PX <= n) {
+    v4f v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = *(gp<const v4f>)(gs + i0 + 4 * (k * SP_BLOCK + threadIdx.x));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) *(gp<v4f>)(gd + i0 + 4 * (k * SP_BLOCK + threadIdx.x)) = v[k];
+    return;
+  }
+#pragma unroll 4
+  for (uint32_t i = i0 + threadIdx.x; i < min(i0 + (uint32_t)CO_PX, n); i += SP_BLOCK) gd[i] = gs[i];
 }
 
 }  // namespace
@@ -3447,9 +3465,9 @@ hipError_t sp_launch_batch_reset(int n, BatchState* st, hipStream_t stream) {
   return chk();
 }
 
-hipError_t sp_launch_batch_copy_out(int n, const BatchState* st, const StreamDesc* sds, float* const* out,
-                                    hipStream_t stream) {
-  hipLaunchKernelGGL(k_batch_copy_out, dim3(64, n), dim3(SP_BLOCK), 0, stream, st, sds, out);
+hipError_t sp_launch_batch_copy_out(int n, size_t max_px, const BatchState* st, const StreamDesc* sds,
+                                    float* const* out, hipStream_t stream) {
+  hipLaunchKernelGGL(k_batch_copy_out, dim3((unsigned)((max_px + CO_PX - 1) / CO_PX), n), dim3(SP_BLOCK), 0, stream, st, sds, out);
   return chk();
 }
 
