@@ -2008,8 +2008,9 @@ struct PairNp {
   static constexpr int C = 10;   // tiles per lane requested by load()
   Part3 v[C];
 
-  __device__ void load(const StreamDesc& sd, int p) {
-    const int nt = sd.cs_nt[p], j = lane_id() & 7;
+  // the lane's tiles j, j + 8, ... of the C from t0 on (past the last: the last again)
+  __device__ void load(const StreamDesc& sd, int p, int t0 = 0) {
+    const int nt = sd.cs_nt[p], j = t0 + (lane_id() & 7);
     const gp<const float> part = G((const float*)sd.cs_part) + 3 * (size_t)sd.cs_off[p];   // uniform base
     const uint32_t ko = (uint32_t)(lane_id() >> 3) * (uint32_t)nt;
 #pragma unroll
@@ -2027,24 +2028,22 @@ struct PairNp {
     const int k = lane_id() >> 3, j = lane_id() & 7;
     float mn = INFINITY, mx = -INFINITY;
     double s = 0.0;
-    // a position past the last tile read the last tile again: harmless to the minimum and
-    // maximum, masked to +0 in the sum (sums of F >= 0 start at +0, so adding +0 is exact)
+    // Large frames take further rounds of C tiles a lane, all of a round's loads in flight (one
+    // tile at a time, a 1280x720 stream's 240 tiles were a chain of twenty loads: 32 streams up to
+    // that size 37 -> 30 us).
+    for (int t0 = 0;;) {
+      // a position past the last tile read the last tile again: harmless to the minimum and
+      // maximum, masked to +0 in the sum (sums of F >= 0 start at +0, so adding +0 is exact)
 #pragma unroll
-    for (int u = 0; u < C; ++u) {
-      const int keep = -(int)(j + 8 * u < nt);
-      mn = fminf(mn, v[u].mn);
-      mx = fmaxf(mx, v[u].mx);
-      s += (double)__int_as_float(__float_as_int(v[u].sb) & keep);
-    }
-    if (nt > 8 * C) {   // large frames
-      const gp<const float> part = G((const float*)sd.cs_part) + 3 * (size_t)sd.cs_off[p];
-      const uint32_t ko = (uint32_t)k * (uint32_t)nt;
-      for (int t = 8 * C + j; t < nt; t += 8) {
-        const gp<const Part3> q = (gp<const Part3>)at_bytes(part, 12u * (ko + (uint32_t)t));
-        mn = fminf(mn, q->mn);
-        mx = fmaxf(mx, q->mx);
-        s += (double)q->sb;
+      for (int u = 0; u < C; ++u) {
+        const int keep = -(int)(t0 + j + 8 * u < nt);
+        mn = fminf(mn, v[u].mn);
+        mx = fmaxf(mx, v[u].mx);
+        s += (double)__int_as_float(__float_as_int(v[u].sb) & keep);
       }
+      t0 += 8 * C;
+      if (t0 >= nt) break;   // uniform
+      load(sd, p, t0);
     }
     // quad_perm [1,0,3,2], quad_perm [2,3,0,1], then row_half_mirror (lane i with lane
     // 7 - i of its eight)
@@ -2067,7 +2066,10 @@ struct PairNp {
 };
 
 // F-bar_k on a 16x16 c_max tile = sum over pairs of N(reduced map), all 8 channels; then
-// its partial statistics (one 8x8 block per wavefront).
+// its partial statistics.  Rows of whole aligned quads: wavefront w takes channels 2 w and 2 w + 1,
+// a lane four pixels of a row, so a map of the tile is one 16-byte load a lane (16 streams of 640x480
+// 14.0 -> 11.8 us, a 160x120 step 5.2 -> 4.5); otherwise a wavefront takes an 8x8 block of every
+// channel, a pixel a lane.  The sums and their order are the same.
 template <bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_csmix(const Job* __restrict__ jobs,
                                                     const StreamDesc* __restrict__ sds,
@@ -2078,6 +2080,86 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csmix(const Job* __restrict__ jobs
   const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const int cm = sd.c_max, Hm = sd.Hl[cm], Wm = sd.Wl[cm];
   const size_t plane = (size_t)Hm * Wm;
+  if ((Wm & 3) == 0 && (reinterpret_cast<uintptr_t>(sd.gmap) & 15) == 0 &&
+      (reinterpret_cast<uintptr_t>(fbar_ptr(sd, IOF(fbar))) & 15) == 0) {   // uniform
+    typedef float v4f __attribute__((ext_vector_type(4)));
+    constexpr int KW = SP_NCH / 4, PG = 4;   // channels per wavefront, pairs loaded together
+    const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id()), np = sd.n_pairs;
+    const int yy = lane >> 2, xx = 4 * (lane & 3);
+    const bool valid = yy < J.th && xx < J.tw;   // J.tw is a multiple of 4
+    const uint32_t ob = ((uint32_t)(J.y0 + min(yy, J.th - 1)) * (uint32_t)Wm + (uint32_t)(J.x0 + min(xx, J.tw - 4))) * 4u;
+    v4f g[PG][KW];
+    auto load_group = [&](int p0) {
+#pragma unroll
+      for (int u = 0; u < PG; ++u) {
+        const int p = max(min(p0 + u, np - 1), 0);   // past the last pair: loaded again, not added
+#pragma unroll
+        for (int k = 0; k < KW; ++k)
+          g[u][k] = *(gp<const v4f>)at_bytes(G((const float*)sd.gmap + ((size_t)p * SP_NCH + KW * w + k) * plane), ob);
+      }
+    };
+    {
+      PairNp q;
+      q.load(sd, min(w, np - 1));
+      __builtin_amdgcn_sched_barrier(0);
+      load_group(0);
+      if (w < np) q.finish(sd, w, nps[w]);
+    }
+    for (int p = w + SP_BLOCK / 64; p < np; p += SP_BLOCK / 64) {
+      PairNp q;
+      q.load(sd, p);
+      q.finish(sd, p, nps[p]);
+    }
+    __syncthreads();
+    v4f acc[KW];
+#pragma unroll
+    for (int k = 0; k < KW; ++k) acc[k] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int p0 = 0; p0 < np; p0 += PG) {
+      if (p0 > 0) load_group(p0);
+#pragma unroll
+      for (int u = 0; u < PG; ++u) {
+        const int p = p0 + u;
+        if (p < np) {
+#pragma unroll
+          for (int k = 0; k < KW; ++k) {
+            const float* q = nps[p][KW * w + k];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[k][c] = fmaf((g[u][k][c] - q[0]) * q[1], q[2], acc[k][c]);
+          }
+        }
+      }
+    }
+    const gp<float> fbar = G(fbar_ptr(sd, IOF(fbar)));
+#pragma unroll
+    for (int k = 0; k < KW; ++k) {
+      if (valid) *(gp<v4f>)at_bytes(fbar + (size_t)(KW * w + k) * plane, ob) = acc[k];
+      // the 8x8 block of a lane: eight rows (lanes 4 apart) of two lanes
+      float mn = valid ? fminf(fminf(acc[k][0], acc[k][1]), fminf(acc[k][2], acc[k][3])) : INFINITY;
+      float mx = valid ? fmaxf(fmaxf(acc[k][0], acc[k][1]), fmaxf(acc[k][2], acc[k][3])) : -INFINITY;
+      mn = fminf(mn, dpp_f<0xB1>(mn));
+      mx = fmaxf(mx, dpp_f<0xB1>(mx));
+#pragma unroll
+      for (int d = 4; d < 32; d *= 2) {
+        mn = fminf(mn, __shfl_xor(mn, d));
+        mx = fmaxf(mx, __shfl_xor(mx, d));
+      }
+      if ((lane & 0x1d) == 0) {   // lanes 0, 2, 32, 34: blocks (0, 0), (0, 1), (1, 0), (1, 1)
+        const int b = (lane >> 5) * 2 + ((lane >> 1) & 1);
+        wacc[b][KW * w + k][0] = mn;
+        wacc[b][KW * w + k][1] = mx;
+        wacc[b][KW * w + k][2] = 8 * (b >> 1) < J.th && 8 * (b & 1) < J.tw ? mx : 0.f;
+      }
+    }
+    // a wavefront's own channels: no barrier
+    if (lane < KW) {
+      const int k = KW * w + lane;
+      const gp<float> out = G(sd.fbar_part) + 3 * ((size_t)k * sd.n_cmax_tiles + J.tid);
+      out[0] = fminf(fminf(wacc[0][k][0], wacc[1][k][0]), fminf(wacc[2][k][0], wacc[3][k][0]));
+      out[1] = fmaxf(fmaxf(wacc[0][k][1], wacc[1][k][1]), fmaxf(wacc[2][k][1], wacc[3][k][1]));
+      out[2] = (wacc[0][k][2] + wacc[1][k][2]) + (wacc[2][k][2] + wacc[3][k][2]);
+    }
+    return;
+  }
   const int lane = lane_id(), w = wave_id();
   const int by = w >> 1, bx = w & 1;
   const int yy = 8 * by + (lane >> 3), xx = 8 * bx + (lane & 7);
@@ -3175,7 +3257,7 @@ __global__ void k_batch_reset(int n, BatchState* __restrict__ st) {
 // Copies each stream's current prior to the caller's buffers (blockIdx.y = stream, blockIdx.x =
 // CO_PX pixels of it).  Memory-bound: four 16-byte accesses a thread, all in flight, where both sides
 // are aligned; 32 streams of 160x120 to 1280x720 (9.9 Mpixel, 79 MB, 15 us at the rate of a large copy)
-// COPY_OLD us with 64 workgroups a stream of any size and 4-byte flat accesses, COPY_NEW us here.
+// 36 us with 64 workgroups a stream of any size and 4-byte flat accesses, 18 us here.
 constexpr int CO_PX = 16 * SP_BLOCK;
 __global__ __launch_bounds__(SP_BLOCK) void k_batch_copy_out(const BatchState* __restrict__ st,
                                                              const StreamDesc* __restrict__ sds,
