@@ -71,6 +71,14 @@ int csg_set(const Geo& g) {
   return 1;
 }
 
+// The same for the across-scale sum of three centre levels.
+int ca_set(const Geo& g) {
+  if (g.n_pairs != CA_SET1_N) return 0;
+  for (int p = 0; p < g.n_pairs; ++p)
+    if (g.c_max - g.pc[p] != ca_set1_r(p) || g.ps[p] - g.pc[p] != ca_set1_d(p)) return 0;
+  return 1;
+}
+
 size_t csg_lds_bytes(const Geo& g) {
   return sizeof(float) * (size_t)csg_layout(g.pc, g.ps, g.n_pairs, g.c_max).total;
 }
@@ -831,7 +839,7 @@ int forward_phases(const Geo& g, const sp_params& p, const StreamDesc& sd, const
   for (size_t i = 0; i < parts.size(); ++i) {
     const bool grp = kinds[i] == JOB_CSAPPLY || kinds[i] == JOB_CSG;
     const bool pyr = kinds[i] == JOB_DOWN || kinds[i] == JOB_TAIL;   // flag: Gabor radius
-    const int gflag = nc | (kinds[i] == JOB_CSG ? csg_set(g) << 8 : 0);
+    const int gflag = nc | ((kinds[i] == JOB_CSG ? csg_set(g) : ca_set(g)) << 8);
     if (tune.xcd) xcd_order(parts[i]);
     out.push_back(js.add(kinds[i], grp ? gflag : (pyr ? p.gabor_radius : 0), parts[i], 1));
     if (grp) out.back().lds = ca_lds;
@@ -1039,7 +1047,7 @@ int clip_tables(sp_ctx* c) {
   for (size_t i = 0; i < all.size(); ++i) {
     const bool grp = kinds[i] == JOB_CSAPPLY || kinds[i] == JOB_CSG;
     const bool pyr = kinds[i] == JOB_DOWN || kinds[i] == JOB_TAIL;
-    const int flag = grp ? nc | (kinds[i] == JOB_CSG ? csg_set(g) << 8 : 0) : (pyr ? c->p.gabor_radius : 0);
+    const int flag = grp ? nc | ((kinds[i] == JOB_CSG ? csg_set(g) : ca_set(g)) << 8) : (pyr ? c->p.gabor_radius : 0);
     c->clip_part.push_back(c->jobs.add(kinds[i], flag, all[i], c->CH));
     std::vector<Job> first, rest;
     for (const Job& jb : all[i])
@@ -2075,7 +2083,10 @@ int batch_build_tables(sp_batch* b) {
   }
   if (!csf.empty()) b->phases.push_back(b->jobs.add(JOB_CSFINAL, 0, order(csf), n));
   if (!csa.empty()) {
-    b->phases.push_back(b->jobs.add(JOB_CSAPPLY, nc, order(csa), n));
+    int set = 1;
+    for (const Geo& g : b->geo)
+      if (!gpath_ok(g)) set = std::min(set, ca_set(g));
+    b->phases.push_back(b->jobs.add(JOB_CSAPPLY, nc | (set << 8), order(csa), n));
     b->phases.back().lds = nc * lds_a;
   }
   if (!csm.empty()) b->phases.push_back(b->jobs.add(JOB_CSMIX, 0, order(csm), n));

@@ -222,18 +222,19 @@ struct CaLayout {
 };
 
 // Footprint capacity (floats) of pair (c, s) for the region of centre level c.
-__host__ __device__ inline int csapply_foot_cap(int r, int d) {
+__host__ __device__ constexpr int csapply_foot_cap(int r, int d) {
   const int n1 = 2 * SP_CA_T + 3, n2 = 2 * n1 + 3;
   const int n = (r == 0) ? SP_CA_T : ((r == 1) ? n1 : n2);
   const int e = ((n - 1) >> d) + 3;
   return e * e;
 }
 
-__host__ __device__ inline CaLayout csapply_layout(const int32_t* pc, const int32_t* ps, int n_pairs, int c_max) {
+// of pairs (r, d) = (c_max - c, s - c)
+__host__ __device__ constexpr CaLayout csapply_layout_rd(const int* r, const int* d, int n_pairs) {
   bool has[3] = {false, false, false};
-  for (int p = 0; p < n_pairs; ++p) has[c_max - pc[p]] = true;
+  for (int p = 0; p < n_pairs; ++p) has[r[p]] = true;
   const int n1 = 2 * SP_CA_T + 3, n2 = 2 * n1 + 3;
-  CaLayout L;
+  CaLayout L{};
   int o = 0;
   L.x0 = o;
   if (has[0]) o += SP_CA_T * SP_CA_T;
@@ -244,10 +245,23 @@ __host__ __device__ inline CaLayout csapply_layout(const int32_t* pc, const int3
   L.tm = o;
   o += has[2] ? n2 * n1 : ((has[1]) ? n1 * SP_CA_T : 0);
   L.foot0 = o;
-  for (int p = 0; p < n_pairs; ++p) o += csapply_foot_cap(c_max - pc[p], ps[p] - pc[p]);
+  for (int p = 0; p < n_pairs; ++p) o += csapply_foot_cap(r[p], d[p]);
   L.total = o;
   return L;
 }
+__host__ __device__ inline CaLayout csapply_layout(const int32_t* pc, const int32_t* ps, int n_pairs, int c_max) {
+  int r[SP_MAXP], d[SP_MAXP];
+  for (int p = 0; p < n_pairs; ++p) {
+    r[p] = c_max - pc[p];
+    d[p] = ps[p] - pc[p];
+  }
+  return csapply_layout_rd(r, d, n_pairs);
+}
+// Pair set 1 of the across-scale sum: centre levels c_max - 2 .. c_max, each with the surrounds 3
+// and 4 levels above, as (r, d) in the stream's pair order.
+#define CA_SET1_N 6
+__host__ __device__ constexpr int ca_set1_r(int p) { return 2 - p / 2; }
+__host__ __device__ constexpr int ca_set1_d(int p) { return 3 + (p & 1); }
 
 // LDS of the reduced-map job for a group of NC channels, in floats per channel:
 // x1n, the centre region of the level below c_max in whole 16-byte quads per row

@@ -1100,8 +1100,16 @@ struct CaPair {
 // to every channel.  Each channel owns a block of L.total floats of dynamic LDS with the
 // layout of csapply_layout.  A flat map has zero N parameters (inv = scale = 0), which
 // adds exactly 0.
-template <int NC, bool ONE>
-__global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jobs,
+// SET: the pairs as compile-time (r, d) (set 1, one channel a workgroup), else read from the stream.
+// With the set known every loop over pairs unrolls, offsets are constants, and the bilinear taps of
+// the regions' rows and columns are formed once per workgroup, which takes 512 threads: the uniform
+// geometry, a thousand scalar instructions in every wavefront, and the taps per pixel and pair bound
+// the launch, 23 us for a 1920x1080 frame's 320 workgroups, 14 us so (17 with 256 threads, 19 with 1024).
+constexpr int CA_NT1 = 2 * SP_BLOCK;
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Wpass-failed"
+template <int NC, int SET, bool ONE>
+__global__ __launch_bounds__(SET ? CA_NT1 : SP_BLOCK) void k_csapply(const Job* __restrict__ jobs,
                                                       const StreamDesc* __restrict__ sds,
                                                       const StepIO* __restrict__ ios, StepIO io0) {
   extern __shared__ float dyn[];
@@ -1110,14 +1118,33 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
   __shared__ int ncp[3];
   __shared__ float fb[NC][CA_T * CA_T];
   __shared__ float wacc[4][NC][3];
+  constexpr int NT_ = SET ? CA_NT1 : SP_BLOCK;
+  constexpr bool TAB = SET != 0;
+  static_assert(NC == 1 || !TAB, "one channel with the tables");
+  constexpr int E0 = CA_T, E1 = 2 * E0 + 3, E2 = 2 * E1 + 3;   // region edges
+  // taps per pair slot and line of the regions (levels 0, 1, 2 back to back): rows (LDS offsets of
+  // the two footprint rows, weights), columns (the two footprint columns, weights)
+  __shared__ float4 tabr[TAB ? 4 : 1][TAB ? E0 + E1 + E2 : 1], tabc[TAB ? 4 : 1][TAB ? E0 + E1 + E2 : 1];
   const Job J = jobs[blockIdx.x];
   const StreamDesc& sd = sds[ONE ? 0 : J.stream];
   const int k0 = J.a, cm = sd.c_max;
   const int Hm = sd.Hl[cm], Wm = sd.Wl[cm];
-  const CaLayout L = csapply_layout(sd.pc, sd.ps, sd.n_pairs, cm);
+  const int np = SET ? CA_SET1_N : sd.n_pairs;
+  auto pr = [&](int p) { return SET ? ca_set1_r(p) : cm - sd.pc[p]; };
+  auto pd = [&](int p) { return SET ? ca_set1_d(p) : sd.ps[p] - sd.pc[p]; };
+  CaLayout L;
+  if constexpr (SET != 0) {
+    constexpr int R[CA_SET1_N] = {ca_set1_r(0), ca_set1_r(1), ca_set1_r(2), ca_set1_r(3), ca_set1_r(4), ca_set1_r(5)};
+    constexpr int D[CA_SET1_N] = {ca_set1_d(0), ca_set1_d(1), ca_set1_d(2), ca_set1_d(3), ca_set1_d(4), ca_set1_d(5)};
+    constexpr CaLayout LS = csapply_layout_rd(R, D, CA_SET1_N);
+    L = LS;
+  } else {
+    L = csapply_layout(sd.pc, sd.ps, sd.n_pairs, cm);
+  }
   const int CS = L.total;   // floats per channel block
   unsigned hm = 0;
-  for (int p = 0; p < sd.n_pairs; ++p) hm |= 1u << (cm - sd.pc[p]);
+#pragma unroll
+  for (int p = 0; p < np; ++p) hm |= 1u << pr(p);
   const bool has0 = (hm & 1u) != 0, has1 = (hm & 2u) != 0, has2 = (hm & 4u) != 0;
   // regions of the tile on the centre levels (r = c_max - c)
   const Range rg0{J.y0, J.th}, cg0{J.x0, J.tw};
@@ -1140,8 +1167,8 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
     for (int j = 0; j < NC; ++j) {
       const float* Xc = chan_ptr(sd, k0 + j, c);
       float* X = dyn + j * CS + xoff;
-      Walk2 wk(threadIdx.x, cc.n);
-      for (int i = threadIdx.x; i < n; i += SP_BLOCK, wk.next())
+      WalkB<NT_> wk(threadIdx.x, cc.n);
+      for (int i = threadIdx.x; i < n; i += NT_, wk.next())
         lds_load(X + i, Xc + (size_t)(rr.lo + wk.r) * Wc + cc.lo + wk.c);
     }
   };
@@ -1150,11 +1177,12 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
   if (has2) stage(rg2, cg2, cm - 2, L.x2);
   if (!has1 && has2)
     for (int j = 0; j < NC; ++j)
-      for (int i = threadIdx.x; i < rg1.n * cg1.n; i += SP_BLOCK) dyn[j * CS + L.x1 + i] = 0.f;
+      for (int i = threadIdx.x; i < rg1.n * cg1.n; i += NT_) dyn[j * CS + L.x1 + i] = 0.f;
   {
     int off = L.foot0;
-    for (int p = 0; p < sd.n_pairs; ++p) {
-      const int c = sd.pc[p], r = cm - c, s = sd.ps[p], Ws = sd.Wl[s];
+#pragma unroll
+    for (int p = 0; p < np; ++p) {
+      const int r = pr(p), c = cm - r, s = c + pd(p), Ws = sd.Wl[s];
       const Range rr = (r == 0) ? rg0 : ((r == 1) ? rg1 : rg2);
       const Range cc = (r == 0) ? cg0 : ((r == 1) ? cg1 : cg2);
       const Foot f = footprint(rr.lo, rr.n, cc.lo, cc.n, s - c, sd.Hl[s], Ws);
@@ -1162,8 +1190,8 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
       for (int j = 0; j < NC; ++j) {
         const float* Xs = chan_ptr(sd, k0 + j, s);
         float* dst = dyn + j * CS + off;
-        Walk2 wk(threadIdx.x, f.w);
-        for (int i = threadIdx.x; i < f.h * f.w; i += SP_BLOCK, wk.next())
+        WalkB<NT_> wk(threadIdx.x, f.w);
+        for (int i = threadIdx.x; i < f.h * f.w; i += NT_, wk.next())
           lds_load(dst + i, Xs + (size_t)(f.y0 + wk.r) * Ws + f.x0 + wk.c);
       }
       off += csapply_foot_cap(r, s - c);
@@ -1171,49 +1199,98 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
   }
   // pair table: thread p fills pair p (its slot and LDS offset follow from the pairs
   // before it)
-  if ((int)threadIdx.x < sd.n_pairs) {
-    const int p = threadIdx.x;
-    const int c = sd.pc[p], r = cm - c, s = sd.ps[p];
+  auto fill = [&](int p, int q, int off) {
+    const int r = pr(p), c = cm - r, s = c + pd(p);
+    const Range rr = (r == 0) ? rg0 : ((r == 1) ? rg1 : rg2);
+    const Range cc = (r == 0) ? cg0 : ((r == 1) ? cg1 : cg2);
+    const Foot f = footprint(rr.lo, rr.n, cc.lo, cc.n, s - c, sd.Hl[s], sd.Wl[s]);
+    CaPair& P = cpt[r][q];
+    P.off = off;
+    P.fy0 = f.y0;
+    P.fx0 = f.x0;
+    P.fw = f.w;
+    P.fh = f.h;
+    P.d = s - c;
+    P.Hs = sd.Hl[s];
+    P.Ws = sd.Wl[s];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const NParams np = load_np(G((const float*)sd.cs_np) + 4 * ((size_t)p * SP_NCH + k0 + j));
+      cnp[r][q][j][0] = np.mn;
+      cnp[r][q][j][1] = np.flat ? 0.f : np.inv;
+      cnp[r][q][j][2] = np.flat ? 0.f : np.scale;
+    }
+  };
+  if constexpr (SET != 0) {
+    int off = L.foot0;
+#pragma unroll
+    for (int p = 0; p < CA_SET1_N; ++p) {
+      if ((int)threadIdx.x == p) fill(p, p & 1, off);
+      off += csapply_foot_cap(ca_set1_r(p), ca_set1_d(p));
+    }
+  } else if ((int)threadIdx.x < sd.n_pairs) {
+    const int p = threadIdx.x, c = sd.pc[p];
     int q = 0, off = L.foot0;
     for (int pp = 0; pp < p; ++pp) {
       q += (sd.pc[pp] == c) ? 1 : 0;
       off += csapply_foot_cap(cm - sd.pc[pp], sd.ps[pp] - sd.pc[pp]);
     }
-    if (q < 4) {
-      const Range rr = (r == 0) ? rg0 : ((r == 1) ? rg1 : rg2);
-      const Range cc = (r == 0) ? cg0 : ((r == 1) ? cg1 : cg2);
-      const Foot f = footprint(rr.lo, rr.n, cc.lo, cc.n, s - c, sd.Hl[s], sd.Wl[s]);
-      CaPair& P = cpt[r][q];
-      P.off = off;
-      P.fy0 = f.y0;
-      P.fx0 = f.x0;
-      P.fw = f.w;
-      P.fh = f.h;
-      P.d = s - c;
-      P.Hs = sd.Hl[s];
-      P.Ws = sd.Wl[s];
-#pragma unroll
-      for (int j = 0; j < NC; ++j) {
-        const NParams np = load_np(G((const float*)sd.cs_np) + 4 * ((size_t)p * SP_NCH + k0 + j));
-        cnp[r][q][j][0] = np.mn;
-        cnp[r][q][j][1] = np.flat ? 0.f : np.inv;
-        cnp[r][q][j][2] = np.flat ? 0.f : np.scale;
-      }
-    }
+    if (q < 4) fill(p, q, off);
   }
   if (threadIdx.x < 3) {
     int n = 0;
-    for (int p = 0; p < sd.n_pairs; ++p) n += (cm - sd.pc[p] == (int)threadIdx.x) ? 1 : 0;
+#pragma unroll
+    for (int p = 0; p < np; ++p) n += pr(p) == (int)threadIdx.x ? 1 : 0;
     ncp[threadIdx.x] = min(n, 4);
   }
-  for (int i = threadIdx.x; i < NC * CA_T * CA_T; i += SP_BLOCK) (&fb[0][0])[i] = 0.f;
+  for (int i = threadIdx.x; i < NC * CA_T * CA_T; i += NT_) (&fb[0][0])[i] = 0.f;
   lds_wait();
   __syncthreads();
+  if constexpr (TAB) {
+    for (int i = threadIdx.x; i < 4 * (E0 + E1 + E2); i += NT_) {
+      const int q = i / (E0 + E1 + E2), e = i - q * (E0 + E1 + E2);
+      const int r = e < E0 ? 0 : (e < E0 + E1 ? 1 : 2), k = e - (r == 0 ? 0 : (r == 1 ? E0 : E0 + E1));
+      if (q >= ncp[r]) continue;
+      const Range rr = (r == 0) ? rg0 : ((r == 1) ? rg1 : rg2), cc = (r == 0) ? cg0 : ((r == 1) ? cg1 : cg2);
+      const CaPair& P = cpt[r][q];
+      if (k < rr.n) {
+        const Tap t = bilinear_tap(rr.lo + k, P.d, P.Hs);
+        tabr[q][e] = make_float4(__int_as_float(P.off + (t.i0 - P.fy0) * P.fw - P.fx0),
+                                 __int_as_float(P.off + (t.i1 - P.fy0) * P.fw - P.fx0), t.w, 1.f - t.w);
+      }
+      if (k < cc.n) {
+        const Tap t = bilinear_tap(cc.lo + k, P.d, P.Ws);
+        tabc[q][e] = make_float4(__int_as_float(t.i0), __int_as_float(t.i1), t.w, 1.f - t.w);
+      }
+    }
+    __syncthreads();
+  }
   // ---- N(F) summed over the pairs of each centre level, in place of the centre values
   auto nsum = [&](int r, Range rr, Range cc, int xoff) {
-    const int n = rr.n * cc.n, nq = ncp[r];
-    Walk2 wk(threadIdx.x, cc.n);
-    for (int i = threadIdx.x; i < n; i += SP_BLOCK, wk.next()) {
+    const int n = rr.n * cc.n, nq = SET ? CA_SET1_N / 3 : ncp[r];
+    if constexpr (TAB) {
+      const int e0 = r == 0 ? 0 : (r == 1 ? E0 : E0 + E1);
+      WalkB<NT_> wk(threadIdx.x, cc.n);
+      for (int i = threadIdx.x; i < n; i += NT_, wk.next()) {
+        const float xc = dyn[xoff + i];
+        float acc = 0.f;
+#pragma unroll
+        for (int q = 0; q < nq; ++q) {
+          const float4 ty = tabr[q][e0 + wk.r], tx = tabc[q][e0 + wk.c];
+          const float* b0 = dyn + __float_as_int(ty.x);
+          const float* b1 = dyn + __float_as_int(ty.y);
+          const int x0 = __float_as_int(tx.x), x1 = __float_as_int(tx.y);
+          const float top = fmaf(tx.z, b0[x1], tx.w * b0[x0]);
+          const float bot = fmaf(tx.z, b1[x1], tx.w * b1[x0]);
+          const float v = fabsf(xc - fmaf(ty.z, bot, ty.w * top));
+          acc = fmaf((v - cnp[r][q][0][0]) * cnp[r][q][0][1], cnp[r][q][0][2], acc);
+        }
+        dyn[xoff + i] = acc;
+      }
+      return;
+    }
+    WalkB<NT_> wk(threadIdx.x, cc.n);
+    for (int i = threadIdx.x; i < n; i += NT_, wk.next()) {
       const int y = rr.lo + wk.r, x = cc.lo + wk.c;
       float xc[NC], acc[NC];
 #pragma unroll
@@ -1249,8 +1326,8 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
   auto reduce = [&](int xin, int ldi, Range ri, Range ci, int xout_dyn, float* fbo, int ldo, Range ro, Range co,
                     int nh, int nw) {
     const int ldt = co.n;
-    Walk2 wk(threadIdx.x, co.n);
-    for (int i = threadIdx.x; i < ri.n * co.n; i += SP_BLOCK, wk.next()) {
+    WalkB<NT_> wk(threadIdx.x, co.n);
+    for (int i = threadIdx.x; i < ri.n * co.n; i += NT_, wk.next()) {
       const int r = wk.r, X = co.lo + wk.c;
       int ix[5];
 #pragma unroll
@@ -1265,8 +1342,8 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
       }
     }
     __syncthreads();
-    Walk2 wk2(threadIdx.x, co.n);
-    for (int i = threadIdx.x; i < ro.n * co.n; i += SP_BLOCK, wk2.next()) {
+    WalkB<NT_> wk2(threadIdx.x, co.n);
+    for (int i = threadIdx.x; i < ro.n * co.n; i += NT_, wk2.next()) {
       const int r = wk2.r, c = wk2.c, Y = ro.lo + r;
       int iy[5];
 #pragma unroll
@@ -1288,8 +1365,8 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
   if (has1 || has2)
     reduce(L.x1, cg1.n, rg1, cg1, 0, &fb[0][0], CA_T, rg0, cg0, sd.Hl[cm - 1], sd.Wl[cm - 1]);
   if (has0) {
-    Walk2 wk(threadIdx.x, J.tw);
-    for (int i = threadIdx.x; i < J.th * J.tw; i += SP_BLOCK, wk.next())
+    WalkB<NT_> wk(threadIdx.x, J.tw);
+    for (int i = threadIdx.x; i < J.th * J.tw; i += NT_, wk.next())
 #pragma unroll
       for (int j = 0; j < NC; ++j) fb[j][wk.r * CA_T + wk.c] += dyn[j * CS + L.x0 + i];
     __syncthreads();
@@ -1310,7 +1387,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
       wmn = wave_reduce<OpMin>(valid ? v : INFINITY);
       wmx = wave_reduce<OpMax>(valid ? v : -INFINITY);
     }
-    if (lane == 0) {
+    if (lane == 0 && w < 4) {
       wacc[w][j][0] = wmn;
       wacc[w][j][1] = wmx;
       wacc[w][j][2] = act ? wmx : 0.f;
@@ -1325,6 +1402,8 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csapply(const Job* __restrict__ jo
     out[2] = (wacc[0][j][2] + wacc[1][j][2]) + (wacc[2][j][2] + wacc[3][j][2]);
   }
 }
+
+#pragma clang diagnostic pop
 
 // ---------------------------------------------------------------- reduced-map path
 // N(.) is affine in F on every map and REDUCE is linear with weights summing to one, so
@@ -3409,16 +3488,20 @@ hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, co
       else
         hipLaunchKernelGGL(k_csmix<true>, g, b, 0, st, jobs, sds, ios, io);
       break;
-    case JOB_CSAPPLY:   // flag: channels per workgroup
-      if (flag == 8)
-        SP_STEP_KERNEL(k_csapply<8);
-      else if (flag == 4)
-        SP_STEP_KERNEL(k_csapply<4);
-      else if (flag == 2)
-        SP_STEP_KERNEL(k_csapply<2);
+    case JOB_CSAPPLY: {   // flag: channels per workgroup | pair set << 8
+      const int nc = flag & 0xff, set = flag >> 8;
+      if (nc == 8)
+        SP_STEP_KERNEL(k_csapply<8, 0);
+      else if (nc == 4)
+        SP_STEP_KERNEL(k_csapply<4, 0);
+      else if (nc == 2)
+        SP_STEP_KERNEL(k_csapply<2, 0);
+      else if (set == 1)
+        SP_STEP_KERNEL_B(CA_NT1, k_csapply<1, 1);
       else
-        SP_STEP_KERNEL(k_csapply<1);
+        SP_STEP_KERNEL(k_csapply<1, 0);
       break;
+    }
     case JOB_CONSP:
       if (ios)
         hipLaunchKernelGGL(k_consp<false>, g, b, 0, st, jobs, sds, ios, io);
@@ -3557,7 +3640,8 @@ hipError_t sp_csapply_reserve_lds(size_t bytes) {
   if (bytes <= 65536) return hipSuccess;
   const void* fns[] = {
 #define SP_BOTH(...) reinterpret_cast<const void*>(&__VA_ARGS__, false>), reinterpret_cast<const void*>(&__VA_ARGS__, true>)
-      SP_BOTH(k_csapply<1), SP_BOTH(k_csapply<2), SP_BOTH(k_csapply<4), SP_BOTH(k_csapply<8),
+      SP_BOTH(k_csapply<1, 0), SP_BOTH(k_csapply<1, 1), SP_BOTH(k_csapply<2, 0), SP_BOTH(k_csapply<4, 0),
+      SP_BOTH(k_csapply<8, 0),
       SP_BOTH(k_csg<1, 0),  SP_BOTH(k_csg<2, 0),  SP_BOTH(k_csg<4, 0),  SP_BOTH(k_csg<8, 0),
       SP_BOTH(k_csg1<1),    SP_BOTH(k_csg1<2),    SP_BOTH(k_csg1<4),    SP_BOTH(k_csg1<8)};
 #undef SP_BOTH
