@@ -62,13 +62,17 @@ bool gpath_ok(const Geo& g) {
 }
 
 // Pair set the reduced-map kernel is compiled for (see cg_set1_r/d): 1 when the
-// geometry's pairs are, in order, (c_max - c, s - c) = (1,2), (1,3), (0,2), (0,3); 0 reads
-// the pairs at run time.
+// geometry's pairs are, in order, (c_max - c, s - c) = (1,2), (1,3), (0,2), (0,3); 2 when
+// they are (1,3), (1,4), (0,3); 0 reads the pairs at run time.
 int csg_set(const Geo& g) {
-  if (!gpath_ok(g) || g.n_pairs != CG_SET1_N) return 0;
-  for (int p = 0; p < g.n_pairs; ++p)
-    if (g.c_max - g.pc[p] != cg_set1_r(p) || g.ps[p] - g.pc[p] != cg_set1_d(p)) return 0;
-  return 1;
+  if (!gpath_ok(g)) return 0;
+  for (int set = 1; set <= 2; ++set) {
+    bool same = g.n_pairs == CG_SET1_N - (set - 1);
+    for (int p = 0; same && p < g.n_pairs; ++p)
+      same = g.c_max - g.pc[p] == cg_set1_r(p) && g.ps[p] - g.pc[p] == cg_set1_d(p) + set - 1;
+    if (same) return set;
+  }
+  return 0;
 }
 
 // The same for the across-scale sum of three centre levels.
@@ -2075,9 +2079,9 @@ int batch_build_tables(sp_batch* b) {
     return fail(SP_EHIP, "cannot reserve %zu bytes of LDS for the across-scale sum", nc * std::max(lds_a, lds_g));
   if (!css.empty()) b->phases.push_back(b->jobs.add(JOB_CSSTATS, 0, order(css), n));
   if (!csg.empty()) {
-    int set = 1;
+    int set = -1;   // one the streams share, or none
     for (const Geo& g : b->geo)
-      if (gpath_ok(g)) set = std::min(set, csg_set(g));
+      if (gpath_ok(g)) set = set < 0 || set == csg_set(g) ? csg_set(g) : 0;
     b->phases.push_back(b->jobs.add(JOB_CSG, nc | (set << 8), order(csg), n));
     b->phases.back().lds = nc * lds_g;
   }

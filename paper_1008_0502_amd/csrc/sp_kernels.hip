@@ -1774,8 +1774,10 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg(const Job* __restrict__ jobs,
   }
 }
 
-// The reduced-map job for pair set 1 ((r, d) = (1,2), (1,3), (0,2), (0,3) in the stream's
-// pair order; the default pairs), with a fixed geometry.  The region one level below c_max
+// The reduced-map job for the NP first of the pairs (r, d) = (1,D0), (1,D0+1), (0,D0), (0,D0+1), in
+// the stream's pair order, with a fixed geometry: D0 = 2 and all four (set 1, the default pairs), or
+// D0 = 3 and three, where the pyramid ends below the last surround (set 2; a 320x240 frame 9.6 us with
+// the geometry from the description, 6.5 us so).  The region one level below c_max
 // is always the 35x35 block at (2 y0 - 2, 2 x0 - 2) and each footprint the block at the
 // region's (or the tile's) origin shifted down by d levels, staged from coordinates clamped
 // into their level: a replicated row or column holds exactly the value that clamp-to-edge
@@ -1788,19 +1790,28 @@ constexpr int T = SP_CA_T;             // c_max tile edge
 constexpr int N1 = 2 * T + 3;          // region edge one level below c_max
 constexpr int PW = CG_PW1;             // LDS row stride of the region: whole quads, region column cc at cc + 2
 constexpr int X1N = N1 * PW;
-constexpr int FN = 11 * 11 + 7 * 7 + 5 * 5 + 3 * 3;   // footprints of pairs 0..3, back to back
 constexpr int FQN = N1 * N1;
 constexpr int TTN = N1 * T;            // >= 11 * N1, the widest footprint table
-constexpr int PER_CH = X1N + T * T + FN + FQN + TTN;
-__host__ __device__ constexpr int fe(int p) { return p == 0 ? 11 : (p == 1 ? 7 : (p == 2 ? 5 : 3)); }
-__host__ __device__ constexpr int fo(int p) { return p == 0 ? 0 : (p == 1 ? 121 : (p == 2 ? 170 : 195)); }
+// Pair p's surround is D0 + (p & 1) levels above; its footprint's edge, and where its block starts.
+template <int D0, int NP>
+struct Foots {
+  static constexpr int d(int p) { return D0 + (p & 1); }
+  static constexpr int fe(int p) { return p < 2 ? (2 * T >> d(p)) + 3 : (T >> d(p)) + 1; }
+  static constexpr int fo(int p) { return p == 0 ? 0 : fo(p - 1) + fe(p - 1) * fe(p - 1); }
+  static constexpr int FN = fo(NP);    // footprints of the pairs, back to back
+};
 }  // namespace cg1
 
-template <int NC, bool ONE>
+template <int NC, int D0, int NP, bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_csg1(const Job* __restrict__ jobs,
                                                    const StreamDesc* __restrict__ sds,
                                                    const StepIO* __restrict__ ios, StepIO io0) {
   using namespace cg1;
+  using FT_ = Foots<D0, NP>;
+  constexpr int FN = FT_::FN;
+  auto fe = [](int p) constexpr { return FT_::fe(p); };
+  auto fo = [](int p) constexpr { return FT_::fo(p); };
+  static_assert(TTN >= FT_::fe(0) * N1 && FT_::fe(0) * FT_::fe(0) <= SP_BLOCK, "tables and footprints fit");
   static_assert(PW == 40 && N1 == 35 && T == 16, "layout of the fixed-geometry job");
   extern __shared__ __align__(16) float dyn[];
   __shared__ float4 rtab[2][N1], ctab[2][N1];   // pairs 0, 1: taps (i0, i1 as offsets, w, 1 - w)
@@ -1873,8 +1884,8 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg1(const Job* __restrict__ jobs,
   }
   // footprints, one pair at a time (uniform level and base; lane = element)
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const int d = 2 + (p & 1), s = (p < 2 ? c1 : cm) + d;
+  for (int p = 0; p < NP; ++p) {
+    const int d = FT_::d(p), s = (p < 2 ? c1 : cm) + d;
     const int oy = (p < 2 ? ry0 : y0) >> d, ox = (p < 2 ? rx0 : x0) >> d;
     const int Hs = sd.Hl[s], Ws = sd.Wl[s];
     if (tid < fe(p) * fe(p)) {
@@ -1888,7 +1899,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg1(const Job* __restrict__ jobs,
     // taps of the region's rows (which = 0, 2) and columns (1, 3) for pairs 0 and 1, at the
     // clamped coordinate, relative to the footprint's first (unclamped) row or column
     const int which = tid / N1, k = tid - which * N1;
-    const int p = which >> 1, d = 2 + p, s = c1 + d;
+    const int p = which >> 1, d = D0 + p, s = c1 + d;
     const bool col = which & 1;
     const int o = col ? rx0 : ry0;
     const Tap t = bilinear_tap(clampi(o + k, 0, (col ? W1 : H1) - 1), d, col ? sd.Wl[s] : sd.Hl[s]);
@@ -1907,7 +1918,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg1(const Job* __restrict__ jobs,
   const size_t plane = (size_t)Hm * Wm;
   const int lane = lane_id(), w = wave_id();
   const int sy = (lane >> 2) & 3, sx = lane & 3;
-  // ---- pairs 2 and 3 (c = c_max): one wavefront per map covers the tile's four 8x8
+  // ---- pairs 2 on (c = c_max): one wavefront per map covers the tile's four 8x8
   // blocks (a 2x2 quad per lane, DPP inside each 16-lane row)
   {
     const int blk = lane >> 4, by = blk >> 1, bx = blk & 1;
@@ -1915,8 +1926,8 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg1(const Job* __restrict__ jobs,
     const bool bvalid = 8 * by < J.th && 8 * bx < J.tw;   // the lane's 8x8 block lies in the tile
     int m = 0;
 #pragma unroll
-    for (int p = 2; p < 4; ++p) {
-      const int d = 2 + (p & 1), s = cm + d;
+    for (int p = 2; p < NP; ++p) {
+      const int d = FT_::d(p), s = cm + d;
       int yl[2], xl[2];
       Tap ty[2], tx[2];
 #pragma unroll
@@ -1973,7 +1984,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg1(const Job* __restrict__ jobs,
     const int rc = tid & (T - 1), rq = tid >> 4;     // reduction: tile column rc, row group rq
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
-      constexpr int NTAB[2] = {fe(0) * N1, fe(1) * N1};
+      constexpr int NTAB[2] = {FT_::fe(0) * N1, FT_::fe(1) * N1};
 #pragma unroll
       for (int e0 = 0; e0 < NTAB[p]; e0 += SP_BLOCK) {
         const int e = e0 + tid;
@@ -2078,7 +2089,7 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csg1(const Job* __restrict__ jobs,
 
 // N(.) parameters of the eight maps of a pair from their per-tile partials, one wavefront:
 // lanes 8k..8k+7 take map k, lane 8k+j its tiles j, j+8, j+16, ...  The first 80 tiles are
-// requested at once by load(); finish() takes any further tiles one at a time, then the
+// requested at once by load(); finish() takes any further tiles in rounds of 80, then the
 // eight lanes of each map combine by DPP in a fixed order, so the parameters are
 // reproducible bit for bit.  Other loads can be issued between the two calls.
 struct Part3 { float mn, mx, sb; };   // one tile's (min, max, sum of block maxima), 12 bytes
@@ -3463,13 +3474,22 @@ hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, co
       const int nc = flag & 0xff, set = flag >> 8;
       if (set == 1) {
         if (nc == 8)
-          SP_STEP_KERNEL(k_csg1<8);
+          SP_STEP_KERNEL(k_csg1<8, 2, 4);
         else if (nc == 4)
-          SP_STEP_KERNEL(k_csg1<4);
+          SP_STEP_KERNEL(k_csg1<4, 2, 4);
         else if (nc == 2)
-          SP_STEP_KERNEL(k_csg1<2);
+          SP_STEP_KERNEL(k_csg1<2, 2, 4);
         else
-          SP_STEP_KERNEL(k_csg1<1);
+          SP_STEP_KERNEL(k_csg1<1, 2, 4);
+      } else if (set == 2) {
+        if (nc == 8)
+          SP_STEP_KERNEL(k_csg1<8, 3, 3);
+        else if (nc == 4)
+          SP_STEP_KERNEL(k_csg1<4, 3, 3);
+        else if (nc == 2)
+          SP_STEP_KERNEL(k_csg1<2, 3, 3);
+        else
+          SP_STEP_KERNEL(k_csg1<1, 3, 3);
       } else {
         if (nc == 8)
           SP_STEP_KERNEL(k_csg<8, 0);
@@ -3643,7 +3663,8 @@ hipError_t sp_csapply_reserve_lds(size_t bytes) {
       SP_BOTH(k_csapply<1, 0), SP_BOTH(k_csapply<1, 1), SP_BOTH(k_csapply<2, 0), SP_BOTH(k_csapply<4, 0),
       SP_BOTH(k_csapply<8, 0),
       SP_BOTH(k_csg<1, 0),  SP_BOTH(k_csg<2, 0),  SP_BOTH(k_csg<4, 0),  SP_BOTH(k_csg<8, 0),
-      SP_BOTH(k_csg1<1),    SP_BOTH(k_csg1<2),    SP_BOTH(k_csg1<4),    SP_BOTH(k_csg1<8)};
+      SP_BOTH(k_csg1<1, 2, 4), SP_BOTH(k_csg1<2, 2, 4), SP_BOTH(k_csg1<4, 2, 4), SP_BOTH(k_csg1<8, 2, 4),
+      SP_BOTH(k_csg1<1, 3, 3), SP_BOTH(k_csg1<2, 3, 3), SP_BOTH(k_csg1<4, 3, 3), SP_BOTH(k_csg1<8, 3, 3)};
 #undef SP_BOTH
   for (const void* f : fns) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);

@@ -1,6 +1,6 @@
-"""Across-scale sums built for a known set of pairs (one channel a workgroup) against the general
-ones (two channels) bit for bit, and against the FP64 oracle with the bar of the parity tests: frames
-whose c_max map is below a tile, a tile and an odd remainder, several tiles."""
+"""Across-scale sums built for a known set of pairs, one channel a workgroup against two (with three
+centre levels the general job) bit for bit, and against the FP64 oracle with the bar of the parity
+tests: frames whose c_max map is below a tile, a tile and an odd remainder, several tiles."""
 import numpy as np
 import pytest
 
