@@ -2158,7 +2158,7 @@ struct PairNp {
 // F-bar_k on a 16x16 c_max tile = sum over pairs of N(reduced map), all 8 channels; then
 // its partial statistics.  Rows of whole aligned quads: wavefront w takes channels 2 w and 2 w + 1,
 // a lane four pixels of a row, so a map of the tile is one 16-byte load a lane (16 streams of 640x480
-// 14.0 -> 11.8 us, a 160x120 step 5.2 -> 4.5); otherwise a wavefront takes an 8x8 block of every
+// 14.0 -> 12-13 us, a 160x120 step 5.2 -> 4.6); otherwise a wavefront takes an 8x8 block of every
 // channel, a pixel a lane.  The sums and their order are the same.
 template <bool ONE>
 __global__ __launch_bounds__(SP_BLOCK) void k_csmix(const Job* __restrict__ jobs,
