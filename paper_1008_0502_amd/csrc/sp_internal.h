@@ -229,10 +229,11 @@ __host__ __device__ constexpr int csapply_foot_cap(int r, int d) {
   return e * e;
 }
 
-// of pairs (r, d) = (c_max - c, s - c)
-__host__ __device__ constexpr CaLayout csapply_layout_rd(const int* r, const int* d, int n_pairs) {
+// of pairs (r(p), d(p)) = (c_max - c, s - c)
+template <class PairR, class PairD>
+__host__ __device__ constexpr CaLayout csapply_layout_of(PairR r, PairD d, int n_pairs) {
   bool has[3] = {false, false, false};
-  for (int p = 0; p < n_pairs; ++p) has[r[p]] = true;
+  for (int p = 0; p < n_pairs; ++p) has[r(p)] = true;
   const int n1 = 2 * SP_CA_T + 3, n2 = 2 * n1 + 3;
   CaLayout L{};
   int o = 0;
@@ -245,17 +246,12 @@ __host__ __device__ constexpr CaLayout csapply_layout_rd(const int* r, const int
   L.tm = o;
   o += has[2] ? n2 * n1 : ((has[1]) ? n1 * SP_CA_T : 0);
   L.foot0 = o;
-  for (int p = 0; p < n_pairs; ++p) o += csapply_foot_cap(r[p], d[p]);
+  for (int p = 0; p < n_pairs; ++p) o += csapply_foot_cap(r(p), d(p));
   L.total = o;
   return L;
 }
 __host__ __device__ inline CaLayout csapply_layout(const int32_t* pc, const int32_t* ps, int n_pairs, int c_max) {
-  int r[SP_MAXP], d[SP_MAXP];
-  for (int p = 0; p < n_pairs; ++p) {
-    r[p] = c_max - pc[p];
-    d[p] = ps[p] - pc[p];
-  }
-  return csapply_layout_rd(r, d, n_pairs);
+  return csapply_layout_of([=](int p) { return c_max - pc[p]; }, [=](int p) { return ps[p] - pc[p]; }, n_pairs);
 }
 // Pair set 1 of the across-scale sum: centre levels c_max - 2 .. c_max, each with the surrounds 3
 // and 4 levels above, as (r, d) in the stream's pair order.

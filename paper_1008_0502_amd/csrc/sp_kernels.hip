@@ -1088,6 +1088,12 @@ __device__ __forceinline__ Range finer_range(Range r, int n_finer) {
   return Range{lo, hi - lo + 1};
 }
 
+// The range of level r, chosen value by value (a choice among the structures themselves keeps
+// them in scratch memory).
+__device__ __forceinline__ Range pick(int r, Range a, Range b, Range c) {
+  return Range{r == 0 ? a.lo : (r == 1 ? b.lo : c.lo), r == 0 ? a.n : (r == 1 ? b.n : c.n)};
+}
+
 // One pair of a centre level as the per-pixel loop needs it.  Its footprint sits at the
 // same offset in the LDS block of every channel of the workgroup.
 struct CaPair {
@@ -1100,7 +1106,7 @@ struct CaPair {
 // to every channel.  Each channel owns a block of L.total floats of dynamic LDS with the
 // layout of csapply_layout.  A flat map has zero N parameters (inv = scale = 0), which
 // adds exactly 0.
-// SET: the pairs as compile-time (r, d) (set 1, one channel a workgroup), else read from the stream.
+// SET: the pairs as compile-time (r, d) (set 1, one or two channels a workgroup), else read from the stream.
 // With the set known every loop over pairs unrolls, offsets are constants, and the bilinear taps of
 // the regions' rows and columns are formed once per workgroup, which takes 512 threads: the uniform
 // geometry, a thousand scalar instructions in every wavefront, and the taps per pixel and pair bound
@@ -1120,7 +1126,6 @@ __global__ __launch_bounds__(SET ? CA_NT1 : SP_BLOCK) void k_csapply(const Job* 
   __shared__ float wacc[4][NC][3];
   constexpr int NT_ = SET ? CA_NT1 : SP_BLOCK;
   constexpr bool TAB = SET != 0;
-  static_assert(NC == 1 || !TAB, "one channel with the tables");
   constexpr int E0 = CA_T, E1 = 2 * E0 + 3, E2 = 2 * E1 + 3;   // region edges
   // taps per pair slot and line of the regions (levels 0, 1, 2 back to back): rows (LDS offsets of
   // the two footprint rows, weights), columns (the two footprint columns, weights)
@@ -1134,9 +1139,7 @@ __global__ __launch_bounds__(SET ? CA_NT1 : SP_BLOCK) void k_csapply(const Job* 
   auto pd = [&](int p) { return SET ? ca_set1_d(p) : sd.ps[p] - sd.pc[p]; };
   CaLayout L;
   if constexpr (SET != 0) {
-    constexpr int R[CA_SET1_N] = {ca_set1_r(0), ca_set1_r(1), ca_set1_r(2), ca_set1_r(3), ca_set1_r(4), ca_set1_r(5)};
-    constexpr int D[CA_SET1_N] = {ca_set1_d(0), ca_set1_d(1), ca_set1_d(2), ca_set1_d(3), ca_set1_d(4), ca_set1_d(5)};
-    constexpr CaLayout LS = csapply_layout_rd(R, D, CA_SET1_N);
+    constexpr CaLayout LS = csapply_layout_of(ca_set1_r, ca_set1_d, CA_SET1_N);
     L = LS;
   } else {
     L = csapply_layout(sd.pc, sd.ps, sd.n_pairs, cm);
@@ -1201,8 +1204,7 @@ __global__ __launch_bounds__(SET ? CA_NT1 : SP_BLOCK) void k_csapply(const Job* 
   // before it)
   auto fill = [&](int p, int q, int off) {
     const int r = pr(p), c = cm - r, s = c + pd(p);
-    const Range rr = (r == 0) ? rg0 : ((r == 1) ? rg1 : rg2);
-    const Range cc = (r == 0) ? cg0 : ((r == 1) ? cg1 : cg2);
+    const Range rr = pick(r, rg0, rg1, rg2), cc = pick(r, cg0, cg1, cg2);
     const Foot f = footprint(rr.lo, rr.n, cc.lo, cc.n, s - c, sd.Hl[s], sd.Wl[s]);
     CaPair& P = cpt[r][q];
     P.off = off;
@@ -1251,7 +1253,7 @@ __global__ __launch_bounds__(SET ? CA_NT1 : SP_BLOCK) void k_csapply(const Job* 
       const int q = i / (E0 + E1 + E2), e = i - q * (E0 + E1 + E2);
       const int r = e < E0 ? 0 : (e < E0 + E1 ? 1 : 2), k = e - (r == 0 ? 0 : (r == 1 ? E0 : E0 + E1));
       if (q >= ncp[r]) continue;
-      const Range rr = (r == 0) ? rg0 : ((r == 1) ? rg1 : rg2), cc = (r == 0) ? cg0 : ((r == 1) ? cg1 : cg2);
+      const Range rr = pick(r, rg0, rg1, rg2), cc = pick(r, cg0, cg1, cg2);
       const CaPair& P = cpt[r][q];
       if (k < rr.n) {
         const Tap t = bilinear_tap(rr.lo + k, P.d, P.Hs);
@@ -1272,20 +1274,28 @@ __global__ __launch_bounds__(SET ? CA_NT1 : SP_BLOCK) void k_csapply(const Job* 
       const int e0 = r == 0 ? 0 : (r == 1 ? E0 : E0 + E1);
       WalkB<NT_> wk(threadIdx.x, cc.n);
       for (int i = threadIdx.x; i < n; i += NT_, wk.next()) {
-        const float xc = dyn[xoff + i];
-        float acc = 0.f;
+        float xc[NC], acc[NC];
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+          xc[j] = dyn[j * CS + xoff + i];
+          acc[j] = 0.f;
+        }
 #pragma unroll
         for (int q = 0; q < nq; ++q) {
           const float4 ty = tabr[q][e0 + wk.r], tx = tabc[q][e0 + wk.c];
-          const float* b0 = dyn + __float_as_int(ty.x);
-          const float* b1 = dyn + __float_as_int(ty.y);
           const int x0 = __float_as_int(tx.x), x1 = __float_as_int(tx.y);
-          const float top = fmaf(tx.z, b0[x1], tx.w * b0[x0]);
-          const float bot = fmaf(tx.z, b1[x1], tx.w * b1[x0]);
-          const float v = fabsf(xc - fmaf(ty.z, bot, ty.w * top));
-          acc = fmaf((v - cnp[r][q][0][0]) * cnp[r][q][0][1], cnp[r][q][0][2], acc);
+#pragma unroll
+          for (int j = 0; j < NC; ++j) {
+            const float* b0 = dyn + j * CS + __float_as_int(ty.x);
+            const float* b1 = dyn + j * CS + __float_as_int(ty.y);
+            const float top = fmaf(tx.z, b0[x1], tx.w * b0[x0]);
+            const float bot = fmaf(tx.z, b1[x1], tx.w * b1[x0]);
+            const float v = fabsf(xc[j] - fmaf(ty.z, bot, ty.w * top));
+            acc[j] = fmaf((v - cnp[r][q][j][0]) * cnp[r][q][j][1], cnp[r][q][j][2], acc[j]);
+          }
         }
-        dyn[xoff + i] = acc;
+#pragma unroll
+        for (int j = 0; j < NC; ++j) dyn[j * CS + xoff + i] = acc[j];
       }
       return;
     }
@@ -3514,6 +3524,8 @@ hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, co
         SP_STEP_KERNEL(k_csapply<8, 0);
       else if (nc == 4)
         SP_STEP_KERNEL(k_csapply<4, 0);
+      else if (nc == 2 && set == 1)
+        SP_STEP_KERNEL_B(CA_NT1, k_csapply<2, 1);
       else if (nc == 2)
         SP_STEP_KERNEL(k_csapply<2, 0);
       else if (set == 1)
@@ -3660,7 +3672,7 @@ hipError_t sp_csapply_reserve_lds(size_t bytes) {
   if (bytes <= 65536) return hipSuccess;
   const void* fns[] = {
 #define SP_BOTH(...) reinterpret_cast<const void*>(&__VA_ARGS__, false>), reinterpret_cast<const void*>(&__VA_ARGS__, true>)
-      SP_BOTH(k_csapply<1, 0), SP_BOTH(k_csapply<1, 1), SP_BOTH(k_csapply<2, 0), SP_BOTH(k_csapply<4, 0),
+      SP_BOTH(k_csapply<1, 0), SP_BOTH(k_csapply<1, 1), SP_BOTH(k_csapply<2, 0), SP_BOTH(k_csapply<2, 1), SP_BOTH(k_csapply<4, 0),
       SP_BOTH(k_csapply<8, 0),
       SP_BOTH(k_csg<1, 0),  SP_BOTH(k_csg<2, 0),  SP_BOTH(k_csg<4, 0),  SP_BOTH(k_csg<8, 0),
       SP_BOTH(k_csg1<1, 2, 4), SP_BOTH(k_csg1<2, 2, 4), SP_BOTH(k_csg1<4, 2, 4), SP_BOTH(k_csg1<8, 2, 4),

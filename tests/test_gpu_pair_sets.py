@@ -1,6 +1,7 @@
-"""Across-scale sums built for a known set of pairs, one channel a workgroup against two (with three
-centre levels the general job) bit for bit, and against the FP64 oracle with the bar of the parity
-tests: frames whose c_max map is below a tile, a tile and an odd remainder, several tiles."""
+"""Across-scale sums built for a known set of pairs (three centre levels with surrounds 3 and 4 levels
+above; three pairs of two centre levels) and the general ones (surrounds 2 and 3 above): one channel a
+workgroup against two bit for bit, and against the FP64 oracle with the bar of the parity tests; frames
+whose c_max map is below a tile, a tile and an odd remainder, several tiles."""
 import numpy as np
 import pytest
 
@@ -13,10 +14,12 @@ from test_gpu_variants import _torch
 pytestmark = pytest.mark.gpu
 
 DEEP = dict(depth=9, centers=(2, 3, 4), deltas=(3, 4))
+GENERAL = dict(depth=9, centers=(2, 3, 4), deltas=(2, 3))
 MID = dict(depth=6, centers=(2, 3), deltas=(3, 4))
 
 
 @pytest.mark.parametrize("levels,H,W", [(DEEP, 256, 256), (DEEP, 273, 531), (DEEP, 600, 400), (DEEP, 257, 1040),
+                                        (GENERAL, 273, 531), (GENERAL, 256, 256),
                                         (MID, 97, 131), (MID, 128, 256), (MID, 240, 320), (MID, 259, 133)])
 def test_known_and_general(levels, H, W):
     torch = _torch()
