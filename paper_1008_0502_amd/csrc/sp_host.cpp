@@ -978,10 +978,10 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
       }
     } else {
       // upload static tables
+      std::vector<StepIO> rio(c->cap);   // read until the stream is waited for
       hipError_t e = hipMemcpyAsync(c->d_sd, &c->h_sd, sizeof(StreamDesc), hipMemcpyHostToDevice, c->stream);
       if (e == hipSuccess && c->cap > 0) {
         e = hipMemcpyAsync(c->d_sd + 1, c->h_slots.data(), sizeof(StreamDesc) * c->CH, hipMemcpyHostToDevice, c->stream);
-        std::vector<StepIO> rio(c->cap);
         const size_t plane = (size_t)Hc * Wc;
         for (int t = 0; t < c->cap; ++t) {
           std::memset(&rio[t], 0, sizeof(StepIO));
