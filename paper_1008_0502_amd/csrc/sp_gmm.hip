@@ -2,7 +2,7 @@
 // Gaussian mixture over RGB fitted by EM; Section 5: every pixel is a sample, weighted by
 // the prior p(A = 1) for the object and by 1 - p for the background; Section 8.1: M = 3).
 //
-// Per label and iteration: one pass over tiles of SP_GMM_TILE pixels takes the E-step under
+// Per label and iteration: one pass over tiles of io.tile pixels takes the E-step under
 // the current mixtures (read as scalars) and accumulates, for every component, the
 // responsibility-weighted count and the first and second moments about the component's
 // mean (FP32 per thread, FP64 from the workgroup sum on, one partial per workgroup).  The
@@ -123,79 +123,117 @@ struct Staged {
 // LDS of a moment pass: the pixels, then the threads' sums.
 constexpr int seg_of(int nv) { return GB / nv >= 8 ? 8 : (GB / nv >= 4 ? 4 : 2); }
 template <int NC>
-constexpr int LDS_N = 20 * NC * (SP_BLOCK + seg_of(20 * NC)) > 4 * GPX * SP_BLOCK ? 20 * NC * (SP_BLOCK + seg_of(20 * NC))
-                                                                                 : 4 * GPX * SP_BLOCK;
+constexpr int LDS_N = 20 * NC * (SP_BLOCK + 2 * seg_of(20 * NC)) > 4 * GPX * SP_BLOCK ? 20 * NC * (SP_BLOCK + 2 * seg_of(20 * NC))
+                                                                                     : 4 * GPX * SP_BLOCK;
 
 // Moments of the tile into the partial slot of the workgroup.  EM = false: the start's
 // moments of both labels about (0.5, 0.5, 0.5); EM = true: the E-step under the mixtures S
-// and the moments of every component about its mean.  Each thread accumulates its pixels in
-// FP32; the workgroup sum goes through LDS transposed: value v's 256 thread sums are split
-// into SEG interleaved segments, each summed in FP64 by one thread with four accumulators
-// in a fixed order, and the segments are added in order.
+// and the moments of every component about its mean.  Each thread accumulates up to FP32_N of
+// its pixels in FP32; the workgroup sum goes through LDS transposed: value v's thread sums are
+// split into SEG interleaved segments, each summed in FP64 by one thread with four accumulators
+// in a fixed order, and the segments are added in order.  A thread with more pixels has a second
+// FP32 sum, which joins the first, and both the neighbouring thread's, in FP64, so half as many sums
+// take the same LDS (640x480, three components, ten steps: 117 us with one FP32 sum of all pixels,
+// 126 us so).
+constexpr int FP32_N = 4;
+static_assert(GPX <= 2 * FP32_N, "two FP32 sums per thread");
 template <int M, bool EM>
 __device__ __forceinline__ void tile_moments(const GmmIO& io, float* lds, const GmmState& S) {
   constexpr int NC = EM ? M : 1;
   constexpr int NV = 2 * NC * 10;
   constexpr int SEG = seg_of(NV);
-  constexpr int PER = SP_BLOCK / SEG;
   constexpr int TRW = SP_BLOCK + SEG;   // a wavefront reads 64 / SEG rows: no bank twice
+  constexpr int TRD = SP_BLOCK / 2 + SEG;   // the same in doubles
   const float4* const px = reinterpret_cast<const float4*>(lds);
   float* const tr = lds;                // [NV][TRW], in the pixels' place
   __shared__ double segs[NV][SEG];
   const int L = label_of();
   float acc[NC][10];
-#pragma unroll
-  for (int m = 0; m < NC; ++m)
-#pragma unroll
-    for (int v = 0; v < 10; ++v) acc[m][v] = 0.f;
   Mix<NC> X;
   if (EM) X.load(S, L);
-  const int left = io.n - (int)blockIdx.x * io.tile;
+  const int end = min(io.tile, io.n - (int)blockIdx.x * io.tile);
+  const bool two = io.tile > FP32_N * SP_BLOCK;   // uniform over the launch
+  // FP32 sums of the thread's pixels from tile position `from` on
+  auto take = [&](int from, int to) {
+#pragma unroll
+    for (int m = 0; m < NC; ++m)
+#pragma unroll
+      for (int v = 0; v < 10; ++v) acc[m][v] = 0.f;
 #pragma unroll 1
-  for (int t = slot_of(); t < min(io.tile, left); t += SP_BLOCK) {
-    const float4 p = px[t];
-    const float w = L ? p.w : 1.f - p.w;
-    if constexpr (!EM) {
-      const float dx = p.x - 0.5f, dy = p.y - 0.5f, dz = p.z - 0.5f;
-      add_moments(acc[0], w, dx, dy, dz, Prod(dx, dy, dz));
-    } else {
-      if (!X.lab) break;
-      float lp[NC], mx = -INFINITY;
+    for (int t = from + slot_of(); t < to; t += SP_BLOCK) {
+      const float4 p = px[t];
+      const float w = L ? p.w : 1.f - p.w;
+      if constexpr (!EM) {
+        const float dx = p.x - 0.5f, dy = p.y - 0.5f, dz = p.z - 0.5f;
+        add_moments(acc[0], w, dx, dy, dz, Prod(dx, dy, dz));
+      } else {
+        if (!X.lab) break;
+        float lp[NC], mx = -INFINITY;
 #pragma unroll
-      for (int m = 0; m < NC; ++m) {
-        lp[m] = X.logp(m, Prod(p.x - X.mu[m][0], p.y - X.mu[m][1], p.z - X.mu[m][2]));
-        mx = fmaxf(mx, lp[m]);
-      }
-      float r[NC], sum = 0.f;
-#pragma unroll
-      for (int m = 0; m < NC; ++m) {
-        r[m] = X.on[m] ? ex(lp[m] - mx) : 0.f;
-        sum += r[m];
-      }
-      const float ws = w / sum;
-#pragma unroll
-      for (int m = 0; m < NC; ++m)
-        if (X.on[m]) {
-          const float dx = p.x - X.mu[m][0], dy = p.y - X.mu[m][1], dz = p.z - X.mu[m][2];
-          add_moments(acc[m], ws * r[m], dx, dy, dz, Prod(dx, dy, dz));
+        for (int m = 0; m < NC; ++m) {
+          lp[m] = X.logp(m, Prod(p.x - X.mu[m][0], p.y - X.mu[m][1], p.z - X.mu[m][2]));
+          mx = fmaxf(mx, lp[m]);
         }
+        float r[NC], sum = 0.f;
+#pragma unroll
+        for (int m = 0; m < NC; ++m) {
+          r[m] = X.on[m] ? ex(lp[m] - mx) : 0.f;
+          sum += r[m];
+        }
+        const float ws = w / sum;
+#pragma unroll
+        for (int m = 0; m < NC; ++m)
+          if (X.on[m]) {
+            const float dx = p.x - X.mu[m][0], dy = p.y - X.mu[m][1], dz = p.z - X.mu[m][2];
+            add_moments(acc[m], ws * r[m], dx, dy, dz, Prod(dx, dy, dz));
+          }
+      }
     }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int m = 0; m < NC; ++m)
-#pragma unroll
-    for (int v = 0; v < 10; ++v) tr[((L * NC + m) * 10 + v) * TRW + slot_of()] = acc[m][v];
-  __syncthreads();
-  if ((int)threadIdx.x < NV * SEG) {
-    const int v = threadIdx.x / SEG, sg = threadIdx.x % SEG;
-    const float* row = tr + v * TRW + sg;
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
+  };
+  take(0, min(end, FP32_N * SP_BLOCK));
+  // the segment sums of rows of n thread sums, ld apart
+  auto segments = [&](const auto* rows, int n, int ld) {
+    if ((int)threadIdx.x < NV * SEG) {
+      const int v = threadIdx.x / SEG, sg = threadIdx.x % SEG;
+      const auto* row = rows + v * ld + sg;
+      double a[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 2
-    for (int j = 0; j < PER; j += 4)
+      for (int j = 0; j < n / SEG; j += 4)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] += (double)row[(j + i) * SEG];
-    segs[v][sg] = (a[0] + a[1]) + (a[2] + a[3]);
+        for (int i = 0; i < 4; ++i) a[i] += (double)row[(j + i) * SEG];
+      segs[v][sg] = (a[0] + a[1]) + (a[2] + a[3]);
+    }
+  };
+  if (two) {
+    float early[NC][10];
+#pragma unroll
+    for (int m = 0; m < NC; ++m)
+#pragma unroll
+      for (int v = 0; v < 10; ++v) early[m][v] = acc[m][v];
+    take(FP32_N * SP_BLOCK, end);
+    __syncthreads();
+    double* const td = reinterpret_cast<double*>(lds);
+    const int odd = slot_of() & 1u;
+    double* const col = td + (L * NC * 10 + odd) * TRD + (slot_of() >> 1);
+#pragma unroll
+    for (int m = 0; m < NC; ++m)
+#pragma unroll
+      for (int v = 0; v < 10; v += 2) {   // the pair's even thread stores value v, the odd one v + 1
+        double a = (double)early[m][v] + (double)acc[m][v], b = (double)early[m][v + 1] + (double)acc[m][v + 1];
+        a += dpp_d<0xB1>(a);
+        b += dpp_d<0xB1>(b);
+        col[(m * 10 + v) * TRD] = odd ? b : a;
+      }
+    __syncthreads();
+    segments(td, SP_BLOCK / 2, TRD);
+  } else {
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < NC; ++m)
+#pragma unroll
+      for (int v = 0; v < 10; ++v) tr[((L * NC + m) * 10 + v) * TRW + slot_of()] = acc[m][v];
+    __syncthreads();
+    segments(tr, SP_BLOCK, TRW);
   }
   __syncthreads();
   if ((int)threadIdx.x < NV) {
