@@ -8,7 +8,7 @@
 // mean (FP32 per thread, FP64 from the workgroup sum on, one partial per workgroup).  The
 // partials are reduced in a fixed order and the new weights, means and covariances, their
 // inverses and log-normalisers fitted in FP64, one thread per label and component: by every
-// workgroup of the next pass for itself up to SP_GMM_FUSE tiles, by one workgroup in a launch
+// workgroup of the next pass for itself up to gmm_fuse tiles, by one workgroup in a launch
 // between the passes above.  The start is the weighted mean and covariance of each label's samples with
 // the means spread along the covariance's leading eigenvector.  A final pass adds psi_1 of
 // both labels to the unary costs.
@@ -168,6 +168,13 @@ __device__ __forceinline__ void tile_moments(const GmmIO& io, float* lds, const 
         add_moments(acc[0], w, dx, dy, dz, Prod(dx, dy, dz));
       } else {
         if (!X.lab) break;
+        if constexpr (NC == 1) {   // its responsibility is 1: nothing to evaluate (1920x1080 212 -> 195 us)
+          if (X.on[0]) {
+            const float dx = p.x - X.mu[0][0], dy = p.y - X.mu[0][1], dz = p.z - X.mu[0][2];
+            add_moments(acc[0], w, dx, dy, dz, Prod(dx, dy, dz));
+          }
+          continue;
+        }
         float lp[NC], mx = -INFINITY;
 #pragma unroll
         for (int m = 0; m < NC; ++m) {

@@ -828,6 +828,24 @@ void pixadj_layout(sp_ctx* c, Bump& b) {
   }
 }
 
+// Pixels of a workgroup of the colour likelihood: SP_BLOCK times as many as keep the launch at one
+// workgroup per CU, up to SP_GMM_GPX.  Above that, one or four components halve the tile while two
+// workgroups per CU are enough (540x1000, one component 132 -> 114 us, four 279 -> 269): a few CUs
+// with two full tiles held the launch up.  Two or three components take their fit inside the pass there, and more
+// workgroups cost what the balance gives (two 168 -> 172, three 195 -> 195).
+int gmm_tile(size_t n, int M) {
+  const size_t per_cu = (n + (size_t)SP_BLOCK * SP_CUS - 1) / ((size_t)SP_BLOCK * SP_CUS);
+  const bool halve = per_cu > SP_GMM_GPX && per_cu <= 2 * SP_GMM_GPX && (M == 1 || M == 4);
+  return SP_BLOCK * (int)std::min<size_t>(halve ? (per_cu + 1) / 2 : per_cu, SP_GMM_GPX);
+}
+
+// Most tiles with the fit inside the next pixel pass: every workgroup reads the moments of all of
+// them (2 M 10 doubles each) from L2, against one workgroup and a launch of its own.  Ten steps, one
+// launch a step against two: 576x1000 with three components (282 tiles) 196 against 209 us, with four
+// 333 against 280; 1280x720 (450 tiles) with one 137 against 144, two 191 against 193, three 218
+// against 223; 1500x800 (586 tiles) 214 against 179, 274 against 239, 315 against 281.
+int gmm_fuse(int M) { return M == 4 ? SP_CUS : 2 * SP_CUS; }
+
 // Phases of one stream's forward saliency map (stream index 0), appended to `js` with
 // their launch flags and LDS sizes; *nc_out receives the channels per across-scale
 // workgroup.  Contexts and the allocation-free entry point build identical tables.
@@ -938,8 +956,7 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
     c->S_scratch = b.take<float>((size_t)Hc * Wc);
     if (p->f_mode == 1) c->f_map = b.take<float>(HW);
     if (p->gmm_components > 0) {
-      const size_t per_cu = (HW + (size_t)SP_BLOCK * SP_CUS - 1) / ((size_t)SP_BLOCK * SP_CUS);
-      c->gmm_tile = SP_BLOCK * (int)std::min<size_t>(per_cu, SP_GMM_GPX);
+      c->gmm_tile = gmm_tile(HW, p->gmm_components);
       c->gmm_tiles = (int)((HW + c->gmm_tile - 1) / c->gmm_tile);
       c->gmm_state = b.take<GmmState>(2);
       c->gmm_part = b.take<double>((size_t)2 * 2 * p->gmm_components * 10 * c->gmm_tiles);
@@ -1229,7 +1246,7 @@ int sp_colour_likelihood(sp_ctx* c, const uint8_t* rgb_t, const float* prior, fl
   // Every launch that fits reads the moments and the mixtures of the one before and writes the
   // other of the two buffers.
   const size_t part_n = (size_t)2 * M * 10 * c->gmm_tiles;
-  const bool fused = c->gmm_tiles <= SP_GMM_FUSE;
+  const bool fused = c->gmm_tiles <= gmm_fuse(M);
   int moments = 0, mix = 0;   // the buffers last written
   auto launch = [&](int pass, int fit, int kind, float* out) -> int {
     io.out = out;

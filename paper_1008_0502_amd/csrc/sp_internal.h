@@ -320,14 +320,7 @@ __host__ __device__ constexpr int cg_set1_d(int p) { return 2 + (p & 1); }
 // Colour likelihood of the t-links: per label (0 background, 1 object) a mixture of up to
 // SP_GMM_MAXM Gaussians over RGB in [0, 1].
 #define SP_GMM_MAXM 4
-// Pixels of an accumulation workgroup: SP_BLOCK times as many as keep the launch at one workgroup
-// per CU (two on some of them take twice as long), from 1 to SP_GMM_GPX per thread and label.
-#define SP_GMM_GPX 8
-// Most tiles with the fit inside the next pixel pass: every workgroup reads the moments of all of
-// them (2 M 10 doubles each) from L2, against one workgroup and a launch of its own.  Ten steps with
-// three components, one launch a step against two: 160x120 (75 tiles) 81 against 97 us, 640x480 (240)
-// 116 against 133, 1280x720 (450) 207 against 203, 1920x1080 (1013) 484 against 334.
-#define SP_GMM_FUSE SP_CUS
+#define SP_GMM_GPX 8       // most pixels of an accumulation workgroup per thread and label
 struct GmmComp {           // E-step form of one component (FP32)
   float mu[3];             // mean, also the centre of the moments accumulated for it
   float P[6];              // precision: xx, xy, xz, yy, yz, zz
