@@ -846,6 +846,14 @@ int gmm_tile(size_t n, int M) {
 // against 223; 1500x800 (586 tiles) 214 against 179, 274 against 239, 315 against 281.
 int gmm_fuse(int M) { return M == 4 ? SP_CUS : 2 * SP_CUS; }
 
+// The dynamic LDS of an across-scale launch.
+int set_lds(Phase& ph, size_t bytes) {
+  ph.lds = bytes;
+  if (sp_across_reserve_lds(ph.kind, ph.flag, bytes) == hipSuccess) return SP_OK;
+  (void)hipGetLastError();
+  return fail(SP_EHIP, "cannot reserve %zu bytes of LDS for the across-scale sum", bytes);
+}
+
 // Phases of one stream's forward saliency map (stream index 0), appended to `js` with
 // their launch flags and LDS sizes; *nc_out receives the channels per across-scale
 // workgroup.  Contexts and the allocation-free entry point build identical tables.
@@ -855,8 +863,6 @@ int forward_phases(const Geo& g, const sp_params& p, const StreamDesc& sd, const
   std::vector<int> kinds;
   const int nc = csapply_nc(g, tune.ca_nc);
   const size_t ca_lds = nc * (gpath_ok(g) ? csg_lds_bytes(g) : csapply_lds_bytes(g));
-  if (sp_csapply_reserve_lds(ca_lds) != hipSuccess)
-    return fail(SP_EHIP, "cannot reserve %zu bytes of LDS for the across-scale sum", ca_lds);
   build_forward_jobs(parts, kinds, sd, g, 0, nc);
   for (size_t i = 0; i < parts.size(); ++i) {
     const bool grp = kinds[i] == JOB_CSAPPLY || kinds[i] == JOB_CSG;
@@ -864,7 +870,8 @@ int forward_phases(const Geo& g, const sp_params& p, const StreamDesc& sd, const
     const int gflag = nc | ((kinds[i] == JOB_CSG ? csg_set(g) : ca_set(g)) << 8);
     if (tune.xcd) xcd_order(parts[i]);
     out.push_back(js.add(kinds[i], grp ? gflag : (pyr ? p.gabor_radius : 0), parts[i], 1));
-    if (grp) out.back().lds = ca_lds;
+    if (grp)
+      if (int rc = set_lds(out.back(), ca_lds)) return rc;
   }
   *nc_out = nc;
   return SP_OK;
@@ -1019,10 +1026,6 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
       }
     }
   }
-  if (sp_csapply_reserve_lds(csapply_lds_bytes(g)) != hipSuccess) {
-    sp_destroy(c);
-    return fail(SP_EHIP, "cannot reserve %zu bytes of LDS for the across-scale sum", csapply_lds_bytes(g));
-  }
   TileCount tiles;
   tiles.add(g);
   c->tune = cached_tune(H, W, tiles);
@@ -1063,8 +1066,6 @@ int clip_tables(sp_ctx* c) {
     for (size_t i = 0; i < parts.size(); ++i) all[i].insert(all[i].end(), parts[i].begin(), parts[i].end());
   }
   const size_t lds = nc * (gpath_ok(g) ? csg_lds_bytes(g) : csapply_lds_bytes(g));
-  if (sp_csapply_reserve_lds(lds) != hipSuccess)
-    return fail(SP_EHIP, "cannot reserve %zu bytes of LDS for the across-scale sum", lds);
   for (size_t i = 0; i < all.size(); ++i) {
     const bool grp = kinds[i] == JOB_CSAPPLY || kinds[i] == JOB_CSG;
     const bool pyr = kinds[i] == JOB_DOWN || kinds[i] == JOB_TAIL;
@@ -1078,7 +1079,9 @@ int clip_tables(sp_ctx* c) {
     xcd_order(rest);
     first.insert(first.end(), rest.begin(), rest.end());
     c->clip_full.push_back(c->jobs.add(kinds[i], flag, first, c->CH));
-    if (grp) c->clip_part.back().lds = c->clip_full.back().lds = lds;
+    if (!grp) continue;
+    for (Phase* ph : {&c->clip_part.back(), &c->clip_full.back()})
+      if (int rc = set_lds(*ph, lds)) return rc;
   }
   return SP_OK;
 }
@@ -2092,15 +2095,13 @@ int batch_build_tables(sp_batch* b) {
     else
       lds_a = std::max(lds_a, csapply_lds_bytes(g));
   }
-  if (sp_csapply_reserve_lds(nc * std::max(lds_a, lds_g)) != hipSuccess)
-    return fail(SP_EHIP, "cannot reserve %zu bytes of LDS for the across-scale sum", nc * std::max(lds_a, lds_g));
   if (!css.empty()) b->phases.push_back(b->jobs.add(JOB_CSSTATS, 0, order(css), n));
   if (!csg.empty()) {
     int set = -1;   // one the streams share, or none
     for (const Geo& g : b->geo)
       if (gpath_ok(g)) set = set < 0 || set == csg_set(g) ? csg_set(g) : 0;
     b->phases.push_back(b->jobs.add(JOB_CSG, nc | (set << 8), order(csg), n));
-    b->phases.back().lds = nc * lds_g;
+    if (int rc = set_lds(b->phases.back(), nc * lds_g)) return rc;
   }
   if (!csf.empty()) b->phases.push_back(b->jobs.add(JOB_CSFINAL, 0, order(csf), n));
   if (!csa.empty()) {
@@ -2108,7 +2109,7 @@ int batch_build_tables(sp_batch* b) {
     for (const Geo& g : b->geo)
       if (!gpath_ok(g)) set = std::min(set, ca_set(g));
     b->phases.push_back(b->jobs.add(JOB_CSAPPLY, nc | (set << 8), order(csa), n));
-    b->phases.back().lds = nc * lds_a;
+    if (int rc = set_lds(b->phases.back(), nc * lds_a)) return rc;
   }
   if (!csm.empty()) b->phases.push_back(b->jobs.add(JOB_CSMIX, 0, order(csm), n));
   b->phases.push_back(b->jobs.add(JOB_CONSP, 0, order(cons), n));
@@ -2348,14 +2349,6 @@ int sp_batch_create(const sp_params* p, int32_t n, const int32_t* H, const int32
   for (int i = 0; i < n; ++i) b->tune[i] = cached_tune(H[i], W[i], tiles);
   b->xcd = b->tune[0].xcd;
   b->ca_nc = b->tune[0].ca_nc;
-  {
-    size_t lds = 0;
-    for (const Geo& g : b->geo) lds = std::max(lds, csapply_lds_bytes(g));
-    if (sp_csapply_reserve_lds(lds) != hipSuccess) {
-      batch_free(b);
-      return fail(SP_EHIP, "cannot reserve %zu bytes of LDS for the across-scale sum", lds);
-    }
-  }
   rc = batch_build_tables(b);
   if (rc) {
     std::string msg = g_err;

@@ -5,7 +5,9 @@
 
 hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, const StepIO* ios,
                      const StepIO* io0, int flag, const float* aux, hipStream_t st, size_t lds = 0);
-hipError_t sp_csapply_reserve_lds(size_t bytes);
+// Lets the across-scale kernel that sp_launch takes for this kind and flag use `bytes` of dynamic
+// LDS.  Only that one: others hold more static LDS and would not fit a CU beside it.
+hipError_t sp_across_reserve_lds(int kind, int flag, size_t bytes);
 hipError_t sp_launch_bwd(int kind, int flag, const Job* jobs, int n, const StreamDesc* sds, const BwdIO* bios,
                          const BwdIO* b0, hipStream_t st);
 // The recorded conspicuity maps of T steps dotted with each step's saliency adjoint (buffers

@@ -1140,6 +1140,7 @@ __global__ __launch_bounds__(SET ? CA_NT1 : SP_BLOCK) void k_csapply(const Job* 
   CaLayout L;
   if constexpr (SET != 0) {
     constexpr CaLayout LS = csapply_layout_of(ca_set1_r, ca_set1_d, CA_SET1_N);
+    static_assert(NC * LS.total * sizeof(float) + sizeof(tabr) + sizeof(tabc) + 4096 <= 160 * 1024, "fits a CU's LDS");
     L = LS;
   } else {
     L = csapply_layout(sd.pc, sd.ps, sd.n_pairs, cm);
@@ -3437,6 +3438,28 @@ static inline hipError_t chk() { return hipGetLastError(); }
   } while (0)
 #define SP_STEP_KERNEL(...) SP_STEP_KERNEL_B(SP_BLOCK, __VA_ARGS__)
 
+// The across-scale kernel of a launch (flag: channels per workgroup | pair set << 8).
+typedef void (*StepKernel)(const Job*, const StreamDesc*, const StepIO*, StepIO);
+template <bool ONE>
+static StepKernel csg_kernel(int nc, int set) {
+  if (set == 1) return nc == 8 ? k_csg1<8, 2, 4, ONE> : nc == 4 ? k_csg1<4, 2, 4, ONE> : nc == 2 ? k_csg1<2, 2, 4, ONE> : k_csg1<1, 2, 4, ONE>;
+  if (set == 2) return nc == 8 ? k_csg1<8, 3, 3, ONE> : nc == 4 ? k_csg1<4, 3, 3, ONE> : nc == 2 ? k_csg1<2, 3, 3, ONE> : k_csg1<1, 3, 3, ONE>;
+  return nc == 8 ? k_csg<8, 0, ONE> : nc == 4 ? k_csg<4, 0, ONE> : nc == 2 ? k_csg<2, 0, ONE> : k_csg<1, 0, ONE>;
+}
+template <bool ONE>
+static StepKernel csapply_kernel(int nc, int set) {
+  if (set == 1 && nc <= 2) return nc == 2 ? k_csapply<2, 1, ONE> : k_csapply<1, 1, ONE>;
+  return nc == 8 ? k_csapply<8, 0, ONE> : nc == 4 ? k_csapply<4, 0, ONE> : nc == 2 ? k_csapply<2, 0, ONE> : k_csapply<1, 0, ONE>;
+}
+static StepKernel across_kernel(int kind, int flag, bool one) {
+  const int nc = flag & 0xff, set = flag >> 8;
+  if (kind == JOB_CSG) return one ? csg_kernel<true>(nc, set) : csg_kernel<false>(nc, set);
+  return one ? csapply_kernel<true>(nc, set) : csapply_kernel<false>(nc, set);
+}
+static int across_threads(int kind, int flag) {
+  return kind == JOB_CSAPPLY && flag >> 8 == 1 && (flag & 0xff) <= 2 ? CA_NT1 : SP_BLOCK;
+}
+
 hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, const StepIO* ios,
                      const StepIO* io0, int flag, const float* aux, hipStream_t st, size_t lds) {
   if (n <= 0) return hipSuccess;
@@ -3480,60 +3503,16 @@ hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, co
       else
         hipLaunchKernelGGL(k_csfinal<true>, g, b, 0, st, jobs, sds, ios, io);
       break;
-    case JOB_CSG: {   // flag: channels per workgroup | pair set << 8
-      const int nc = flag & 0xff, set = flag >> 8;
-      if (set == 1) {
-        if (nc == 8)
-          SP_STEP_KERNEL(k_csg1<8, 2, 4);
-        else if (nc == 4)
-          SP_STEP_KERNEL(k_csg1<4, 2, 4);
-        else if (nc == 2)
-          SP_STEP_KERNEL(k_csg1<2, 2, 4);
-        else
-          SP_STEP_KERNEL(k_csg1<1, 2, 4);
-      } else if (set == 2) {
-        if (nc == 8)
-          SP_STEP_KERNEL(k_csg1<8, 3, 3);
-        else if (nc == 4)
-          SP_STEP_KERNEL(k_csg1<4, 3, 3);
-        else if (nc == 2)
-          SP_STEP_KERNEL(k_csg1<2, 3, 3);
-        else
-          SP_STEP_KERNEL(k_csg1<1, 3, 3);
-      } else {
-        if (nc == 8)
-          SP_STEP_KERNEL(k_csg<8, 0);
-        else if (nc == 4)
-          SP_STEP_KERNEL(k_csg<4, 0);
-        else if (nc == 2)
-          SP_STEP_KERNEL(k_csg<2, 0);
-        else
-          SP_STEP_KERNEL(k_csg<1, 0);
-      }
+    case JOB_CSG:
+    case JOB_CSAPPLY:
+      hipLaunchKernelGGL(across_kernel(kind, flag, !ios), g, dim3(across_threads(kind, flag)), lds, st, jobs, sds, ios, io);
       break;
-    }
     case JOB_CSMIX:
       if (ios)
         hipLaunchKernelGGL(k_csmix<false>, g, b, 0, st, jobs, sds, ios, io);
       else
         hipLaunchKernelGGL(k_csmix<true>, g, b, 0, st, jobs, sds, ios, io);
       break;
-    case JOB_CSAPPLY: {   // flag: channels per workgroup | pair set << 8
-      const int nc = flag & 0xff, set = flag >> 8;
-      if (nc == 8)
-        SP_STEP_KERNEL(k_csapply<8, 0);
-      else if (nc == 4)
-        SP_STEP_KERNEL(k_csapply<4, 0);
-      else if (nc == 2 && set == 1)
-        SP_STEP_KERNEL_B(CA_NT1, k_csapply<2, 1);
-      else if (nc == 2)
-        SP_STEP_KERNEL(k_csapply<2, 0);
-      else if (set == 1)
-        SP_STEP_KERNEL_B(CA_NT1, k_csapply<1, 1);
-      else
-        SP_STEP_KERNEL(k_csapply<1, 0);
-      break;
-    }
     case JOB_CONSP:
       if (ios)
         hipLaunchKernelGGL(k_consp<false>, g, b, 0, st, jobs, sds, ios, io);
@@ -3668,18 +3647,11 @@ hipError_t sp_launch_batch_copy_out(int n, size_t max_px, const BatchState* st, 
   return chk();
 }
 
-hipError_t sp_csapply_reserve_lds(size_t bytes) {
+hipError_t sp_across_reserve_lds(int kind, int flag, size_t bytes) {
   if (bytes <= 65536) return hipSuccess;
-  const void* fns[] = {
-#define SP_BOTH(...) reinterpret_cast<const void*>(&__VA_ARGS__, false>), reinterpret_cast<const void*>(&__VA_ARGS__, true>)
-      SP_BOTH(k_csapply<1, 0), SP_BOTH(k_csapply<1, 1), SP_BOTH(k_csapply<2, 0), SP_BOTH(k_csapply<2, 1), SP_BOTH(k_csapply<4, 0),
-      SP_BOTH(k_csapply<8, 0),
-      SP_BOTH(k_csg<1, 0),  SP_BOTH(k_csg<2, 0),  SP_BOTH(k_csg<4, 0),  SP_BOTH(k_csg<8, 0),
-      SP_BOTH(k_csg1<1, 2, 4), SP_BOTH(k_csg1<2, 2, 4), SP_BOTH(k_csg1<4, 2, 4), SP_BOTH(k_csg1<8, 2, 4),
-      SP_BOTH(k_csg1<1, 3, 3), SP_BOTH(k_csg1<2, 3, 3), SP_BOTH(k_csg1<4, 3, 3), SP_BOTH(k_csg1<8, 3, 3)};
-#undef SP_BOTH
-  for (const void* f : fns) {
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  for (bool one : {false, true}) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(across_kernel(kind, flag, one)),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
