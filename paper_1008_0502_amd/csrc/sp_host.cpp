@@ -513,17 +513,22 @@ struct JobStore {
 int upload_jobs(JobStore& js, hipStream_t st) {
   const size_t n = std::max<size_t>(1, js.host.size());
   if (n > js.cap) {
-    if (js.dev) {
-      (void)hipStreamSynchronize(st);
-      (void)hipFree(js.dev);
-      js.dev = nullptr;
-      js.cap = 0;
-    }
-    if (hipMalloc(&js.dev, sizeof(Job) * n) != hipSuccess) {
+    Job* dev = nullptr;
+    if (hipMalloc(&dev, sizeof(Job) * n) != hipSuccess) {
       (void)hipGetLastError();
       return fail(SP_ENOMEM, "hipMalloc of the job tables failed");
     }
+    // the old table may still be read, and stays in use until the new one is there
+    hipError_t e = hipMemcpyAsync(dev, js.host.data(), sizeof(Job) * js.host.size(), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) {
+      (void)hipFree(dev);
+      return fail(SP_EHIP, "upload of the job tables: %s", hipGetErrorString(e));
+    }
+    if (js.dev) (void)hipFree(js.dev);
+    js.dev = dev;
     js.cap = n;
+    return SP_OK;
   }
   HIPCHK(hipMemcpyAsync(js.dev, js.host.data(), sizeof(Job) * js.host.size(), hipMemcpyHostToDevice, st));
   HIPCHK(hipStreamSynchronize(st));
@@ -634,7 +639,16 @@ struct HostStage {
 };
 
 // ---------------------------------------------------------------- context
-struct sp_ctx {
+// The launches of a context, made by ctx_build_tables.
+struct CtxTables {
+  std::vector<Phase> fwd, prior, mrf, bwd;
+  std::vector<Phase> dt;          // distance-transform prediction
+  Phase dot;                      // recorded conspicuity dotted with the saliency adjoint
+  std::vector<Phase> clip_full;   // the forward of CH frames, jobs in XCD order
+  std::vector<Phase> clip_part;   // the same, slot by slot: a prefix serves fewer frames
+};
+
+struct sp_ctx : CtxTables {
   sp_params p{};
   Geo g;
   hipStream_t stream = nullptr;
@@ -644,8 +658,6 @@ struct sp_ctx {
   StreamDesc h_sd{};
   StreamDesc* d_sd = nullptr;     // the stream, followed by the CH clip slots
   JobStore jobs;
-  std::vector<Phase> fwd, prior, mrf, bwd;
-  Phase dot;                      // recorded conspicuity dotted with the saliency adjoint
   // Kalman state
   int64_t t = 0;
   double P = 0.0;
@@ -679,14 +691,11 @@ struct sp_ctx {
   // maps and partials of its own
   int CH = 0;
   std::vector<StreamDesc> h_slots;
-  std::vector<Phase> clip_full;   // the forward of CH frames, jobs in XCD order
-  std::vector<Phase> clip_part;   // the same, slot by slot: a prefix serves fewer frames
   StepIO* d_cio = nullptr;        // [cap] io of the clip's frames
   HostStage cstage;               // its pinned host copy
   float* S_scratch = nullptr;     // [Hc][Wc] saliency map of the autotuner's steps
   // variants of the prior
   float* f_map = nullptr;         // [H][W] distance-transform prediction (f_mode 1)
-  std::vector<Phase> dt;          // its launch
   float* ssm[2] = {nullptr, nullptr};   // [Hc][Wc] stochastic saliency means (ping-pong)
   int ssm_cur = 0;
   int64_t ssm_t = 0;              // maps filtered since the reset
@@ -1086,19 +1095,27 @@ int clip_tables(sp_ctx* c) {
   return SP_OK;
 }
 
+// Makes tables anew by fill() (the jobs, the launches and their upload); what was there before is
+// put back when that fails.
+template <class T, class Fill>
+int rebuild_tables(T& tables, JobStore& jobs, Fill&& fill) {
+  T old = std::move(tables);
+  std::vector<Job> old_jobs = std::move(jobs.host);
+  tables = T{};
+  jobs.host.clear();
+  const int rc = fill();
+  if (rc) {
+    tables = std::move(old);
+    jobs.host = std::move(old_jobs);
+  }
+  return rc;
+}
+
 // (Re)builds every job table of a context from its geometry and tuning knobs.
 int ctx_build_tables(sp_ctx* c) {
   const Geo& g = c->g;
   const int H = g.H, W = g.W, Hc = g.Hl[g.c_max], Wc = g.Wl[g.c_max];
-  c->jobs.host.clear();
-  c->fwd.clear();
-  c->prior.clear();
-  c->mrf.clear();
-  c->bwd.clear();
-  c->dt.clear();
-  c->clip_full.clear();
-  c->clip_part.clear();
-  {
+  return rebuild_tables(static_cast<CtxTables&>(*c), c->jobs, [&]() -> int {
     int nc = 0;
     int rc = forward_phases(g, c->p, c->h_sd, c->tune, c->jobs, c->fwd, &nc);
     if (rc) return rc;
@@ -1129,8 +1146,8 @@ int ctx_build_tables(sp_ctx* c) {
     if (g.c_max > kSweepMax) c->bwd.push_back(c->jobs.add(JOB_BWD_GS, 0, v, 1));
     c->dot = c->jobs.add(JOB_CONSP_DOT, 0, v, 1);
     if (c->CH > 0 && (rc = clip_tables(c))) return rc;
-  }
-  return upload_jobs(c->jobs, c->stream);
+    return upload_jobs(c->jobs, c->stream);
+  });
 }
 
 }  // namespace
@@ -1609,7 +1626,8 @@ int sp_autotune(sp_ctx* c, const uint8_t* rgb_t, const uint8_t* rgb_prev, int32_
   };
   int rc = SP_OK;
   double best = 1e30, t = 0;
-  Tune bt = c->tune;
+  const Tune was = c->tune;
+  Tune bt = was;
   for (int x = 0; x < 2 && !rc; ++x)
     for (int tw : {16, 32, 64}) {
       c->tune.xcd = x != 0;
@@ -1638,10 +1656,18 @@ int sp_autotune(sp_ctx* c, const uint8_t* rgb_t, const uint8_t* rgb_prev, int32_
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  if (rc) return rc;
-  c->tune = bt;
-  rc = ctx_build_tables(c);
-  if (rc) return rc;
+  if (!rc) {
+    c->tune = bt;
+    rc = ctx_build_tables(c);
+  }
+  if (rc) {   // the shapes and the state of before
+    const std::string msg = g_err;
+    c->tune = was;
+    (void)ctx_build_tables(c);
+    (void)sp_reset(c);
+    g_err = msg;
+    return rc;
+  }
   {
     std::lock_guard<std::mutex> lk(tune_mutex());
     tune_cache_tw()[{g.H, g.W}] = bt.kalman_tw;
@@ -1662,11 +1688,14 @@ int sp_set_tune(sp_ctx* c, int32_t kalman_tw, int32_t xcd_order, int32_t channel
   if (channels != 1 && channels != 2 && channels != 4 && channels != 8) return fail(SP_EINVAL, "channels must be 1, 2, 4 or 8");
   if (csapply_nc(c->g, channels) != channels)
     return fail(SP_EINVAL, "%d channels per across-scale workgroup exceed the LDS limit for this geometry", channels);
+  HIPCHK(hipStreamSynchronize(c->stream));
+  const Tune was = c->tune;
   c->tune.kalman_tw = kalman_tw;
   c->tune.xcd = xcd_order != 0;
   c->tune.ca_nc = channels;
-  HIPCHK(hipStreamSynchronize(c->stream));
-  return ctx_build_tables(c);
+  const int rc = ctx_build_tables(c);
+  if (rc) c->tune = was;
+  return rc;
 }
 
 int sp_tune_cache_clear(void) {
@@ -1921,7 +1950,14 @@ struct BatchAdj {
   int n_lvl0_tiles;
 };
 
-struct sp_batch {
+// The launches of a batch, made by batch_build_tables.
+struct BatchTables {
+  std::vector<Phase> phases;
+  std::vector<Phase> bwd;   // reverse step
+  Phase dot;                // recorded conspicuity dotted with the saliency adjoint
+};
+
+struct sp_batch : BatchTables {
   sp_params p{};
   int n = 0;
   hipStream_t stream = nullptr;     // caller's stream: graph launches go here
@@ -1937,7 +1973,6 @@ struct sp_batch {
   hipGraphNode_t rgb_node = nullptr;         // its first node: colour statistics + step start
   RgbNodeArgs rgb_args{};
   JobStore jobs;
-  std::vector<Phase> phases;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   // several consecutive steps in one graph (sp_batch_steps): captured for mn steps, step k's
@@ -1964,8 +1999,6 @@ struct sp_batch {
   char* d_bstage = nullptr;                   // gains, variances, [cap][n] BwdIO, [n] BwdFin
   char* d_lstage = nullptr;                   // [n] LossIO
   HostStage bstage, lstage;                   // pinned host copies of the two tables
-  std::vector<Phase> bwd;                     // reverse step
-  Phase dot;                                  // recorded conspicuity dotted with the saliency adjoint
   int loss_nblk = 1024;
 };
 
@@ -1976,7 +2009,6 @@ namespace {
 // maps of every stream.
 void batch_adjoint_tables(sp_batch* b) {
   const int n = b->n;
-  b->bwd.clear();
   std::vector<Job> dot;
   for (int i = 0; i < n; ++i) add_tiles(dot, i, 0, b->geo[i].Hl[b->geo[i].c_max], b->geo[i].Wl[b->geo[i].c_max]);
   for (int cm = 0; cm <= kSweepMax; ++cm) {   // 0: the streams above kSweepMax
@@ -1993,6 +2025,19 @@ void batch_adjoint_tables(sp_batch* b) {
   }
   b->dot = b->jobs.add(JOB_CONSP_DOT, 0, dot, n);
 }
+
+// A batch's launch shapes, to put back.
+struct BatchShapes {
+  std::vector<Tune> tune;
+  bool xcd;
+  int ca_nc;
+  explicit BatchShapes(const sp_batch* b) : tune(b->tune), xcd(b->xcd), ca_nc(b->ca_nc) {}
+  void put(sp_batch* b) const {
+    b->tune = tune;
+    b->xcd = xcd;
+    b->ca_nc = ca_nc;
+  }
+};
 
 // Drops the graph of several steps (recaptured by the next sp_batch_steps).
 void batch_drop_multi(sp_batch* b) {
@@ -2011,10 +2056,11 @@ void batch_drop_multi(sp_batch* b) {
   b->margs.clear();
 }
 
-// (Re)builds the batch's phase program: one launch per phase over every stream.  Drops
-// the captured graphs, which are captured again on the next step.
+// The batch's phase program: one launch per phase over every stream.
+int batch_fill_tables(sp_batch* b);
+
+// (Re)builds it.  Drops the captured graphs, which are captured again on the next step.
 int batch_build_tables(sp_batch* b) {
-  const int n = b->n;
   if (b->exec) {
     (void)hipStreamSynchronize(b->stream);
     (void)hipGraphExecDestroy(b->exec);
@@ -2027,8 +2073,11 @@ int batch_build_tables(sp_batch* b) {
   batch_drop_multi(b);
   b->rgb_node = nullptr;
   b->in_node = nullptr;
-  b->jobs.host.clear();
-  b->phases.clear();
+  return rebuild_tables(static_cast<BatchTables&>(*b), b->jobs, [b] { return batch_fill_tables(b); });
+}
+
+int batch_fill_tables(sp_batch* b) {
+  const int n = b->n;
   std::vector<Job> rgb, feat, fin, css, csf, csa, csg, csm, cons, kal;
   std::vector<std::vector<Job>> mids;
   bool any_big = false;
@@ -2519,6 +2568,7 @@ int sp_batch_autotune(sp_batch* b, const uint8_t* const* rgb_ptrs, int32_t steps
   HIPCHK(hipEventCreate(&e0));
   HIPCHK(hipEventCreate(&e1));
   const bool was = b->prof.on;
+  const BatchShapes shapes(b);
   b->prof.on = false;
   std::string rep;
   int rc = SP_OK;
@@ -2593,9 +2643,14 @@ int sp_batch_autotune(sp_batch* b, const uint8_t* const* rgb_ptrs, int32_t steps
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   b->prof.on = was;
-  if (rc) return rc;
-  rc = batch_build_tables(b);
-  if (rc) return rc;
+  if (!rc) rc = batch_build_tables(b);
+  if (rc) {   // the shapes of before
+    const std::string msg = g_err;
+    shapes.put(b);
+    (void)batch_build_tables(b);
+    g_err = msg;
+    return rc;
+  }
   {
     std::lock_guard<std::mutex> lk(tune_mutex());
     tune_cache_xcd() = b->xcd ? 1 : 0;
@@ -2625,10 +2680,13 @@ int sp_batch_set_tune(sp_batch* b, int32_t kalman_tw, int32_t xcd_order, int32_t
   for (const Geo& g : b->geo)
     if (csapply_nc(g, channels) != channels)
       return fail(SP_EINVAL, "%d channels per across-scale workgroup exceed the LDS limit of a stream", channels);
+  const BatchShapes was(b);
   for (Tune& t : b->tune) t.kalman_tw = kalman_tw;
   b->xcd = xcd_order != 0;
   b->ca_nc = channels;
-  return batch_build_tables(b);
+  const int rc = batch_build_tables(b);
+  if (rc) was.put(b);
+  return rc;
 }
 
 int sp_batch_set_weights(sp_batch* b, const float* w, double q, double r) {

@@ -63,6 +63,15 @@ int hipEventRecord(void* e, void* s) { return 0; }
 int hipEventSynchronize(void* e) { ++shim_waits; settle(); return 0; }
 int hipEventElapsedTime(float* ms, void* a, void* b) { *ms = 1.f; return 0; }
 int hipFuncSetAttribute(const void* f, int a, int v) { return 0; }
+static struct { dim3_ grid, block; size_t lds; void* st; } conf;
+int __hipPushCallConfiguration(dim3_ grid, dim3_ block, size_t lds, void* st) {
+  conf.grid = grid; conf.block = block; conf.lds = lds; conf.st = st;
+  return 0;
+}
+int __hipPopCallConfiguration(dim3_* grid, dim3_* block, size_t* lds, void** st) {
+  *grid = conf.grid; *block = conf.block; *lds = conf.lds; *st = conf.st;
+  return 0;
+}
 int hipLaunchKernel(const void* f, dim3_ grid, dim3_ block, void** args, size_t lds, void* st) {
   if (shim_launches < 65536) launches[shim_launches] = (Launch){grid.x, block.x, *(void**)args[0]};
   ++shim_launches;

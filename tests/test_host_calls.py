@@ -1,5 +1,6 @@
 """The library's host code on the CPU, over a stand-in for the HIP runtime (_hip_host.c): what an
-asynchronous copy reads is still there when the copy runs."""
+asynchronous copy reads is still there when the copy runs; launch tables that could not be made anew
+leave the old ones in use."""
 import os
 import subprocess
 import sys
@@ -55,4 +56,62 @@ w = (ctypes.c_float * 8)(*range(8))
 L.check(lib.sp_set_weights(h, w, 1e-3, 1e-1), "sp_set_weights")
 L.check(lib.sp_set_tune(h, 16, 0, 1), "sp_set_tune")
 assert count("shim_pending").value == 0 and count("shim_stale").value == 0, count("shim_stale").value
+""")
+
+
+STEP = """
+JOB = 8 * 4
+def launches(call):
+    "grid, threads and (where its first argument is a job table) the jobs of every launch of a call"
+    n0 = count("shim_launches").value
+    call()
+    shim.shim_launch.restype = ctypes.POINTER(ctypes.c_uint * 4)
+    out = []
+    for i in range(n0, count("shim_launches").value):
+        r = shim.shim_launch(i).contents
+        jobs = r[2] | r[3] << 32
+        out.append((r[0], r[1], ctypes.string_at(jobs, r[0] * JOB)))
+    return out
+def mem(n):
+    bufs.append(ctypes.create_string_buffer(n))
+    return ctypes.addressof(bufs[-1])
+bufs = []
+"""
+
+
+@pytest.mark.parametrize("fault", ["malloc", "copy"])
+def test_refused_tables_keep_the_context(shim, fault):
+    run(shim, STEP + f"""
+h = create(721, 1000)
+rgb, S, P = mem(721 * 1000 * 3), mem(4 * 721 * 1000), mem(4 * 721 * 1000)
+def step():
+    L.check(lib.sp_step(h, rgb, None, None, S, None, P, None, None, None), "sp_step")
+L.check(lib.sp_set_tune(h, 64, 0, 4), "sp_set_tune")
+before = launches(step)
+count("shim_fail_{fault}").value = 1
+assert lib.sp_set_tune(h, 16, 1, 1) != 0
+count("shim_fail_{fault}").value = 0
+assert launches(step) == before and before
+L.check(lib.sp_set_tune(h, 16, 1, 1), "sp_set_tune")
+assert launches(step) != before
+""")
+
+
+def test_refused_tables_keep_the_batch(shim):
+    run(shim, STEP + """
+b = ctypes.c_void_p()
+dims = (ctypes.c_int32 * 2)(96, 120), (ctypes.c_int32 * 2)(128, 97)
+L.check(lib.sp_batch_create(ctypes.byref(params(record_tape=3)), 2, *dims, 0, None, ctypes.byref(b)), "sp_batch_create")
+L.check(lib.sp_batch_profile_enable(b, 1), "sp_batch_profile_enable")   # steps by launches, not a graph
+tab = (ctypes.c_void_p * 2)(mem(96 * 128 * 3), mem(120 * 97 * 3))
+def step():
+    L.check(lib.sp_batch_step(b, ctypes.cast(tab, ctypes.c_void_p), None), "sp_batch_step")
+L.check(lib.sp_batch_set_tune(b, 64, 0, 8), "sp_batch_set_tune")
+before = launches(step)
+count("shim_fail_copy").value = 1
+assert lib.sp_batch_set_tune(b, 16, 1, 1) != 0
+count("shim_fail_copy").value = 0
+assert launches(step) == before and before
+L.check(lib.sp_batch_set_tune(b, 16, 1, 1), "sp_batch_set_tune")
+assert launches(step) != before
 """)
