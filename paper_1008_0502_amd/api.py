@@ -373,15 +373,20 @@ class Context:
         U = torch.empty((T, 2, g.H, g.W), dtype=torch.float32, device=self.device) if with_mrf else None
         PW = torch.empty((T, 4, g.H, g.W), dtype=torch.float32, device=self.device) if with_mrf else None
         B = torch.empty((T, 1), dtype=torch.float32, device=self.device) if with_mrf else None
-        if T and manual is None and MU is None:
+        # One call for the clip where frames and segmentations are all there: tensors, or a list or tuple
+        # of segmentations.  Any other sequence may make each one when it is asked for (in a buffer that
+        # it uses again, say), so those are taken frame by frame.
+        if T and manual is None and MU is None and isinstance(frames, torch.Tensor) and (
+                segs is None or type(segs) in (list, tuple) or isinstance(segs, torch.Tensor)):
             _need(frames[0], "frames[0]", torch.uint8, (g.H, g.W, 3), self.device)   # every frame has its strides
             ptrs = (c_void_p * T)(*[frames.data_ptr() + t * frames.stride(0) for t in range(T)])
             sp = None
             if segs is not None:
-                for t in range(T):
-                    if segs[t] is not None:
-                        _need(segs[t], "seg_prev", torch.uint8, (g.H, g.W), self.device)
-                sp = (c_void_p * T)(*[_ptr(segs[t]) for t in range(T)])
+                held = [segs[t] for t in range(T)]
+                for s in held:
+                    if s is not None:
+                        _need(s, "seg_prev", torch.uint8, (g.H, g.W), self.device)
+                sp = (c_void_p * T)(*[_ptr(s) for s in held])
             self._bind_stream()
             check(self.lib.sp_run_clip(self._handle, ptrs, T, sp, _ptr(S), _ptr(C), _ptr(P), _ptr(U), _ptr(PW), _ptr(B)),
                   "sp_run_clip")
