@@ -692,7 +692,6 @@ struct sp_ctx : CtxTables {
   int CH = 0;
   std::vector<StreamDesc> h_slots;
   StepIO* d_cio = nullptr;        // [cap] io of the clip's frames
-  HostStage cstage;               // its pinned host copy
   float* S_scratch = nullptr;     // [Hc][Wc] saliency map of the autotuner's steps
   // variants of the prior
   float* f_map = nullptr;         // [H][W] distance-transform prediction (f_mode 1)
@@ -929,7 +928,6 @@ int sp_destroy(sp_ctx* c) {
   if (!c) return SP_OK;
   if (c->stream || c->arena) (void)hipStreamSynchronize(c->stream);
   c->prof.destroy();
-  c->cstage.destroy();
   if (c->arena) (void)hipFree(c->arena);
   if (c->jobs.dev) (void)hipFree(c->jobs.dev);
   delete c;
@@ -1038,8 +1036,7 @@ int sp_create(const sp_params* p, int32_t H, int32_t W, void* hip_stream, sp_ctx
   TileCount tiles;
   tiles.add(g);
   c->tune = cached_tune(H, W, tiles);
-  int rc2 = c->cap > 0 ? c->cstage.init(sizeof(StepIO) * c->cap) : SP_OK;
-  if (!rc2) rc2 = ctx_build_tables(c);
+  const int rc2 = ctx_build_tables(c);
   if (rc2) {
     std::string msg = g_err;
     sp_destroy(c);
@@ -1452,6 +1449,30 @@ int sp_step(sp_ctx* c, const uint8_t* rgb_t, const uint8_t* rgb_prev, const uint
   return SP_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// The io table of T steps whose frames are frame(0) .. frame(T - 1), outputs as in `a`.
+template <class Frame>
+int clip_io(sp_ctx* c, ClipIO a, int T, Frame&& frame) {
+  for (int t0 = 0; t0 < T; t0 += SP_CLIP_IO) {
+    a.io = c->d_cio + t0;
+    a.n = std::min(SP_CLIP_IO, T - t0);
+    a.rgb[0] = t0 ? frame(t0 - 1) : nullptr;
+    for (int s = 0; s < a.n; ++s) a.rgb[s + 1] = frame(t0 + s);
+    const hipError_t e = sp_launch_clip_io(a, c->stream);
+    if (e != hipSuccess) return fail(SP_EHIP, "clip table launch: %s", hipGetErrorString(e));
+    for (ClipOut* o : {&a.S_out, &a.C_out, &a.S_tape, &a.fbar, &a.np_tape, &a.pairwise, &a.beta_out})
+      if (o->p) o->p += (size_t)a.n * o->stride;
+  }
+  return SP_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 int sp_run_clip(sp_ctx* c, const uint8_t* const* frames, int32_t T, const uint8_t* const* seg_prev, float* S_out,
                 float* C_out, float* prior_out, float* unary_out, float* pairwise_out, float* beta_out) {
   g_err.clear();
@@ -1468,45 +1489,22 @@ int sp_run_clip(sp_ctx* c, const uint8_t* const* frames, int32_t T, const uint8_
   auto at = [](float* p, size_t off) { return p ? p + off : nullptr; };
   int rc = sp_reset(c);
   if (rc) return rc;
-  // no frame slots, or a graph under capture (a captured upload would read the host table at
-  // replay): one step after the other
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (c->CH > 0) HIPCHK(hipStreamIsCapturing(c->stream, &cap));
-  if (c->CH == 0 || cap != hipStreamCaptureStatusNone) {
+  if (c->CH == 0) {   // no frame slots: one step after the other
     for (size_t t = 0; t < (size_t)T && !rc; ++t)
       rc = sp_step(c, frames[t], t ? frames[t - 1] : nullptr, seg_prev ? seg_prev[t] : nullptr, S_out + t * plane,
                    at(C_out, t * SP_NCH * plane), at(prior_out, t * HW), at(unary_out, t * 2 * HW),
                    at(pairwise_out, t * 4 * HW), at(beta_out, t));
     return rc;
   }
-  // the io of every step (a context with a tape runs the default prior: no variants)
-  rc = c->cstage.acquire();
-  if (rc) return rc;
-  StepIO* io = reinterpret_cast<StepIO*>(c->cstage.host);
-  double P = 0.0;
-  for (size_t t = 0; t < (size_t)T; ++t) {
-    StepIO& o = io[t];
-    std::memset(&o, 0, sizeof o);
-    o.rgb = frames[t];
-    o.rgb_prev = t ? frames[t - 1] : nullptr;
-    o.S_out = S_out + t * plane;
-    o.S_in = o.S_out;
-    o.C_out = at(C_out, t * SP_NCH * plane);
-    o.seg_prev = seg_prev ? seg_prev[t] : nullptr;
-    o.pi_prev = c->pi_state[(c->cur + t) & 1];
-    o.pi_next = c->pi_state[(c->cur + t + 1) & 1];
-    o.prior_out = at(prior_out, t * HW);
-    o.unary = at(unary_out, t * 2 * HW);
-    o.pairwise = at(pairwise_out, t * 4 * HW);
-    o.beta_out = unary_out ? at(beta_out, t) : nullptr;
-    const double K = now_gain((int64_t)t, P, c->p.q, c->p.r, &P);
-    o.K = (float)K;
-    o.t = (int32_t)t;
-    tape_forward(c, (int64_t)t, o);
-    o.f_tape = c->f_tape + t * HW;
-    o.ms_tape = c->ms_tape + t * 2;
-  }
-  rc = c->cstage.upload(c->d_cio, sizeof(StepIO) * (size_t)T, c->stream);
+  ClipIO a{};
+  a.S_out = {S_out, plane};
+  a.C_out = {C_out, SP_NCH * plane};
+  a.pairwise = {pairwise_out, 4 * HW};
+  a.beta_out = {unary_out ? beta_out : nullptr, 1};
+  a.S_tape = {c->S_tape, plane};
+  a.fbar = {c->fbar_tape, SP_NCH * plane};
+  a.np_tape = {c->np_tape, 4 * SP_NCH};
+  rc = clip_io(c, a, T, [&](int t) { return frames[t]; });
   if (rc) return rc;
   for (int t0 = 0; t0 < T; t0 += c->CH) {
     const int n = std::min(c->CH, T - t0);
@@ -1516,16 +1514,30 @@ int sp_run_clip(sp_ctx* c, const uint8_t* const* frames, int32_t T, const uint8_
       rc = run_phase(c, ph, c->d_sd + 1, c->d_cio + t0, nullptr, ph.upto[n]);
       if (rc) return rc;
     }
-    for (int t = t0; t < t0 + n; ++t) {
-      rc = run_phase(c, c->prior.back(), c->d_sd + 1 + (t - t0), nullptr, &io[t], c->prior.back().n);
+    // the priors (a context with a tape runs the default prior: no variants)
+    for (size_t t = t0; t < (size_t)(t0 + n); ++t) {
+      StepIO o{};
+      o.rgb = frames[t];
+      o.S_in = S_out + t * plane;
+      o.seg_prev = seg_prev ? seg_prev[t] : nullptr;
+      o.pi_prev = c->pi_state[c->cur];
+      o.pi_next = c->pi_state[c->cur ^ 1];
+      o.prior_out = at(prior_out, t * HW);
+      o.unary = at(unary_out, t * 2 * HW);
+      double Pn = 0.0;
+      o.K = (float)now_gain((int64_t)t, c->P, c->p.q, c->p.r, &Pn);
+      o.t = (int32_t)t;
+      o.f_tape = c->f_tape + t * HW;
+      o.ms_tape = c->ms_tape + t * 2;
+      rc = run_phase(c, c->prior.back(), c->d_sd + 1 + (t - t0), nullptr, &o, c->prior.back().n);
       if (rc) return rc;
-      c->Kf.push_back(io[t].K);
-      c->uses_pi.push_back(io[t].seg_prev == nullptr && t > 0);
+      c->Kf.push_back(o.K);
+      c->uses_pi.push_back(o.seg_prev == nullptr && t > 0);
+      c->P = Pn;
+      c->cur ^= 1;
+      c->t += 1;
     }
   }
-  c->P = P;
-  c->cur = (c->cur + T) & 1;
-  c->t = T;
   return SP_OK;
 }
 
@@ -1794,40 +1806,16 @@ int saliency_backward_frames(sp_ctx* c, const uint8_t* frames, int32_t T, float*
     return fail(SP_ESTATE, "saliency_backward of this %d-step clip must run first", T);
   const Geo& g = c->g;
   const size_t HW3 = 3 * (size_t)g.H * g.W, plc = (size_t)g.Hl[g.c_max] * g.Wl[g.c_max];
-  auto frame_io = [&](int t) {
-    StepIO io;
-    std::memset(&io, 0, sizeof io);
-    io.rgb = frames + (size_t)t * HW3;
-    io.rgb_prev = t ? frames + (size_t)(t - 1) * HW3 : nullptr;
-    return io;
-  };
-  // the frames' pyramids and Gabor maps, recomputed into the slots from a table of their
-  // inputs (under capture, where an upload would read the host table at replay, slot by slot)
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  HIPCHK(hipStreamIsCapturing(c->stream, &cap));
-  const bool table = cap == hipStreamCaptureStatusNone;
-  int rc = SP_OK;
-  if (table) {
-    if ((rc = c->cstage.acquire())) return rc;
-    StepIO* io = reinterpret_cast<StepIO*>(c->cstage.host);
-    for (int t = 0; t < T; ++t) io[t] = frame_io(t);
-    if ((rc = c->cstage.upload(c->d_cio, sizeof(StepIO) * (size_t)T, c->stream))) return rc;
-  }
+  // the frames' pyramids and Gabor maps, recomputed into the slots
+  int rc = clip_io(c, ClipIO{}, T, [&](int t) { return frames + (size_t)t * HW3; });
+  if (rc) return rc;
   for (int t0 = 0; t0 < T; t0 += c->pa_slots) {
     const int n = std::min(c->pa_slots, T - t0);
-    for (const Phase& ph0 : table && n == c->CH ? c->clip_full : c->clip_part) {
+    for (const Phase& ph0 : n == c->CH ? c->clip_full : c->clip_part) {
       Phase ph = ph0;
       if (ph.kind != JOB_RGB && ph.kind != JOB_FEAT && ph.kind != JOB_DOWN && ph.kind != JOB_TAIL) break;
       if (ph.kind == JOB_RGB) ph.flag = 0;
-      if (table) {
-        if ((rc = run_phase(c, ph, c->d_sd + 1, c->d_cio + t0, nullptr, ph.upto[n]))) return rc;
-        continue;
-      }
-      for (int z = 0; z < n; ++z) {
-        const StepIO io = frame_io(t0 + z);
-        ph.off = ph0.off + ph.upto[z];
-        if ((rc = run_phase(c, ph, c->d_sd + 1 + z, nullptr, &io, ph.upto[z + 1] - ph.upto[z]))) return rc;
-      }
+      if ((rc = run_phase(c, ph, c->d_sd + 1, c->d_cio + t0, nullptr, ph.upto[n]))) return rc;
     }
     const hipError_t e = timed(c, JOB_PIX_ADJ, [&] {
       return sp_pixel_adjoint(c->pa, c->d_sd + 1, c->h_slots[0], t0, n, frames, c->gs_all + (size_t)t0 * plc,

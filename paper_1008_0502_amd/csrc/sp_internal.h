@@ -140,6 +140,20 @@ struct StepIO {
   int32_t t;                 // step index
 };
 
+// Fills the io table of consecutive steps of a clip with what the saliency phases read.  The frames
+// go by value: nothing on the host is read after the call, and a captured launch keeps them.
+#define SP_CLIP_IO 256   // most steps of a launch
+struct ClipOut {
+  float* p;                  // step 0's (null: none)
+  size_t stride;             // floats from one step's to the next's
+};
+struct ClipIO {
+  StepIO* io;                // [n]
+  int32_t n;
+  ClipOut S_out, C_out, S_tape, fbar, np_tape, pairwise, beta_out;
+  const uint8_t* rgb[SP_CLIP_IO + 1];   // the frame before step 0 (or null), then every step's
+};
+
 // Arguments of the adjoint sweep (one frame at a time).
 struct BwdIO {
   const float* grad;         // [H][W] dL/dpi_t

@@ -8,6 +8,7 @@ hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, co
 // Lets the across-scale kernel that sp_launch takes for this kind and flag use `bytes` of dynamic
 // LDS.  Only that one: others hold more static LDS and would not fit a CU beside it.
 hipError_t sp_across_reserve_lds(int kind, int flag, size_t bytes);
+hipError_t sp_launch_clip_io(const ClipIO& a, hipStream_t st);
 hipError_t sp_launch_bwd(int kind, int flag, const Job* jobs, int n, const StreamDesc* sds, const BwdIO* bios,
                          const BwdIO* b0, hipStream_t st);
 // The recorded conspicuity maps of T steps dotted with each step's saliency adjoint (buffers

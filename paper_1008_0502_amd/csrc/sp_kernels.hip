@@ -3346,6 +3346,25 @@ __device__ void batch_begin_stream(int i, BatchState* __restrict__ st, const Str
   st[i] = s;
 }
 
+// One thread a step: 1.4 us for 8 steps, 4.8 for 120.  A table copied from pinned memory made the call wait
+// for the copy of the one before.
+__global__ __launch_bounds__(SP_CLIP_IO) void k_clip_io(ClipIO a) {
+  const int s = threadIdx.x;
+  if (s >= a.n) return;
+  auto at = [s](const ClipOut& o) { return o.p ? o.p + s * o.stride : nullptr; };
+  StepIO io{};
+  io.rgb_prev = a.rgb[s];
+  io.rgb = a.rgb[s + 1];
+  io.S_out = at(a.S_out);
+  io.C_out = at(a.C_out);
+  io.S_tape = at(a.S_tape);
+  io.fbar = at(a.fbar);
+  io.np_tape = at(a.np_tape);
+  io.pairwise = at(a.pairwise);
+  io.beta_out = at(a.beta_out);
+  a.io[s] = io;
+}
+
 __global__ void k_batch_reset(int n, BatchState* __restrict__ st) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -3634,6 +3653,11 @@ void sp_batch_rgb_node_params(RgbNodeArgs* a, int n_jobs, hipKernelNodeParams* p
   p->sharedMemBytes = 0;
   p->kernelParams = a->argv;
   p->extra = nullptr;
+}
+
+hipError_t sp_launch_clip_io(const ClipIO& a, hipStream_t st) {
+  hipLaunchKernelGGL(k_clip_io, dim3(1), dim3(SP_CLIP_IO), 0, st, a);
+  return chk();
 }
 
 hipError_t sp_launch_batch_reset(int n, BatchState* st, hipStream_t stream) {

@@ -1,6 +1,6 @@
 """The library's host code on the CPU, over a stand-in for the HIP runtime (_hip_host.c): what an
 asynchronous copy reads is still there when the copy runs; launch tables that could not be made anew
-leave the old ones in use."""
+leave the old ones in use; clips are queued without waiting for the ones before."""
 import os
 import subprocess
 import sys
@@ -114,4 +114,27 @@ count("shim_fail_copy").value = 0
 assert launches(step) == before and before
 L.check(lib.sp_batch_set_tune(b, 16, 1, 1), "sp_batch_set_tune")
 assert launches(step) != before
+""")
+
+
+def test_clips_are_queued_without_a_wait(shim):
+    run(shim, STEP + """
+H, W, T = 48, 64, 5
+h = create(H, W, record_tape=T)
+n = H * W
+frames = [mem(3 * n) for _ in range(T)]
+clip = mem(3 * n * T)
+table = (ctypes.c_void_p * T)(*frames)
+S, P, U, PW, B, G, gw, gf = (mem(4 * k * n * T) for k in (1, 1, 2, 4, 1, 1, 1, 3))
+def clips(k):
+    for _ in range(k):
+        L.check(lib.sp_run_clip(h, table, T, None, S, None, P, U, PW, B), "sp_run_clip")
+w0 = count("shim_waits").value
+clips(4)
+assert count("shim_waits").value == w0 and count("shim_pending").value == 0
+L.check(lib.saliency_backward(h, G, T, gw, gw + 64, gw + 128), "saliency_backward")
+w0 = count("shim_waits").value
+for _ in range(3):
+    L.check(lib.saliency_backward_frames(h, clip, T, gf), "saliency_backward_frames")
+assert count("shim_waits").value == w0 and count("shim_pending").value == 0
 """)
