@@ -368,6 +368,14 @@ struct GmmIO {
 // of d), the excess, the height (distance to the sink in the residual graph; SP_CUT_INF:
 // the sink cannot be reached) and the residual capacity to the sink.
 #define SP_CUT_INF (1 << 30)
+// The push pass holds a height above a direction of three bits.  A height is at most the pixels of a
+// frame (2^28) after a relabel, and grows by at most one in each of a round's 256 cycles.
+#define SP_CUT_HMAX ((1 << 28) + 256)
+#define SP_CUT_HINF 0xC0000000u   // in the place of SP_CUT_INF; stays above the others with any bits set
+__host__ __device__ constexpr uint32_t cut_pack(int32_t h) { return h >= SP_CUT_INF ? SP_CUT_HINF : (uint32_t)h << 3; }
+__host__ __device__ constexpr int32_t cut_unpack(uint32_t p) { return p >= SP_CUT_HINF ? SP_CUT_INF : (int32_t)(p >> 3); }
+static_assert((cut_pack(SP_CUT_HMAX) | 7u) < SP_CUT_HINF && cut_unpack(cut_pack(SP_CUT_HMAX) | 7u) == SP_CUT_HMAX &&
+              cut_unpack(cut_pack(SP_CUT_INF) | 7u) == SP_CUT_INF, "every height has its place");
 #define SP_CUT_T 32        // tile edge of the relabel pass
 #define SP_CUT_PT 16       // tile edge of the push launches
 #define SP_CUT_CTL 64      // counter slots of the relabel passes (a power of two)

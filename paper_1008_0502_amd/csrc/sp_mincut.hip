@@ -44,8 +44,8 @@ __device__ __forceinline__ int32_t quant(float c, float scale) {
 }
 
 // Capacities and the saturated t-links.  The flow goes to one partial per workgroup (1200
-// workgroups adding to one address took 20.6 us of a 640x480 cut, 7.7 us now); the counters and
-// tile flags start at zero.
+// workgroups adding to one address took 20.6 us of a 640x480 cut, 7.7 us now); the counters start at
+// zero.  The push tiles' flags hold anything until a cut's first relabel pass sets them all.
 __global__ __launch_bounds__(SP_BLOCK) void k_cut_init(CutIO io) {
   __shared__ unsigned long long sh4[4];
   const int n = io.H * io.W;
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(RB) void k_cut_relabel(CutIO io) {
 constexpr int PT = SP_CUT_PT, PB = PT * PT;
 __global__ __launch_bounds__(PB) void k_cut_push(CutIO io) {
   constexpr int RN = PT + 2;
-  __shared__ int32_t hl[RN * RN];     // heights << 4
+  __shared__ uint32_t hl[RN * RN];    // heights, packed
   __shared__ uint32_t box[RN * RN];   // pushed amount << 4 | direction + 1 (amounts < 2^26)
   __shared__ int wpush[PB / 64 + 2];  // the wavefront (whole rows of the tile) pushed in this cycle
   __shared__ unsigned long long sunk_sh;
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(PB) void k_cut_push(CutIO io) {
   if (threadIdx.x < PB / 64 + 2) wpush[threadIdx.x] = 0;
   __syncthreads();
   if (go == 0) return;   // uniform
-  constexpr int32_t INF4 = SP_CUT_INF;   // heights stay far below INF >> 4
+  constexpr uint32_t INF = SP_CUT_HINF;
   const int ntx = (io.W + PT - 1) / PT;
   const int tyi = blockIdx.x / ntx, txi = blockIdx.x % ntx;
   const int ty0 = tyi * PT, tx0 = txi * PT;
@@ -220,40 +220,40 @@ __global__ __launch_bounds__(PB) void k_cut_push(CutIO io) {
   for (int k = threadIdx.x; k < RN * RN; k += PB) {
     const int yy = ty0 - 1 + k / RN, xx = tx0 - 1 + k % RN;
     const int32_t v = (yy >= 0 && yy < io.H && xx >= 0 && xx < io.W) ? io.h[yy * io.W + xx] : SP_CUT_INF;
-    hl[k] = v >= SP_CUT_INF ? INF4 : v << 4;
+    hl[k] = cut_pack(v);
     box[k] = 0u;
   }
   // key[d]: d where the residual in direction d is positive, else above every height
-  int32_t r[8], r0[8], key[8];
+  int32_t r[8], r0[8];
+  uint32_t key[8];
 #pragma unroll
   for (int d = 0; d < 8; ++d) r[d] = r0[d] = in ? io.r[(size_t)d * n + i] : 0;
 #pragma unroll
-  for (int d = 0; d < 8; ++d) key[d] = r[d] > 0 ? d : INF4;
+  for (int d = 0; d < 8; ++d) key[d] = r[d] > 0 ? d : INF;
   const int32_t e0 = e, rt0 = rt;
   const int w = wave_id();
   __syncthreads();
-  int32_t h = hl[li];
-  const int32_t h0 = h;
+  uint32_t h = hl[li];
+  const uint32_t h0 = h;
   unsigned long long sunk = 0;
   uint32_t out_tiles = 0;   // neighbouring tiles pushed to: bit (dy + 1) * 3 + dx + 1
   for (int cyc = 0; cyc < io.cycles; ++cyc) {
     uint32_t word = 0u;
-    if (e > 0 && h < INF4) {
+    if (e > 0 && h < INF) {
       if (rt > 0) {   // the sink, at height 0
         const int32_t delta = min(e, rt);
         e -= delta;
         rt -= delta;
         sunk += (unsigned long long)delta;
       } else {
-        uint32_t bu = (uint32_t)INF4;   // unsigned: INF4 + INF4 = 2^31 stays above every height
+        uint32_t best = INF;
 #pragma unroll
-        for (int d = 0; d < 8; ++d) bu = min(bu, (uint32_t)hl[li + DYf(d) * RN + DXf(d)] + (uint32_t)key[d]);
-        const int32_t best = (int32_t)bu;
-        if (best >= INF4) {
-          h = INF4;   // no residual path: it cannot reach the sink
+        for (int d = 0; d < 8; ++d) best = min(best, hl[li + DYf(d) * RN + DXf(d)] | key[d]);
+        if (best >= INF) {
+          h = INF;   // no residual path: it cannot reach the sink
           hl[li] = h;
-        } else if (h > (best & ~15)) {
-          const int dm = best & 7;
+        } else if (h > (best & ~7u)) {
+          const int dm = best & 7u;
           int32_t cap = 0;
           int dy = 0, dx = 0;
 #pragma unroll
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(PB) void k_cut_push(CutIO io) {
           for (int d = 0; d < 8; ++d)
             if (d == dm) {
               r[d] -= delta;
-              key[d] = r[d] > 0 ? d : INF4;
+              key[d] = r[d] > 0 ? d : INF;
             }
           if ((unsigned)(ly + dy) < (unsigned)PT && (unsigned)(lx + dx) < (unsigned)PT) {
             word = ((uint32_t)delta << 4) | (uint32_t)(dm + 1);
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(PB) void k_cut_push(CutIO io) {
             out_tiles |= 1u << ((by + 1) * 3 + bx + 1);
           }
         } else {
-          h = (best & ~15) + 16;
+          h = (best & ~7u) + 8u;
           hl[li] = h;
         }
       }
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(PB) void k_cut_push(CutIO io) {
       }
     }
     if ((cyc & 3) == 3) {
-      if (!__syncthreads_or(e > 0 && h < INF4)) break;
+      if (!__syncthreads_or(e > 0 && h < INF)) break;
     } else {
       __syncthreads();
     }
@@ -314,10 +314,10 @@ __global__ __launch_bounds__(PB) void k_cut_push(CutIO io) {
     for (int d = 0; d < 8; ++d)
       if (r[d] != r0[d]) atomicAdd(io.r + (size_t)d * n + i, r[d] - r0[d]);
     if (rt != rt0) io.rt[i] = rt;
-    if (h != h0) io.h[i] = h >= INF4 ? SP_CUT_INF : h >> 4;
+    if (h != h0) io.h[i] = cut_unpack(h);
   }
   if (sunk) atomicAdd(&sunk_sh, sunk);
-  const bool more = __syncthreads_or(e > 0 && h < INF4);
+  const bool more = __syncthreads_or(e > 0 && h < INF);
 #pragma unroll
   for (int b = 0; b < 9; ++b)
     if ((out_tiles >> b) & 1u) atomicOr(&io.tile[(tyi + b / 3 - 1) * ntx + txi + b % 3 - 1], 1);
