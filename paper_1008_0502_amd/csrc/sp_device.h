@@ -79,6 +79,14 @@ __device__ __forceinline__ void rows4_combine_nn(float mn, float mx, bool valid,
   osum = c;
 }
 
+// LDS stores of a wavefront's lanes before it are seen by the wavefront's loads after it.  The hardware
+// keeps a wavefront's LDS accesses in order; this tells the compiler.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 struct OpMax { __device__ static float f(float a, float b) { return fmaxf(a, b); } };
 struct OpMin { __device__ static float f(float a, float b) { return fminf(a, b); } };
 struct OpSum { __device__ static float f(float a, float b) { return a + b; } };

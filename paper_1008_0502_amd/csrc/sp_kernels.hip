@@ -2251,7 +2251,8 @@ __global__ __launch_bounds__(SP_BLOCK) void k_csmix(const Job* __restrict__ jobs
         wacc[b][KW * w + k][2] = 8 * (b >> 1) < J.th && 8 * (b & 1) < J.tw ? mx : 0.f;
       }
     }
-    // a wavefront's own channels: no barrier
+    // a wavefront's own channels: its lanes' stores before its loads, no workgroup barrier
+    wave_sync();
     if (lane < KW) {
       const int k = KW * w + lane;
       const gp<float> out = G(sd.fbar_part) + 3 * ((size_t)k * sd.n_cmax_tiles + J.tid);
