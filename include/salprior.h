@@ -396,8 +396,10 @@ int sp_autotune(sp_ctx* ctx, const uint8_t* rgb_t, const uint8_t* rgb_prev, int3
 /* Forces the launch shapes the autotuner would otherwise choose: the width (16, 32 or
  * 64) of the level-0 update tiles, the XCD-aware job order (0/1) and the channels per
  * across-scale workgroup (1, 2, 4 or 8; rejected when the LDS of that many channels
- * exceeds the limit for the geometry).  Every choice computes identical results.  The
- * context form synchronises its stream; the batch form drops the captured graph, which
+ * exceeds the limit for the geometry).  Every choice computes identical results.  In a context
+ * with a tape, order and channels hold for the frames that sp_run_clip computes side by side too
+ * (unforced, those launches follow their own number of tiles, also after an autotuner's choice for
+ * single frames).  The context form synchronises its stream; the batch form drops the captured graph, which
  * is captured again at the next step. */
 int sp_set_tune(sp_ctx* ctx, int32_t kalman_tw, int32_t xcd_order, int32_t channels);
 int sp_batch_set_tune(sp_batch* b, int32_t kalman_tw, int32_t xcd_order, int32_t channels);

@@ -202,6 +202,7 @@ struct Tune {
   int kalman_tw = 32;   // 16, 32 or 64
   bool xcd = true;
   int ca_nc = 2;        // channels per workgroup of the across-scale sum: 1, 2, 4 or 8
+  bool forced = false;  // by sp_set_tune: they hold for the frames of a recorded clip too
 };
 
 // Launch shapes where the autotuner has made no choice, from the tiles the launch holds.  Wide
@@ -1053,12 +1054,14 @@ namespace {
 
 // The forward phases over the clip slots: slot by slot (a prefix serves a shorter chunk), and
 // for whole chunks in XCD order with the longer jobs of a pyramid launch (Gabor tiles, small
-// levels) first, as in the batched step.
+// levels) first, as in the batched step.  The autotuner's shapes are those of single frames, so
+// only forced ones take the place of the rule by the number of tiles.
 int clip_tables(sp_ctx* c) {
   const Geo& g = c->g;
   TileCount tiles;
   for (int s = 0; s < c->CH; ++s) tiles.add(g);
-  const int nc = csapply_nc(g, tiles.nc());
+  const int nc = csapply_nc(g, c->tune.forced ? c->tune.ca_nc : tiles.nc());
+  const bool xcd = !c->tune.forced || c->tune.xcd;
   std::vector<std::vector<Job>> all;
   std::vector<int> kinds;
   for (int s = 0; s < c->CH; ++s) {
@@ -1081,8 +1084,10 @@ int clip_tables(sp_ctx* c) {
     for (const Job& jb : all[i])
       (jb.kind == JOB_GABOR ? kinds[i] == JOB_DOWN : jb.kind == JOB_TAIL || jb.kind == JOB_TAILGAB) ? first.push_back(jb)
                                                                                                    : rest.push_back(jb);
-    xcd_order(first);
-    xcd_order(rest);
+    if (xcd) {
+      xcd_order(first);
+      xcd_order(rest);
+    }
     first.insert(first.end(), rest.begin(), rest.end());
     c->clip_full.push_back(c->jobs.add(kinds[i], flag, first, c->CH));
     if (!grp) continue;
@@ -1705,6 +1710,7 @@ int sp_set_tune(sp_ctx* c, int32_t kalman_tw, int32_t xcd_order, int32_t channel
   c->tune.kalman_tw = kalman_tw;
   c->tune.xcd = xcd_order != 0;
   c->tune.ca_nc = channels;
+  c->tune.forced = true;
   const int rc = ctx_build_tables(c);
   if (rc) c->tune = was;
   return rc;

@@ -1,6 +1,7 @@
 """The library's host code on the CPU, over a stand-in for the HIP runtime (_hip_host.c): what an
 asynchronous copy reads is still there when the copy runs; launch tables that could not be made anew
-leave the old ones in use; clips are queued without waiting for the ones before."""
+leave the old ones in use; clips are queued without waiting for the ones before,
+and take forced launch shapes."""
 import os
 import subprocess
 import sys
@@ -137,4 +138,24 @@ w0 = count("shim_waits").value
 for _ in range(3):
     L.check(lib.saliency_backward_frames(h, clip, T, gf), "saliency_backward_frames")
 assert count("shim_waits").value == w0 and count("shim_pending").value == 0
+""")
+
+
+def test_forced_shapes_reach_the_clip(shim):
+    run(shim, STEP + """
+H, W, T = 120, 160, 6
+h = create(H, W, record_tape=T)
+n = H * W
+table = (ctypes.c_void_p * T)(*[mem(3 * n) for _ in range(T)])
+S, P = mem(4 * n * T), mem(4 * n * T)
+def clip():
+    L.check(lib.sp_run_clip(h, table, T, None, S, None, P, None, None, None), "sp_run_clip")
+def shaped(xcd, channels):
+    L.check(lib.sp_set_tune(h, 16, xcd, channels), "sp_set_tune")
+    return [j for _, _, j in launches(clip) if j]
+a, b, c = shaped(1, 1), shaped(1, 4), shaped(0, 4)
+assert len(a) == len(b) == len(c)
+assert sum(map(len, b)) < sum(map(len, a))                      # fewer across-scale workgroups
+cut = lambda j: sorted(j[i:i + JOB] for i in range(0, len(j), JOB))
+assert b != c and [cut(x) for x in b] == [cut(x) for x in c]     # the same jobs in another order
 """)
