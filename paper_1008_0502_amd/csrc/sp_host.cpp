@@ -1557,14 +1557,16 @@ int sp_saliency_noalloc(const sp_params* p, int32_t H, int32_t W, const uint8_t*
   if (rc) return rc;
   TileCount tiles;
   tiles.add(g);
-  const Tune tune = cached_tune(H, W, tiles);
-  const int nc = csapply_nc(g, tune.ca_nc);
+  Tune tune = cached_tune(H, W, tiles);
   // sizing pass (no device call): stream description, job table, then the stream's
   // pyramid, maps and partials, in the order the placing pass takes them
   StreamDesc sd;
   size_t n_jobs = 0;
   size_t need = 0;
-  {
+  int nc = 0;
+  auto size_up = [&] {
+    nc = csapply_nc(g, tune.ca_nc);
+    n_jobs = 0;
     Bump b;
     b.take<StreamDesc>(1);
     layout_stream(sd, g, *p, b);
@@ -1574,6 +1576,11 @@ int sp_saliency_noalloc(const sp_params* p, int32_t H, int32_t W, const uint8_t*
     for (const auto& v : parts) n_jobs += v.size();
     b.take<Job>(n_jobs);
     need = b.off;
+  };
+  size_up();
+  if (need > SP_NOALLOC_BYTES && tune.ca_nc == 1) {   // two channels a workgroup take half of those jobs
+    tune.ca_nc = 2;
+    size_up();
   }
   if (need > SP_NOALLOC_BYTES)
     return fail(SP_ESHAPE, "a %dx%d frame needs %zu bytes of scratch; the allocation-free entry point holds %zu "

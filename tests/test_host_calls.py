@@ -1,7 +1,7 @@
 """The library's host code on the CPU, over a stand-in for the HIP runtime (_hip_host.c): what an
 asynchronous copy reads is still there when the copy runs; launch tables that could not be made anew
 leave the old ones in use; clips are queued without waiting for the ones before,
-and take forced launch shapes."""
+and take forced launch shapes; the allocation-free call takes the frames that it took."""
 import os
 import subprocess
 import sys
@@ -158,4 +158,18 @@ assert len(a) == len(b) == len(c)
 assert sum(map(len, b)) < sum(map(len, a))                      # fewer across-scale workgroups
 cut = lambda j: sorted(j[i:i + JOB] for i in range(0, len(j), JOB))
 assert b != c and [cut(x) for x in b] == [cut(x) for x in c]     # the same jobs in another order
+""")
+
+
+@pytest.mark.parametrize("levels,H,W", [(dict(depth=9, centers=(2, 3, 4), deltas=(3, 4)), 1080, 8968),
+                                        (dict(depth=9, centers=(2, 3, 4), deltas=(3, 4)), 1501, 6448),
+                                        (dict(depth=8, centers=(3, 4), deltas=(3,)), 2000, 5514),
+                                        (dict(depth=9, centers=(4,), deltas=(3, 4, 5)), 2160, 5216)])
+def test_largest_frames_without_allocation(shim, levels, H, W):
+    """The largest width at this height whose scratch fits with two channels a workgroup; the next does not."""
+    run(shim, STEP + f"""
+p, buf = params(**{levels}), mem(64)
+call = lambda W: lib.sp_saliency_noalloc(ctypes.byref(p), {H}, W, buf, None, buf, None, None)
+assert call({W}) == L.SP_OK, lib.sp_last_error()
+assert call({W} + 16) == L.SP_ESHAPE
 """)
