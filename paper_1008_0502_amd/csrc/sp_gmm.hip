@@ -38,7 +38,7 @@ constexpr double kLog2Pi = 1.8378770664093453;
 __device__ __forceinline__ float ex(float x) { return __builtin_amdgcn_exp2f(x * kLog2e); }
 __device__ __forceinline__ float lg(float x) { return __builtin_amdgcn_logf(x) * kLn2; }
 
-// Products of a difference, shared by the distance and the second moments (xx, xy, xz, yy, yz, zz).
+// Products of a difference (xx, xy, xz, yy, yz, zz).
 struct Prod {
   float v[6];
   __device__ __forceinline__ Prod(float dx, float dy, float dz)
@@ -52,14 +52,22 @@ __device__ __forceinline__ float quad(const float* P, const Prod& d) {
   return fmaf(2.f, b, a);
 }
 
-// Moments of one sample with weight wr about the centre: count, first (3) and second (6).
-__device__ __forceinline__ void add_moments(float* a, float wr, float dx, float dy, float dz, const Prod& d) {
+// Moments of one sample with weight wr about the centre: count, first (3) and second (6).  Both orders
+// take the rounded product of weight and difference: its rounding varies with the weight and averages
+// out, where that of a product of differences is the same for all samples of one colour (a plain frame's
+// covariance came out 1e-9 off).
+__device__ __forceinline__ void add_moments(float* a, float wr, float dx, float dy, float dz) {
+  const float ux = wr * dx, uy = wr * dy, uz = wr * dz;
   a[0] += wr;
-  a[1] = fmaf(wr, dx, a[1]);
-  a[2] = fmaf(wr, dy, a[2]);
-  a[3] = fmaf(wr, dz, a[3]);
-#pragma unroll
-  for (int i = 0; i < 6; ++i) a[4 + i] = fmaf(wr, d.v[i], a[4 + i]);
+  a[1] += ux;
+  a[2] += uy;
+  a[3] += uz;
+  a[4] = fmaf(ux, dx, a[4]);
+  a[5] = fmaf(ux, dy, a[5]);
+  a[6] = fmaf(ux, dz, a[6]);
+  a[7] = fmaf(uy, dy, a[7]);
+  a[8] = fmaf(uy, dz, a[8]);
+  a[9] = fmaf(uz, dz, a[9]);
 }
 
 // A label's mixture as the pixel loops use it, in scalar registers (read from LDS once).
@@ -165,13 +173,13 @@ __device__ __forceinline__ void tile_moments(const GmmIO& io, float* lds, const 
       const float w = L ? p.w : 1.f - p.w;
       if constexpr (!EM) {
         const float dx = p.x - 0.5f, dy = p.y - 0.5f, dz = p.z - 0.5f;
-        add_moments(acc[0], w, dx, dy, dz, Prod(dx, dy, dz));
+        add_moments(acc[0], w, dx, dy, dz);
       } else {
         if (!X.lab) break;
         if constexpr (NC == 1) {   // its responsibility is 1: nothing to evaluate (1920x1080 212 -> 195 us)
           if (X.on[0]) {
             const float dx = p.x - X.mu[0][0], dy = p.y - X.mu[0][1], dz = p.z - X.mu[0][2];
-            add_moments(acc[0], w, dx, dy, dz, Prod(dx, dy, dz));
+            add_moments(acc[0], w, dx, dy, dz);
           }
           continue;
         }
@@ -192,7 +200,7 @@ __device__ __forceinline__ void tile_moments(const GmmIO& io, float* lds, const 
         for (int m = 0; m < NC; ++m)
           if (X.on[m]) {
             const float dx = p.x - X.mu[m][0], dy = p.y - X.mu[m][1], dz = p.z - X.mu[m][2];
-            add_moments(acc[m], ws * r[m], dx, dy, dz, Prod(dx, dy, dz));
+            add_moments(acc[m], ws * r[m], dx, dy, dz);
           }
       }
     }
