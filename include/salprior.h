@@ -384,7 +384,8 @@ const char* sp_kernel_name(int32_t k);
  * pixels) of the level-0 update tiles per resolution, and the XCD-aware order of the
  * job tables on or off -- over `steps` eager steps each on the given frames (device
  * array of n device pointers, as in sp_batch_step), keeps the fastest, records the
- * choice per resolution for batches and contexts created later in this process, and
+ * choice (the width per resolution, order and channels for all) for batches and contexts
+ * created later in this process, whatever their number of streams, and
  * resets the batch.  The candidates compute identical results.  report (may be NULL)
  * receives a text summary.  Synchronises. */
 int sp_batch_autotune(sp_batch* b, const uint8_t* const* rgb_ptrs, int32_t steps, char* report, size_t report_len);

@@ -142,7 +142,7 @@ constexpr int LDS_N = 20 * NC * (SP_BLOCK + 2 * seg_of(20 * NC)) > 4 * GPX * SP_
 // in a fixed order, and the segments are added in order.  A thread with more pixels has a second
 // FP32 sum, which joins the first, and both the neighbouring thread's, in FP64, so half as many sums
 // take the same LDS (640x480, three components, ten steps: 117 us with one FP32 sum of all pixels,
-// 126 us so).
+// 127 us so).
 constexpr int FP32_N = 4;
 static_assert(GPX <= 2 * FP32_N, "two FP32 sums per thread");
 template <int M, bool EM>
@@ -522,8 +522,8 @@ __device__ __forceinline__ void mixtures(const GmmIO& io, GmmState& S, Put put) 
 // The moments of every tile: the start's (EM = false) or the E-step's under the launch's
 // mixtures.  A pass bounded by its chain (pixels, mixtures, E-step, workgroup sum), not by its
 // 7 bytes a pixel: at 640x480 with three components 9.2 us with both labels on
-// a thread and four pixels unrolled on 300 workgroups, 6.6 us so; with the fit in the same launch
-// 10.4 us against 6.6 + 5.2 for the two.
+// a thread and four pixels unrolled on 300 workgroups, 6.6 us so with one FP32 sum per thread; with
+// the fit in the same launch 10.4 us against 6.6 + 5.2 for the two, 11.4 us with two FP32 sums.
 template <int M, bool EM, int FIT>
 __global__ __launch_bounds__(GB) void k_gmm_acc(GmmIO io) {
   __shared__ __align__(16) float lds[LDS_N<EM ? M : 1>];
