@@ -3347,25 +3347,6 @@ __device__ void batch_begin_stream(int i, BatchState* __restrict__ st, const Str
   st[i] = s;
 }
 
-// One thread a step: 1.4 us for 8 steps, 4.8 for 120.  A table copied from pinned memory made the call wait
-// for the copy of the one before.
-__global__ __launch_bounds__(SP_CLIP_IO) void k_clip_io(ClipIO a) {
-  const int s = threadIdx.x;
-  if (s >= a.n) return;
-  auto at = [s](const ClipOut& o) { return o.p ? o.p + s * o.stride : nullptr; };
-  StepIO io{};
-  io.rgb_prev = a.rgb[s];
-  io.rgb = a.rgb[s + 1];
-  io.S_out = at(a.S_out);
-  io.C_out = at(a.C_out);
-  io.S_tape = at(a.S_tape);
-  io.fbar = at(a.fbar);
-  io.np_tape = at(a.np_tape);
-  io.pairwise = at(a.pairwise);
-  io.beta_out = at(a.beta_out);
-  a.io[s] = io;
-}
-
 __global__ void k_batch_reset(int n, BatchState* __restrict__ st) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -3458,27 +3439,10 @@ static inline hipError_t chk() { return hipGetLastError(); }
   } while (0)
 #define SP_STEP_KERNEL(...) SP_STEP_KERNEL_B(SP_BLOCK, __VA_ARGS__)
 
-// The across-scale kernel of a launch (flag: channels per workgroup | pair set << 8).
+// The across-scale kernel of a launch (flag: channels per workgroup | pair set << 8), and its threads.
 typedef void (*StepKernel)(const Job*, const StreamDesc*, const StepIO*, StepIO);
-template <bool ONE>
-static StepKernel csg_kernel(int nc, int set) {
-  if (set == 1) return nc == 8 ? k_csg1<8, 2, 4, ONE> : nc == 4 ? k_csg1<4, 2, 4, ONE> : nc == 2 ? k_csg1<2, 2, 4, ONE> : k_csg1<1, 2, 4, ONE>;
-  if (set == 2) return nc == 8 ? k_csg1<8, 3, 3, ONE> : nc == 4 ? k_csg1<4, 3, 3, ONE> : nc == 2 ? k_csg1<2, 3, 3, ONE> : k_csg1<1, 3, 3, ONE>;
-  return nc == 8 ? k_csg<8, 0, ONE> : nc == 4 ? k_csg<4, 0, ONE> : nc == 2 ? k_csg<2, 0, ONE> : k_csg<1, 0, ONE>;
-}
-template <bool ONE>
-static StepKernel csapply_kernel(int nc, int set) {
-  if (set == 1 && nc <= 2) return nc == 2 ? k_csapply<2, 1, ONE> : k_csapply<1, 1, ONE>;
-  return nc == 8 ? k_csapply<8, 0, ONE> : nc == 4 ? k_csapply<4, 0, ONE> : nc == 2 ? k_csapply<2, 0, ONE> : k_csapply<1, 0, ONE>;
-}
-static StepKernel across_kernel(int kind, int flag, bool one) {
-  const int nc = flag & 0xff, set = flag >> 8;
-  if (kind == JOB_CSG) return one ? csg_kernel<true>(nc, set) : csg_kernel<false>(nc, set);
-  return one ? csapply_kernel<true>(nc, set) : csapply_kernel<false>(nc, set);
-}
-static int across_threads(int kind, int flag) {
-  return kind == JOB_CSAPPLY && flag >> 8 == 1 && (flag & 0xff) <= 2 ? CA_NT1 : SP_BLOCK;
-}
+static StepKernel across_kernel(int kind, int flag, bool one);
+static int across_threads(int kind, int flag);
 
 hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, const StepIO* ios,
                      const StepIO* io0, int flag, const float* aux, hipStream_t st, size_t lds) {
@@ -3568,6 +3532,26 @@ hipError_t sp_launch(int kind, const Job* jobs, int n, const StreamDesc* sds, co
   return chk();
 }
 
+template <bool ONE>
+static StepKernel csg_kernel(int nc, int set) {
+  if (set == 1) return nc == 8 ? k_csg1<8, 2, 4, ONE> : nc == 4 ? k_csg1<4, 2, 4, ONE> : nc == 2 ? k_csg1<2, 2, 4, ONE> : k_csg1<1, 2, 4, ONE>;
+  if (set == 2) return nc == 8 ? k_csg1<8, 3, 3, ONE> : nc == 4 ? k_csg1<4, 3, 3, ONE> : nc == 2 ? k_csg1<2, 3, 3, ONE> : k_csg1<1, 3, 3, ONE>;
+  return nc == 8 ? k_csg<8, 0, ONE> : nc == 4 ? k_csg<4, 0, ONE> : nc == 2 ? k_csg<2, 0, ONE> : k_csg<1, 0, ONE>;
+}
+template <bool ONE>
+static StepKernel csapply_kernel(int nc, int set) {
+  if (set == 1 && nc <= 2) return nc == 2 ? k_csapply<2, 1, ONE> : k_csapply<1, 1, ONE>;
+  return nc == 8 ? k_csapply<8, 0, ONE> : nc == 4 ? k_csapply<4, 0, ONE> : nc == 2 ? k_csapply<2, 0, ONE> : k_csapply<1, 0, ONE>;
+}
+static StepKernel across_kernel(int kind, int flag, bool one) {
+  const int nc = flag & 0xff, set = flag >> 8;
+  if (kind == JOB_CSG) return one ? csg_kernel<true>(nc, set) : csg_kernel<false>(nc, set);
+  return one ? csapply_kernel<true>(nc, set) : csapply_kernel<false>(nc, set);
+}
+static int across_threads(int kind, int flag) {
+  return kind == JOB_CSAPPLY && flag >> 8 == 1 && (flag & 0xff) <= 2 ? CA_NT1 : SP_BLOCK;
+}
+
 hipError_t sp_launch_bwd(int kind, int flag, const Job* jobs, int n, const StreamDesc* sds, const BwdIO* bios,
                          const BwdIO* b0, hipStream_t st) {
   if (n <= 0) return hipSuccess;
@@ -3654,11 +3638,6 @@ void sp_batch_rgb_node_params(RgbNodeArgs* a, int n_jobs, hipKernelNodeParams* p
   p->sharedMemBytes = 0;
   p->kernelParams = a->argv;
   p->extra = nullptr;
-}
-
-hipError_t sp_launch_clip_io(const ClipIO& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_clip_io, dim3(1), dim3(SP_CLIP_IO), 0, st, a);
-  return chk();
 }
 
 hipError_t sp_launch_batch_reset(int n, BatchState* st, hipStream_t stream) {
