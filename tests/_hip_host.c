@@ -15,28 +15,28 @@ typedef struct { unsigned grid, block; void* arg0; } Launch;
 
 static Copy pending[4096];
 static Launch launches[65536];
-int shim_pending, shim_stale, shim_waits, shim_launches, shim_fail_malloc, shim_fail_copy;
+int standin_pending, standin_stale, standin_waits, standin_launches, standin_fail_malloc, standin_fail_copy;
 
-const Launch* shim_launch(int i) { return &launches[i]; }
+const Launch* standin_launch(int i) { return &launches[i]; }
 
 static void settle(void) {
-  for (int i = 0; i < shim_pending; ++i) {
+  for (int i = 0; i < standin_pending; ++i) {
     Copy* c = &pending[i];
     char* now = malloc(c->n);
     struct iovec l = {now, c->n}, r = {(void*)c->src, c->n};
-    if (process_vm_readv(getpid(), &l, 1, &r, 1, 0) != (ssize_t)c->n || memcmp(now, c->was, c->n)) ++shim_stale;
+    if (process_vm_readv(getpid(), &l, 1, &r, 1, 0) != (ssize_t)c->n || memcmp(now, c->was, c->n)) ++standin_stale;
     memcpy(c->dst, c->was, c->n);
     free(now);
     free(c->was);
   }
-  shim_pending = 0;
+  standin_pending = 0;
 }
 
 int hipGetDevice(int* d) { return *d = 0; }
 int hipGetLastError(void) { return 0; }
 const char* hipGetErrorString(int e) { return e ? "error" : "ok"; }
 int hipMalloc(void** p, size_t n) {
-  if (shim_fail_malloc && --shim_fail_malloc == 0) return 2;
+  if (standin_fail_malloc && --standin_fail_malloc == 0) return 2;
   return (*p = calloc(1, n)) ? 0 : 2;
 }
 int hipFree(void* p) { free(p); return 0; }
@@ -45,15 +45,15 @@ int hipHostFree(void* p) { free(p); return 0; }
 int hipHostGetDevicePointer(void** d, void* h, unsigned f) { *d = h; return 0; }
 int hipMemcpy(void* d, const void* s, size_t n, int kind) { settle(); memmove(d, s, n); return 0; }
 int hipMemcpyAsync(void* d, const void* s, size_t n, int kind, void* st) {
-  if (shim_fail_copy && --shim_fail_copy == 0) return 1;
-  if (kind != 1 || shim_pending == 4096) { settle(); memmove(d, s, n); return 0; }
+  if (standin_fail_copy && --standin_fail_copy == 0) return 1;
+  if (kind != 1 || standin_pending == 4096) { settle(); memmove(d, s, n); return 0; }
   Copy c = {d, s, malloc(n), n};
   memcpy(c.was, s, n);
-  pending[shim_pending++] = c;
+  pending[standin_pending++] = c;
   return 0;
 }
 int hipGetSymbolAddress(void** p, const void* s) { static char scratch[64 << 20]; *p = scratch; return 0; }
-int hipStreamSynchronize(void* st) { ++shim_waits; settle(); return 0; }
+int hipStreamSynchronize(void* st) { ++standin_waits; settle(); return 0; }
 int hipStreamIsCapturing(void* st, int* s) { return *s = 0; }
 int hipStreamCreateWithFlags(void** s, unsigned f) { *s = malloc(1); return 0; }
 int hipStreamDestroy(void* s) { free(s); return 0; }
@@ -61,7 +61,7 @@ int hipEventCreate(void** e) { *e = malloc(1); return 0; }
 int hipEventCreateWithFlags(void** e, unsigned f) { *e = malloc(1); return 0; }
 int hipEventDestroy(void* e) { free(e); return 0; }
 int hipEventRecord(void* e, void* s) { return 0; }
-int hipEventSynchronize(void* e) { ++shim_waits; settle(); return 0; }
+int hipEventSynchronize(void* e) { ++standin_waits; settle(); return 0; }
 int hipEventElapsedTime(float* ms, void* a, void* b) { *ms = 1.f; return 0; }
 int hipFuncSetAttribute(const void* f, int a, int v) { return 0; }
 static struct { dim3_ grid, block; size_t lds; void* st; } conf;
@@ -74,7 +74,7 @@ int __hipPopCallConfiguration(dim3_* grid, dim3_* block, size_t* lds, void** st)
   return 0;
 }
 int hipLaunchKernel(const void* f, dim3_ grid, dim3_ block, void** args, size_t lds, void* st) {
-  if (shim_launches < 65536) launches[shim_launches] = (Launch){grid.x, block.x, *(void**)args[0]};
-  ++shim_launches;
+  if (standin_launches < 65536) launches[standin_launches] = (Launch){grid.x, block.x, *(void**)args[0]};
+  ++standin_launches;
   return 0;
 }
